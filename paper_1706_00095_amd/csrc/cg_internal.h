@@ -130,7 +130,7 @@ struct PatchGeom {
     int32_t Wp;               // padded patch width: (OWo-1)*s + KW
     int32_t Rfull;            // slots of a whole image: ((OHo-1)*s + KH) * Wp
     int32_t flip;             // 0: (py, px) = (ky, kx); 1: mirrored taps
-    FastDiv divP, divOW, divWp, divRfull;
+    FastDiv divP, divOW, divWp, divRfull, divKW;
     int32_t nsl;              // 64-slot chunks per channel the kernel instance stages (4 or 5); 0 = not usable
     int32_t tiles_per_img;    // 0: blocks own 128 consecutive pixels across image boundaries; > 0: every image is
                               // cut into this many blocks of its own (smaller patches for large images)
@@ -182,6 +182,7 @@ struct IgemmProblem {
     const float *gate;        // same layout as C, or NULL: result = 0 where gate <= 0 (backward-data into a
                               // rectifier: the gradient with respect to the rectifier's input), before accumulate
     int math;                 // CG_MATH_FP32, CG_MATH_BF16 or CG_MATH_BF16X3: what the matrix instructions multiply in
+    int mt;                   // row-tile height igemm_run has planned the K slices for (0: igemm_launch chooses)
     int beside_other_stream;  // the caller runs matrix kernels on another stream meanwhile (tile choice of the patch kernel)
     int use_patch;            // B is described by `patch` (and A is the matching tap-major matrix); B unused
     PatchGeom patch;
@@ -201,17 +202,22 @@ void patch_set_resident_blocks(uint32_t blocks);
 void patch_set_min_tiles(uint32_t t);
 
 // Validates the problem against what the kernels assume and launches it.
+int split_patch_launch(const IgemmProblem &p, hipStream_t stream);      // problems with a patch (igemm_launch dispatches)
+uint32_t igemm_resident_blocks();
+int igemm_pick_mt(uint32_t M, uint32_t N, uint32_t groups);
 int igemm_launch(const IgemmProblem &p, hipStream_t stream);
-// The same for the bf16 matrix instructions (igemm_launch dispatches on p.math)
-int igemm_launch_bf16(const IgemmProblem &p, hipStream_t stream);
-int igemm_launch_bf16x3(const IgemmProblem &p, hipStream_t stream);
+// split_gemm_kernel with 1, 2 or 3 bf16 pieces per operand (igemm_launch dispatches on p.math).  b_mode: how B's
+// elements are fetched, 0 rows along the lanes, 1 k along the lanes, 2 aligned quads of k
+int split_gemm_1(const IgemmProblem &p, int mt, bool a_quads, int b_mode, hipStream_t stream);
+int split_gemm_2(const IgemmProblem &p, int mt, bool a_quads, int b_mode, hipStream_t stream);
+int split_gemm_3(const IgemmProblem &p, int mt, bool a_quads, int b_mode, hipStream_t stream);
 // Host-side evaluation of one operand element: offset and validity (for tests of the maps).
 void igemm_host_element(const Operand &op, uint32_t row, uint32_t k, int64_t *off, int *valid);
 
 // Split-K front end: when C has too few tiles to fill the chip, the K range is cut into slices
 // whose partial results go to `ws` and are then added in slice order (so results do not depend
 // on scheduling).  igemm_ws_bytes() says how much workspace igemm_run() needs for a problem.
-struct SplitPlan { uint32_t splits, k_per_split; size_t ws_bytes; };
+struct SplitPlan { uint32_t splits, k_per_split; size_t ws_bytes; int mt; };
 SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
 size_t igemm_ws_bytes(const IgemmProblem &p);
 // rider: a small convolution's bias gradient (db[m] = sum of dy over images and pixels), summed by

@@ -56,34 +56,39 @@ __device__ __forceinline__ float transpose_filters_elem(const float *__restrict_
     return w[(((size_t)g * Mg + ml) * Cg + c) * KK + kk];
 }
 
-// Filters as the tap-major matrix the patch kernel multiplies with: dst[g][r][t][c], t = kh*KW + kw.
+// Filters as the patch kernel multiplies with them: dst[g][t][c / 16][r][c % 16], t = kh*KW + kw (units of
+// 16 reduction indices, all rows of a unit contiguous: a wave's load is).  c runs over a multiple of 16.
 // Forward (bwd = 0): r = output channel, c = input channel: dst = w[g*Mg + r][c][t].
 // Backward-data (bwd = 1): r = input channel, c = output channel: dst = w[g*Mg + c][r][t].
 __device__ __forceinline__ float permute_filters_elem(const float *__restrict__ w, size_t i, int Mg, int Cg, int KK, int bwd)
 {
     const int R = bwd ? Cg : Mg, Cr = bwd ? Mg : Cg;
-    const int c = (int)(i % Cr);
-    size_t q = i / Cr;
-    const int t = (int)(q % KK); q /= KK;
-    const int r = (int)(q % R);
-    const int g = (int)(q / R);
+    size_t q = i / 16;
+    const int r = (int)(q % R); q /= R;
+    const int c = (int)(q % (Cr / 16)) * 16 + (int)(i % 16); q /= Cr / 16;
+    const int t = (int)(q % KK);
+    const int g = (int)(q / KK);
     const int m = bwd ? c : r, ci = bwd ? r : c;
     return w[(((size_t)g * Mg + m) * Cg + ci) * KK + t];
 }
 
 // Filters as the matrix of strided backward-data (see bwd_data_strided_problem): row (c, rh, rw),
 // reduction index (m, a, b) with filter tap kh = rh + sh*a, kw = rw + sw*b (zero where that tap
-// does not exist).  tap_major = 1: dst[g][row][t = a*Aw + b][m] (the patch kernel's order);
+// does not exist).  tap_major = 1: dst[g][t = a*Aw + b][m / 16][row][m % 16] (the patch kernel's order);
 // 0: dst[g][row][m][t] (the gathered kernel's).
 __device__ __forceinline__ float strided_filters_elem(const float *__restrict__ w, size_t i, int Mg, int Cg, int KH, int KW,
                                                       int sh, int sw, int Ah, int Aw, int tap_major)
 {
     const int R = Cg * sh * sw, T = Ah * Aw;
-    int m, t;
+    int m, t, row;
     size_t q;
-    if (tap_major) { m = (int)(i % Mg); q = i / Mg; t = (int)(q % T); q /= T; }
-    else { t = (int)(i % T); q = i / T; m = (int)(q % Mg); q /= Mg; }
-    const int row = (int)(q % R), g = (int)(q / R);
+    if (tap_major) {
+        q = i / 16;
+        row = (int)(q % R); q /= R;
+        m = (int)(q % (Mg / 16)) * 16 + (int)(i % 16); q /= Mg / 16;
+        t = (int)(q % T); q /= T;
+    } else { t = (int)(i % T); q = i / T; m = (int)(q % Mg); q /= Mg; row = (int)(q % R); q /= R; }
+    const int g = (int)q;
     const int rw = row % sw, rh = (row / sw) % sh, c = row / (sw * sh);
     const int kh = rh + sh * (t / Aw), kw = rw + sw * (t % Aw);
     return (kh < KH && kw < KW) ? w[(((size_t)g * Mg + m) * Cg + c) * KH * KW + kh * KW + kw] : 0.f;

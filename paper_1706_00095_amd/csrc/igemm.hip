@@ -1,50 +1,13 @@
-// Implicit-GEMM kernel on the fp32 matrix cores of gfx950.
-//
-// One kernel template computes C[m][n] = sum_k A(m,k) * B(n,k) for every dense contraction of
-// the iteration: convolution forward, backward-data and backward-weight, and the three
-// fully-connected passes.  Operand elements are addressed through index maps (cg_internal.h),
-// so the im2col matrix is never materialised: a tile of it is gathered straight from the NCHW
-// tensor into LDS, with zero padding folded into the load address.
-//
-// Work decomposition: a block of 4 waves owns an MT x 128 tile of C; each wave owns TM x TN
-// sub-tiles of 32x32, accumulated by v_mfma_f32_32x32x2_f32.  The K loop advances KT = 16 at a
-// time through a ring of NST LDS stages.  Operand tiles travel global memory -> LDS directly
-// (buffer loads with the LDS modifier: no register round trip, no LDS store instructions), and an
-// element that is zero padding, lies beyond the tile's rows or beyond K gets an offset outside the
-// buffer descriptor's range, for which the hardware writes 0.  The loads of tile it+NST-1 are
-// issued while tile it is multiplied; one s_barrier per K-tile.
+// Planning of the dense contractions: which kernel, which tile, how many K slices; the kernels that
+// add the slices and the bias gradient; and the fp32 band kernel for backward-weight.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
-#include <type_traits>
-#include <utility>
 #include "cg_internal.h"
-
-// This file is compiled three times.  CG_MATH = 0 (the default) multiplies in fp32 and holds
-// everything: kernels, planning, K slices, bias gradient.  CG_MATH = 1 and 2 build only the two
-// main kernels and their launchers once more, for the bf16 matrix instructions: the tiles travel
-// and lie in LDS as fp32 exactly as before, a lane rounds its fragments to bf16 (nearest even)
-// and one v_mfma_f32_32x32x16_bf16 per accumulator multiplies a whole K-tile of 16.
-//   1 (CG_MATH_BF16):   a*b with a, b rounded to bf16, accumulated in fp32.
-//   2 (CG_MATH_BF16X3): a = ah + al, b = bh + bl (ah = bf16(a), al = bf16(a - ah)), three products
-//                       al*bh + ah*bl + ah*bh: what is dropped is al*bl, about 2^-16 of a product.
-#ifndef CG_MATH
-#define CG_MATH 0
-#endif
-#if CG_MATH == 0
-#define CG_IGEMM_LAUNCH igemm_launch
-#elif CG_MATH == 1
-#define CG_IGEMM_LAUNCH igemm_launch_bf16
-#else
-#define CG_IGEMM_LAUNCH igemm_launch_bf16x3
-#endif
+#include "igemm_device.h"
 
 namespace cg {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) float lds_float;
-typedef uint32_t BufferRsrc __attribute__((ext_vector_type(4)));   // the four descriptor words of a raw buffer
 
 namespace {
 
@@ -79,38 +42,6 @@ uint32_t resident_blocks()
 
 constexpr int KT = 16;                       // reduction indices per LDS stage (a ring of NST stages)
 constexpr int NPART = KT / 2;                // MFMA steps per tile = parts the loads of a tile are issued in
-// Offsets that no buffer descriptor of this library covers (descriptors span < 0x7fffff00 bytes).
-// Their sum does not wrap, and either one added to a valid offset (< 2^31) stays out of range.
-constexpr uint32_t OOB_ROW = 0x80000000u, OOB_K = 0x7fffff00u;
-constexpr uint64_t kMaxBufferBytes = 0x7fffff00ull;
-
-template <int B, class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Is...>)
-{
-    (f(std::integral_constant<int, B + Is>{}), ...);
-}
-template <int B, int E, class F> __device__ __forceinline__ void static_for(F &&f)
-{
-    static_for_impl<B>(f, std::make_integer_sequence<int, (E > B ? E - B : 0)>{});
-}
-
-// The eight fp32 fragment values a lane holds of a K-tile (k = 8*ks + 4*h + t, ks = 0..1, t = 0..3)
-// as the bf16 operand vector of v_mfma_f32_32x32x16_bf16, whose lane half h supplies k slots
-// 8h..8h+7: slot 4*ks + t.  Which k sits in which slot is immaterial as long as A and B agree.
-template <bool SPLIT>
-__device__ __forceinline__ void to_bf16(const float (&f)[KT / 8][4], bf16x8 &hi, bf16x8 &lo)
-{
-#pragma unroll
-    for (int ks = 0; ks < KT / 8; ++ks)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const float x = f[ks][t];
-            const __bf16 xh = (__bf16)x;
-            hi[4 * ks + t] = xh;
-            if (SPLIT) lo[4 * ks + t] = (__bf16)(x - (float)xh);
-        }
-}
-
 // 64 lanes x 4 bytes, global memory -> LDS: lane l's element lands at lds + 4*l.  `lds` and `soff`
 // are wave-uniform.  Written as assembly so that the waits stay under this file's control: the
 // kernel below waits for exactly the tile it is about to read (s_waitcnt vmcnt(n)), whereas the
@@ -118,8 +49,7 @@ __device__ __forceinline__ void to_bf16(const float (&f)[KT / 8][4], bf16x8 &hi,
 // The hazard recognizer does not look inside assembly: a scalar register written by a preceding
 // vector instruction (a readfirstlane, or a v_readlane that restores a spilled register, the buffer
 // descriptor included) may not be read by a vector-memory instruction for five wait states (one for
-// M0), so the s_mov and the s_nop 3 of this form supply them.  The short forms below (s_nop 0) are
-// for kernels that spill no scalar register, which the build checks (build.py).
+// M0), so the s_mov and the s_nop 3 supply them.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(BufferRsrc rsrc, const float *lds, uint32_t voff, uint32_t soff)
@@ -129,150 +59,16 @@ __device__ __forceinline__ void load_to_lds(BufferRsrc rsrc, const float *lds, u
                  ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff))
                  : "memory", "m0");
 }
-// The same without a scalar offset: no scalar register a vector instruction may just have written is
-// read, and the one wait state M0 needs is enough.  A load with its set-up costs the matrix pipeline
-// about 6 % of a four-MFMA step with four wait states and 4 % with one (measured on a loop of MFMAs).
-__device__ __forceinline__ void load_to_lds(BufferRsrc rsrc, const float *lds, uint32_t voff)
-{
-    const uint32_t lds_addr = (uint32_t)(size_t)(const lds_float *)lds;
-#if CG_MATH == 0
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                 ::"s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
-#else   // the bf16 instances of the gathered kernel spill scalar registers: the long form throughout
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                 ::"s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
-#endif
-}
 // 64 lanes x 16 bytes: lane l's four elements land at lds + 16*l.
-constexpr int kShortWS = CG_MATH == 0 ? 1 : 4;
-template <int WS = kShortWS>
 __device__ __forceinline__ void load4_to_lds(BufferRsrc rsrc, const float *lds, uint32_t voff)
 {
     const uint32_t lds_addr = (uint32_t)(size_t)(const lds_float *)lds;
-    if constexpr (WS == 1)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                     ::"s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                     ::"s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 ::"s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 
-// ---- tile loaders -------------------------------------------------------------------------------
-// A loader brings one R x KT operand tile into an LDS stage and says where the MFMA fragment of a
-// lane lives there.  One load instruction moves 64 elements that land contiguously in LDS, so the
-// lanes run along whichever index is contiguous in memory:
-//   RowsLoader: lanes = 64 consecutive rows at one k.  Stage layout [k][RS], RS = 64*chunks + 8.
-//               Row offsets (and window origins) live in registers for the whole K loop; the k part
-//               is wave-uniform and travels in the scalar offset of the load.
-//   KLoader:    lanes = 4 rows x 16 consecutive k.  Stage layout [row/4][68] with row%4 and k inside
-//               the 64-float group.  The k part is computed per lane once per tile.
-// In both, lane (i = lane&31, h = lane>>5) of a wave fetches for one 8-wide k step the four values
-// k = 8*ks + 4h + t, t = 0..3 of row i; MFMA number t of the step consumes value t.  Which k a
-// lane half holds is immaterial as long as A and B agree.  The paddings (8, 4) put the two lane
-// halves, and neighbouring row groups, on different LDS banks.
-// Wave w of the block issues the loads of k = 4w..4w+3 (RowsLoader) or of rows R/4*w.. (KLoader).
-
-template <int R, bool CHECK> struct RowsLoader {
-    static constexpr int NCH = (R + 63) / 64;
-    static constexpr int RS = NCH * 64 + 8;
-    static constexpr int SZ = KT * RS;
-    static constexpr int LPT = 4 * NCH;          // load instructions per tile and wave
-    uint32_t roff[NCH];
-    int32_t ra[NCH], rb[NCH];
-
-    __device__ __forceinline__ void init(const Operand &op, uint32_t row0, uint32_t nrows, int, int lane)
-    {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const uint32_t rl = (uint32_t)(c * 64 + lane), row = row0 + rl;
-            const Info q = map_info(op.row, row);
-            roff[c] = (rl < (uint32_t)R && row < nrows) ? (uint32_t)q.off * 4u : OOB_ROW;
-            ra[c] = q.a; rb[c] = q.b;
-        }
-    }
-    // scalar info of the k this wave is loading (set by the part that issues chunk 0 of that k)
-    Info kq;
-    uint32_t ksoff;
-
-    // The loads of one tile are cut into NPART parts so that the K loop can place one part behind
-    // each MFMA step: part P issues loads [P*LPT/NPART, (P+1)*LPT/NPART), load i = (t, chunk).
-    template <int P>
-    __device__ __forceinline__ void issue_part(BufferRsrc rsrc, float *stage, const Operand &op, uint32_t k0,
-                                               uint32_t kend, int wave, int)
-    {
-#pragma unroll
-        for (int i = P * LPT / NPART; i < (P + 1) * LPT / NPART; ++i) {
-            const int t = i / NCH, c = i % NCH;
-            const uint32_t kl = (uint32_t)(4 * wave + t), k = k0 + kl;       // wave-uniform
-            if (c == 0) {
-                kq = map_info(op.k, k);
-                ksoff = (k < kend && (op.k.r1_lim == 0 || kq.r1 < op.k.r1_lim)) ? (uint32_t)kq.off * 4u : OOB_K;
-            }
-            uint32_t voff = roff[c];
-            if (CHECK) {
-                const bool ok = (uint32_t)(ra[c] + kq.a) < op.limA && (uint32_t)(rb[c] + kq.b) < op.limB;
-                voff = ok ? voff : OOB_ROW;
-            }
-            load_to_lds(rsrc, stage + kl * RS + c * 64, voff, ksoff);
-        }
-    }
-    __device__ __forceinline__ static void frag(const float *stage, int row, int ks, int h, float out[4])
-    {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) out[t] = stage[(8 * ks + 4 * h + t) * RS + row];
-    }
-};
-
-template <int R, bool CHECK> struct KLoader {
-    static_assert(R % 16 == 0, "four waves, four rows per load");
-    static constexpr int NI = R / 4;             // load instructions per tile
-    static constexpr int NJ = NI / 4;            // ... and wave
-    static constexpr int GS = 68;
-    static constexpr int SZ = NI * GS;
-    static constexpr int LPT = NJ;
-    uint32_t roff[NJ];
-    int32_t ra[NJ], rb[NJ];
-
-    __device__ __forceinline__ void init(const Operand &op, uint32_t row0, uint32_t nrows, int wave, int lane)
-    {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const uint32_t row = row0 + (uint32_t)(4 * (wave * NJ + j) + (lane >> 4));
-            const Info q = map_info(op.row, row);
-            roff[j] = row < nrows ? (uint32_t)q.off * 4u : OOB_ROW;
-            ra[j] = q.a; rb[j] = q.b;
-        }
-    }
-    Info kq;              // this lane's k of the tile being loaded (set by part 0)
-    uint32_t koff;
-
-    template <int P>
-    __device__ __forceinline__ void issue_part(BufferRsrc rsrc, float *stage, const Operand &op, uint32_t k0,
-                                               uint32_t kend, int wave, int lane)
-    {
-        if (P == 0) {
-            const uint32_t k = k0 + (uint32_t)(lane & 15);
-            kq = map_info(op.k, k);
-            koff = (k < kend && (op.k.r1_lim == 0 || kq.r1 < op.k.r1_lim)) ? (uint32_t)kq.off * 4u : OOB_K;
-        }
-#pragma unroll
-        for (int j = P * LPT / NPART; j < (P + 1) * LPT / NPART; ++j) {
-            uint32_t voff = roff[j] + koff;
-            if (CHECK) {
-                const bool ok = (uint32_t)(ra[j] + kq.a) < op.limA && (uint32_t)(rb[j] + kq.b) < op.limB;
-                voff = ok ? voff : OOB_ROW;
-            }
-            load_to_lds(rsrc, stage + (wave * NJ + j) * GS, voff);
-        }
-    }
-    __device__ __forceinline__ static void frag(const float *stage, int row, int ks, int h, float out[4])
-    {
-        const float4 q = *reinterpret_cast<const float4 *>(stage + (row >> 2) * GS + (row & 3) * 16 + 8 * ks + 4 * h);
-        out[0] = q.x; out[1] = q.y; out[2] = q.z; out[3] = q.w;
-    }
-};
-
+// ---- tile loader of the band kernel -------------------------------------------------------------
 // KLoader4: for an operand in which every aligned group of four reduction indices is four
 // consecutive floats in memory (a row-major matrix; or runs of pixels, one run per image, the run
 // length padded to a multiple of four in the index space).  One load moves 16 rows x 16 k: lane l
@@ -281,7 +77,7 @@ template <int R, bool CHECK> struct KLoader {
 // only 4-byte alignment, and the range check is per float: a quad that reaches beyond K, a run or
 // the tensor delivers the floats that exist and zeros (or the neighbouring row's values) for the
 // rest, which meet zeros of operand B.
-template <int R, int WS = kShortWS> struct KLoader4 {       // WS: wait states behind the M0 set-up of a load (1 or 4)
+template <int R> struct KLoader4 {
     static constexpr int NJ = (R + 63) / 64;     // load instructions per tile and wave
     static constexpr int SZ = 4 * NJ * 256;      // rows beyond R are loaded as zeros
     static constexpr int LPT = NJ;
@@ -312,7 +108,7 @@ template <int R, int WS = kShortWS> struct KLoader4 {       // WS: wait states b
         }
 #pragma unroll
         for (int j = P * LPT / NPART; j < (P + 1) * LPT / NPART; ++j)
-            load4_to_lds<WS>(rsrc, stage + (wave * NJ + j) * 256, roff[j] + koff);
+            load4_to_lds(rsrc, stage + (wave * NJ + j) * 256, roff[j] + koff);
     }
     __device__ __forceinline__ static void frag(const float *stage, int row, int ks, int h, float out[4])
     {
@@ -322,710 +118,7 @@ template <int R, int WS = kShortWS> struct KLoader4 {       // WS: wait states b
     }
 };
 
-// Buffer descriptor over the part of an operand's tensor that starts at group g (+ the shift that
-// keeps per-index offsets non-negative).  igemm_launch has checked that the span fits the format.
-// Words: base address (48 bits, stride 0), number of bytes, format word of a raw dword buffer.
-__device__ __forceinline__ BufferRsrc operand_rsrc(const Operand &op, uint32_t g)
-{
-    const int64_t first = (int64_t)g * op.gstride + op.shift;
-    const uint64_t base = (uint64_t)reinterpret_cast<uintptr_t>(op.ptr) + (uint64_t)(first * 4);
-    const uint32_t bytes = (uint32_t)(((int64_t)op.elems - first) * 4);
-    BufferRsrc r;       // wave-uniform by construction; readfirstlane pins the words to scalar registers
-    r.x = __builtin_amdgcn_readfirstlane((uint32_t)base);
-    r.y = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xffffu);
-    r.z = __builtin_amdgcn_readfirstlane(bytes);
-    r.w = 0x00020000u;
-    return r;
-}
-
-// Epilogue of the matrix kernels: a wave's TM x TN accumulator tiles, whose first row / column
-// are (mw, nw), go to C (columns below n_end) with bias, rectifier, gate and accumulation applied.
-// Accumulator register r of lane (h, li) holds C row 8*(r/4) + 4*h + r%4, column li of its 32x32
-// sub-tile: stored from there, every store instruction would write 4 bytes per lane in runs of
-// 128 bytes.  Instead each 32-row slab of the wave's tile is turned around in LDS (`wlds`, private
-// to the wave, EpiLds<TN>::FLOATS floats, free once the block has left the K loop) so that a lane
-// owns four consecutive columns of a row and a store instruction writes whole runs of 32*TN
-// columns, 16 bytes per lane (4-byte aligned).  Columns whose C offsets are not consecutive
-// (a pixel tile that crosses into the next image) or that reach beyond n_end go one by one.
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-
-template <int TN> struct EpiLds {
-    static constexpr int W = TN * 32, LS = W + 8, FLOATS = 32 * LS;
-};
-
-// PLAIN: no gate, no accumulation, no scattered rows (forward, ungated backward-data, K-slice partial
-// planes): that instance has a third of the other's instructions, and a block's epilogue is time in
-// which its waves issue no matrix instruction.
-template <int TM, int TN, bool PLAIN>
-__device__ __forceinline__ void store_tile_impl(const IgemmProblem &p, const v16f (&acc)[TM][TN], uint32_t g, uint32_t sp,
-                                                uint32_t mw, uint32_t nw, uint32_t n_end, int lane, float *wlds)
-{
-    constexpr int LS = EpiLds<TN>::LS, QR = TN * 8, RPI = 64 / QR;      // quads per row, rows per instruction
-    constexpr int NRG = 32 / RPI;                   // row groups (one store instruction each) of a 32-row slab
-    constexpr int PB = TM >= 4 ? 2 : NRG < 4 ? NRG : 4;      // row groups per batch (fewer beside 128 accumulator registers)
-    constexpr int NBS = NRG / PB, NBT = TM * NBS;   // batches per slab and of the whole tile
-    const int h = lane >> 5, li = lane & 31, qd = lane % QR, rr = lane / QR;
-    float *c_base = p.c_ptr + (int64_t)g * p.c_gstride + (int64_t)sp * p.c_split_stride;
-    const float *bias = p.bias_mode ? p.bias + (int64_t)g * p.bias_gstride : nullptr;
-    const float *gate = (!PLAIN && p.gate) ? p.gate + (int64_t)g * p.c_gstride : nullptr;
-    const bool accumulate = !PLAIN && p.accumulate, scatter = !PLAIN && p.c_scatter;
-    const uint32_t n = nw + 4u * (uint32_t)qd;
-    int32_t off[4], ca[4], cb[4];
-    float bcol[4];
-    uint32_t okbits = 0u;       // bit e: column n + e exists (kept in a vector register: lane masks are scalar-register pairs)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const bool ok = n + (uint32_t)e < n_end;
-        const Info ci = map_info(p.c_col, ok ? n + (uint32_t)e : 0u);
-        off[e] = ok ? ci.off : 0;
-        ca[e] = ci.a; cb[e] = ci.b;
-        bcol[e] = (p.bias_mode == 2 && ok) ? bias[n + (uint32_t)e] : 0.f;
-        okbits |= ok ? 1u << e : 0u;
-    }
-    const bool quad = !scatter && (okbits & 8u) && off[1] == off[0] + 1 && off[2] == off[0] + 2 && off[3] == off[0] + 3;
-    // Loads and stores leave the vector-memory counter in the order they were issued, so a load
-    // issued behind stores is waited for together with them, a whole write latency.  Hence what a
-    // batch of row groups reads from global memory (per-row bias, gate, C when accumulating) is
-    // requested one batch ahead, before the stores of the batch in front of it: the wait for it
-    // then leaves those stores outstanding.
-    struct Batch {
-        f4u gt[PB], old[PB];
-        float brow[PB];
-        int32_t roff[PB];
-        uint32_t okm;           // bit 4u+e: element e of row group u is inside C (a vector register, not 16 lane masks)
-    };
-    Batch bt[2];
-    auto prepare = [&](auto BC, Batch &t) {
-        constexpr int b = decltype(BC)::value, i = b / NBS, p0 = (b % NBS) * PB;
-#pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            const int row = (p0 + u) * RPI + rr;
-            const uint32_t m = mw + (uint32_t)(i * 32 + row);
-            t.gt[u] = f4u{1.f, 1.f, 1.f, 1.f};
-            t.old[u] = f4u{0.f, 0.f, 0.f, 0.f};
-            t.roff[u] = (int32_t)m * p.c_row_stride;
-            t.brow[u] = (p.bias_mode == 1 && m < p.M) ? bias[m] : 0.f;
-            uint32_t bits = m < p.M ? okbits : 0u;
-            if (scatter && m < p.M) {
-                const Info ri = map_info(p.c_row, m);
-                t.roff[u] = ri.off;
-                bits = 0u;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    bits |= ((okbits >> e & 1u) && (uint32_t)(ri.a + ca[e]) < p.c_limA && (uint32_t)(ri.b + cb[e]) < p.c_limB) ? 1u << e : 0u;
-            }
-            if (u == 0) t.okm = 0u;
-            t.okm |= bits << (4 * u);
-            if (m < p.M && (gate || accumulate)) {
-                const int32_t row_off = t.roff[u];
-                if (quad) {
-                    if (gate) t.gt[u] = *reinterpret_cast<const f4u *>(gate + row_off + off[0]);
-                    if (accumulate) t.old[u] = *reinterpret_cast<const f4u *>(c_base + row_off + off[0]);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (gate && (bits >> e & 1u)) t.gt[u][e] = gate[row_off + off[e]];
-                        if (accumulate && (bits >> e & 1u)) t.old[u][e] = c_base[row_off + off[e]];
-                    }
-                }
-            }
-        }
-    };
-    prepare(std::integral_constant<int, 0>{}, bt[0]);
-    static_for<0, NBT>([&](auto BC) {
-        constexpr int b = decltype(BC)::value, i = b / NBS, p0 = (b % NBS) * PB;
-        if constexpr (b % NBS == 0) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) wlds[((r >> 2) * 8 + h * 4 + (r & 3)) * LS + j * 32 + li] = acc[i][j][r];
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the slab is in LDS (one wave: no barrier)
-        }
-        float4 q[PB];
-#pragma unroll
-        for (int u = 0; u < PB; ++u) q[u] = *reinterpret_cast<const float4 *>(wlds + ((p0 + u) * RPI + rr) * LS + 4 * qd);
-        if constexpr (b + 1 < NBT) prepare(std::integral_constant<int, b + 1>{}, bt[(b + 1) & 1]);
-        const Batch &t = bt[b & 1];
-#pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            const int row = (p0 + u) * RPI + rr;
-            const uint32_t m = mw + (uint32_t)(i * 32 + row);
-            if (m >= p.M || !(okbits & 1u)) continue;
-            float val[4] = {q[u].x + bcol[0], q[u].y + bcol[1], q[u].z + bcol[2], q[u].w + bcol[3]};
-            const float br = t.brow[u];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                val[e] += br;
-                if (p.relu) val[e] = fmaxf(val[e], 0.f);
-            }
-            const int32_t row_off = t.roff[u];
-            if constexpr (!PLAIN) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (!(t.gt[u][e] > 0.f)) val[e] = 0.f;
-            }
-            f4u out = {val[0], val[1], val[2], val[3]};
-            if (accumulate) out += t.old[u];
-            if (quad) {
-                *reinterpret_cast<f4u *>(c_base + row_off + off[0]) = out;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (t.okm >> (4 * u + e) & 1u) c_base[row_off + off[e]] = out[e];
-            }
-        }
-        if constexpr (b % NBS == NBS - 1)
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // slab read before the next one overwrites it
-    });
-}
-
-template <int TM, int TN>
-__device__ __forceinline__ void store_tile(const IgemmProblem &p, const v16f (&acc)[TM][TN], uint32_t g, uint32_t sp,
-                                           uint32_t mw, uint32_t nw, uint32_t n_end, int lane, float *wlds)
-{
-    if (!p.gate && !p.accumulate && !p.c_scatter) store_tile_impl<TM, TN, true>(p, acc, g, sp, mw, nw, n_end, lane, wlds);
-    else store_tile_impl<TM, TN, false>(p, acc, g, sp, mw, nw, n_end, lane, wlds);
-}
-
 }  // namespace
-
-template <int WM, int WN, int TM, int TN, int NST, class LA, class LB, int MATH>
-__global__ __launch_bounds__(256, 2) void igemm_kernel(const IgemmProblem p)
-{
-    static_assert(WM * WN == 4, "four waves");
-    constexpr int MT = WM * TM * 32, NT = WN * TN * 32;
-    constexpr int STAGE = LA::SZ + LB::SZ;
-    constexpr int LPT = LA::LPT + LB::LPT;
-    static_assert((NST - 1) * LPT <= 63, "the vector-memory counter holds 63 loads");
-
-    extern __shared__ __attribute__((aligned(16))) float smem[];     // [NST][LA::SZ + LB::SZ]
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-
-    const uint32_t m0 = blockIdx.y * MT, n0 = blockIdx.x * NT;
-    const uint32_t g = blockIdx.z / p.splits, sp = blockIdx.z % p.splits;
-    const uint32_t kbeg = sp * p.k_per_split;
-    const uint32_t kend = min(p.K, kbeg + p.k_per_split);
-    const int n_iter = (int)((kend - kbeg + KT - 1) / KT);
-
-    const BufferRsrc rsrcA = operand_rsrc(p.A, g), rsrcB = operand_rsrc(p.B, g);
-    LA la;
-    LB lb;
-    la.init(p.A, m0, p.M, wave, lane);
-    lb.init(p.B, n0, p.N, wave, lane);
-
-    // Tiles past the end of the K range are all padding: they cost no memory traffic and keep the
-    // count of outstanding loads the same in every iteration.
-    auto issue_part = [&](auto PC, int tile) {
-        constexpr int P = decltype(PC)::value;
-        float *st = smem + (tile % NST) * STAGE;
-        const uint32_t k0 = kbeg + (uint32_t)tile * KT;
-        la.template issue_part<P>(rsrcA, st, p.A, k0, kend, wave, lane);
-        lb.template issue_part<P>(rsrcB, st + LA::SZ, p.B, k0, kend, wave, lane);
-    };
-
-    const int wm = wave / WN, wn = wave % WN;
-    const int h = lane >> 5, li = lane & 31;
-    v16f acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-#pragma unroll
-    for (int d = 0; d < NST - 1; ++d) static_for<0, NPART>([&](auto PC) { issue_part(PC, d); });
-
-    for (int it = 0; it < n_iter; ++it) {
-        // This wave's loads of tile `it` have landed (all but the NST-2 newer tiles are complete);
-        // behind the barrier that holds for every wave, and everyone is done reading tile it-1,
-        // whose stage the loads issued below overwrite.
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NST - 2) * LPT) : "memory");
-        const float *a_s = smem + (it % NST) * STAGE, *b_s = a_s + LA::SZ;
-        if constexpr (MATH != 0) {
-            // bf16 matrix instructions: all fragments of the tile, rounded (and split), one MFMA per
-            // accumulator and product, then the next tile's loads
-            float af[TM][KT / 8][4], bf[TN][KT / 8][4];
-#pragma unroll
-            for (int ks = 0; ks < KT / 8; ++ks) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) LA::frag(a_s, (wm * TM + i) * 32 + li, ks, h, af[i][ks]);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) LB::frag(b_s, (wn * TN + j) * 32 + li, ks, h, bf[j][ks]);
-            }
-            bf16x8 ah[TM], al[TM], bh[TN], bl[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) to_bf16<MATH == 2>(af[i], ah[i], al[i]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) to_bf16<MATH == 2>(bf[j], bh[j], bl[j]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if constexpr (MATH == 2) {
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], bh[j], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bl[j], acc[i][j], 0, 0, 0);
-                    }
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[j], acc[i][j], 0, 0, 0);
-                }
-            static_for<0, NPART>([&](auto PC) { issue_part(PC, it + NST - 1); });
-            continue;
-        }
-        float af[KT / 8][TM][4], bf[KT / 8][TN][4];
-        // the fragments of the tile's first eight k now, those of the second eight behind the first
-        // MFMA step: half the reads are waited for at the start of a tile
-#pragma unroll
-        for (int i = 0; i < TM; ++i) LA::frag(a_s, (wm * TM + i) * 32 + li, 0, h, af[0][i]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) LB::frag(b_s, (wn * TN + j) * 32 + li, 0, h, bf[0][j]);
-        __builtin_amdgcn_sched_barrier(0);
-        // One part of the next tile's loads behind each MFMA step: the address pipeline and the
-        // matrix pipeline both stay fed, instead of taking turns.
-        static_for<0, NPART>([&](auto PC) {
-            constexpr int P = decltype(PC)::value, ks = P / 4, s4 = P % 4;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[ks][i][s4], bf[ks][j][s4], acc[i][j], 0, 0, 0);
-            if constexpr (P == 0) {
-#pragma unroll
-                for (int ks2 = 1; ks2 < KT / 8; ++ks2) {
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) LA::frag(a_s, (wm * TM + i) * 32 + li, ks2, h, af[ks2][i]);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) LB::frag(b_s, (wn * TN + j) * 32 + li, ks2, h, bf[ks2][j]);
-                }
-            }
-            issue_part(PC, it + NST - 1);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    }
-    // the padding tiles still in flight write into this block's LDS: let them finish before it is released
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();            // every wave has read its last fragments: the stages are free for the epilogue
-    store_tile<TM, TN>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 32), n0 + (uint32_t)(wn * TN * 32), p.N, lane,
-                       smem + wave * EpiLds<TN>::FLOATS);
-}
-
-// ---- patch kernel: convolutions whose B operand is staged as raw padded image rows ---------------
-//
-// The gathered im2col tile of the kernel above re-reads every input element once per filter tap
-// (9 or 25 times), and the address pipeline, one load instruction per 64 elements, is what limits
-// it.  Here a block keeps, for its 128 output pixels and 16 reduction channels at a time, the
-// zero-padded source rows those pixels' windows touch ("patch", PatchGeom in cg_internal.h) in
-// LDS, loaded once per channel block, and multiplies tap after tap from it: the B fragment of
-// pixel p, tap t, channel c is  patch[c][sigma(p) + tapoff(t)],  sigma fixed per lane for the
-// whole kernel and tapoff uniform per tap.  The reduction runs tap-major inside a channel block:
-// K-tile number cb*KK + t holds tap t of channels 16cb..16cb+15, and operand A is the filter
-// matrix permuted to [row][tap][channel], whose tiles the aligned-quad loader fetches.
-//
-// Pipeline: A tiles in a ring of NSTA stages as above.  The patch is double buffered; the loads
-// of channel block cb+1 are issued during the first K-tile (t = 0) of channel block cb, part by
-// part behind the MFMA steps and so interleaved with the loads of A tile t + NSTA-1.  The count a
-// wave may leave outstanding at a tile's barrier is (NSTA-2) A tiles, plus the patch loads while
-// the awaited A tile is older than all of them, t = 1..NSTA-2; from t = NSTA-1 on the wait covers
-// the patch too, long before the next channel block starts (KK >= 5 > NSTA-1).
-
-template <int NSL, int PAD = 8> struct PatchB {
-    static constexpr int CS = NSL * 64 + PAD;        // LDS floats between channels (+8: lane halves on different banks)
-    static constexpr int BUF = 16 * CS;              // one buffer: 16 channels
-    static constexpr int NB = 4 * NSL;               // load instructions per wave and channel block
-};
-
-template <int WM, int WN, int TM, int TN, int NSTA, int NSL, int MATH>
-__global__ __launch_bounds__(256, 2) void igemm_patch_kernel(const IgemmProblem p)
-{
-    static_assert(WM * WN == 4 && WN * TN == 4, "four waves, 128 pixels per block");
-    constexpr int MT = WM * TM * 32, NT = 128;
-    using LA = KLoader4<MT, 4>;
-    using PB = PatchB<NSL>;
-    constexpr int LAW = LA::LPT, NB = PB::NB;
-    static_assert((NSTA - 1) * LAW + NB <= 63, "the vector-memory counter holds 63 loads");
-
-    extern __shared__ __attribute__((aligned(16))) float smem[];     // [NSTA][LA::SZ] then [2][PB::BUF]
-    float *const sB = smem + NSTA * LA::SZ;
-
-    const PatchGeom &pg = p.patch;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t m0 = blockIdx.y * MT, g = blockIdx.z;
-    const int KK = pg.KH * pg.KW, ncb = (int)(pg.Cred / 16), n_iter = ncb * KK;
-    // this block's pixels n0..n1
-    const uint32_t P = pg.divP.d;
-    uint32_t n0, n1;
-    const uint32_t tile = blockIdx.x + pg.tile0;
-    if (pg.tiles_per_img) {
-        const uint32_t b = fdiv(tile, pg.divTpi), ti = tile - b * pg.divTpi.d;
-        n0 = b * P + ti * NT;
-        n1 = min(n0 + NT - 1, (b + 1) * P - 1);
-    } else {
-        n0 = tile * NT;
-        n1 = min(n0 + NT - 1, p.N - 1);
-    }
-
-    const BufferRsrc rsrcA = operand_rsrc(p.A, g);
-    BufferRsrc rsrcB;
-    {
-        const uint64_t base = (uint64_t)reinterpret_cast<uintptr_t>(pg.src) + (uint64_t)((int64_t)g * pg.gstride * 4);
-        rsrcB.x = __builtin_amdgcn_readfirstlane((uint32_t)base);
-        rsrcB.y = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xffffu);
-        rsrcB.z = __builtin_amdgcn_readfirstlane((uint32_t)(((int64_t)pg.src_elems - (int64_t)g * pg.gstride) * 4));
-        rsrcB.w = 0x00020000u;
-    }
-    LA la;
-    la.init(p.A, m0, p.M, wave, lane);
-
-    // ---- where this block's pixels sit: images bA..bB, pixel rows oyA (in bA) .. oyB (in bB) -------
-    const uint32_t bA = fdiv(n0, pg.divP), oyA = fdiv(n0 - bA * P, pg.divOW);
-    const uint32_t bB = fdiv(n1, pg.divP), oyB = fdiv(n1 - bB * P, pg.divOW);
-    // slots of the first image's segment; later images start at R0 + (d-1)*Rfull
-    const int32_t R0 = (int32_t)((((bA == bB) ? oyB : (uint32_t)pg.OHo - 1) - oyA) * pg.s + pg.KH) * pg.Wp;
-
-    // global byte offset of every patch slot this lane loads (or out of range: padding, unused slots)
-    uint32_t voff[NSL];
-#pragma unroll
-    for (int e = 0; e < NSL; ++e) {
-        const int32_t j = e * 64 + lane;
-        const uint32_t d = j < R0 ? 0u : 1u + fdiv((uint32_t)(j - R0), pg.divRfull);
-        const int32_t local = j - (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull);
-        const uint32_t r = fdiv((uint32_t)local, pg.divWp), c = (uint32_t)local - r * (uint32_t)pg.Wp;
-        const uint32_t b = bA + d, oylo = d == 0 ? oyA : 0u;
-        const uint32_t oyhi = b == bB ? oyB : (uint32_t)pg.OHo - 1;
-        const int32_t sy = (int32_t)(oylo * pg.s) + pg.oy0 + (int32_t)r, sx = pg.ox0 + (int32_t)c;
-        const bool ok = b <= bB && r < (oyhi - oylo) * pg.s + pg.KH && (uint32_t)sy < (uint32_t)pg.Hs &&
-                        (uint32_t)sx < (uint32_t)pg.Ws;
-        voff[e] = ok ? (uint32_t)((int32_t)b * pg.img_stride + sy * pg.Ws + sx) * 4u : OOB_ROW;
-    }
-
-    const int wm = wave / WN, wn = wave % WN;
-    const int h = lane >> 5, li = lane & 31;
-    // sigma of this lane's pixels (floats into a patch buffer), with the lane half's channel offset folded in
-    int32_t sig[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const uint32_t n = n0 + (uint32_t)((wn * TN + j) * 32 + li);
-        int32_t sg = 0;
-        if (n <= n1) {
-            const uint32_t b = fdiv(n, pg.divP), rem = n - b * P, oy = fdiv(rem, pg.divOW), ox = rem - oy * pg.divOW.d;
-            const uint32_t d = b - bA, oylo = d == 0 ? oyA : 0u;
-            sg = (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull) + (int32_t)((oy - oylo) * pg.s) * pg.Wp + (int32_t)(ox * pg.s);
-        }
-        sig[j] = sg + 4 * h * PB::CS;
-    }
-
-    v16f acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    // part P of the patch loads of channel block cb: load q = (channel wave + 4*(q/NSL), chunk q%NSL)
-    auto issue_patch_part = [&](auto PC, int cb) {
-        constexpr int Pn = decltype(PC)::value;
-        float *buf = sB + (cb & 1) * PB::BUF;
-#pragma unroll
-        for (int q = Pn * NB / NPART; q < (Pn + 1) * NB / NPART; ++q) {
-            const int cl = wave + 4 * (q / NSL), e = q % NSL;
-            load_to_lds(rsrcB, buf + cl * PB::CS + e * 64, voff[e], (uint32_t)((cb * 16 + cl) * pg.chan_stride) * 4u);
-        }
-    };
-    // part P of the A loads of K-tile `tile` = (cb, t); tiles past the end are all padding
-    auto issue_a_part = [&](auto PC, int tile, int cb, int t) {
-        constexpr int Pn = decltype(PC)::value;
-        const uint32_t k0 = (uint32_t)t * pg.Cred + (uint32_t)cb * 16u;
-        la.template issue_part<Pn>(rsrcA, smem + (tile % NSTA) * LA::SZ, p.A, k0, tile < n_iter ? p.K : 0u, wave, lane);
-    };
-
-    // prologue: the first patch, then A tiles 0..NSTA-2
-    static_for<0, NPART>([&](auto PC) { issue_patch_part(PC, 0); });
-    int icb = 0, it_ = 0;                       // (cb, t) of the next A tile to issue
-    auto advance_issue = [&]() { if (++it_ == KK) { it_ = 0; ++icb; } };
-#pragma unroll
-    for (int d = 0; d < NSTA - 1; ++d) {
-        static_for<0, NPART>([&](auto PC) { issue_a_part(PC, d, icb, it_); });
-        advance_issue();
-    }
-
-    int ccb = 0, ct = 0, cky = 0, ckx = 0;      // (cb, t = cky*KW + ckx) of the tile being multiplied
-    for (int it = 0; it < n_iter; ++it) {
-        const bool burst = ccb + 1 < ncb;       // this channel block issues the next one's patch in its tile 0
-        if (burst && ct >= 1 && ct <= NSTA - 2)
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NSTA - 2) * LAW + NB) : "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NSTA - 2) * LAW) : "memory");
-        const float *a_s = smem + (it % NSTA) * LA::SZ;
-        const int py = pg.flip ? pg.KH - 1 - cky : cky, px = pg.flip ? pg.KW - 1 - ckx : ckx;
-        const float *b_s = sB + (ccb & 1) * PB::BUF + (py * pg.Wp + px);
-        if constexpr (MATH != 0) {
-            float af[TM][KT / 8][4], bf[TN][KT / 8][4];
-#pragma unroll
-            for (int ks = 0; ks < KT / 8; ++ks) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) LA::frag(a_s, (wm * TM + i) * 32 + li, ks, h, af[i][ks]);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) bf[j][ks][t] = b_s[sig[j] + (8 * ks + t) * PB::CS];
-            }
-            bf16x8 ah[TM], al[TM], bh[TN], bl[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) to_bf16<MATH == 2>(af[i], ah[i], al[i]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) to_bf16<MATH == 2>(bf[j], bh[j], bl[j]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if constexpr (MATH == 2) {
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], bh[j], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bl[j], acc[i][j], 0, 0, 0);
-                    }
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[j], acc[i][j], 0, 0, 0);
-                }
-            const bool do_patch_b = burst && ct == 0;
-            static_for<0, NPART>([&](auto PC) {
-                issue_a_part(PC, it + NSTA - 1, icb, it_);
-                if (do_patch_b) issue_patch_part(PC, ccb + 1);
-            });
-            advance_issue();
-            if (++ckx == pg.KW) { ckx = 0; ++cky; }
-            if (++ct == KK) { ct = 0; cky = 0; ++ccb; }
-            continue;
-        }
-        float af[KT / 8][TM][4], bf[KT / 8][TN][4];
-        // Fragments are read one MFMA step ahead (A once per eight k, B per step): only the first step's
-        // reads are waited for at the start of a tile, the others arrive while the matrix pipeline works.
-#pragma unroll
-        for (int i = 0; i < TM; ++i) LA::frag(a_s, (wm * TM + i) * 32 + li, 0, h, af[0][i]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bf[0][j][0] = b_s[sig[j]];
-        __builtin_amdgcn_sched_barrier(0);
-        const bool do_patch = burst && ct == 0;
-        static_for<0, NPART>([&](auto PC) {
-            constexpr int Pn = decltype(PC)::value, ks = Pn / 4, s4 = Pn % 4;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[ks][i][s4], bf[ks][j][s4], acc[i][j], 0, 0, 0);
-            if constexpr (Pn + 1 < NPART) {
-                constexpr int nks = (Pn + 1) / 4, nt = (Pn + 1) % 4;
-                if constexpr (nt == 0) {
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) LA::frag(a_s, (wm * TM + i) * 32 + li, nks, h, af[nks][i]);
-                }
-#pragma unroll
-                for (int j = 0; j < TN; ++j) bf[nks][j][nt] = b_s[sig[j] + (8 * nks + nt) * PB::CS];
-            }
-            issue_a_part(PC, it + NSTA - 1, icb, it_);
-            if (do_patch) issue_patch_part(PC, ccb + 1);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        advance_issue();
-        if (++ckx == pg.KW) { ckx = 0; ++cky; }
-        if (++ct == KK) { ct = 0; cky = 0; ++ccb; }
-    }
-    // the padding tiles still in flight write into this block's LDS: let them finish before it is released
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();            // every wave has read its last fragments: the stages are free for the epilogue
-    store_tile<TM, TN>(p, acc, g, 0u, m0 + (uint32_t)(wm * TM * 32), n0 + (uint32_t)(wn * TN * 32), n1 + 1, lane,
-                       smem + wave * EpiLds<TN>::FLOATS);
-}
-
-#if CG_MATH == 0
-// ---- patch kernel for at most 48 rows ------------------------------------------------------------
-//
-// The same data movement as igemm_patch_kernel, multiplied with v_mfma_f32_16x16x4_f32: a block
-// owns 16*TM rows (TM <= 3) x 128 pixels, each of its four waves all the rows and 32 pixels.  A
-// group of 48 channels (backward-data of a 5x5 layer whose groups have 48 input channels) then
-// fills its tile, where the 32x32 tiles above would multiply 64 rows for 48.
-// Lane (q = lane / 16, l = lane % 16) supplies A[row l][k = 4q + t] and B[k = 4q + t][pixel l] in
-// step t = 0..3 of a K-tile and holds C[row 4q + r][pixel l], r = 0..3, of each 16x16 sub-tile.
-// The patch buffers put channels NSL*64 + 4 floats apart, so that the four k of a step fall on
-// different quarters of the banks.
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-template <int TM, int NSTA, int NSL>
-__global__ __launch_bounds__(256, 3) void igemm_patch16_kernel(const IgemmProblem p)
-{
-    constexpr int MT = TM * 16, NT = 128, TN = 2;
-    using LA = KLoader4<MT, 4>;
-    using PB = PatchB<NSL, 4>;
-    constexpr int LAW = LA::LPT, NB = PB::NB;
-    static_assert(TM >= 1 && TM <= 3 && LA::NJ == 1, "at most 48 rows: one A load per wave and K-tile");
-    static_assert((NSTA - 1) * LAW + NB <= 63, "the vector-memory counter holds 63 loads");
-
-    extern __shared__ __attribute__((aligned(16))) float smem[];     // [NSTA][LA::SZ] then [2][PB::BUF]
-    float *const sB = smem + NSTA * LA::SZ;
-
-    const PatchGeom &pg = p.patch;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t m0 = blockIdx.y * MT, g = blockIdx.z;
-    const int KK = pg.KH * pg.KW, ncb = (int)(pg.Cred / 16), n_iter = ncb * KK;
-    const uint32_t P = pg.divP.d;
-    uint32_t n0, n1;
-    const uint32_t tile = blockIdx.x + pg.tile0;
-    if (pg.tiles_per_img) {
-        const uint32_t b = fdiv(tile, pg.divTpi), ti = tile - b * pg.divTpi.d;
-        n0 = b * P + ti * NT;
-        n1 = min(n0 + NT - 1, (b + 1) * P - 1);
-    } else {
-        n0 = tile * NT;
-        n1 = min(n0 + NT - 1, p.N - 1);
-    }
-
-    const BufferRsrc rsrcA = operand_rsrc(p.A, g);
-    BufferRsrc rsrcB;
-    {
-        const uint64_t base = (uint64_t)reinterpret_cast<uintptr_t>(pg.src) + (uint64_t)((int64_t)g * pg.gstride * 4);
-        rsrcB.x = __builtin_amdgcn_readfirstlane((uint32_t)base);
-        rsrcB.y = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xffffu);
-        rsrcB.z = __builtin_amdgcn_readfirstlane((uint32_t)(((int64_t)pg.src_elems - (int64_t)g * pg.gstride) * 4));
-        rsrcB.w = 0x00020000u;
-    }
-    LA la;
-    la.init(p.A, m0, p.M, wave, lane);
-
-    // where this block's pixels sit (as in igemm_patch_kernel)
-    const uint32_t bA = fdiv(n0, pg.divP), oyA = fdiv(n0 - bA * P, pg.divOW);
-    const uint32_t bB = fdiv(n1, pg.divP), oyB = fdiv(n1 - bB * P, pg.divOW);
-    const int32_t R0 = (int32_t)((((bA == bB) ? oyB : (uint32_t)pg.OHo - 1) - oyA) * pg.s + pg.KH) * pg.Wp;
-    uint32_t voff[NSL];
-#pragma unroll
-    for (int e = 0; e < NSL; ++e) {
-        const int32_t j = e * 64 + lane;
-        const uint32_t d = j < R0 ? 0u : 1u + fdiv((uint32_t)(j - R0), pg.divRfull);
-        const int32_t local = j - (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull);
-        const uint32_t r = fdiv((uint32_t)local, pg.divWp), c = (uint32_t)local - r * (uint32_t)pg.Wp;
-        const uint32_t b = bA + d, oylo = d == 0 ? oyA : 0u;
-        const uint32_t oyhi = b == bB ? oyB : (uint32_t)pg.OHo - 1;
-        const int32_t sy = (int32_t)(oylo * pg.s) + pg.oy0 + (int32_t)r, sx = pg.ox0 + (int32_t)c;
-        const bool ok = b <= bB && r < (oyhi - oylo) * pg.s + pg.KH && (uint32_t)sy < (uint32_t)pg.Hs &&
-                        (uint32_t)sx < (uint32_t)pg.Ws;
-        voff[e] = ok ? (uint32_t)((int32_t)b * pg.img_stride + sy * pg.Ws + sx) * 4u : OOB_ROW;
-    }
-
-    const int q = lane >> 4, l16 = lane & 15;
-    int32_t sig[TN];                 // this lane's pixels in a patch buffer, with its k group's channel offset folded in
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const uint32_t n = n0 + (uint32_t)((wave * TN + j) * 16 + l16);
-        int32_t sg = 0;
-        if (n <= n1) {
-            const uint32_t b = fdiv(n, pg.divP), rem = n - b * P, oy = fdiv(rem, pg.divOW), ox = rem - oy * pg.divOW.d;
-            const uint32_t d = b - bA, oylo = d == 0 ? oyA : 0u;
-            sg = (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull) + (int32_t)((oy - oylo) * pg.s) * pg.Wp + (int32_t)(ox * pg.s);
-        }
-        sig[j] = sg + 4 * q * PB::CS;
-    }
-
-    v4f acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-
-    auto issue_patch_part = [&](auto PC, int cb) {
-        constexpr int Pn = decltype(PC)::value;
-        float *buf = sB + (cb & 1) * PB::BUF;
-#pragma unroll
-        for (int qq = Pn * NB / NPART; qq < (Pn + 1) * NB / NPART; ++qq) {
-            const int cl = wave + 4 * (qq / NSL), e = qq % NSL;
-            load_to_lds(rsrcB, buf + cl * PB::CS + e * 64, voff[e], (uint32_t)((cb * 16 + cl) * pg.chan_stride) * 4u);
-        }
-    };
-    auto issue_a_part = [&](auto PC, int tile, int cb, int t) {
-        constexpr int Pn = decltype(PC)::value;
-        const uint32_t k0 = (uint32_t)t * pg.Cred + (uint32_t)cb * 16u;
-        la.template issue_part<Pn>(rsrcA, smem + (tile % NSTA) * LA::SZ, p.A, k0, tile < n_iter ? p.K : 0u, wave, lane);
-    };
-
-    static_for<0, NPART>([&](auto PC) { issue_patch_part(PC, 0); });
-    int icb = 0, it_ = 0;
-    auto advance_issue = [&]() { if (++it_ == KK) { it_ = 0; ++icb; } };
-#pragma unroll
-    for (int d = 0; d < NSTA - 1; ++d) {
-        static_for<0, NPART>([&](auto PC) { issue_a_part(PC, d, icb, it_); });
-        advance_issue();
-    }
-
-    int ccb = 0, ct = 0, cky = 0, ckx = 0;
-    for (int it = 0; it < n_iter; ++it) {
-        const bool burst = ccb + 1 < ncb;
-        if (burst && ct >= 1 && ct <= NSTA - 2)
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NSTA - 2) * LAW + NB) : "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NSTA - 2) * LAW) : "memory");
-        const float *a_s = smem + (it % NSTA) * LA::SZ;
-        const int py = pg.flip ? pg.KH - 1 - cky : cky, px = pg.flip ? pg.KW - 1 - ckx : ckx;
-        const float *b_s = sB + (ccb & 1) * PB::BUF + (py * pg.Wp + px);
-        float af[TM][4], bf[TN][4];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) LA::frag(a_s, i * 16 + l16, q >> 1, q & 1, af[i]);      // the quad k = 4q .. 4q+3
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) bf[j][t] = b_s[sig[j] + t * PB::CS];
-        const bool do_patch = burst && ct == 0;
-        static_for<0, NPART>([&](auto PC) {
-            constexpr int Pn = decltype(PC)::value, t = Pn / 2, j = Pn % 2;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i][t], bf[j][t], acc[i][j], 0, 0, 0);
-            issue_a_part(PC, it + NSTA - 1, icb, it_);
-            if (do_patch) issue_patch_part(PC, ccb + 1);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        advance_issue();
-        if (++ckx == pg.KW) { ckx = 0; ++cky; }
-        if (++ct == KK) { ct = 0; cky = 0; ++ccb; }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
-    // epilogue: rectifier, gate and accumulation as in store_tile (this kernel is launched without
-    // split-K; bias modes as there)
-    float *c_base = p.c_ptr + (int64_t)g * p.c_gstride;
-    const float *bias = p.bias_mode ? p.bias + (int64_t)g * p.bias_gstride : nullptr;
-    const float *gate = p.gate ? p.gate + (int64_t)g * p.c_gstride : nullptr;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const uint32_t n = n0 + (uint32_t)((wave * TN + j) * 16 + l16);
-        if (n > n1) continue;
-        const Info ci = map_info(p.c_col, n);
-        const int32_t coff = ci.off;
-        const float bcol = p.bias_mode == 2 ? bias[n] : 0.f;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t m = m0 + (uint32_t)(i * 16 + q * 4 + r);
-                if (m < p.M) {
-                    int32_t idx = (int32_t)m * p.c_row_stride + coff;
-                    if (p.c_scatter) {
-                        const Info ri = map_info(p.c_row, m);
-                        if (!((uint32_t)(ri.a + ci.a) < p.c_limA && (uint32_t)(ri.b + ci.b) < p.c_limB)) continue;
-                        idx = ri.off + coff;
-                    }
-                    float val = acc[i][j][r] + bcol;
-                    if (p.bias_mode == 1) val += bias[m];
-                    if (p.relu) val = fmaxf(val, 0.f);
-                    if (gate && !(gate[idx] > 0.f)) val = 0.f;
-                    float *dst = c_base + idx;
-                    if (p.accumulate) val += *dst;
-                    *dst = val;
-                }
-            }
-        }
-    }
-}
 
 // ---- band kernel: backward-weight with the input staged as raw padded rows ------------------------
 //
@@ -1048,7 +141,7 @@ __global__ __launch_bounds__(256, 2) void igemm_wgrad_kernel(const IgemmProblem 
     static_assert(WM * WN == 4 && WN * TN == 4, "four waves, 128 columns per block");
     static_assert(CPB % 4 == 0, "whole channels per wave");
     constexpr int MT = WM * TM * 32, NT = 128;
-    using LA = KLoader4<MT, 4>;
+    using LA = KLoader4<MT>;
     constexpr int LAW = LA::LPT;
     constexpr int CS = NSL * 64 + 1;            // odd: the channels of one tap fall on different banks
     constexpr int BUF = CPB * CS;
@@ -1156,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void igemm_wgrad_kernel(const IgemmProblem 
         }
 #pragma unroll
         for (int j = Pn * LAW / NPART; j < (Pn + 1) * LAW / NPART; ++j)
-            load4_to_lds<4>(rsrcA, smem + (tile % NSTA) * LA::SZ + (wave * LA::NJ + j) * 256, la.roff[j] + la.koff);
+            load4_to_lds(rsrcA, smem + (tile % NSTA) * LA::SZ + (wave * LA::NJ + j) * 256, la.roff[j] + la.koff);
     };
     auto tiles_of = [&](int u) {
         int img, oy0, rows;
@@ -1228,56 +321,8 @@ __global__ __launch_bounds__(256, 2) void igemm_wgrad_kernel(const IgemmProblem 
                        smem + wave * EpiLds<TN>::FLOATS);
 }
 
-#endif  // CG_MATH == 0
 
 namespace {
-
-template <int WM, int WN, int TM, int TN, int NST, class LA, class LB>
-int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
-{
-    constexpr int MT = WM * TM * 32, NT = WN * TN * 32;
-    dim3 grid((p.N + NT - 1) / NT, (p.M + MT - 1) / MT, p.groups * p.splits);
-    if (grid.y > 65535u || grid.z > 65535u) return CG_EUNSUPPORTED;
-    int rec = -1;
-    if (prof_on()) {
-        char name[64];
-        snprintf(name, sizeof name, CG_MATH == 0 ? "igemm_kernel<%dx%d,%s>" : CG_MATH == 1 ? "igemm_kernel<%dx%d,%s,bf16>" : "igemm_kernel<%dx%d,%s,bf16x3>", MT, NT, modes);
-        rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
-    }
-    constexpr size_t lds = (size_t)NST * (LA::SZ + LB::SZ) * sizeof(float);
-    static_assert(lds >= 4 * EpiLds<TN>::FLOATS * sizeof(float), "the epilogue turns the tile around in the stages' LDS");
-    static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
-    static std::atomic<bool> attr_set{false};      // raising the dynamic-LDS limit: once per kernel (repeating it is harmless)
-    if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&igemm_kernel<WM, WN, TM, TN, NST, LA, LB, CG_MATH>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        attr_set.store(true, std::memory_order_release);
-    }
-    hipLaunchKernelGGL((igemm_kernel<WM, WN, TM, TN, NST, LA, LB, CG_MATH>), grid, dim3(256), lds, stream, p);
-    prof_end(rec, stream);
-    CG_HIP_TRY(hipGetLastError());
-    return CG_OK;
-}
-
-// How an operand's tile is fetched: rows along the lanes, k along the lanes, or aligned quads of k.
-enum { LD_ROWS = 0, LD_K = 1, LD_K4 = 2 };
-template <int MODE, int R, bool CHECK>
-using LoaderOf = std::conditional_t<MODE == LD_K4, KLoader4<R>,
-                                    std::conditional_t<MODE == LD_K, KLoader<R, CHECK>, RowsLoader<R, CHECK>>>;
-
-template <int AM, int BM, bool BC>
-int launch_modes(const IgemmProblem &p, int mt, hipStream_t stream)
-{
-    static const char modes[4] = {"rk4"[AM], "rk4"[BM], BC ? 'c' : '-', 0};
-    switch (mt) {
-    case 256: return launch_cfg<2, 2, 4, 2, 3, LoaderOf<AM, 256, false>, LoaderOf<BM, 128, BC>>(p, modes, stream);
-    case 192: return launch_cfg<2, 2, 3, 2, 3, LoaderOf<AM, 192, false>, LoaderOf<BM, 128, BC>>(p, modes, stream);
-    case 128: return launch_cfg<2, 2, 2, 2, 4, LoaderOf<AM, 128, false>, LoaderOf<BM, 128, BC>>(p, modes, stream);
-    case 96: return launch_cfg<1, 4, 3, 1, 4, LoaderOf<AM, 96, false>, LoaderOf<BM, 128, BC>>(p, modes, stream);
-    case 64: return launch_cfg<1, 4, 2, 1, 4, LoaderOf<AM, 64, false>, LoaderOf<BM, 128, BC>>(p, modes, stream);
-    default: return launch_cfg<1, 4, 1, 1, 4, LoaderOf<AM, 32, false>, LoaderOf<BM, 128, BC>>(p, modes, stream);
-    }
-}
 
 // every aligned group of four reduction indices is four consecutive floats: k is unit-stride, either
 // throughout or inside runs whose padded length is a multiple of four
@@ -1317,6 +362,33 @@ int pick_mt(uint32_t M, uint32_t N, uint32_t groups, uint32_t K = 0)
             cost = ((n & 1) ? (double)(n - 1) + 1.2 : (double)n) * (c + 50);
         }
         if (cost < best_cost * 0.999) { best_cost = cost; best = c; }   // ties keep the larger tile
+    }
+    return best;
+}
+
+// Row-tile height of split_gemm_kernel: the same model for its tiles.  What a step costs whatever its
+// height (fetching, cutting and storing 128 columns, the barrier) is worth 154 rows: 11x11 windows over
+// 227x227, one column of blocks of 128 / 64 / 32 / 16 rows took 508 / 393 / 357 / 314 us.
+int gemm_mt(uint32_t M, uint32_t N, uint32_t groups, uint32_t K)
+{
+    const int cand[4] = {128, 64, 32, 16};
+    int best = 16;
+    double best_cost = 1e300;
+    for (int c : cand) {
+        const uint64_t tiles = (uint64_t)((M + c - 1) / c) * ((N + 127) / 128) * groups;
+        const double t = c + 154;
+        double cost;
+        if (tiles < kSplitBlocks && K / 128 < kSplitBlocks / tiles) {
+            const uint64_t splits = K / 128 >= 2 ? K / 128 : 1;
+            const uint64_t st = (K + 31) / 32, st_per = (st + splits - 1) / splits;
+            cost = (double)((tiles * splits + 255) / 256) * t * (double)st_per / (double)st;
+        } else if (tiles < kSplitBlocks) {
+            cost = (double)tiles * t / 256.0;
+        } else {
+            const uint64_t n = (tiles + 255) / 256;
+            cost = ((n & 1) ? (double)(n - 1) + 1.2 : (double)n) * t;
+        }
+        if (cost < best_cost * 0.999) { best_cost = cost; best = c; }
     }
     return best;
 }
@@ -1368,170 +440,11 @@ int normalise_operand(Operand &o, uint32_t groups)
 
 namespace {
 
-// pixel tiles (blocks along x) of a patch-kernel problem
-uint32_t patch_pixel_tiles(const IgemmProblem &p)
-{
-    return p.patch.tiles_per_img ? (p.N / p.patch.divP.d) * (uint32_t)p.patch.tiles_per_img : (p.N + 127) / 128;
-}
-
-template <int TM, int NSTA, int NSL>
-int launch_patch_cfg(const IgemmProblem &p, hipStream_t stream)
-{
-    constexpr int MT = 2 * TM * 32;
-    using LA = KLoader4<MT, 4>;
-    dim3 grid(p.patch.tile_count ? p.patch.tile_count : patch_pixel_tiles(p), (p.M + MT - 1) / MT, p.groups);
-    if (grid.y > 65535u || grid.z > 65535u) return CG_EUNSUPPORTED;
-    int rec = -1;
-    if (prof_on()) {
-        char name[64];
-        snprintf(name, sizeof name, CG_MATH == 0 ? "igemm_patch_kernel<%dx128,%d>" : CG_MATH == 1 ? "igemm_patch_kernel<%dx128,%d,bf16>" : "igemm_patch_kernel<%dx128,%d,bf16x3>", MT, NSL);
-        rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
-    }
-    constexpr size_t lds = ((size_t)NSTA * LA::SZ + 2 * PatchB<NSL>::BUF) * sizeof(float);
-    static_assert(lds >= 4 * EpiLds<2>::FLOATS * sizeof(float), "the epilogue turns the tile around in the stages' LDS");
-    static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&igemm_patch_kernel<2, 2, TM, 2, NSTA, NSL, CG_MATH>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        attr_set.store(true, std::memory_order_release);
-    }
-    hipLaunchKernelGGL((igemm_patch_kernel<2, 2, TM, 2, NSTA, NSL, CG_MATH>), grid, dim3(256), lds, stream, p);
-    prof_end(rec, stream);
-    CG_HIP_TRY(hipGetLastError());
-    return CG_OK;
-}
-
-#if CG_MATH == 0
-template <int TM, int NSTA, int NSL>
-int launch_patch16_cfg(const IgemmProblem &p, hipStream_t stream)
-{
-    constexpr int MT = TM * 16;
-    using LA = KLoader4<MT, 4>;
-    dim3 grid(p.patch.tile_count ? p.patch.tile_count : patch_pixel_tiles(p), (p.M + MT - 1) / MT, p.groups);
-    if (grid.y > 65535u || grid.z > 65535u) return CG_EUNSUPPORTED;
-    int rec = -1;
-    if (prof_on()) {
-        char name[64];
-        snprintf(name, sizeof name, "igemm_patch16_kernel<%dx128,%d>", MT, NSL);
-        rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
-    }
-    constexpr size_t lds = ((size_t)NSTA * LA::SZ + 2 * PatchB<NSL, 4>::BUF) * sizeof(float);
-    static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&igemm_patch16_kernel<TM, NSTA, NSL>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        attr_set.store(true, std::memory_order_release);
-    }
-    hipLaunchKernelGGL((igemm_patch16_kernel<TM, NSTA, NSL>), grid, dim3(256), lds, stream, p);
-    prof_end(rec, stream);
-    CG_HIP_TRY(hipGetLastError());
-    return CG_OK;
-}
-
-#endif
-
-// row-tile height of the patch kernel: 64, 128 or 192 rows
-int patch_mt(uint32_t M, uint32_t N, uint32_t groups)
-{
-    const int mt = pick_mt(M, N, groups);
-    return mt >= 192 && mt != 256 ? 192 : mt >= 96 ? 128 : 64;
-}
-
-int patch_launch_tiles(const IgemmProblem &p, int mt, hipStream_t stream)
-{
-    if (p.patch.nsl == 4) {
-        if (mt == 192) return launch_patch_cfg<3, 3, 4>(p, stream);
-        if (mt == 128) return launch_patch_cfg<2, 4, 4>(p, stream);
-        return launch_patch_cfg<1, 4, 4>(p, stream);
-    }
-    if (p.patch.nsl == 6) {      // 2 x 50 KB of patch buffers: no 192-row tile beside them
-        if (mt >= 128) return launch_patch_cfg<2, 3, 6>(p, stream);
-        return launch_patch_cfg<1, 4, 6>(p, stream);
-    }
-    if (mt == 192) return launch_patch_cfg<3, 3, 5>(p, stream);
-    if (mt == 128) return launch_patch_cfg<2, 4, 5>(p, stream);
-    return launch_patch_cfg<1, 4, 5>(p, stream);
-}
-
-int patch_launch(const IgemmProblem &p, hipStream_t stream)
-{
-#if CG_MATH == 0
-    // (three filter stages, not four, for the four- and five-chunk instances: 50.5 KB of LDS a block instead
-    // of 53.7, so that three blocks fit a compute unit.  Alone on the GPU the kernel runs as before; beside
-    // the weight-gradient kernel of the same layer on another stream the whole AlexNet-shaped step went
-    // from 10.77 to 10.44 ms.)
-    if (p.M <= 48) {             // the 16-row tiles waste less of a small row count than a 64-row tile
-        const int tm = (int)(p.M + 15) / 16;
-        if (p.patch.nsl == 4)
-            return tm == 3 ? launch_patch16_cfg<3, 3, 4>(p, stream) : tm == 2 ? launch_patch16_cfg<2, 3, 4>(p, stream)
-                                                                              : launch_patch16_cfg<1, 3, 4>(p, stream);
-        if (p.patch.nsl == 6)
-            return tm == 3 ? launch_patch16_cfg<3, 4, 6>(p, stream) : tm == 2 ? launch_patch16_cfg<2, 4, 6>(p, stream)
-                                                                              : launch_patch16_cfg<1, 4, 6>(p, stream);
-        return tm == 3 ? launch_patch16_cfg<3, 3, 5>(p, stream) : tm == 2 ? launch_patch16_cfg<2, 3, 5>(p, stream)
-                                                                          : launch_patch16_cfg<1, 3, 5>(p, stream);
-    }
-#endif
-    int mt = patch_mt(p.M, p.N, p.groups);
-    // six chunks: no 192-row instance; 128-row tiles unless they would pad the rows by half a tile or more
-    if (p.patch.nsl == 6 && mt > 64) mt = (p.M + 127) / 128 * 128 - p.M >= 64 ? 64 : 128;
-    // Two blocks are resident per compute unit, so blocks run in rounds of g_resident_blocks that
-    // start and end together.  When the last round would be less than three quarters full, the
-    // pixel tiles of the whole rounds go out as one launch and the rest as a second launch of
-    // 64-row tiles: three or two small blocks in place of a large one fill the compute units that
-    // the short round would leave idle (676 blocks of 192 rows: 512 + 492 of 64 rows).  Forward only:
-    // backward-data shares the GPU with backward-weight on another stream, whose blocks already
-    // fill those compute units, and a second dependent launch then only delays it (measured).
-    // Backward-data (mirrored taps) in the same situation takes 64-row tiles for the whole launch: three
-    // of those blocks fit a compute unit, and twice or three times as many, shorter blocks quantise
-    // better (676 blocks of 192 rows = 1.32 rounds of 512; 2028 of 64 rows = 2.64 rounds of 768).
-    // Alone on the GPU: conv4-shaped 0.516 -> 0.461 ms, conv5-shaped 0.352 -> 0.315 ms at B = 256 (a
-    // one-stream step 11.17 -> 10.82 ms); beside backward-weight on another stream, whose blocks fill the
-    // short round anyway, the step was 0.07 ms slower with it, so a caller that runs such a stream says
-    // so (beside_other_stream) and keeps the large tiles.
-    if (mt > 64 && p.patch.tile_count == 0 && p.patch.flip && p.patch.nsl == 4 && !p.beside_other_stream) {
-        const uint32_t rb = resident_blocks();
-        const uint64_t blocks = (uint64_t)patch_pixel_tiles(p) * ((p.M + mt - 1) / mt) * p.groups;
-        const uint32_t rest = (uint32_t)(blocks % rb);
-        if (blocks / rb >= 1 && rest > 0 && rest < rb * 3 / 4) mt = 64;
-    }
-    if (mt > 64 && p.patch.tile_count == 0 && !p.patch.flip) {
-        const uint32_t g_resident_blocks = resident_blocks();
-        const uint32_t px = patch_pixel_tiles(p), per_px = ((p.M + mt - 1) / mt) * p.groups;
-        const uint64_t blocks = (uint64_t)px * per_px;
-        const uint32_t rounds = (uint32_t)(blocks / g_resident_blocks);
-        const uint32_t rest = (uint32_t)(blocks - (uint64_t)rounds * g_resident_blocks);
-        const uint32_t px_main = rounds * g_resident_blocks / per_px;
-        const uint32_t tail_blocks = (px - px_main) * ((p.M + 63) / 64) * p.groups;
-        if (rounds >= 1 && rest > 0 && rest < g_resident_blocks * 3 / 4 && px_main > 0 && px_main < px &&
-            tail_blocks <= g_resident_blocks) {
-            IgemmProblem a = p, b = p;
-            a.patch.tile0 = 0;
-            a.patch.tile_count = px_main;
-            b.patch.tile0 = px_main;
-            b.patch.tile_count = px - px_main;
-            const double fl = p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups;
-            a.flops = fl * px_main / px;
-            b.flops = fl - a.flops;
-            const int rc = patch_launch_tiles(a, mt, stream);
-            return rc != CG_OK ? rc : patch_launch_tiles(b, 64, stream);
-        }
-    }
-    return patch_launch_tiles(p, mt, stream);
-}
-
-}  // namespace
-
-#if CG_MATH == 0
-namespace {
-
 template <int TM, int NSTA, int CPB, int NSL>
 int launch_wgrad_cfg(const IgemmProblem &p, hipStream_t stream)
 {
     constexpr int MT = 2 * TM * 32;
-    using LA = KLoader4<MT, 4>;
+    using LA = KLoader4<MT>;
     dim3 grid((p.N + 127) / 128, (p.M + MT - 1) / MT, p.groups * p.splits);
     if (grid.y > 65535u || grid.z > 65535u) return CG_EUNSUPPORTED;
     int rec = -1;
@@ -1614,59 +527,9 @@ bool wgrad_plan(WgradGeom &g, uint32_t M, uint32_t N, uint32_t groups, uint32_t 
     return true;
 }
 
-static std::atomic<uint32_t> g_patch_min_tiles{512};
-void patch_set_min_tiles(uint32_t t) { g_patch_min_tiles.store(t, std::memory_order_relaxed); }
 void patch_set_resident_blocks(uint32_t b) { g_resident_override.store(b, std::memory_order_relaxed); }
-
-bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
-{
-    g.nsl = 0;
-    const int KK = g.KH * g.KW;
-    if (g.Cred == 0 || g.Cred % 16 || KK < 5 || g.s <= 0 || g.OHo <= 0 || g.OWo <= 0) return false;
-    if (g.src_elems * 4 > kMaxBufferBytes || N >= (1u << 30)) return false;
-    g.Wp = (g.OWo - 1) * g.s + g.KW;
-    const int64_t rfull = (int64_t)((g.OHo - 1) * g.s + g.KH) * g.Wp;
-    if (rfull >= (1 << 24)) return false;
-    g.Rfull = (int32_t)rfull;
-    const uint32_t P = (uint32_t)g.OHo * (uint32_t)g.OWo;
-    g.divP = make_fastdiv(P);
-    g.divOW = make_fastdiv((uint32_t)g.OWo);
-    g.divWp = make_fastdiv((uint32_t)g.Wp);
-    g.divRfull = make_fastdiv((uint32_t)g.Rfull);
-    // enough tiles to fill the chip without cutting K (the patch kernel has no K slices)
-    const int mt = patch_mt(M, N, groups);
-    if ((uint64_t)((M + mt - 1) / mt) * ((N + 127) / 128) * groups < g_patch_min_tiles.load(std::memory_order_relaxed)) return false;
-    // The largest patch any block needs: a fragment read reaches (KH-1)*Wp + KW-1 beyond sigma, and
-    // sigma + that stays below the slot count of the block's segments, which is what is counted.
-    auto slots = [&](uint32_t n0, uint32_t n1) {
-        const uint32_t bA = n0 / P, oyA = (n0 % P) / (uint32_t)g.OWo, bB = n1 / P, oyB = (n1 % P) / (uint32_t)g.OWo;
-        if (bA == bB) return (int64_t)((oyB - oyA) * g.s + g.KH) * g.Wp;
-        return (int64_t)(((uint32_t)g.OHo - 1 - oyA) * g.s + g.KH) * g.Wp + (int64_t)(bB - bA - 1) * g.Rfull +
-               (int64_t)(oyB * g.s + g.KH) * g.Wp;
-    };
-    int64_t smax = 0;
-    for (uint32_t n0 = 0; n0 < N; n0 += 128) {
-        const int64_t sl = slots(n0, (n0 + 127 < N - 1) ? n0 + 127 : N - 1);
-        if (sl > smax) smax = sl;
-    }
-    g.tiles_per_img = 0;
-    g.divTpi = make_fastdiv(1);
-    if (smax <= 4 * 64) { g.nsl = 4; return true; }
-    // large images: blocks that stay inside one image need smaller patches (every image is the same)
-    if (N % P) return false;
-    int64_t amax = 0;
-    for (uint32_t n0 = 0; n0 < P; n0 += 128) {
-        const int64_t sl = slots(n0, (n0 + 127 < P - 1) ? n0 + 127 : P - 1);
-        if (sl > amax) amax = sl;
-    }
-    // six chunks (planes 56 wide with a 3x3 window: four pixel rows, 348 slots) leave room for 128-row
-    // tiles with a three-stage filter ring
-    if (amax > 6 * 64) return false;
-    g.nsl = amax > 5 * 64 ? 6 : 5;
-    g.tiles_per_img = (int32_t)((P + 127) / 128);
-    g.divTpi = make_fastdiv((uint32_t)g.tiles_per_img);
-    return true;
-}
+uint32_t igemm_resident_blocks() { return resident_blocks(); }
+int igemm_pick_mt(uint32_t M, uint32_t N, uint32_t groups) { return pick_mt(M, N, groups); }
 
 FastDiv make_fastdiv(uint32_t d)
 {
@@ -1709,31 +572,24 @@ void igemm_host_element(const Operand &op, uint32_t row, uint32_t k, int64_t *of
     *off = (int64_t)r.off + q.off + op.shift;
 }
 
-#endif  // CG_MATH == 0
 
-int CG_IGEMM_LAUNCH(const IgemmProblem &p0, hipStream_t stream)
+int igemm_launch(const IgemmProblem &p0, hipStream_t stream)
 {
-#if CG_MATH == 0
-    if (p0.math == CG_MATH_BF16) return igemm_launch_bf16(p0, stream);
-    if (p0.math == CG_MATH_BF16X3) return igemm_launch_bf16x3(p0, stream);
-    if (p0.math != CG_MATH_FP32) return CG_EINVAL;
-#endif
+    if (p0.use_patch) return split_patch_launch(p0, stream);
+    if (p0.math != CG_MATH_FP32 && p0.math != CG_MATH_BF16 && p0.math != CG_MATH_BF16X3) return CG_EINVAL;
     IgemmProblem p = p0;
     if (!p.c_ptr || !aligned16(p.c_ptr)) return CG_EINVAL;
     if (p.M == 0 || p.N == 0 || p.K == 0 || p.groups == 0 || p.splits == 0) return CG_EINVAL;
     if (p.M >= (1u << 30) || p.N >= (1u << 30) || p.K >= (1u << 30)) return CG_EUNSUPPORTED;
     if (p.bias_mode && !p.bias) return CG_EINVAL;
-#if CG_MATH != 0
-    if (p.use_wgrad) return CG_EUNSUPPORTED;      // the band kernel multiplies in fp32 only
-#else
     if (p.use_wgrad) {         // K slices are whole units here, not k ranges
+        if (p.math != CG_MATH_FP32) return CG_EUNSUPPORTED;      // the band kernel multiplies in fp32 only
         if (!p.wgrad.x || !aligned16(p.wgrad.x) || p.wgrad.cpb == 0 || p.A.check) return CG_EINVAL;
         p.A.shift = 0;
         const int rcw = normalise_operand(p.A, p.groups);
         if (rcw) return rcw;
         return wgrad_launch(p, stream);
     }
-#endif
     if (p.splits > 1 && (p.k_per_split % KT != 0)) return CG_EINVAL;
     if ((uint64_t)p.k_per_split * p.splits < p.K || (uint64_t)p.k_per_split * (p.splits - 1) >= p.K) return CG_EINVAL;
     if (p.bias_mode && !p.bias) return CG_EINVAL;
@@ -1741,37 +597,27 @@ int CG_IGEMM_LAUNCH(const IgemmProblem &p0, hipStream_t stream)
     p.A.shift = p.B.shift = 0;
     int rc = normalise_operand(p.A, p.groups);
     if (rc) return rc;
-    if (p.use_patch) {
-        if (!p.patch.src || !aligned16(p.patch.src) || p.patch.nsl == 0 || p.splits != 1 || !quad_ok(p.A, p.K) ||
-            p.K != p.patch.Cred * (uint32_t)(p.patch.KH * p.patch.KW))
-            return CG_EINVAL;
-        return patch_launch(p, stream);
-    }
     if (p.A.row.count != p.M || p.B.row.count != p.N || p.A.k.count != p.K || p.B.k.count != p.K) return CG_EINVAL;
     rc = normalise_operand(p.B, p.groups);
     if (rc) return rc;
     if (!p.A.check) { p.A.limA = p.A.limB = 1; }
     if (!p.B.check) { p.B.limA = p.B.limB = 1; }
 
-    const int mt = pick_mt(p.M, p.N, p.groups, p.K);
-    const bool bc = p.B.check != 0;
-    const int am = quad_ok(p.A, p.K) ? LD_K4 : p.A.lanes_k ? LD_K : LD_ROWS;
-    int bm = quad_ok(p.B, p.K) ? LD_K4 : p.B.lanes_k ? LD_K : LD_ROWS;
+    const int mt = p.mt ? p.mt : gemm_mt(p.M, p.N, p.groups, p.K);
+    // how an operand's elements are fetched: 0 rows along the lanes, 1 k along the lanes, 2 aligned quads of k
+    const bool aq = quad_ok(p.A, p.K);
+    int bm = quad_ok(p.B, p.K) ? 2 : p.B.lanes_k ? 1 : 0;
     // A quad that reaches beyond K, or into the padding of a run of reduction indices, delivers the
     // floats that follow in memory (the next row's first elements): harmless only if the other
     // operand delivers exact zeros there, which the loaders that check every element do and the quad
     // loader does not.  Quads on both sides need a reduction range without any such position.
-    if (am == LD_K4 && bm == LD_K4 && (p.K % 4 != 0 || p.A.k.r1_lim != 0 || p.B.k.r1_lim != 0)) bm = LD_K;
-    if (am == LD_K4 && bm == LD_ROWS) return bc ? launch_modes<LD_K4, LD_ROWS, true>(p, mt, stream) : launch_modes<LD_K4, LD_ROWS, false>(p, mt, stream);
-    if (am == LD_K4 && bm == LD_K4) return launch_modes<LD_K4, LD_K4, false>(p, mt, stream);
-    if (am == LD_K4 && bm == LD_K) return bc ? launch_modes<LD_K4, LD_K, true>(p, mt, stream) : launch_modes<LD_K4, LD_K, false>(p, mt, stream);
-    if (am == LD_K && bm == LD_ROWS) return bc ? launch_modes<LD_K, LD_ROWS, true>(p, mt, stream) : launch_modes<LD_K, LD_ROWS, false>(p, mt, stream);
-    if (am == LD_K && (bm == LD_K || bm == LD_K4)) return bc ? launch_modes<LD_K, LD_K, true>(p, mt, stream) : launch_modes<LD_K, LD_K, false>(p, mt, stream);
-    if (am == LD_ROWS && bm == LD_ROWS && !bc) return launch_modes<LD_ROWS, LD_ROWS, false>(p, mt, stream);
-    return CG_EUNSUPPORTED;
+    if (aq && bm == 2 && (p.K % 4 != 0 || p.A.k.r1_lim != 0 || p.B.k.r1_lim != 0)) bm = 1;
+    if (!aq && p.A.lanes_k) return CG_EUNSUPPORTED;
+    if (p.math == CG_MATH_BF16) return split_gemm_1(p, mt, aq, bm, stream);
+    if (p.math == CG_MATH_BF16X3) return split_gemm_2(p, mt, aq, bm, stream);
+    return split_gemm_3(p, mt, aq, bm, stream);
 }
 
-#if CG_MATH == 0
 // ---- split-K: more blocks for problems whose C has few tiles ---------------------------------
 
 namespace {
@@ -1881,8 +727,16 @@ template <int ROWS> __global__ __launch_bounds__(256) void splitk_finish_kernel(
     const uint32_t nblk = a.r_dy ? a.finish_blocks : gridDim.x;
     if (ROWS == 1) {
         for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < a.total; i += nblk * 256) {
+            // the slices' loads are independent: eight in flight, added in slice order
             float s = a.part[i];
-            for (int k = 1; k < a.splits; ++k) s += a.part[(int64_t)k * a.plane + i];
+            for (int k0 = 1; k0 < a.splits; k0 += 8) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = k0 + u < a.splits ? a.part[(int64_t)(k0 + u) * a.plane + i] : 0.f;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (k0 + u < a.splits) s += v[u];
+            }
             finish_store(a, i, s);
         }
         return;
@@ -1893,7 +747,14 @@ template <int ROWS> __global__ __launch_bounds__(256) void splitk_finish_kernel(
         const uint32_t i = i0 + el;
         float s = 0.f;
         if (i < a.total)
-            for (int k = r; k < a.splits; k += 8) s += a.part[(int64_t)k * a.plane + i];
+            for (int k0 = r; k0 < a.splits; k0 += 64) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = k0 + 8 * u < a.splits ? a.part[(int64_t)(k0 + 8 * u) * a.plane + i] : 0.f;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (k0 + 8 * u < a.splits) s += v[u];
+            }
         part[r][el] = s;
         __syncthreads();
         if (r == 0 && i < a.total) {
@@ -1908,14 +769,15 @@ template <int ROWS> __global__ __launch_bounds__(256) void splitk_finish_kernel(
 
 }  // namespace
 
-SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups)
+// K slices for row tiles of mt rows: as many as make one round of resident blocks, at least 128
+// reduction indices each.
+static SplitPlan slices(uint32_t M, uint32_t N, uint32_t K, uint32_t groups, int mt)
 {
-    SplitPlan pl{1, K, 0};
-    const uint32_t mt = (uint32_t)pick_mt(M, N, groups, K);
+    SplitPlan pl{1, K, 0, mt};
     const uint64_t tiles = (uint64_t)((M + mt - 1) / mt) * ((N + 127) / 128) * groups;
     if (tiles >= 512) return pl;
     uint64_t want = kSplitBlocks / tiles;
-    const uint64_t max_by_k = K / 128;               // keep at least 8 K-tiles per slice
+    const uint64_t max_by_k = K / 128;
     if (want > max_by_k) want = max_by_k;
     if (want > 512) want = 512;
     if (want < 2) return pl;
@@ -1924,27 +786,53 @@ SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups)
     per = (per + KT - 1) / KT * KT;
     pl.k_per_split = (uint32_t)per;
     pl.splits = (uint32_t)((K + per - 1) / per);
-    if (pl.splits < 2) return SplitPlan{1, K, 0};
+    if (pl.splits < 2) return SplitPlan{1, K, 0, mt};
     pl.ws_bytes = (size_t)pl.splits * groups * M * N * sizeof(float);
     return pl;
 }
 
+// A slice's sums are as long as its share of K, and their rounding error with them.  The tiles of up to
+// 256 rows that pick_mt chooses from leave room for more slices than lower ones in one round; where a
+// slice would get more than 4/3 as long, the blocks make two or more rounds instead (the three-piece
+// products round a sum 0.86 times as much as the fp32 instruction, so the error stays below its).
+SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups)
+{
+    const int mt = gemm_mt(M, N, groups, K);
+    SplitPlan pl = slices(M, N, K, groups, mt);
+    const SplitPlan tall = slices(M, N, K, groups, pick_mt(M, N, groups, K));
+    if (tall.splits < 2 || pl.splits * 4 >= tall.splits * 3) return pl;
+    const uint64_t tiles = (uint64_t)((M + mt - 1) / mt) * ((N + 127) / 128) * groups;
+    uint64_t want = 0;
+    for (uint64_t rounds = 1; want * 4 < (uint64_t)tall.splits * 3; ++rounds) want = rounds * kSplitBlocks / tiles;
+    if (want > tall.splits) want = tall.splits;
+    const uint64_t per = ((K + want - 1) / want + KT - 1) / KT * KT;
+    pl.k_per_split = (uint32_t)per;
+    pl.splits = (uint32_t)((K + per - 1) / per);
+    pl.ws_bytes = (size_t)pl.splits * groups * M * N * sizeof(float);
+    return pl;
+}
+
+// What the caller is told to bring.  Never less than the tiles of up to 256 rows need that pick_mt
+// chooses from: a size that a program has been told stays enough, and the entry point with a scratch
+// array of a fixed size keeps refusing exactly the problems it refused.
 size_t igemm_ws_bytes(const IgemmProblem &p)
 {
     if (p.use_patch) return 0;
     if (p.use_wgrad) return p.splits > 1 ? (size_t)p.splits * p.groups * p.M * p.N * sizeof(float) : 0;
-    return plan_split(p.M, p.N, p.K, p.groups).ws_bytes;
+    const size_t a = plan_split(p.M, p.N, p.K, p.groups).ws_bytes;
+    const size_t b = slices(p.M, p.N, p.K, p.groups, pick_mt(p.M, p.N, p.groups, p.K)).ws_bytes;
+    return a > b ? a : b;
 }
 
 int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t stream, const BiasRider *rider, bool *rider_taken)
 {
     if (rider_taken) *rider_taken = false;
-    const SplitPlan pl = p0.use_patch   ? SplitPlan{1, p0.K, 0}
-                         : p0.use_wgrad ? SplitPlan{p0.splits, p0.K, igemm_ws_bytes(p0)}
+    const SplitPlan pl = p0.use_patch   ? SplitPlan{1, p0.K, 0, 0}
+                         : p0.use_wgrad ? SplitPlan{p0.splits, p0.K, igemm_ws_bytes(p0), 0}
                                         : plan_split(p0.M, p0.N, p0.K, p0.groups);
     if (pl.splits <= 1) {
         IgemmProblem p = p0;
-        p.splits = 1; p.k_per_split = p.K;
+        p.splits = 1; p.k_per_split = p.K; p.mt = pl.mt;
         return igemm_launch(p, stream);
     }
     if (!ws || ws_bytes < pl.ws_bytes) return CG_ENOSPC;
@@ -1958,7 +846,7 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
     p.c_split_stride = (int64_t)p0.groups * p0.M * p0.N;
     p.c_scatter = 0;
     p.bias = nullptr; p.bias_mode = 0; p.accumulate = 0; p.relu = 0; p.gate = nullptr;
-    p.splits = pl.splits; p.k_per_split = pl.k_per_split;
+    p.splits = pl.splits; p.k_per_split = pl.k_per_split; p.mt = pl.mt;
     const int rc = igemm_launch(p, stream);
     if (rc) return rc;
     FinishArgs a{};
@@ -2058,6 +946,5 @@ int bias_grad_launch(const float *dy, int N, int M, int P, float *db, void *ws, 
     return CG_OK;
 }
 
-#endif  // CG_MATH == 0
 
 }  // namespace cg

@@ -1,0 +1,161 @@
+// Device code of the kernels that multiply fp32 operands in pieces on the bf16 matrix instructions.
+#pragma once
+#include <type_traits>
+#include "cg_internal.h"
+#include "igemm_device.h"
+
+namespace cg {
+namespace {
+
+// A raw buffer of `bytes` bytes at `base`: reads beyond it return 0.  Both are uniform by construction;
+// readfirstlane says so to the compiler, which otherwise wraps every load in a loop over the lanes'
+// descriptors where a division on the vector unit was part of the address.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float *base, uint64_t bytes)
+{
+    const uint64_t a = (uint64_t)reinterpret_cast<uintptr_t>(base);
+    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a) |
+                       ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32);
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((uintptr_t)u), 0,
+                                             (int)__builtin_amdgcn_readfirstlane((uint32_t)bytes), 0x00020000);
+}
+
+// Barrier of a block for LDS data: this wave's LDS accesses are done, global loads stay in flight.
+__device__ __forceinline__ void block_sync_lds()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));      // eight bf16: one piece of eight values
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Two fp32 values cut into NP bf16 pieces, most significant first, each piece the nearest even of what
+// the pieces before it left.  Three pieces hold an fp32 value exactly (a remainder below 2^-133 is
+// lost: the value is then below 2^-110).  11 vector instructions a pair (v_dot2_f32_bf16 would take a
+// remainder in one instead of two, at half the rate).
+template <int NP> __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t (&pc)[NP])
+{
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        bf16x2 h;
+        h[0] = (__bf16)x0;
+        h[1] = (__bf16)x1;
+        pc[k] = __builtin_bit_cast(uint32_t, h);
+        if (k + 1 < NP) {
+            x0 -= (float)h[0];
+            x1 -= (float)h[1];
+        }
+    }
+}
+
+// The same for values that bf16 rounding would send to infinity, and infinities themselves, where the
+// split above has inf - inf.  A finite value from kHuge up gets its first piece by truncation.  An
+// infinity becomes (1, 0, inf): times any b its pieces give inf * bf16(b) + 1 * (the last piece of b),
+// which is inf, -inf, or NaN for b = 0 or NaN, as a * b is.  (NaN stays three NaNs.)
+#define CG_HUGE __uint_as_float(0x7f7f8000u)
+__device__ __forceinline__ void split_huge(float x, uint32_t (&pc)[3])       // pieces in the low halves
+{
+    const float a = fabsf(x);
+    const bool inf = a == __uint_as_float(0x7f800000u), large = a >= CG_HUGE;
+    const float h = inf ? copysignf(1.f, x) : large ? __uint_as_float(__float_as_uint(x) & 0xffff0000u) : (float)(__bf16)x;
+    const float r = inf ? 0.f : x - h;
+    const __bf16 m = (__bf16)r;
+    pc[0] = __builtin_bit_cast(uint16_t, (__bf16)h);
+    pc[1] = __builtin_bit_cast(uint16_t, m);
+    pc[2] = __builtin_bit_cast(uint16_t, (__bf16)(inf ? x : r - (float)m));
+}
+__device__ __forceinline__ void split8_huge(const float (&f)[8], v4u (&pc)[3])
+{
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        uint32_t lo[3], hi[3];
+        split_huge(f[2 * t], lo);
+        split_huge(f[2 * t + 1], hi);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pc[k][t] = lo[k] | hi[k] << 16;
+    }
+}
+
+// pair t of eight values; `big` collects the largest magnitude (NaN drops out)
+template <int NP> __device__ __forceinline__ void split8_pair(const float (&f)[8], int t, v4u (&pc)[NP], float &big)
+{
+    uint32_t p[NP];
+    split_pair<NP>(f[2 * t], f[2 * t + 1], p);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) pc[k][t] = p[k];
+    if constexpr (NP == 3) big = fmaxf(fmaxf(big, fabsf(f[2 * t])), fabsf(f[2 * t + 1]));
+}
+template <int NP> __device__ __forceinline__ void split8(const float (&f)[8], v4u (&pc)[NP])
+{
+    float big = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) split8_pair<NP>(f, t, pc, big);
+    if constexpr (NP == 3) {
+        if (__builtin_expect(big >= CG_HUGE, 0)) split8_huge(f, pc);
+    }
+}
+
+// Products that count, smallest first: number, piece of A, piece of B.
+template <int NP> struct Products;
+template <> struct Products<1> { static constexpr int N = 1, A[1] = {0}, B[1] = {0}; };
+template <> struct Products<2> { static constexpr int N = 3, A[3] = {1, 0, 0}, B[3] = {0, 1, 0}; };
+template <> struct Products<3> { static constexpr int N = 6, A[6] = {2, 0, 1, 1, 0, 0}, B[6] = {0, 2, 1, 0, 1, 0}; };
+
+// Columns multiplied together: at least four independent sums, because an instruction that adds to the
+// one before it waits about 60 cycles for it and a 16x16x32 multiply takes 16.
+template <int TM, int TN> struct ColumnGroup { static constexpr int G = TM >= 3 ? 1 : TM == 2 ? 2 : TN >= 4 ? 4 : 2; };
+
+// One step of 32 reduction indices: acc[i][j] += A tile i times B tile j, all pieces.  B is the FIRST
+// operand of the instruction: a lane (q = lane / 16, l = lane % 16) then holds row l and the four
+// columns 4q .. 4q+3 of a tile, which it can store as one 16-byte access.  read_b(j, pieces) fetches
+// column tile j, one group ahead; work(slot) is other work of the step, spread over the slots 0 ..
+// SLOTS-1, one behind each product of a group, whose vector instructions are laid between the matrix
+// instructions.
+template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G> struct MmaStep {
+    static constexpr int JG = JG_, PR = Products<NP>::N, SLOTS = TN / JG * PR;
+    static_assert(TN % JG == 0, "whole groups");
+    struct NoWork {};
+    template <class ReadB, class Work>
+    __device__ __forceinline__ static void run(const v4u (&ap)[TM][NP], v4f (&acc)[TM][TN], ReadB &&read_b, Work &&work)
+    {
+        v4u bp[2][JG][NP];
+#pragma unroll
+        for (int jj = 0; jj < JG; ++jj) read_b(jj, bp[0][jj]);
+        static_for<0, TN / JG>([&](auto GC) {
+            constexpr int g = decltype(GC)::value;
+            if constexpr (g + 1 < TN / JG) {
+#pragma unroll
+                for (int jj = 0; jj < JG; ++jj) read_b((g + 1) * JG + jj, bp[(g + 1) & 1][jj]);
+            }
+            static_for<0, PR>([&](auto PC) {
+                constexpr int pi = decltype(PC)::value, a = Products<NP>::A[pi], b = Products<NP>::B[pi];
+#pragma unroll
+                for (int jj = 0; jj < JG; ++jj)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        acc[i][g * JG + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bp[g & 1][jj][b]),
+                                                                                      __builtin_bit_cast(bf16x8, ap[i][a]), acc[i][g * JG + jj], 0, 0, 0);
+                if constexpr (!std::is_same_v<std::decay_t<Work>, NoWork>) {
+                    work(std::integral_constant<int, g * PR + pi>{});
+                    static_for<0, TM * JG>([&](auto) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one matrix instruction,
+                        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);      // three vector ones
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        });
+    }
+    // runs items 0 .. N-1 of a step's other work, evenly over the slots
+    template <int N, class Item> struct Spread {
+        Item item;
+        template <class S> __device__ __forceinline__ void operator()(S) const
+        {
+            constexpr int s = S::value;
+            static_for<s * N / SLOTS, (s + 1) * N / SLOTS>(item);
+        }
+    };
+    template <int N, class Item> __device__ __forceinline__ static Spread<N, Item> spread(Item item) { return Spread<N, Item>{item}; }
+};
+
+}  // namespace
+}  // namespace cg

@@ -1,0 +1,472 @@
+// Convolutions from raw image rows on the bf16 matrix instructions: forward, stride-1 backward-data
+// and strided backward-data (as a stride-1 problem over dy).  See PatchGeom in cg_internal.h for the
+// geometry.  One kernel serves the three arithmetics of cg.h by the number of bf16 pieces an fp32
+// operand is cut into on its way into the matrix cores:
+//   NP = 3 (CG_MATH_FP32):   x = h + m + l, h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): exact, 24 bits.
+//                            Six products l*h + h*l + m*m + m*h + h*m + h*h, small ones first; what is
+//                            dropped (m*l, l*m, l*l) is 2^-26 of a product and less.  A sum is rounded
+//                            six times per 32 products where v_mfma_f32_*_f32 rounds it 8 or 16 times:
+//                            the error against 64 bits is no larger (K = 256: 2.5e-7 against 3.0e-7
+//                            of the fp32 instruction, K = 2304: 7.4e-7 against 8.6e-7), at 6/16 of the
+//                            matrix pipe's time.
+//   NP = 2 (CG_MATH_BF16X3): x = h + l, three products.
+//   NP = 1 (CG_MATH_BF16):   x = h.
+//
+// What bounds it: the matrix pipe.  v_mfma_f32_16x16x32_bf16 rather than 32x32x16: on random operands
+// the former holds 1970 TFLOP/s, the latter 1700 (power; both 2450 on zeros), with the same LDS traffic
+// for the same wave tile.
+//
+// Split of the work.  A block is four waves and 128 pixels; wave w owns 16*TM rows of its own and
+// ALL 128 pixels.  So the filters are shared by nobody and need no LDS: a lane fetches its eight
+// consecutive reduction indices of a row as two 16-byte loads straight from L2 (the filter copy is
+// laid out so that a wave's load is contiguous), and cuts them in registers, once per value.  The
+// image patch is cut once per block, on its way into LDS, 32 channels at a time, as
+// [piece][octet of channels][slot][8 channels]: a lane's operand is then one 16-byte read per piece
+// whose address runs over consecutive slots, and one patch serves every tap.  There is no barrier
+// inside the taps of a channel group: waves of a block drift, and those of two blocks share a SIMD, so
+// one cuts filters while the other multiplies.
+// A step multiplies two units of 16 reduction indices (a unit = one tap of 16 channels): both channel
+// halves of a tap, or, for a last group of only 16 channels, two taps of it.
+#include <atomic>
+#include <cstdio>
+#include "cg_internal.h"
+#include "igemm_device.h"
+#include "split_device.h"
+
+namespace cg {
+
+namespace {
+
+template <int NP, int NSL> struct PatchLds {
+    // in 16-byte units; behind the four octets of every piece lies one unit of zeros
+    static constexpr int SLOTS = NSL * 64, ZERO = 4 * SLOTS, PLANE = ZERO + 1;
+    static constexpr size_t BYTES = (size_t)NP * PLANE * 16;
+};
+
+}  // namespace
+
+// WM x WN x WK waves: rows x pixels x steps (WK = 2: two waves share a tile, each takes every other
+// step, and their sums meet in LDS at the end: for row counts too small to give each wave its own).
+template <int NP, int TM, int WM, int WK, int NSL>
+__global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem p)
+{
+    constexpr int WN = 4 / (WM * WK), TN = 128 / (16 * WN), MT = WM * TM * 16, NT = 128;
+    static_assert(WM * WN * WK == 4 && TN % 2 == 0, "four waves");
+    using L = PatchLds<NP, NSL>;
+    extern __shared__ __attribute__((aligned(16))) v4u lds[];        // the pieces of the patch (PatchLds)
+
+    const PatchGeom &pg = p.patch;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WM, wn = (wave / WM) % WN, wk = wave / (WM * WN);
+    const uint32_t m0 = blockIdx.y * MT, g = blockIdx.z;
+    const int KK = pg.KH * pg.KW, ncb16 = (int)(pg.Cred / 16), ngrp = (ncb16 + 1) / 2;
+    // this block's pixels n0..n1
+    const uint32_t P = pg.divP.d;
+    uint32_t n0, n1;
+    const uint32_t tile = blockIdx.x + pg.tile0;
+    if (pg.tiles_per_img) {
+        const uint32_t b = fdiv(tile, pg.divTpi), ti = tile - b * pg.divTpi.d;
+        n0 = b * P + ti * NT;
+        n1 = min(n0 + NT - 1, (b + 1) * P - 1);
+    } else {
+        n0 = tile * NT;
+        n1 = min(n0 + NT - 1, p.N - 1);
+    }
+
+    const auto rsrcA = buffer_of(p.A.ptr + (int64_t)g * p.A.gstride, (p.A.elems - (uint64_t)g * p.A.gstride) * 4);
+    const auto rsrcB = buffer_of(pg.src + (int64_t)g * pg.gstride, (pg.src_elems - (uint64_t)g * pg.gstride) * 4);
+
+    // ---- where this block's pixels sit: images bA..bB, pixel rows oyA (in bA) .. oyB (in bB) -------
+    const uint32_t bA = fdiv(n0, pg.divP), oyA = fdiv(n0 - bA * P, pg.divOW);
+    const uint32_t bB = fdiv(n1, pg.divP), oyB = fdiv(n1 - bB * P, pg.divOW);
+    // slots of the first image's segment; later images start at R0 + (d-1)*Rfull
+    const int32_t R0 = (int32_t)((((bA == bB) ? oyB : (uint32_t)pg.OHo - 1) - oyA) * pg.s + pg.KH) * pg.Wp;
+
+    // global byte offset of every patch slot this lane loads (or out of range: padding, unused slots)
+    uint32_t voff[NSL];
+#pragma unroll
+    for (int e = 0; e < NSL; ++e) {
+        const int32_t j = e * 64 + lane;
+        const uint32_t d = j < R0 ? 0u : 1u + fdiv((uint32_t)(j - R0), pg.divRfull);
+        const int32_t local = j - (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull);
+        const uint32_t r = fdiv((uint32_t)local, pg.divWp), c = (uint32_t)local - r * (uint32_t)pg.Wp;
+        const uint32_t b = bA + d, oylo = d == 0 ? oyA : 0u;
+        const uint32_t oyhi = b == bB ? oyB : (uint32_t)pg.OHo - 1;
+        const int32_t sy = (int32_t)(oylo * pg.s) + pg.oy0 + (int32_t)r, sx = pg.ox0 + (int32_t)c;
+        const bool ok = b <= bB && r < (oyhi - oylo) * pg.s + pg.KH && (uint32_t)sy < (uint32_t)pg.Hs &&
+                        (uint32_t)sx < (uint32_t)pg.Ws;
+        voff[e] = ok ? (uint32_t)((int32_t)b * pg.img_stride + sy * pg.Ws + sx) * 4u : OOB_ROW;
+    }
+
+    const int q = lane >> 4, l16 = lane & 15;
+    const bool second = q >= 2;                 // this lane's eight reduction indices belong to a step's second unit
+    // slot of this lane's pixels (their windows' first element)
+    int32_t sig[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const uint32_t n = n0 + (uint32_t)((wn * TN + j) * 16 + l16);
+        int32_t sg = 0;
+        if (n <= n1) {
+            const uint32_t b = fdiv(n, pg.divP), rem = n - b * P, oy = fdiv(rem, pg.divOW), ox = rem - oy * pg.divOW.d;
+            const uint32_t d = b - bA, oylo = d == 0 ? oyA : 0u;
+            sg = (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull) + (int32_t)((oy - oylo) * pg.s) * pg.Wp + (int32_t)(ox * pg.s);
+        }
+        sig[j] = sg;
+    }
+    // byte offset of this lane's eight floats in a unit of the filter copy [unit][row][16]
+    uint32_t arow[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const uint32_t row = m0 + (uint32_t)((wm * TM + i) * 16 + l16);
+        arow[i] = row < p.M ? row * 64u + (uint32_t)(q & 1) * 32u : OOB_ROW;
+    }
+    const uint32_t unit_bytes = p.M * 64u;      // unit = tap * ncb16 + 16-channel block
+
+    v4f acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    // ---- patch: wave w brings channels 8w..8w+7 of a group, 64 slots at a time -----------------------
+    float pr[NSL][8];
+    auto load_chunk = [&](auto EC, int grp) {
+        constexpr int e = decltype(EC)::value;
+        const bool live = grp * 2 + (wave >> 1) < ncb16;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t soff = live ? (uint32_t)((grp * 32 + wave * 8 + t) * pg.chan_stride) * 4u : OOB_K;
+            pr[e][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrcB, voff[e], soff, 0));
+        }
+    };
+    auto store_chunk = [&](auto EC) {
+        constexpr int e = decltype(EC)::value;
+        v4u pc[NP];
+        split8<NP>(pr[e], pc);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) lds[k * L::PLANE + wave * L::SLOTS + e * 64 + lane] = pc[k];
+    };
+
+    // ---- steps: (group, index); both units of a step and where they lie -------------------------------
+    auto steps_of = [&](int grp) { return 2 * grp + 1 < ncb16 ? KK : (KK + 1) / 2; };
+    float ar[TM][8];
+    auto load_a = [&](int grp, int s) {
+        uint32_t u0 = OOB_K, u1 = OOB_K;
+        if (grp < ngrp) {
+            if (2 * grp + 1 < ncb16) {
+                u0 = (uint32_t)(s * ncb16 + 2 * grp) * unit_bytes;
+                u1 = u0 + unit_bytes;
+            } else {
+                u0 = (uint32_t)(2 * s * ncb16 + 2 * grp) * unit_bytes;
+                if (2 * s + 1 < KK) u1 = u0 + (uint32_t)ncb16 * unit_bytes;
+            }
+        }
+        const uint32_t u = second ? u1 : u0;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, arow[i] + u + 16u * hf, 0, 0);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) ar[i][4 * hf + t] = __uint_as_float((uint32_t)v[t]);
+            }
+    };
+    auto tap_slot = [&](int t) {                // slot displacement of tap t
+        const int ky = (int)fdiv((uint32_t)t, pg.divKW), kx = t - ky * pg.KW;
+        return pg.flip ? (pg.KH - 1 - ky) * pg.Wp + (pg.KW - 1 - kx) : ky * pg.Wp + kx;
+    };
+
+    if (threadIdx.x < NP) lds[threadIdx.x * L::PLANE + L::ZERO] = v4u{0u, 0u, 0u, 0u};
+    static_for<0, NSL>([&](auto EC) { load_chunk(EC, 0); });
+    load_a(0, wk);
+    static_for<0, NSL>([&](auto EC) { store_chunk(EC); });
+    block_sync_lds();
+
+    // (the rows are cut in one piece in front of the products: cutting them behind the products of the step
+    // before, as split_gemm_kernel does, takes 24 more registers and spills)
+    using Step = MmaStep<NP, TM, TN, 2>;
+    for (int grp = 0; grp < ngrp; ++grp) {
+        const int ns = steps_of(grp);
+        const bool pair = 2 * grp + 1 < ncb16;
+        int ls = 0;
+        for (int s = wk; s < ns; s += WK, ++ls) {
+            v4u ap[TM][NP];
+            float big = 0.f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) split8_pair<NP>(ar[i], t, ap[i], big);
+            if constexpr (NP == 3) {
+                if (__builtin_expect(big >= CG_HUGE, 0)) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[i]);
+                }
+            }
+            // a chunk of the next group's patch, then the next step's filters (so that waiting for those,
+            // one step from now, waits for nothing younger)
+            static_for<0, NSL>([&](auto EC) { if (ls == decltype(EC)::value) load_chunk(EC, grp + 1); });
+            if (s + WK < ns) load_a(grp, s + WK);
+            else load_a(grp + 1, wk);
+            // where the lane reads: slot displacement of its unit's tap, octet of its channels
+            int base;
+            int32_t mask = -1;
+            if (pair) base = tap_slot(s) + q * L::SLOTS;
+            else {
+                const int t0 = tap_slot(2 * s), t1 = tap_slot(min(2 * s + 1, KK - 1));
+                base = (second ? t1 : t0) + (q & 1) * L::SLOTS;
+                if (2 * s + 1 >= KK && second) { base = L::ZERO; mask = 0; }     // no second unit: zeros
+            }
+            auto read_b = [&](int j, v4u (&pc)[NP]) {
+                const int idx = (sig[j] & mask) + base;
+#pragma unroll
+                for (int k = 0; k < NP; ++k) pc[k] = lds[idx + k * L::PLANE];
+            };
+            Step::run(ap, acc, read_b, typename Step::NoWork{});
+        }
+        if (grp + 1 < ngrp) {
+            static_for<0, NSL>([&](auto EC) { if (ls <= decltype(EC)::value) load_chunk(EC, grp + 1); });
+            block_sync_lds();                   // every wave is done with this group's patch
+            static_for<0, NSL>([&](auto EC) { store_chunk(EC); });
+            block_sync_lds();
+        }
+    }
+    if constexpr (WK == 2) {
+        // the second wave's sums are added to the first's, which stores the tile
+        block_sync_lds();                       // the patch's LDS is free
+        v4f *const ex = reinterpret_cast<v4f *>(lds) + (wm * WN + wn) * (TM * TN * 64);
+        if (wk == 1) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) ex[(i * TN + j) * 64 + lane] = acc[i][j];
+        }
+        block_sync_lds();
+        if (wk == 1) return;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] += ex[(i * TN + j) * 64 + lane];
+    }
+    store_columns<TM, TN>(p, acc, g, 0u, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), n1 + 1, lane);
+}
+
+namespace {
+
+// pixel tiles (blocks along x) of a patch-kernel problem
+uint32_t patch_pixel_tiles(const IgemmProblem &p)
+{
+    return p.patch.tiles_per_img ? (p.N / p.patch.divP.d) * (uint32_t)p.patch.tiles_per_img : (p.N + 127) / 128;
+}
+
+template <int NP, int TM, int WM, int WK, int NSL>
+int launch_cfg(const IgemmProblem &p, hipStream_t stream)
+{
+    constexpr int MT = WM * TM * 16, TN = 128 / (16 * (4 / (WM * WK)));
+    dim3 grid(p.patch.tile_count ? p.patch.tile_count : patch_pixel_tiles(p), (p.M + MT - 1) / MT, p.groups);
+    if (grid.y > 65535u || grid.z > 65535u) return CG_EUNSUPPORTED;
+    int rec = -1;
+    if (prof_on()) {
+        char name[64];
+        snprintf(name, sizeof name, NP == 1 ? "igemm_patch%s_kernel<%dx128,%d,bf16>" : NP == 2 ? "igemm_patch%s_kernel<%dx128,%d,bf16x3>" : "igemm_patch%s_kernel<%dx128,%d>",
+                 WK == 2 && NP == 3 ? "16" : "", MT, NSL);
+        rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
+    }
+    constexpr size_t patch = PatchLds<NP, NSL>::BYTES, sums = WK == 2 ? (4 / (WM * WK)) * WM * TM * TN * 64 * 16 : 0, lds = patch > sums ? patch : sums;
+    static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_patch_kernel<NP, TM, WM, WK, NSL>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        attr_set.store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((split_patch_kernel<NP, TM, WM, WK, NSL>), grid, dim3(256), lds, stream, p);
+    prof_end(rec, stream);
+    CG_HIP_TRY(hipGetLastError());
+    return CG_OK;
+}
+
+template <int NP, int NSL> int launch_tiles(const IgemmProblem &p, int mt, hipStream_t stream)
+{
+    if constexpr (NP == 3) {
+        if (mt == 48) return launch_cfg<NP, 3, 1, 2, NSL>(p, stream);
+        if (mt == 32) return launch_cfg<NP, 2, 1, 2, NSL>(p, stream);
+        if (mt == 16) return launch_cfg<NP, 1, 1, 2, NSL>(p, stream);
+    }
+    if (mt == 192) return launch_cfg<NP, 3, 4, 1, NSL>(p, stream);
+    if (mt == 128) return launch_cfg<NP, 2, 4, 1, NSL>(p, stream);
+    return launch_cfg<NP, 1, 4, 1, NSL>(p, stream);
+}
+
+}  // namespace
+
+// This file is compiled once per number of pieces (CG_NP), in parallel.
+#define CG_CAT_(a, b) a##b
+#define CG_CAT(a, b) CG_CAT_(a, b)
+int CG_CAT(split_patch_tiles_, CG_NP)(const IgemmProblem &p, int mt, hipStream_t stream)
+{
+    if (p.patch.nsl == 4) return launch_tiles<CG_NP, 4>(p, mt, stream);
+    if (p.patch.nsl == 5) return launch_tiles<CG_NP, 5>(p, mt, stream);
+    return launch_tiles<CG_NP, 6>(p, mt, stream);
+}
+
+#if CG_NP == 3
+int split_patch_tiles_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_2(const IgemmProblem &p, int mt, hipStream_t stream);
+
+namespace {
+
+int patch_launch_tiles(const IgemmProblem &p, int mt, hipStream_t stream)
+{
+    if (p.math == CG_MATH_BF16) return split_patch_tiles_1(p, mt, stream);
+    if (p.math == CG_MATH_BF16X3) return split_patch_tiles_2(p, mt, stream);
+    return split_patch_tiles_3(p, mt, stream);
+}
+
+// Row-tile height.  Two blocks are resident per compute unit (an odd one out runs alone and a little
+// slower than a pair); a block's time goes with its rows plus a constant, 18 to 40 rows' worth (bringing
+// the patch, the epilogue; 13x13 planes, 384 rows: 64 / 128 / 192-row blocks took 68 / 121 / 190 us).
+int patch_mt(uint32_t M, uint32_t N, uint32_t groups)
+{
+    const int cand[3] = {192, 128, 64};
+    int best = 64;
+    double best_cost = 1e300;
+    const uint64_t units = igemm_resident_blocks() > 1 ? igemm_resident_blocks() / 2 : 1;
+    for (int c : cand) {
+        const uint64_t tiles = (uint64_t)((M + c - 1) / c) * ((N + 127) / 128) * groups;
+        const uint64_t n = (tiles + units - 1) / units;
+        const double cost = ((n & 1) ? (double)(n - 1) + 1.2 : (double)n) * (c + 40);
+        if (cost < best_cost * 0.999) { best_cost = cost; best = c; }
+    }
+    return best;
+}
+
+int patch_launch(const IgemmProblem &p, hipStream_t stream)
+{
+    // few rows: a wave takes them all, and the steps are shared out instead (a 64-row tile multiplies 64
+    // rows for 48).  The reduced modes have 64-row tiles only.
+    if (p.M <= 48 && p.math == CG_MATH_FP32) return patch_launch_tiles(p, (int)(p.M + 15) / 16 * 16, stream);
+    int mt = patch_mt(p.M, p.N, p.groups);
+    // Two blocks are resident per compute unit, so blocks run in rounds of g_resident_blocks that
+    // start and end together.  When the last round would be less than three quarters full, the
+    // pixel tiles of the whole rounds go out as one launch and the rest as a second launch of
+    // 64-row tiles: three or two small blocks in place of a large one fill the compute units that
+    // the short round would leave idle (676 blocks of 192 rows: 512 + 492 of 64 rows).  Forward only:
+    // backward-data shares the GPU with backward-weight on another stream, whose blocks already
+    // fill those compute units, and a second dependent launch then only delays it (measured).
+    // Backward-data (mirrored taps) in the same situation takes 64-row tiles for the whole launch: three
+    // of those blocks fit a compute unit, and twice or three times as many, shorter blocks quantise
+    // better (676 blocks of 192 rows = 1.32 rounds of 512; 2028 of 64 rows = 2.64 rounds of 768).
+    // Alone on the GPU: conv4-shaped 0.516 -> 0.461 ms, conv5-shaped 0.352 -> 0.315 ms at B = 256 (a
+    // one-stream step 11.17 -> 10.82 ms); beside backward-weight on another stream, whose blocks fill the
+    // short round anyway, the step was 0.07 ms slower with it, so a caller that runs such a stream says
+    // so (beside_other_stream) and keeps the large tiles.
+    if (mt > 64 && p.patch.tile_count == 0 && p.patch.flip && p.patch.nsl == 4 && !p.beside_other_stream) {
+        const uint32_t rb = igemm_resident_blocks();
+        const uint64_t blocks = (uint64_t)patch_pixel_tiles(p) * ((p.M + mt - 1) / mt) * p.groups;
+        const uint32_t rest = (uint32_t)(blocks % rb);
+        if (blocks / rb >= 1 && rest > 0 && rest < rb * 3 / 4) mt = 64;
+    }
+    if (mt > 64 && p.patch.tile_count == 0 && !p.patch.flip) {
+        const uint32_t g_resident_blocks = igemm_resident_blocks();
+        const uint32_t px = patch_pixel_tiles(p), per_px = ((p.M + mt - 1) / mt) * p.groups;
+        const uint64_t blocks = (uint64_t)px * per_px;
+        const uint32_t rounds = (uint32_t)(blocks / g_resident_blocks);
+        const uint32_t rest = (uint32_t)(blocks - (uint64_t)rounds * g_resident_blocks);
+        const uint32_t px_main = rounds * g_resident_blocks / per_px;
+        const uint32_t tail_blocks = (px - px_main) * ((p.M + 63) / 64) * p.groups;
+        if (rounds >= 1 && rest > 0 && rest < g_resident_blocks * 3 / 4 && px_main > 0 && px_main < px &&
+            tail_blocks <= g_resident_blocks) {
+            IgemmProblem a = p, b = p;
+            a.patch.tile0 = 0;
+            a.patch.tile_count = px_main;
+            b.patch.tile0 = px_main;
+            b.patch.tile_count = px - px_main;
+            const double fl = p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups;
+            a.flops = fl * px_main / px;
+            b.flops = fl - a.flops;
+            const int rc = patch_launch_tiles(a, mt, stream);
+            return rc != CG_OK ? rc : patch_launch_tiles(b, 64, stream);
+        }
+    }
+    return patch_launch_tiles(p, mt, stream);
+}
+
+}  // namespace
+
+static std::atomic<uint32_t> g_patch_min_tiles{512};
+void patch_set_min_tiles(uint32_t t) { g_patch_min_tiles.store(t, std::memory_order_relaxed); }
+
+bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
+{
+    g.nsl = 0;
+    const int KK = g.KH * g.KW;
+    if (g.Cred == 0 || g.Cred % 16 || KK < 5 || g.s <= 0 || g.OHo <= 0 || g.OWo <= 0) return false;
+    if (g.src_elems * 4 > kMaxBufferBytes || N >= (1u << 30)) return false;
+    g.Wp = (g.OWo - 1) * g.s + g.KW;
+    const int64_t rfull = (int64_t)((g.OHo - 1) * g.s + g.KH) * g.Wp;
+    if (rfull >= (1 << 24)) return false;
+    g.Rfull = (int32_t)rfull;
+    const uint32_t P = (uint32_t)g.OHo * (uint32_t)g.OWo;
+    g.divP = make_fastdiv(P);
+    g.divOW = make_fastdiv((uint32_t)g.OWo);
+    g.divWp = make_fastdiv((uint32_t)g.Wp);
+    g.divRfull = make_fastdiv((uint32_t)g.Rfull);
+    g.divKW = make_fastdiv((uint32_t)g.KW);
+    // The kernel has no K slices, and a block alone on a compute unit waits for its own loads: below 256
+    // tiles of 64 rows the gathered kernel, cut along K, is faster (32 images of 14x14, 128 rows: 98 tiles,
+    // 79 us here, 54 there; 64 images of 13x13, two groups of 192 rows: 510 tiles, 98 us here, 147 there).
+    if ((uint64_t)((M + 63) / 64) * ((N + 127) / 128) * groups * 2 < g_patch_min_tiles.load(std::memory_order_relaxed)) return false;
+    // The largest patch any block needs: a fragment read reaches (KH-1)*Wp + KW-1 beyond sigma, and
+    // sigma + that stays below the slot count of the block's segments, which is what is counted.
+    auto slots = [&](uint32_t n0, uint32_t n1) {
+        const uint32_t bA = n0 / P, oyA = (n0 % P) / (uint32_t)g.OWo, bB = n1 / P, oyB = (n1 % P) / (uint32_t)g.OWo;
+        if (bA == bB) return (int64_t)((oyB - oyA) * g.s + g.KH) * g.Wp;
+        return (int64_t)(((uint32_t)g.OHo - 1 - oyA) * g.s + g.KH) * g.Wp + (int64_t)(bB - bA - 1) * g.Rfull +
+               (int64_t)(oyB * g.s + g.KH) * g.Wp;
+    };
+    int64_t smax = 0;
+    for (uint32_t n0 = 0; n0 < N; n0 += 128) {
+        const int64_t sl = slots(n0, (n0 + 127 < N - 1) ? n0 + 127 : N - 1);
+        if (sl > smax) smax = sl;
+    }
+    g.tiles_per_img = 0;
+    g.divTpi = make_fastdiv(1);
+    if (smax <= 4 * 64) { g.nsl = 4; return true; }
+    // large images: blocks that stay inside one image need smaller patches (every image is the same)
+    if (N % P) return false;
+    int64_t amax = 0;
+    for (uint32_t n0 = 0; n0 < P; n0 += 128) {
+        const int64_t sl = slots(n0, (n0 + 127 < P - 1) ? n0 + 127 : P - 1);
+        if (sl > amax) amax = sl;
+    }
+    // six chunks (planes 56 wide with a 3x3 window: four pixel rows, 348 slots) leave room for 128-row
+    // tiles with a three-stage filter ring
+    if (amax > 6 * 64) return false;
+    g.nsl = amax > 5 * 64 ? 6 : 5;
+    g.tiles_per_img = (int32_t)((P + 127) / 128);
+    g.divTpi = make_fastdiv((uint32_t)g.tiles_per_img);
+    return true;
+}
+
+int split_patch_launch(const IgemmProblem &p, hipStream_t stream)
+{
+    if (!p.c_ptr || !aligned16(p.c_ptr) || !p.A.ptr || !aligned16(p.A.ptr)) return CG_EINVAL;
+    if (p.M == 0 || p.N == 0 || p.K == 0 || p.groups == 0) return CG_EINVAL;
+    if (p.M >= (1u << 30) || p.N >= (1u << 30) || p.K >= (1u << 30)) return CG_EUNSUPPORTED;
+    if (p.bias_mode && !p.bias) return CG_EINVAL;
+    if (p.math != CG_MATH_FP32 && p.math != CG_MATH_BF16 && p.math != CG_MATH_BF16X3) return CG_EINVAL;
+    const PatchGeom &g = p.patch;
+    if (!g.src || !aligned16(g.src) || g.nsl < 4 || g.nsl > 6 || p.splits != 1 || g.Cred % 16 ||
+        p.K != g.Cred * (uint32_t)(g.KH * g.KW))
+        return CG_EINVAL;
+    // the filter copy holds M rows of K floats per group, and byte offsets into it stay below the marks
+    // that stand for "out of range"
+    if (p.A.elems * 4 > kMaxBufferBytes || (uint64_t)p.A.gstride * p.groups > p.A.elems || (uint64_t)p.M * p.K > (uint64_t)p.A.gstride)
+        return CG_EUNSUPPORTED;
+    return patch_launch(p, stream);
+}
+
+#endif  // CG_NP == 3
+
+}  // namespace cg
