@@ -156,6 +156,23 @@ struct WgradGeom {
     FastDiv divOW, divWp, divKK, divKW;
 };
 
+// Backward-weight from padded source rows in LDS on the bf16 matrix instructions (split_wgrad.hip): the
+// reduction walks units of ipu images x one band of Rb output rows.
+struct BandGeom {
+    const float *x, *dy;
+    uint64_t x_elems, dy_elems;
+    int32_t N, C, Cg, H, W, OH, OW, s, pad_h, pad_w, KH, KW;
+    int32_t M;                // all output channels (dy's channel count)
+    int32_t Wp;               // padded patch width (OW-1)*s + KW
+    int32_t nb, Rb;           // bands per image, output rows per band (the last band of an image takes the rest)
+    int32_t ipu;              // images per unit (1 where an image has several bands)
+    int32_t steps;            // steps of 32 pixels per unit
+    int32_t units, units_per_split;
+    int32_t tap_blocks;       // blocks of nine taps
+    int32_t mt, nsl;          // row-tile height; 64-slot chunks per channel: 4 or 8, 0 = unusable
+    FastDiv divSS, divWp, divP8, divOW, divKW, divNB;       // slots of an image's band; octets of its pixels
+};
+
 // C[m][n] = sum_k A(m,k) * B(n,k)   (+ bias), for `groups` independent problems, the K range
 // optionally cut into `splits` slices whose partial results go to consecutive output planes.
 struct IgemmProblem {
@@ -184,10 +201,15 @@ struct IgemmProblem {
     int math;                 // CG_MATH_FP32, CG_MATH_BF16 or CG_MATH_BF16X3: what the matrix instructions multiply in
     int mt;                   // row-tile height igemm_run has planned the K slices for (0: igemm_launch chooses)
     int beside_other_stream;  // the caller runs matrix kernels on another stream meanwhile (tile choice of the patch kernel)
+    // at most one of the three is set, and names the geometry in use
     int use_patch;            // B is described by `patch` (and A is the matching tap-major matrix); B unused
-    PatchGeom patch;
+    int use_band;             // backward-weight from padded rows in LDS (`band`): A, B unused, K counted in pixels
     int use_wgrad;            // backward-weight from image bands (`wgrad`): A = dy rows, B unused, K counted in pixels
-    WgradGeom wgrad;
+    union {
+        PatchGeom patch;
+        BandGeom band;
+        WgradGeom wgrad;
+    };
 };
 
 // Fills the derived fields of a patch description (Wp, Rfull, dividers) and decides whether the
@@ -203,6 +225,11 @@ void patch_set_min_tiles(uint32_t t);
 
 // Validates the problem against what the kernels assume and launches it.
 int split_patch_launch(const IgemmProblem &p, hipStream_t stream);      // problems with a patch (igemm_launch dispatches)
+int split_wgrad_launch(const IgemmProblem &p, hipStream_t stream);      // use_band (igemm_launch dispatches)
+int split_wgrad_3(const IgemmProblem &p, hipStream_t stream);
+// Fills the derived fields and chooses units, tile and K slices (legacy_splits: what the gathered kernel would use);
+// false where the kernel does not apply.
+bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t legacy_splits, uint32_t *splits);
 uint32_t igemm_resident_blocks();
 int igemm_pick_mt(uint32_t M, uint32_t N, uint32_t groups);
 int igemm_launch(const IgemmProblem &p, hipStream_t stream);
@@ -219,6 +246,7 @@ void igemm_host_element(const Operand &op, uint32_t row, uint32_t k, int64_t *of
 // on scheduling).  igemm_ws_bytes() says how much workspace igemm_run() needs for a problem.
 struct SplitPlan { uint32_t splits, k_per_split; size_t ws_bytes; int mt; };
 SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
+uint32_t tall_tile_splits(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);       // K slices of tiles of up to 256 rows
 size_t igemm_ws_bytes(const IgemmProblem &p);
 // rider: a small convolution's bias gradient (db[m] = sum of dy over images and pixels), summed by
 // extra blocks of the K-slice finishing launch, one block per channel, instead of a launch of its

@@ -576,6 +576,7 @@ void igemm_host_element(const Operand &op, uint32_t row, uint32_t k, int64_t *of
 int igemm_launch(const IgemmProblem &p0, hipStream_t stream)
 {
     if (p0.use_patch) return split_patch_launch(p0, stream);
+    if (p0.use_band) return split_wgrad_launch(p0, stream);
     if (p0.math != CG_MATH_FP32 && p0.math != CG_MATH_BF16 && p0.math != CG_MATH_BF16X3) return CG_EINVAL;
     IgemmProblem p = p0;
     if (!p.c_ptr || !aligned16(p.c_ptr)) return CG_EINVAL;
@@ -793,8 +794,8 @@ static SplitPlan slices(uint32_t M, uint32_t N, uint32_t K, uint32_t groups, int
 
 // A slice's sums are as long as its share of K, and their rounding error with them.  The tiles of up to
 // 256 rows that pick_mt chooses from leave room for more slices than lower ones in one round; where a
-// slice would get more than 4/3 as long, the blocks make two or more rounds instead (the three-piece
-// products round a sum 0.86 times as much as the fp32 instruction, so the error stays below its).
+// slice would get more than 4/3 as long, the blocks make two or more rounds instead (up to kOwnK terms the
+// three-piece products round a sum 0.86 times as much as the fp32 instruction, so the error stays below its).
 SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups)
 {
     const int mt = gemm_mt(M, N, groups, K);
@@ -812,6 +813,11 @@ SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups)
     return pl;
 }
 
+uint32_t tall_tile_splits(uint32_t M, uint32_t N, uint32_t K, uint32_t groups)
+{
+    return slices(M, N, K, groups, pick_mt(M, N, groups, K)).splits;
+}
+
 // What the caller is told to bring.  Never less than the tiles of up to 256 rows need that pick_mt
 // chooses from: a size that a program has been told stays enough, and the entry point with a scratch
 // array of a fixed size keeps refusing exactly the problems it refused.
@@ -819,7 +825,8 @@ size_t igemm_ws_bytes(const IgemmProblem &p)
 {
     if (p.use_patch) return 0;
     if (p.use_wgrad) return p.splits > 1 ? (size_t)p.splits * p.groups * p.M * p.N * sizeof(float) : 0;
-    const size_t a = plan_split(p.M, p.N, p.K, p.groups).ws_bytes;
+    const size_t a = p.use_band ? (p.splits > 1 ? (size_t)p.splits * p.groups * p.M * p.N * sizeof(float) : 0)
+                                : plan_split(p.M, p.N, p.K, p.groups).ws_bytes;
     const size_t b = slices(p.M, p.N, p.K, p.groups, pick_mt(p.M, p.N, p.groups, p.K)).ws_bytes;
     return a > b ? a : b;
 }
@@ -828,7 +835,7 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
 {
     if (rider_taken) *rider_taken = false;
     const SplitPlan pl = p0.use_patch   ? SplitPlan{1, p0.K, 0, 0}
-                         : p0.use_wgrad ? SplitPlan{p0.splits, p0.K, igemm_ws_bytes(p0), 0}
+                         : p0.use_wgrad || p0.use_band ? SplitPlan{p0.splits, p0.K, (size_t)(p0.splits > 1 ? p0.splits : 0) * p0.groups * p0.M * p0.N * sizeof(float), 0}
                                         : plan_split(p0.M, p0.N, p0.K, p0.groups);
     if (pl.splits <= 1) {
         IgemmProblem p = p0;

@@ -110,7 +110,14 @@ template <int TM, int TN> struct ColumnGroup { static constexpr int G = TM >= 3 
 // column tile j, one group ahead; work(slot) is other work of the step, spread over the slots 0 ..
 // SLOTS-1, one behind each product of a group, whose vector instructions are laid between the matrix
 // instructions.
-template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G> struct MmaStep {
+// OWN: a step's products are added up on their own, from zero, and then to the accumulator by four vector
+// adds a tile: the sum is rounded once per 32 terms instead of six times.  That is what long reductions
+// need: the instruction drops what lies below the last place of the sum it adds to, and over thousands of
+// steps the loss adds up.  Error against 64 bits, fp32 instruction / plain / own: 363 terms 3.4e-7 / 2.8e-7 /
+// 0.8e-7, 601 terms 4.2e-7 / 4.1e-7 / 1.7e-7, 4555 terms 1.2e-6 / 3.2e-6 / 1.0e-6.  It costs a tenth of the
+// time and registers, so shorter sums do without.
+constexpr uint32_t kOwnK = 640;
+template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G, bool OWN = false> struct MmaStep {
     static constexpr int JG = JG_, PR = Products<NP>::N, SLOTS = TN / JG * PR;
     static_assert(TN % JG == 0, "whole groups");
     struct NoWork {};
@@ -126,14 +133,18 @@ template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G> struct MmaSt
 #pragma unroll
                 for (int jj = 0; jj < JG; ++jj) read_b((g + 1) * JG + jj, bp[(g + 1) & 1][jj]);
             }
+            v4f own[OWN ? TM : 1][OWN ? JG : 1];
             static_for<0, PR>([&](auto PC) {
                 constexpr int pi = decltype(PC)::value, a = Products<NP>::A[pi], b = Products<NP>::B[pi];
 #pragma unroll
                 for (int jj = 0; jj < JG; ++jj)
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-                        acc[i][g * JG + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bp[g & 1][jj][b]),
-                                                                                      __builtin_bit_cast(bf16x8, ap[i][a]), acc[i][g * JG + jj], 0, 0, 0);
+                    for (int i = 0; i < TM; ++i) {
+                        v4f &to = OWN ? own[OWN ? i : 0][OWN ? jj : 0] : acc[i][g * JG + jj];
+                        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bp[g & 1][jj][b]), __builtin_bit_cast(bf16x8, ap[i][a]),
+                                                                     OWN && pi == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : to, 0, 0, 0);
+                        if constexpr (OWN && pi == PR - 1) acc[i][g * JG + jj] += to;
+                    }
                 if constexpr (!std::is_same_v<std::decay_t<Work>, NoWork>) {
                     work(std::integral_constant<int, g * PR + pi>{});
                     static_for<0, TM * JG>([&](auto) {

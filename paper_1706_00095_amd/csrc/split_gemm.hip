@@ -215,7 +215,7 @@ __device__ __forceinline__ Rsrc rsrc_of(const Operand &op, uint32_t g)
 
 }  // namespace
 
-template <int NP, int TM, int WM, class LA, class LB>
+template <int NP, int TM, int WM, bool OWN, class LA, class LB>
 __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(const IgemmProblem p)
 {
     constexpr int WAVES = WM == 8 ? 8 : 4, WN = WAVES / WM, TN = 128 / (16 * WN), MT = WM * TM * 16, NT = 128, NU = 8 / WAVES;
@@ -239,8 +239,12 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
     lb.init(p.B, n0, p.N, wave, lane);
 
     // raw operands one step ahead of their cutting, pieces one step ahead of their use
+    // (32 rows a wave and sums of their own: the rows are cut in front of the products of their own step instead,
+    // 24 registers less; two column tiles at a time then fit, without which the sums wait for each other:
+    // 11x11 windows over 227x227 forward 725 us with one)
+    constexpr bool LATE = OWN && TM == 2 && WM == 4;
     float ar[TM][8], br[NU][8];
-    v4u ap[2][TM][NP], bc[NP];
+    v4u ap[LATE ? 1 : 2][TM][NP], bc[NP];
     auto store_b = [&](int u, int buf) {
         const int at = buf * BUF + LB::unit(u, wave, lane);
 #pragma unroll
@@ -264,17 +268,30 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
         store_b(u, 0);
     }
     load_columns(kbeg + KS);
+    if constexpr (!LATE) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) split8<NP>(ar[i], ap[0][i]);
-    la.load(rA, p.A, kbeg + KS, kend, lane, ar);
+        for (int i = 0; i < TM; ++i) split8<NP>(ar[i], ap[0][i]);
+        la.load(rA, p.A, kbeg + KS, kend, lane, ar);
+    }
 
-    using Step = MmaStep<NP, TM, TN, WM == 8 ? 2 : ColumnGroup<TM, TN>::G>;
+    using Step = MmaStep<NP, TM, TN, WM == 8 ? 2 : ColumnGroup<TM, TN>::G, OWN>;
     auto step = [&](auto PC, int s) {
-        constexpr int par = decltype(PC)::value;
+        constexpr int par = LATE ? 0 : decltype(PC)::value, nxt = LATE ? 0 : par ^ 1;
         block_sync_lds();           // this step's columns are in LDS, and everyone is done with the other buffer
         const int rd = (s & 1) * BUF + q * OS + wn * TN * 16 + l16;
         const uint32_t k2 = kbeg + (uint32_t)(s + 2) * KS;
         float bigA = 0.f, bigB = 0.f;
+        if constexpr (LATE) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) split8_pair<NP>(ar[i], t, ap[0][i], bigA);
+            if (__builtin_expect(bigA >= CG_HUGE, 0)) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[0][i]);
+            }
+            la.load(rA, p.A, kbeg + (uint32_t)(s + 1) * KS, kend, lane, ar);
+        }
         auto read_b = [&](int j, v4u (&pc)[NP]) {
 #pragma unroll
             for (int k = 0; k < NP; ++k) pc[k] = lds[rd + j * 16 + k * PLANE];
@@ -282,13 +299,13 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
         // The next step's rows are cut (4*TM items, then one to mend infinities and fetch the rows after),
         // then its columns (4*NU, and one to mend), then the columns after are fetched (4).
         auto item = [&](auto OC) {
-            constexpr int o = decltype(OC)::value, A1 = 4 * TM, B0 = A1 + 1, B1 = B0 + 4 * NU;
-            if constexpr (o < A1) split8_pair<NP>(ar[o / 4], o % 4, ap[par ^ 1][o / 4], bigA);
+            constexpr int o = decltype(OC)::value, A1 = LATE ? -1 : 4 * TM, B0 = A1 + 1, B1 = B0 + 4 * NU;
+            if constexpr (o < A1) split8_pair<NP>(ar[o / 4], o % 4, ap[nxt][o / 4], bigA);
             else if constexpr (o == A1) {
                 if constexpr (NP == 3) {
                     if (__builtin_expect(bigA >= CG_HUGE, 0)) {
 #pragma unroll
-                        for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[par ^ 1][i]);
+                        for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[nxt][i]);
                     }
                 }
                 la.load(rA, p.A, k2, kend, lane, ar);
@@ -308,7 +325,7 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
                 }
             } else lb.template load<o - B1 - 1>(rB, p.B, k2, kend, wave, lane, br);
         };
-        Step::run(ap[par], acc, read_b, Step::template spread<4 * TM + 4 * NU + 6>(item));
+        Step::run(ap[par], acc, read_b, Step::template spread<(LATE ? 0 : 4 * TM + 1) + 4 * NU + 5>(item));
     };
     for (int s = 0; s < ns; s += 2) {
         step(std::integral_constant<int, 0>{}, s);
@@ -319,8 +336,8 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
 
 namespace {
 
-template <int NP, int TM, int WM, class LA, class LB>
-int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
+template <int NP, int TM, int WM, bool OWN, class LA, class LB>
+int launch_own(const IgemmProblem &p, const char *modes, hipStream_t stream)
 {
     constexpr int MT = WM * TM * 16;
     dim3 grid((p.N + 127) / 128, (p.M + MT - 1) / MT, p.groups * p.splits);
@@ -335,14 +352,24 @@ int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
     static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
     static std::atomic<bool> attr_set{false};      // raising the dynamic-LDS limit: once per kernel (repeating it is harmless)
     if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_gemm_kernel<NP, TM, WM, LA, LB>),
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_gemm_kernel<NP, TM, WM, OWN, LA, LB>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((split_gemm_kernel<NP, TM, WM, LA, LB>), grid, dim3(WM == 8 ? 512 : 256), lds, stream, p);
+    hipLaunchKernelGGL((split_gemm_kernel<NP, TM, WM, OWN, LA, LB>), grid, dim3(WM == 8 ? 512 : 256), lds, stream, p);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
+}
+
+// three pieces: long sums are added up step by step (kOwnK)
+template <int NP, int TM, int WM, class LA, class LB>
+int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
+{
+    if constexpr (NP == 3) {
+        if (p.k_per_split > kOwnK) return launch_own<NP, TM, WM, true, LA, LB>(p, modes, stream);
+    }
+    return launch_own<NP, TM, WM, false, LA, LB>(p, modes, stream);
 }
 
 // At most one block a compute unit: eight waves of 16 rows instead of four of 32, so that two share a

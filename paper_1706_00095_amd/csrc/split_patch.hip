@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
 
     // (the rows are cut in one piece in front of the products: cutting them behind the products of the step
     // before, as split_gemm_kernel does, takes 24 more registers and spills)
-    using Step = MmaStep<NP, TM, TN, 2>;
+    using Step = MmaStep<NP, TM, TN, TM >= 3 ? 1 : 2, NP == 3>;
     for (int grp = 0; grp < ngrp; ++grp) {
         const int ns = steps_of(grp);
         const bool pair = 2 * grp + 1 < ncb16;

@@ -33,6 +33,29 @@ PATCH = {
 }
 
 
+# backward-weight from padded rows in LDS: several images a unit with the last unit short, bands with a short last
+# one, a stride, a channel block that is not full, more than nine taps, row tiles of 64, 128 and 192, slots beyond 256
+BANDS = {
+    "b13_m384": (7, dict(C=208, H=13, M=384, k=3, stride=1, pad=1, groups=1)),
+    "b7_units_of_images": (50, dict(C=44, H=7, M=70, k=3, stride=1, pad=1, groups=1)),
+    "b5x5_g2": (5, dict(C=96, H=27, M=136, k=5, stride=1, pad=2, groups=2)),
+    "b28_bands": (4, dict(C=64, H=28, W=25, M=64, k=3, stride=1, pad=1, groups=1)),
+    "b_stride2_nopad": (6, dict(C=90, H=31, W=29, M=192, k=3, stride=2, pad=0, groups=1)),
+    "b_wide": (3, dict(C=40, H=19, W=90, M=64, k=3, stride=1, pad=1, groups=1)),
+}
+
+
+@pytest.mark.parametrize("name", list(BANDS))
+def test_band_edges_exact(orc32, name):
+    B, cfg = BANDS[name]
+    cg.cg_debug_resident_blocks(2)          # a small problem fills a small chip
+    try:
+        _, names = _all_three(orc32, B, cfg, seed=sum(map(ord, name)), fwd=False, bwd_data=False)
+    finally:
+        cg.cg_debug_resident_blocks(512)
+    assert any(",band" in n for n in names), names
+
+
 @pytest.mark.parametrize("name", list(EDGES))
 def test_tile_edges_exact(orc32, name):
     B, cfg = EDGES[name]
