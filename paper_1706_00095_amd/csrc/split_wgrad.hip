@@ -251,7 +251,7 @@ template <int NP, int TM, int NSL, bool OWN> int launch_own(const IgemmProblem &
 }
 
 // three pieces: a step's products are added up on their own (MmaStep), whatever the slice: the padding of
-// an image's pixels makes the steps of a short slice many (32 images of 14x14: 3.0e-7 off 64 bits without, 1.4e-7
+// an image's pixels makes the steps of a short slice many (32 images of 14x14: 3.0e-7 off 64 bits without, 1.35e-7
 // with, 2.1e-7 the fp32 instruction)
 template <int NP, int TM, int NSL> int launch_cfg(const IgemmProblem &p, hipStream_t stream)
 {
