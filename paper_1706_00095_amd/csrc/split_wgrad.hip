@@ -149,6 +149,16 @@ __global__ __launch_bounds__(256, 2) void split_wgrad_kernel(const IgemmProblem 
     for (int u = u0; u < u1; ++u) {
         const Unit un = unit_of(u);
         for (int s = 0; s < g.steps; ++s) {
+            // this lane's octet of pixels: image of the unit, first pixel in the band
+            const uint32_t oc = (uint32_t)(4 * s + q), seg = fdiv(oc, g.divP8);
+            const int32_t po = (int32_t)(oc - seg * g.divP8.d) * 8;
+            // A quad that reaches beyond the band's last pixel brings what follows in memory (the next row's
+            // pixels, or the next channel's): it would meet zeros of x, but an infinity or a NaN times zero is NaN.
+            if ((un.npix & 3) != 0 && __any(po < un.npix && po + 8 > un.npix))
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) ar[i][t] = po + t < un.npix ? ar[i][t] : 0.f;
             v4u ap[TM][NP];
             float big = 0.f;
 #pragma unroll
@@ -169,8 +179,7 @@ __global__ __launch_bounds__(256, 2) void split_wgrad_kernel(const IgemmProblem 
             int32_t at[2], mask[2];
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
-                const uint32_t oc = (uint32_t)(4 * s + q), seg = fdiv(oc, g.divP8);
-                const int32_t px = (int32_t)(oc - seg * g.divP8.d) * 8 + 4 * hf + (l16 >> 2);
+                const int32_t px = po + 4 * hf + (l16 >> 2);
                 const uint32_t row = fdiv((uint32_t)px, g.divOW);
                 const int32_t col = px - (int32_t)(row * g.divOW.d);
                 const bool ok = (int)seg < g.ipu && px < un.npix && un.n0 + (int)seg < g.N;
