@@ -717,7 +717,11 @@ __device__ __forceinline__ void finish_store(const FinishArgs &a, uint32_t i, fl
     *dst = s;
 }
 
-template <int ROWS> __global__ __launch_bounds__(256) void splitk_finish_kernel(const FinishArgs a)
+// AHEAD: a thread's next eight loads are in flight together (under a condition each, where fewer are left).  It pays
+// where a thread has many; whole passes, us, plain / ahead: one thread per element, 2 slices 33.8 / 39.8, 3 slices
+// 26.9 / 28.4, 7 slices 16.1 / 15.0, 13 slices 16.1 / 14.4; eight rows of threads, 32 slices 44.8 / 49.4, 49 slices 15.3 / 14.0,
+// 64 slices 113.8 / 109.2, 512 slices 55.6 / 44.9.
+template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_finish_kernel(const FinishArgs a)
 {
     if (a.r_dy && blockIdx.x >= a.finish_blocks) {       // a rider block: one channel of the bias gradient
         const int m = (int)(blockIdx.x - a.finish_blocks);
@@ -728,9 +732,10 @@ template <int ROWS> __global__ __launch_bounds__(256) void splitk_finish_kernel(
     const uint32_t nblk = a.r_dy ? a.finish_blocks : gridDim.x;
     if (ROWS == 1) {
         for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < a.total; i += nblk * 256) {
-            // the slices' loads are independent: eight in flight, added in slice order
             float s = a.part[i];
-            for (int k0 = 1; k0 < a.splits; k0 += 8) {
+            if constexpr (!AHEAD)
+                for (int k = 1; k < a.splits; ++k) s += a.part[(int64_t)k * a.plane + i];
+            else for (int k0 = 1; k0 < a.splits; k0 += 8) {
                 float v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = k0 + u < a.splits ? a.part[(int64_t)(k0 + u) * a.plane + i] : 0.f;
@@ -747,8 +752,10 @@ template <int ROWS> __global__ __launch_bounds__(256) void splitk_finish_kernel(
     for (uint32_t i0 = blockIdx.x * 32; i0 < a.total; i0 += nblk * 32) {
         const uint32_t i = i0 + el;
         float s = 0.f;
-        if (i < a.total)
-            for (int k0 = r; k0 < a.splits; k0 += 64) {
+        if (i < a.total) {
+            if constexpr (!AHEAD)
+                for (int k = r; k < a.splits; k += 8) s += a.part[(int64_t)k * a.plane + i];
+            else for (int k0 = r; k0 < a.splits; k0 += 64) {
                 float v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = k0 + 8 * u < a.splits ? a.part[(int64_t)(k0 + 8 * u) * a.plane + i] : 0.f;
@@ -756,6 +763,7 @@ template <int ROWS> __global__ __launch_bounds__(256) void splitk_finish_kernel(
                 for (int u = 0; u < 8; ++u)
                     if (k0 + 8 * u < a.splits) s += v[u];
             }
+        }
         part[r][el] = s;
         __syncthreads();
         if (r == 0 && i < a.total) {
@@ -879,11 +887,13 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
     if (pl.splits >= 16) {
         const unsigned blocks = (a.total + 31) / 32 < 65536 ? (a.total + 31) / 32 : 65536;
         a.finish_blocks = blocks;
-        hipLaunchKernelGGL(splitk_finish_kernel<8>, dim3(blocks + riders), dim3(256), 0, stream, a);
+        if (pl.splits >= 40) hipLaunchKernelGGL((splitk_finish_kernel<8, true>), dim3(blocks + riders), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((splitk_finish_kernel<8, false>), dim3(blocks + riders), dim3(256), 0, stream, a);
     } else {
         const unsigned blocks = (a.total + 255) / 256 < 16384 ? (a.total + 255) / 256 : 16384;
         a.finish_blocks = blocks;
-        hipLaunchKernelGGL(splitk_finish_kernel<1>, dim3(blocks + riders), dim3(256), 0, stream, a);
+        if (pl.splits >= 6) hipLaunchKernelGGL((splitk_finish_kernel<1, true>), dim3(blocks + riders), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((splitk_finish_kernel<1, false>), dim3(blocks + riders), dim3(256), 0, stream, a);
     }
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
