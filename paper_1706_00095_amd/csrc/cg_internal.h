@@ -200,6 +200,7 @@ struct IgemmProblem {
                               // rectifier: the gradient with respect to the rectifier's input), before accumulate
     int math;                 // CG_MATH_FP32, CG_MATH_BF16 or CG_MATH_BF16X3: what the matrix instructions multiply in
     int mt;                   // row-tile height igemm_run has planned the K slices for (0: igemm_launch chooses)
+    int pieces;               // operands in bf16 pieces (split_gemm_kernel) instead of the gathered kernel
     int beside_other_stream;  // the caller runs matrix kernels on another stream meanwhile (tile choice of the patch kernel)
     // at most one of the three is set, and names the geometry in use
     int use_patch;            // B is described by `patch` (and A is the matching tap-major matrix); B unused
@@ -227,26 +228,36 @@ void patch_set_min_tiles(uint32_t t);
 int split_patch_launch(const IgemmProblem &p, hipStream_t stream);      // problems with a patch (igemm_launch dispatches)
 int split_wgrad_launch(const IgemmProblem &p, hipStream_t stream);      // use_band (igemm_launch dispatches)
 int split_wgrad_3(const IgemmProblem &p, hipStream_t stream);
-// Fills the derived fields and chooses units, tile and K slices (legacy_splits: what the gathered kernel would use);
-// false where the kernel does not apply.
-bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t legacy_splits, uint32_t *splits);
 uint32_t igemm_resident_blocks();
-int igemm_pick_mt(uint32_t M, uint32_t N, uint32_t groups);
 int igemm_launch(const IgemmProblem &p, hipStream_t stream);
-// split_gemm_kernel with 1, 2 or 3 bf16 pieces per operand (igemm_launch dispatches on p.math).  b_mode: how B's
-// elements are fetched, 0 rows along the lanes, 1 k along the lanes, 2 aligned quads of k
-int split_gemm_1(const IgemmProblem &p, int mt, bool a_quads, int b_mode, hipStream_t stream);
-int split_gemm_2(const IgemmProblem &p, int mt, bool a_quads, int b_mode, hipStream_t stream);
-int split_gemm_3(const IgemmProblem &p, int mt, bool a_quads, int b_mode, hipStream_t stream);
+// igemm_kernel (gather.hip) in fp32, bf16, bf16x3 (igemm_launch dispatches).  am, bm: how an operand's elements are
+// fetched, 0 rows along the lanes, 1 k along the lanes, 2 aligned quads of k
+int gather_launch_0(const IgemmProblem &p, int mt, int am, int bm, hipStream_t stream);
+int gather_launch_1(const IgemmProblem &p, int mt, int am, int bm, hipStream_t stream);
+int gather_launch_2(const IgemmProblem &p, int mt, int am, int bm, hipStream_t stream);
+int wgrad_launch(const IgemmProblem &p, hipStream_t stream);            // use_wgrad
+// split_gemm_kernel with 1, 2 or 3 bf16 pieces per operand: 16- or 128-row tiles, k a plain stride in A; *_quads: aligned
+// quads of k, else rows along the lanes
+int split_gemm_1(const IgemmProblem &p, int mt, bool a_quads, bool b_quads, hipStream_t stream);
+int split_gemm_2(const IgemmProblem &p, int mt, bool a_quads, bool b_quads, hipStream_t stream);
+int split_gemm_3(const IgemmProblem &p, int mt, bool a_quads, bool b_quads, hipStream_t stream);
 // Host-side evaluation of one operand element: offset and validity (for tests of the maps).
 void igemm_host_element(const Operand &op, uint32_t row, uint32_t k, int64_t *off, int *valid);
+
+// Blocks a split-K launch aims at, from below: two blocks are resident per compute unit, so up to
+// 512 blocks start together and finish together.  A few blocks more than a whole number of such
+// rounds run an extra round on a nearly empty GPU (1040 blocks took 19 % longer than 1000 on the
+// backward-weight shapes of the benchmark), and one round measured faster than two or three.
+constexpr uint64_t kSplitBlocks = 512;
 
 // Split-K front end: when C has too few tiles to fill the chip, the K range is cut into slices
 // whose partial results go to `ws` and are then added in slice order (so results do not depend
 // on scheduling).  igemm_ws_bytes() says how much workspace igemm_run() needs for a problem.
-struct SplitPlan { uint32_t splits, k_per_split; size_t ws_bytes; int mt; };
-SplitPlan plan_split(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
-uint32_t tall_tile_splits(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);       // K slices of tiles of up to 256 rows
+struct SplitPlan { uint32_t splits, k_per_split; size_t ws_bytes; int mt, pieces; };       // pieces: 1 = split_gemm_kernel
+SplitPlan gathered_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
+// Fills the derived fields and chooses units, tile and K slices (other_splits: what the gathered kernel would use);
+// false where the kernel does not apply.
+bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t other_splits, uint32_t *splits);
 size_t igemm_ws_bytes(const IgemmProblem &p);
 // rider: a small convolution's bias gradient (db[m] = sum of dy over images and pixels), summed by
 // extra blocks of the K-slice finishing launch, one block per channel, instead of a launch of its

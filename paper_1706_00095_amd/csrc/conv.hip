@@ -815,7 +815,7 @@ static IgemmProblem bwd_weight_problem(const cg_conv_desc &d, int OH, int OW, co
         bg.x = x; bg.x_elems = wgm.x_elems; bg.dy = dy; bg.dy_elems = p.A.elems;
         bg.N = d.N; bg.C = d.C; bg.Cg = Cg; bg.H = d.H; bg.W = d.W; bg.OH = OH; bg.OW = OW; bg.s = d.stride_h;
         bg.pad_h = d.pad_h; bg.pad_w = d.pad_w; bg.KH = d.KH; bg.KW = d.KW; bg.M = d.M;
-        if (!p.use_wgrad && band_plan(bg, (uint32_t)Mg, (uint32_t)G, tall_tile_splits(p.M, p.N, p.K, p.groups), &splits)) {
+        if (!p.use_wgrad && band_plan(bg, (uint32_t)Mg, (uint32_t)G, gathered_plan(p.M, p.N, p.K, p.groups).splits, &splits)) {
             p.use_band = 1;
             p.band = bg;
             p.splits = splits;

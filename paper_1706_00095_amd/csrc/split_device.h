@@ -111,12 +111,9 @@ template <int TM, int TN> struct ColumnGroup { static constexpr int G = TM >= 3 
 // SLOTS-1, one behind each product of a group, whose vector instructions are laid between the matrix
 // instructions.
 // OWN: a step's products are added up on their own, from zero, and then to the accumulator by four vector
-// adds a tile: the sum is rounded once per 32 terms instead of six times.  That is what long reductions
-// need: the instruction drops what lies below the last place of the sum it adds to, and over thousands of
-// steps the loss adds up.  Error against 64 bits, fp32 instruction / plain / own: 363 terms 3.4e-7 / 2.8e-7 /
-// 0.8e-7, 601 terms 4.2e-7 / 4.1e-7 / 1.7e-7, 4555 terms 1.2e-6 / 3.2e-6 / 1.0e-6.  It costs a tenth of the
-// time and registers, so shorter sums do without.
-constexpr uint32_t kOwnK = 640;
+// adds a tile: the sum is rounded once per 32 terms instead
+// of six times, and the instruction, which drops what lies below the last place of the sum it adds to,
+// drops it from a sum 32 terms long.  Three pieces always do it.
 template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G, bool OWN = false> struct MmaStep {
     static constexpr int JG = JG_, PR = Products<NP>::N, SLOTS = TN / JG * PR;
     static_assert(TN % JG == 0, "whole groups");

@@ -1,6 +1,5 @@
-// Implicit GEMM on the bf16 matrix instructions: C[m][n] = sum_k A(m,k) * B(n,k) for every dense
-// contraction of the iteration that split_patch.hip does not take: backward-weight, the
-// fully-connected passes, 1x1 windows, few channels, small problems.  Operand elements are addressed
+// Implicit GEMM on the bf16 matrix instructions: C[m][n] = sum_k A(m,k) * B(n,k).  The second kernel for
+// gathered problems; igemm.hip says which of them it gets and what both take.  Operand elements are addressed
 // through index maps (cg_internal.h), so the im2col matrix is never materialised; zero padding is
 // folded into the load address (an offset outside the buffer reads 0).
 //
@@ -8,16 +7,15 @@
 // split_patch.hip say what that does to the error and why v_mfma_f32_16x16x32_bf16).
 //
 // What bounds it: the matrix pipe where the reduction is long, the address arithmetic of the gather
-// (one load per element) where B is an image seen through a window, launches and a short K loop in
-// small layers.
+// (one load per element) where B is an image seen through a window.
 //
-// Split of the work.  A block is four waves, MT rows and 128 columns, 32 reduction indices a step.
-// WM = 4: a wave owns 16*TM rows and all 128 columns; its part of A is shared by nobody, goes from
+// Split of the work.  A block is MT rows and 128 columns, 32 reduction indices a step.
+// 128 rows: a wave owns 16*TM rows and all 128 columns; its part of A is shared by nobody, goes from
 // memory straight into registers in the layout of the matrix instruction (eight consecutive k of a
-// row per lane) and is cut there.  B is shared by all waves: 16 elements per thread and step are
+// row per lane) and is cut there.  B is shared by all waves: 16 (eight waves: 8) elements per thread and step are
 // loaded one step ahead, cut once, and written to LDS as [piece][octet of k][column], from where an
 // operand is one 16-byte read per piece.  Two LDS buffers, one barrier a step.
-// WM = 1 (at most 32 rows): every wave takes all the rows and 32 columns.
+// 16 rows: every one of four waves takes all the rows and 32 columns.
 #include <atomic>
 #include <cstdio>
 #include "cg_internal.h"
@@ -44,20 +42,17 @@ __device__ __forceinline__ void ldq(Rsrc r, uint32_t voff, float *f)
     for (int t = 0; t < 4; ++t) f[t] = __uint_as_float((uint32_t)v[t]);
 }
 
-// byte offset of reduction index k (< kend, else out of range).  LIN: a plain stride, no division
-template <bool LIN> __device__ __forceinline__ uint32_t k_offset(const IndexMap &m, uint32_t k, uint32_t kend)
+// byte offset of reduction index k (< kend, else out of range) of a map that is a plain stride
+__device__ __forceinline__ uint32_t k_offset(const IndexMap &m, uint32_t k, uint32_t kend)
 {
-    const uint32_t off = LIN ? k * (uint32_t)m.s1 + (uint32_t)m.o0 : (uint32_t)map_info(m, k).off;
-    return k < kend ? off * 4u : OOB_K;
+    return k < kend ? (k * (uint32_t)m.s1 + (uint32_t)m.o0) * 4u : OOB_K;
 }
 
 // ---- A: eight consecutive k of row (16 i + lane % 16), octet lane / 16 -------------------------------
-// QUAD: aligned groups of four k are four consecutive floats (4-byte aligned); what a group holds beyond
-// K meets zeros of B.  Otherwise one load per element, neighbouring lanes on neighbouring rows, k a plain
-// stride.  LIN: k is a plain stride (else runs of pixels, one per image).
-enum { A_ROWS = 0, A_QUAD_LIN = 1, A_QUAD_RUNS = 2 };
+// A_QUAD: k is unit-stride and an aligned group of four one 16-byte load (4-byte aligned); what a group holds
+// beyond K meets zeros of B.  A_ROWS: one load per element, neighbouring lanes on neighbouring rows, k a plain stride.
+enum { A_ROWS = 0, A_QUAD = 1 };
 template <int TM, int KIND> struct LoadA {
-    static constexpr bool QUAD = KIND != A_ROWS, LIN = KIND != A_QUAD_RUNS;
     uint32_t roff[TM];
     __device__ __forceinline__ void init(const Operand &op, uint32_t row0, uint32_t nrows, int lane)
     {
@@ -70,8 +65,8 @@ template <int TM, int KIND> struct LoadA {
     __device__ __forceinline__ void load(Rsrc r, const Operand &op, uint32_t k0, uint32_t kend, int lane, float (&f)[TM][8])
     {
         const uint32_t k = k0 + 8u * (uint32_t)(lane >> 4);
-        if constexpr (QUAD) {
-            const uint32_t ka = k_offset<LIN>(op.k, k, kend), kb = k_offset<LIN>(op.k, k + 4u, kend);
+        if constexpr (KIND == A_QUAD) {
+            const uint32_t ka = k_offset(op.k, k, kend), kb = k_offset(op.k, k + 4u, kend);
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 ldq(r, roff[i] + ka, &f[i][0]);
@@ -80,7 +75,7 @@ template <int TM, int KIND> struct LoadA {
         } else {
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                const uint32_t ko = k_offset<LIN>(op.k, k + (uint32_t)t, kend);
+                const uint32_t ko = k_offset(op.k, k + (uint32_t)t, kend);
 #pragma unroll
                 for (int i = 0; i < TM; ++i) f[i][t] = ldf(r, roff[i] + ko);
             }
@@ -92,7 +87,7 @@ template <int TM, int KIND> struct LoadA {
 // Columns along the lanes (an image seen through a window, a row-major matrix read across): wave w
 // takes octet w % 4, lane the columns lane and lane + 64 (with eight waves one of them); k is uniform, its
 // map runs on the scalar unit.
-template <int NU, bool CHECK, bool LIN = false> struct LoadBRows {
+template <int NU, bool CHECK, bool LIN = false> struct LoadBRows {       // LIN: k is a plain stride
     uint32_t roff[NU];
     int32_t ra[NU], rb[NU];
     __device__ __forceinline__ static int column(int u, int wave, int lane) { return (NU == 2 ? u : wave >> 2) * 64 + lane; }
@@ -113,10 +108,8 @@ template <int NU, bool CHECK, bool LIN = false> struct LoadBRows {
 #pragma unroll
         for (int t = 2 * P; t < 2 * P + 2; ++t) {
             const uint32_t k = k0 + (uint32_t)(8 * (wave & 3) + t);
-            Info kq{};
-            if (LIN) kq.off = (int32_t)(k * (uint32_t)op.k.s1) + op.k.o0;
-            else kq = map_info(op.k, k);
-            const uint32_t ko = (k < kend && kq.r1 < op.k.r1_lim) ? (uint32_t)kq.off * 4u : OOB_K;
+            const Info kq = LIN ? Info{} : map_info(op.k, k);
+            const uint32_t ko = LIN ? k_offset(op.k, k, kend) : k < kend ? (uint32_t)kq.off * 4u : OOB_K;
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 uint32_t voff = roff[u];
@@ -131,77 +124,25 @@ template <int NU, bool CHECK, bool LIN = false> struct LoadBRows {
     __device__ __forceinline__ static int unit(int u, int wave, int lane) { return (wave & 3) * OS + column(u, wave, lane); }
 };
 
-// k along the lanes: thread takes octet thread % 4 of columns thread / 4 and thread / 4 + 64.
-// BK_QUAD: aligned groups of four k are four consecutive floats, a plain stride.  BK_LIN: a plain stride,
-// one load per element (K not a multiple of four).  BK_PIXELS: the pixels of an image seen through a
-// window, runs of pixels padded to a multiple of four.
-enum { BK_QUAD = 0, BK_LIN = 1, BK_PIXELS = 2 };
-template <int NU, int KIND, bool CHECK> struct LoadBK {
+// k along the lanes, a plain unit stride: thread takes octet thread % 4 of columns thread / 4 and thread / 4 + 64
+// as aligned quads.
+template <int NU> struct LoadBK {
     uint32_t roff[NU];
-    int32_t ra[NU], rb[NU];
     __device__ __forceinline__ void init(const Operand &op, uint32_t row0, uint32_t nrows, int wave, int lane)
     {
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const uint32_t row = row0 + (uint32_t)(u * 64 + wave * 16 + (lane >> 2));
-            const Info q = map_info(op.row, row);
-            roff[u] = row < nrows ? (uint32_t)q.off * 4u : OOB_ROW;
-            ra[u] = q.a; rb[u] = q.b;
+            roff[u] = row < nrows ? (uint32_t)map_info(op.row, row).off * 4u : OOB_ROW;
         }
     }
-    uint32_t r1;                     // the pixel a part of the loads left off at
-    int32_t off, a, b, x;
     template <int P>
     __device__ __forceinline__ void load(Rsrc r, const Operand &op, uint32_t k0, uint32_t kend, int, int lane, float (&f)[NU][8])
     {
-        const uint32_t k = k0 + 8u * (uint32_t)(lane & 3);
-        if constexpr (KIND == BK_QUAD) {
-            if constexpr (P % 2 == 0) {
-                const uint32_t ka = k_offset<true>(op.k, k + 2u * P, kend);
+        if constexpr (P % 2 == 0) {
+            const uint32_t ka = k_offset(op.k, k0 + 8u * (uint32_t)(lane & 3) + 2u * P, kend);
 #pragma unroll
-                for (int u = 0; u < NU; ++u) ldq(r, roff[u] + ka, &f[u][2 * P]);
-            }
-        } else if constexpr (KIND == BK_LIN) {
-#pragma unroll
-            for (int t = 2 * P; t < 2 * P + 2; ++t) {
-                const uint32_t ko = k_offset<true>(op.k, k + (uint32_t)t, kend);
-#pragma unroll
-                for (int u = 0; u < NU; ++u) f[u][t] = ldf(r, roff[u] + ko);
-            }
-        } else {
-            // one division per group of four (a group never straddles two images), the next pixel of a
-            // group by counting on
-            const IndexMap &m = op.k;
-#pragma unroll
-            for (int t = 2 * P; t < 2 * P + 2; ++t) {
-                if (t % 4 == 0) {
-                    const uint32_t q1 = fdiv(k + (uint32_t)t, m.d1);
-                    r1 = k + (uint32_t)t - q1 * m.d1.d;
-                    const uint32_t q2 = fdiv(r1, m.d2);
-                    x = (int32_t)(r1 - q2 * m.d2.d);
-                    off = (int32_t)q1 * m.s1 + (int32_t)q2 * m.s2 + x * m.s3 + m.o0;
-                    a = (int32_t)q2 * m.sa + m.a0;
-                    b = x * m.sb + m.b0;
-                } else {
-                    ++r1; ++x;
-                    const bool wrap = x == (int32_t)m.d2.d;
-                    off += wrap ? m.s2 - ((int32_t)m.d2.d - 1) * m.s3 : m.s3;
-                    a += wrap ? m.sa : 0;
-                    b = wrap ? m.b0 : b + m.sb;
-                    x = wrap ? 0 : x;
-                }
-                const bool live = k + (uint32_t)t < kend && r1 < m.r1_lim;
-                const uint32_t ko = live ? (uint32_t)off * 4u : OOB_K;
-#pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    uint32_t voff = roff[u] + ko;
-                    if (CHECK) {
-                        const bool ok = (uint32_t)(ra[u] + a) < op.limA && (uint32_t)(rb[u] + b) < op.limB;
-                        voff = ok ? voff : OOB_ROW;
-                    }
-                    f[u][t] = ldf(r, voff);
-                }
-            }
+            for (int u = 0; u < NU; ++u) ldq(r, roff[u] + ka, &f[u][2 * P]);
         }
     }
     __device__ __forceinline__ static int unit(int u, int wave, int lane) { return (lane & 3) * OS + u * 64 + wave * 16 + (lane >> 2); }
@@ -215,7 +156,7 @@ __device__ __forceinline__ Rsrc rsrc_of(const Operand &op, uint32_t g)
 
 }  // namespace
 
-template <int NP, int TM, int WM, bool OWN, class LA, class LB>
+template <int NP, int TM, int WM, class LA, class LB>
 __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(const IgemmProblem p)
 {
     constexpr int WAVES = WM == 8 ? 8 : 4, WN = WAVES / WM, TN = 128 / (16 * WN), MT = WM * TM * 16, NT = 128, NU = 8 / WAVES;
@@ -239,10 +180,9 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
     lb.init(p.B, n0, p.N, wave, lane);
 
     // raw operands one step ahead of their cutting, pieces one step ahead of their use
-    // (32 rows a wave and sums of their own: the rows are cut in front of the products of their own step instead,
-    // 24 registers less; two column tiles at a time then fit, without which the sums wait for each other:
-    // 11x11 windows over 227x227 forward 725 us with one)
-    constexpr bool LATE = OWN && TM == 2 && WM == 4;
+    // (32 rows a wave and three pieces: the rows are cut in front of the products of their own step instead,
+    // 24 registers less; two column tiles at a time then fit, without which the sums wait for each other)
+    constexpr bool LATE = NP == 3 && TM == 2 && WM == 4;
     float ar[TM][8], br[NU][8];
     v4u ap[LATE ? 1 : 2][TM][NP], bc[NP];
     auto store_b = [&](int u, int buf) {
@@ -274,24 +214,18 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
         la.load(rA, p.A, kbeg + KS, kend, lane, ar);
     }
 
-    using Step = MmaStep<NP, TM, TN, WM == 8 ? 2 : ColumnGroup<TM, TN>::G, OWN>;
+    using Step = MmaStep<NP, TM, TN, WM == 8 ? 2 : ColumnGroup<TM, TN>::G, NP == 3>;
     auto step = [&](auto PC, int s) {
         constexpr int par = LATE ? 0 : decltype(PC)::value, nxt = LATE ? 0 : par ^ 1;
         block_sync_lds();           // this step's columns are in LDS, and everyone is done with the other buffer
         const int rd = (s & 1) * BUF + q * OS + wn * TN * 16 + l16;
         const uint32_t k2 = kbeg + (uint32_t)(s + 2) * KS;
-        float bigA = 0.f, bigB = 0.f;
         if constexpr (LATE) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) split8_pair<NP>(ar[i], t, ap[0][i], bigA);
-            if (__builtin_expect(bigA >= CG_HUGE, 0)) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[0][i]);
-            }
+            for (int i = 0; i < TM; ++i) split8<NP>(ar[i], ap[0][i]);
             la.load(rA, p.A, kbeg + (uint32_t)(s + 1) * KS, kend, lane, ar);
         }
+        float bigA = 0.f, bigB = 0.f;
         auto read_b = [&](int j, v4u (&pc)[NP]) {
 #pragma unroll
             for (int k = 0; k < NP; ++k) pc[k] = lds[rd + j * 16 + k * PLANE];
@@ -336,8 +270,8 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
 
 namespace {
 
-template <int NP, int TM, int WM, bool OWN, class LA, class LB>
-int launch_own(const IgemmProblem &p, const char *modes, hipStream_t stream)
+template <int NP, int TM, int WM, class LA, class LB>
+int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
 {
     constexpr int MT = WM * TM * 16;
     dim3 grid((p.N + 127) / 128, (p.M + MT - 1) / MT, p.groups * p.splits);
@@ -345,82 +279,58 @@ int launch_own(const IgemmProblem &p, const char *modes, hipStream_t stream)
     int rec = -1;
     if (prof_on()) {
         char name[64];
-        snprintf(name, sizeof name, NP == 3 ? "igemm_kernel<%dx128,%s>" : NP == 1 ? "igemm_kernel<%dx128,%s,bf16>" : "igemm_kernel<%dx128,%s,bf16x3>", MT, modes);
+        snprintf(name, sizeof name, NP == 3 ? "igemm_kernel<%dx128,%s,pieces>" : NP == 1 ? "igemm_kernel<%dx128,%s,pieces,bf16>" : "igemm_kernel<%dx128,%s,pieces,bf16x3>", MT, modes);
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }
     constexpr size_t lds = (size_t)2 * NP * 4 * OS * 16;
     static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
     static std::atomic<bool> attr_set{false};      // raising the dynamic-LDS limit: once per kernel (repeating it is harmless)
     if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_gemm_kernel<NP, TM, WM, OWN, LA, LB>),
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_gemm_kernel<NP, TM, WM, LA, LB>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((split_gemm_kernel<NP, TM, WM, OWN, LA, LB>), grid, dim3(WM == 8 ? 512 : 256), lds, stream, p);
+    hipLaunchKernelGGL((split_gemm_kernel<NP, TM, WM, LA, LB>), grid, dim3(WM == 8 ? 512 : 256), lds, stream, p);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
 }
 
-// three pieces: long sums are added up step by step (kOwnK)
-template <int NP, int TM, int WM, class LA, class LB>
-int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
-{
-    if constexpr (NP == 3) {
-        if (p.k_per_split > kOwnK) return launch_own<NP, TM, WM, true, LA, LB>(p, modes, stream);
-    }
-    return launch_own<NP, TM, WM, false, LA, LB>(p, modes, stream);
-}
-
 // At most one block a compute unit: eight waves of 16 rows instead of four of 32, so that two share a
 // SIMD (a lone wave issues a step's instructions one after the other: 2.3 us a step).
-template <int AK, template <int> class LB> int launch_rows(const IgemmProblem &p, int mt, const char *modes, hipStream_t stream)
+template <int AK, template <int> class LB, bool ROWS16, bool WAVES8>
+int launch_rows(const IgemmProblem &p, int mt, const char *modes, hipStream_t stream)
 {
-    switch (mt) {
-    case 128:
-        if ((uint64_t)((p.N + 127) / 128) * ((p.M + 127) / 128) * p.groups * p.splits <= 256)
-            return launch_cfg<CG_NP, 1, 8, LoadA<1, AK>, LB<1>>(p, modes, stream);
-        return launch_cfg<CG_NP, 2, 4, LoadA<2, AK>, LB<2>>(p, modes, stream);
-    case 64: return launch_cfg<CG_NP, 1, 4, LoadA<1, AK>, LB<2>>(p, modes, stream);
-    case 32: return launch_cfg<CG_NP, 2, 1, LoadA<2, AK>, LB<2>>(p, modes, stream);
-    default: return launch_cfg<CG_NP, 1, 1, LoadA<1, AK>, LB<2>>(p, modes, stream);
+    if constexpr (ROWS16) {
+        if (mt == 16) return launch_cfg<CG_NP, 1, 1, LoadA<1, AK>, LB<2>>(p, modes, stream);
     }
+    if (mt != 128) return CG_EUNSUPPORTED;
+    if constexpr (WAVES8) if ((uint64_t)((p.N + 127) / 128) * ((p.M + 127) / 128) * p.groups * p.splits <= 256)
+        return launch_cfg<CG_NP, 1, 8, LoadA<1, AK>, LB<1>>(p, modes, stream);
+    return launch_cfg<CG_NP, 2, 4, LoadA<2, AK>, LB<2>>(p, modes, stream);
 }
 template <int NU> using BRowsCheck = LoadBRows<NU, true>;
 template <int NU> using BRowsPlain = LoadBRows<NU, false>;
 template <int NU> using BRowsLin = LoadBRows<NU, false, true>;
-template <int NU> using BKQuad = LoadBK<NU, BK_QUAD, false>;
-template <int NU> using BKLin = LoadBK<NU, BK_LIN, false>;
-template <int NU> using BKPixels = LoadBK<NU, BK_PIXELS, false>;
-template <int NU> using BKPixelsCheck = LoadBK<NU, BK_PIXELS, true>;
 
 }  // namespace
 
-// This file is compiled once per number of pieces (CG_NP), in parallel.
+// This file is compiled once per number of pieces (CG_NP), in parallel.  16 or 128 rows; b_quads: B as aligned quads
+// of k, else rows along the lanes.
 #define CG_CAT_(a, b) a##b
 #define CG_CAT(a, b) CG_CAT_(a, b)
-int CG_CAT(split_gemm_, CG_NP)(const IgemmProblem &p0, int mt, bool a_quads, int b_mode, hipStream_t stream)
+int CG_CAT(split_gemm_, CG_NP)(const IgemmProblem &p, int mt, bool a_quads, bool b_quads, hipStream_t stream)
 {
-    IgemmProblem p = p0;
     const bool bc = p.B.check != 0;
     const bool a_lin = p.A.k.d1.d == 1 && p.A.k.d2.d == 1, b_lin = p.B.k.d1.d == 1 && p.B.k.d2.d == 1;
-    const bool b_runs = p.B.k.d1.d % 4 == 0;
-    const char modes[4] = {a_quads ? '4' : 'r', "rk4"[b_mode], bc ? 'c' : '-', 0};
-    if (!p.B.k.r1_lim) p.B.k.r1_lim = 0xffffffffu;
-    if (!a_quads) {
-        if (b_mode == 0 && !bc && a_lin && b_lin) return launch_rows<A_ROWS, BRowsLin>(p, mt, modes, stream);
-        if (b_mode == 0 && !bc && a_lin) return launch_rows<A_ROWS, BRowsPlain>(p, mt, modes, stream);
-        return CG_EUNSUPPORTED;
-    }
-    if (!a_lin) {            // runs of pixels against an image seen through a window: backward-weight
-        if (b_mode != 1 || !b_runs) return CG_EUNSUPPORTED;
-        return bc ? launch_rows<A_QUAD_RUNS, BKPixelsCheck>(p, mt, modes, stream)
-                  : launch_rows<A_QUAD_RUNS, BKPixels>(p, mt, modes, stream);
-    }
-    if (b_mode == 0) return bc ? launch_rows<A_QUAD_LIN, BRowsCheck>(p, mt, modes, stream) : launch_rows<A_QUAD_LIN, BRowsPlain>(p, mt, modes, stream);
-    if (bc || !b_lin) return CG_EUNSUPPORTED;
-    return b_mode == 2 ? launch_rows<A_QUAD_LIN, BKQuad>(p, mt, modes, stream)
-                       : launch_rows<A_QUAD_LIN, BKLin>(p, mt, modes, stream);
+    const char modes[4] = {a_quads ? '4' : 'r', b_quads ? '4' : 'r', bc ? 'c' : '-', 0};
+    if (!a_lin || p.B.k.r1_lim) return CG_EUNSUPPORTED;
+    // (padding means an image, and images get 128 rows only where there are blocks for more than one a compute unit)
+    if (b_quads) return a_quads && b_lin && !bc ? launch_rows<A_QUAD, LoadBK, false, true>(p, mt, modes, stream) : CG_EUNSUPPORTED;
+    if (a_quads)
+        return bc ? launch_rows<A_QUAD, BRowsCheck, true, false>(p, mt, modes, stream)
+                  : launch_rows<A_QUAD, BRowsPlain, true, true>(p, mt, modes, stream);
+    return bc || !b_lin ? CG_EUNSUPPORTED : launch_rows<A_ROWS, BRowsLin, true, true>(p, mt, modes, stream);
 }
 
 }  // namespace cg

@@ -296,7 +296,7 @@ int split_wgrad_launch(const IgemmProblem &p, hipStream_t stream)
 }
 
 // Fills Wp, bands, dividers; chooses the unit, the row tile and the number of K slices.
-bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t legacy_splits, uint32_t *splits)
+bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t other_splits, uint32_t *splits)
 {
     g.nsl = 0;
     const int KK = g.KH * g.KW;
@@ -335,7 +335,7 @@ bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t legacy_splits,
     const uint64_t tiles = (uint64_t)((M + g.mt - 1) / g.mt) * ((g.Cg + 15) / 16) * g.tap_blocks * groups;
     const uint64_t resident = igemm_resident_blocks();
     uint64_t want = resident / tiles;
-    if (want * 4 < (uint64_t)legacy_splits * 3) want = legacy_splits;      // no slice much longer than the gathered kernel's
+    if (want * 4 < (uint64_t)other_splits * 3) want = other_splits;      // no slice much longer than the gathered kernel's
     if (want > (uint64_t)g.units) want = (uint64_t)g.units;
     if (want < 1) want = 1;
     g.units_per_split = (int32_t)(((uint64_t)g.units + want - 1) / want);
