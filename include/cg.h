@@ -65,10 +65,13 @@ enum { CG_PASS_FWD = 0, CG_PASS_BWD_DATA = 1, CG_PASS_BWD_WEIGHT = 2 };
  * memory and sums are accumulated in fp32 in every mode; the mode is always the
  * caller's explicit choice, nothing selects a reduced one by itself.
  *  CG_MATH_FP32   : fp32 accuracy (the default of every entry point without a math argument).
- *                   The matrix cores multiply every operand as three bf16 numbers that hold its
- *                   24 bits exactly, six products accumulated in fp32; the three products left
- *                   out are below 2^-25 of a term.  The error of a sum is that of fp32 multiply-adds
- *                   or less.  Values below 2^-110 lose bits beyond 2^-133.
+ *                   Some kernels multiply in the fp32 matrix instructions.  The others multiply every
+ *                   operand, subnormal ones included, as three bf16 numbers that hold its 24 bits exactly,
+ *                   six products accumulated in fp32; the three products left out are 2^-29 of a term at
+ *                   the median and at most 2^-24.  A sum is rounded once per 32 terms.  Its error against 64 bits
+ *                   is no larger than that of fp32 multiply-adds in a row for sums of 100 terms and more (tests);
+ *                   a sum of a few terms can be off by one more rounding.  Infinities and NaN come out as in
+ *                   fp32 multiply-adds, several times slower.
  *  CG_MATH_BF16   : both operands rounded to bf16 (nearest even) on their way into the
  *                   matrix cores; parity bound 2e-2 (max-abs-relative).
  *  CG_MATH_BF16X3 : every operand split into two bf16 numbers, a = ah + al, three

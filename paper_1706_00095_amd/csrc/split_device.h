@@ -29,11 +29,19 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));      // eight bf16: on
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Two fp32 values cut into NP bf16 pieces, most significant first, each piece the nearest even of what
-// the pieces before it left.  Three pieces hold an fp32 value exactly (a remainder below 2^-133 is
-// lost: the value is then below 2^-110).  11 vector instructions a pair (v_dot2_f32_bf16 would take a
-// remainder in one instead of two, at half the rate).
+// the pieces before it left.  Three pieces hold 24 bits.  They are cut from the value times 2^24: the
+// smallest fp32 number (2^-149) is then 2^-125, so that every value from there up is held exactly and no
+// piece is subnormal; a product of two operands carries 2^48, which MmaStep takes out again.  What
+// overflows on the way (an operand from 2^104 up, a sum from 2^80 up) or was no finite number leaves a
+// NaN or an infinity in the sum, and sums that end as one are computed anew by fp32 multiply-adds
+// (not_finite).  13 vector instructions a pair.
+constexpr float kCutScale = 0x1p24f, kProductScale = 0x1p-48f;
 template <int NP> __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t (&pc)[NP])
 {
+    if constexpr (NP == 3) {
+        x0 *= kCutScale;
+        x1 *= kCutScale;
+    }
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
         bf16x2 h;
@@ -47,51 +55,60 @@ template <int NP> __device__ __forceinline__ void split_pair(float x0, float x1,
     }
 }
 
-// The same for values that bf16 rounding would send to infinity, and infinities themselves, where the
-// split above has inf - inf.  A finite value from kHuge up gets its first piece by truncation.  An
-// infinity becomes (1, 0, inf): times any b its pieces give inf * bf16(b) + 1 * (the last piece of b),
-// which is inf, -inf, or NaN for b = 0 or NaN, as a * b is.  (NaN stays three NaNs.)
-#define CG_HUGE __uint_as_float(0x7f7f8000u)
-__device__ __forceinline__ void split_huge(float x, uint32_t (&pc)[3])       // pieces in the low halves
-{
-    const float a = fabsf(x);
-    const bool inf = a == __uint_as_float(0x7f800000u), large = a >= CG_HUGE;
-    const float h = inf ? copysignf(1.f, x) : large ? __uint_as_float(__float_as_uint(x) & 0xffff0000u) : (float)(__bf16)x;
-    const float r = inf ? 0.f : x - h;
-    const __bf16 m = (__bf16)r;
-    pc[0] = __builtin_bit_cast(uint16_t, (__bf16)h);
-    pc[1] = __builtin_bit_cast(uint16_t, m);
-    pc[2] = __builtin_bit_cast(uint16_t, (__bf16)(inf ? x : r - (float)m));
-}
-__device__ __forceinline__ void split8_huge(const float (&f)[8], v4u (&pc)[3])
-{
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        uint32_t lo[3], hi[3];
-        split_huge(f[2 * t], lo);
-        split_huge(f[2 * t + 1], hi);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) pc[k][t] = lo[k] | hi[k] << 16;
-    }
-}
-
-// pair t of eight values; `big` collects the largest magnitude (NaN drops out)
-template <int NP> __device__ __forceinline__ void split8_pair(const float (&f)[8], int t, v4u (&pc)[NP], float &big)
+// pair t of eight values
+template <int NP> __device__ __forceinline__ void split8_pair(const float (&f)[8], int t, v4u (&pc)[NP])
 {
     uint32_t p[NP];
     split_pair<NP>(f[2 * t], f[2 * t + 1], p);
 #pragma unroll
     for (int k = 0; k < NP; ++k) pc[k][t] = p[k];
-    if constexpr (NP == 3) big = fmaxf(fmaxf(big, fabsf(f[2 * t])), fabsf(f[2 * t + 1]));
 }
 template <int NP> __device__ __forceinline__ void split8(const float (&f)[8], v4u (&pc)[NP])
 {
-    float big = 0.f;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) split8_pair<NP>(f, t, pc, big);
-    if constexpr (NP == 3) {
-        if (__builtin_expect(big >= CG_HUGE, 0)) split8_huge(f, pc);
-    }
+    for (int t = 0; t < 4; ++t) split8_pair<NP>(f, t, pc);
+}
+
+// Does any lane of the wave hold a sum that is an infinity or a NaN?
+template <int TM, int TN> __device__ __forceinline__ bool not_finite(const v4f (&acc)[TM][TN])
+{
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z = fmaf(acc[i][j][e], 0.f, z);
+    return __builtin_expect(__any(!(z == 0.f)), 0);
+}
+
+// The sums of a wave's tile that are not finite, again, by fp32 matrix instructions from the operands themselves, one
+// column tile after the other: for_k(j, add) calls add(a, b) with four reduction indices at a time, one per lane / 16
+// (a[i], b: of row 16 i + lane % 16 and of column 16 j + lane % 16).  What infinities, NaN and sums beyond 2^80
+// get: a product that is NaN or overflows in fp32 does so here.  Several times slower than the pieces.
+// Sums that came out finite stay as they are.
+template <int TM, int TN, class ForK> __device__ __forceinline__ void sums_in_fp32(v4f (&acc)[TM][TN], ForK &&for_k)
+{
+    static_for<0, TN>([&](auto JC) {
+        constexpr int j = decltype(JC)::value;
+        float z = 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z = fmaf(acc[i][j][e], 0.f, z);
+        if (!__any(!(z == 0.f))) return;
+        v4f s[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) s[i] = v4f{0.f, 0.f, 0.f, 0.f};
+        for_k(j, [&](const float (&a)[TM], float b) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) s[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(b, a[i], s[i], 0, 0, 0);
+        });
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = fmaf(acc[i][j][e], 0.f, 0.f) == 0.f ? acc[i][j][e] : s[i][e];
+    });
 }
 
 // Products that count, smallest first: number, piece of A, piece of B.
@@ -111,12 +128,13 @@ template <int TM, int TN> struct ColumnGroup { static constexpr int G = TM >= 3 
 // SLOTS-1, one behind each product of a group, whose vector instructions are laid between the matrix
 // instructions.
 // OWN: a step's products are added up on their own, from zero, and then to the accumulator by four vector
-// adds a tile: the sum is rounded once per 32 terms instead
+// multiply-adds a tile (which take out the scale of the pieces): the sum is rounded once per 32 terms instead
 // of six times, and the instruction, which drops what lies below the last place of the sum it adds to,
 // drops it from a sum 32 terms long.  Three pieces always do it.
-template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G, bool OWN = false> struct MmaStep {
+template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G, bool OWN = NP == 3> struct MmaStep {
     static constexpr int JG = JG_, PR = Products<NP>::N, SLOTS = TN / JG * PR;
     static_assert(TN % JG == 0, "whole groups");
+    static_assert(OWN || NP < 3, "the scale of three pieces leaves the sum with the step's own products");
     struct NoWork {};
     template <class ReadB, class Work>
     __device__ __forceinline__ static void run(const v4u (&ap)[TM][NP], v4f (&acc)[TM][TN], ReadB &&read_b, Work &&work)
@@ -140,7 +158,12 @@ template <int NP, int TM, int TN, int JG_ = ColumnGroup<TM, TN>::G, bool OWN = f
                         v4f &to = OWN ? own[OWN ? i : 0][OWN ? jj : 0] : acc[i][g * JG + jj];
                         to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bp[g & 1][jj][b]), __builtin_bit_cast(bf16x8, ap[i][a]),
                                                                      OWN && pi == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : to, 0, 0, 0);
-                        if constexpr (OWN && pi == PR - 1) acc[i][g * JG + jj] += to;
+                        if constexpr (OWN && pi == PR - 1) {
+                            if constexpr (NP == 3) {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) acc[i][g * JG + jj][e] = fmaf(to[e], kProductScale, acc[i][g * JG + jj][e]);
+                            } else acc[i][g * JG + jj] += to;
+                        }
                     }
                 if constexpr (!std::is_same_v<std::decay_t<Work>, NoWork>) {
                     work(std::integral_constant<int, g * PR + pi>{});

@@ -214,7 +214,7 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
         la.load(rA, p.A, kbeg + KS, kend, lane, ar);
     }
 
-    using Step = MmaStep<NP, TM, TN, WM == 8 ? 2 : ColumnGroup<TM, TN>::G, NP == 3>;
+    using Step = MmaStep<NP, TM, TN, WM == 8 ? 2 : ColumnGroup<TM, TN>::G>;
     auto step = [&](auto PC, int s) {
         constexpr int par = LATE ? 0 : decltype(PC)::value, nxt = LATE ? 0 : par ^ 1;
         block_sync_lds();           // this step's columns are in LDS, and everyone is done with the other buffer
@@ -225,45 +225,54 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
             for (int i = 0; i < TM; ++i) split8<NP>(ar[i], ap[0][i]);
             la.load(rA, p.A, kbeg + (uint32_t)(s + 1) * KS, kend, lane, ar);
         }
-        float bigA = 0.f, bigB = 0.f;
         auto read_b = [&](int j, v4u (&pc)[NP]) {
 #pragma unroll
             for (int k = 0; k < NP; ++k) pc[k] = lds[rd + j * 16 + k * PLANE];
         };
-        // The next step's rows are cut (4*TM items, then one to mend infinities and fetch the rows after),
-        // then its columns (4*NU, and one to mend), then the columns after are fetched (4).
+        // The next step's rows are cut (4*TM items, then one to fetch the rows after),
+        // then its columns (4*NU), then the columns after are fetched (4).
         auto item = [&](auto OC) {
             constexpr int o = decltype(OC)::value, A1 = LATE ? -1 : 4 * TM, B0 = A1 + 1, B1 = B0 + 4 * NU;
-            if constexpr (o < A1) split8_pair<NP>(ar[o / 4], o % 4, ap[nxt][o / 4], bigA);
-            else if constexpr (o == A1) {
-                if constexpr (NP == 3) {
-                    if (__builtin_expect(bigA >= CG_HUGE, 0)) {
-#pragma unroll
-                        for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[nxt][i]);
-                    }
-                }
-                la.load(rA, p.A, k2, kend, lane, ar);
-            } else if constexpr (o < B1) {
+            if constexpr (o < A1) split8_pair<NP>(ar[o / 4], o % 4, ap[nxt][o / 4]);
+            else if constexpr (o == A1) la.load(rA, p.A, k2, kend, lane, ar);
+            else if constexpr (o < B1) {
                 constexpr int u = (o - B0) / 4, t = (o - B0) % 4;
-                split8_pair<NP>(br[u], t, bc, bigB);
+                split8_pair<NP>(br[u], t, bc);
                 if constexpr (t == 3) store_b(u, (s + 1) & 1);
-            } else if constexpr (o == B1) {
-                if constexpr (NP == 3) {
-                    if (__builtin_expect(bigB >= CG_HUGE, 0)) {
-#pragma unroll
-                        for (int u = 0; u < NU; ++u) {
-                            split8_huge(br[u], bc);
-                            store_b(u, (s + 1) & 1);
-                        }
-                    }
-                }
-            } else lb.template load<o - B1 - 1>(rB, p.B, k2, kend, wave, lane, br);
+            } else lb.template load<o - B1>(rB, p.B, k2, kend, wave, lane, br);
         };
-        Step::run(ap[par], acc, read_b, Step::template spread<(LATE ? 0 : 4 * TM + 1) + 4 * NU + 5>(item));
+        Step::run(ap[par], acc, read_b, Step::template spread<(LATE ? 0 : 4 * TM + 1) + 4 * NU + 4>(item));
     };
     for (int s = 0; s < ns; s += 2) {
         step(std::integral_constant<int, 0>{}, s);
         if (s + 1 < ns) step(std::integral_constant<int, 1>{}, s + 1);
+    }
+    if constexpr (NP == 3) {
+        if (not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
+            const uint32_t col = n0 + (uint32_t)((wn * TN + j) * 16 + l16);
+            const Info r = map_info(p.B.row, col);
+            const uint32_t boff = col < p.N ? (uint32_t)r.off * 4u : OOB_ROW;
+            uint32_t aoff[TM];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const uint32_t row = m0 + (uint32_t)((wm * TM + i) * 16 + l16);
+                aoff[i] = row < p.M ? (uint32_t)map_info(p.A.row, row).off * 4u : OOB_ROW;
+            }
+            for (uint32_t k0 = kbeg; k0 < kend; k0 += 16u) {
+                float a[4][TM], b[4];                   // 16 indices, their loads in flight together
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const uint32_t k = k0 + (uint32_t)(4 * v + q);
+                    const Info kq = map_info(p.B.k, k);
+                    const bool ok = k < kend && (!p.B.check || ((uint32_t)(r.a + kq.a) < p.B.limA && (uint32_t)(r.b + kq.b) < p.B.limB));
+                    b[v] = ldf(rB, ok ? boff + (uint32_t)kq.off * 4u : OOB_ROW);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) a[v][i] = ldf(rA, aoff[i] + k_offset(p.A.k, k, kend));
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) add(a[v], b[v]);
+            }
+        });
     }
     store_columns<TM, TN>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), p.N, lane);
 }

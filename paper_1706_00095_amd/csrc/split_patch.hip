@@ -2,12 +2,14 @@
 // and strided backward-data (as a stride-1 problem over dy).  See PatchGeom in cg_internal.h for the
 // geometry.  One kernel serves the three arithmetics of cg.h by the number of bf16 pieces an fp32
 // operand is cut into on its way into the matrix cores:
-//   NP = 3 (CG_MATH_FP32):   x = h + m + l, h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): exact, 24 bits.
-//                            Six products l*h + h*l + m*m + m*h + h*m + h*h, small ones first; what is
-//                            dropped (m*l, l*m, l*l) is 2^-26 of a product and less.  A step's products
-//                            are added up from zero and then to the accumulator (MmaStep, OWN): the error
-//                            against 64 bits is 1.6e-7 where the fp32 instruction has 4.8e-7 (256 images,
-//                            256 channels of 13x13, 384 rows, 3x3), in 366 us instead of 593.
+//   NP = 3 (CG_MATH_FP32):   x = h + m + l, h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): exact, 24 bits
+//                            (of x times 2^24: split_device.h).  Six products l*h + h*l + m*m + m*h + h*m + h*h,
+//                            small ones first; what is dropped (m*l, l*m, l*l) is 2^-29 of a product at the median, at
+//                            most 2^-24.  A step's products are added up from zero and then to the accumulator
+//                            (MmaStep, OWN): the error against 64 bits is 4.2e-8 where the fp32 instruction has
+//                            1.7e-7 (256 images, 256 channels of 13x13, 384 rows, 3x3), in 373 us instead of 591.
+//                            Sums that end as an infinity or a NaN are computed anew in fp32 (sums_in_fp32):
+//                            1.8 ms for the same pass where every sum is one.
 //   NP = 2 (CG_MATH_BF16X3): x = h + l, three products.
 //   NP = 1 (CG_MATH_BF16):   x = h.
 //
@@ -184,24 +186,15 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
 
     // (the rows are cut in one piece in front of the products: cutting them behind the products of the step
     // before, as split_gemm_kernel does, takes 24 more registers and spills)
-    using Step = MmaStep<NP, TM, TN, TM >= 3 ? 1 : 2, NP == 3>;
+    using Step = MmaStep<NP, TM, TN, TM >= 3 ? 1 : 2>;
     for (int grp = 0; grp < ngrp; ++grp) {
         const int ns = steps_of(grp);
         const bool pair = 2 * grp + 1 < ncb16;
         int ls = 0;
         for (int s = wk; s < ns; s += WK, ++ls) {
             v4u ap[TM][NP];
-            float big = 0.f;
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) split8_pair<NP>(ar[i], t, ap[i], big);
-            if constexpr (NP == 3) {
-                if (__builtin_expect(big >= CG_HUGE, 0)) {
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[i]);
-                }
-            }
+            for (int i = 0; i < TM; ++i) split8<NP>(ar[i], ap[i]);
             // a chunk of the next group's patch, then the next step's filters (so that waiting for those,
             // one step from now, waits for nothing younger)
             static_for<0, NSL>([&](auto EC) { if (ls == decltype(EC)::value) load_chunk(EC, grp + 1); });
@@ -246,6 +239,38 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] += ex[(i * TN + j) * 64 + lane];
+    }
+    if constexpr (NP == 3) {
+        if (not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
+            // this lane's pixel: its image, position of its window
+            const uint32_t n = n0 + (uint32_t)((wn * TN + j) * 16 + l16);
+            const uint32_t b = fdiv(n, pg.divP), rem = n - b * P, oy = fdiv(rem, pg.divOW), ox = rem - oy * pg.divOW.d;
+            const int32_t img = (int32_t)b * pg.img_stride, wy = (int32_t)(oy * pg.s) + pg.oy0, wx = (int32_t)(ox * pg.s) + pg.ox0;
+            for (int t = 0; t < KK; ++t) {
+                const int ky = (int)fdiv((uint32_t)t, pg.divKW), kx = t - ky * pg.KW;
+                const int32_t sy = wy + (pg.flip ? pg.KH - 1 - ky : ky), sx = wx + (pg.flip ? pg.KW - 1 - kx : kx);
+                const bool ok = n <= n1 && (uint32_t)sy < (uint32_t)pg.Hs && (uint32_t)sx < (uint32_t)pg.Ws;
+                for (int cb = 0; cb < ncb16; ++cb) {
+                    // a unit of 16 channels, four consecutive ones a lane, its loads in flight together
+                    float a[4][TM], b[4];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const uint32_t row = m0 + (uint32_t)((wm * TM + i) * 16 + l16), unit = (uint32_t)(t * ncb16 + cb) * unit_bytes;
+                        const auto f = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, row < p.M ? row * 64u + unit + 16u * (uint32_t)q : OOB_K, 0, 0);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) a[v][i] = __uint_as_float((uint32_t)f[v]);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int c = 16 * cb + 4 * q + v;
+                        const uint32_t at = ok ? (uint32_t)(img + c * pg.chan_stride + sy * pg.Ws + sx) * 4u : OOB_K;
+                        b[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrcB, at, 0, 0));
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) add(a[v], b[v]);
+                }
+            }
+        });
     }
     store_columns<TM, TN>(p, acc, g, 0u, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), n1 + 1, lane);
 }

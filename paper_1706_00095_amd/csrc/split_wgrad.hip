@@ -41,7 +41,7 @@ template <int NP, int NSL> struct BandLds {
 
 }  // namespace
 
-template <int NP, int TM, int NSL, bool OWN>
+template <int NP, int TM, int NSL>
 __global__ __launch_bounds__(256, 2) void split_wgrad_kernel(const IgemmProblem p)
 {
     using L = BandLds<NP, NSL>;
@@ -160,17 +160,8 @@ __global__ __launch_bounds__(256, 2) void split_wgrad_kernel(const IgemmProblem 
 #pragma unroll
                     for (int i = 0; i < TM; ++i) ar[i][t] = po + t < un.npix ? ar[i][t] : 0.f;
             v4u ap[TM][NP];
-            float big = 0.f;
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) split8_pair<NP>(ar[i], t, ap[i], big);
-            if constexpr (NP == 3) {
-                if (__builtin_expect(big >= CG_HUGE, 0)) {
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) split8_huge(ar[i], ap[i]);
-                }
-            }
+            for (int i = 0; i < TM; ++i) split8<NP>(ar[i], ap[i]);
             // a chunk of the next unit's patch, then the next step's rows
             static_for<0, NC>([&](auto EC) { if (s == decltype(EC)::value) load_chunk(EC, u + 1); });
             if (s + 1 < g.steps) load_a(u, s + 1);
@@ -186,7 +177,7 @@ __global__ __launch_bounds__(256, 2) void split_wgrad_kernel(const IgemmProblem 
                 mask[hf] = ok ? -1 : 0;
                 at[hf] = (ok ? (int32_t)(seg * g.divSS.d) + (int32_t)row * g.s * g.Wp + col * g.s : L::SLOTS) * 32 + (l16 & 3) * 8;
             }
-            using Step = MmaStep<NP, TM, TT, TM == 1 ? 3 : 1, OWN>;
+            using Step = MmaStep<NP, TM, TT, TM == 1 ? 3 : 1>;
             auto read_b = [&](int j, v4u (&pc)[NP]) {
                 const int32_t a0 = at[0] + (toff[j] & mask[0]), a1 = at[1] + (toff[j] & mask[1]);
 #pragma unroll
@@ -205,6 +196,37 @@ __global__ __launch_bounds__(256, 2) void split_wgrad_kernel(const IgemmProblem 
         }
     }
 
+    if constexpr (NP == 3) {
+        if (not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
+            const int t = min(t0 + j, KK - 1), ky = (int)fdiv((uint32_t)t, g.divKW), kx = t - ky * g.KW;
+            for (int u = u0; u < u1; ++u) {
+                const Unit un = unit_of(u);
+                for (int n = un.n0; n < min(un.n0 + g.ipu, g.N); ++n)
+                    for (int p0 = 0; p0 < un.npix; p0 += 16) {
+                        // 16 pixels, four consecutive ones a lane, their loads in flight together
+                        float a[4][TM], b[4];
+                        const int32_t p4 = p0 + 4 * q;
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) {
+                            const auto f = __builtin_amdgcn_raw_buffer_load_b128(
+                                rY, p4 < un.npix ? yrow[i] + (uint32_t)(n * g.M * P + un.oy0 * g.OW + p4) * 4u : OOB_K, 0, 0);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) a[v][i] = p4 + v < un.npix ? __uint_as_float((uint32_t)f[v]) : 0.f;
+                        }
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int32_t px = p4 + v, row = (int32_t)fdiv((uint32_t)px, g.divOW), col = px - row * g.OW;
+                            const int32_t sy = (un.oy0 + row) * g.s - g.pad_h + ky, sx = col * g.s - g.pad_w + kx;
+                            const bool ok = px < un.npix && c0 + l16 < g.Cg && (uint32_t)sy < (uint32_t)g.H && (uint32_t)sx < (uint32_t)g.W;
+                            b[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                                rX, ok ? (uint32_t)((n * g.C + c0 + l16) * HW + sy * g.W + sx) * 4u : OOB_K, 0, 0));
+                        }
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) add(a[v], b[v]);
+                    }
+            }
+        });
+    }
     // Lane (q, l) holds, for row l of a 16-row tile, the channels 4q .. 4q+3 of every tap: where the block has
     // all nine taps, 36 consecutive floats.
     float *c_base = p.c_ptr + (int64_t)gr * p.c_gstride + (int64_t)sp * p.c_split_stride;
@@ -234,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void split_wgrad_kernel(const IgemmProblem 
 
 namespace {
 
-template <int NP, int TM, int NSL, bool OWN> int launch_own(const IgemmProblem &p, hipStream_t stream)
+template <int NP, int TM, int NSL> int launch_cfg(const IgemmProblem &p, hipStream_t stream)
 {
     constexpr int MT = 64 * TM;
     dim3 grid((unsigned)(((p.band.Cg + 15) / 16) * p.band.tap_blocks), (p.M + MT - 1) / MT, p.groups * p.splits);
@@ -249,22 +271,14 @@ template <int NP, int TM, int NSL, bool OWN> int launch_own(const IgemmProblem &
     static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_wgrad_kernel<NP, TM, NSL, OWN>),
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_wgrad_kernel<NP, TM, NSL>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((split_wgrad_kernel<NP, TM, NSL, OWN>), grid, dim3(256), lds, stream, p);
+    hipLaunchKernelGGL((split_wgrad_kernel<NP, TM, NSL>), grid, dim3(256), lds, stream, p);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
-}
-
-// three pieces: a step's products are added up on their own (MmaStep), whatever the slice: the padding of
-// an image's pixels makes the steps of a short slice many (32 images of 14x14: 3.0e-7 off 64 bits without, 1.35e-7
-// with, 2.1e-7 the fp32 instruction)
-template <int NP, int TM, int NSL> int launch_cfg(const IgemmProblem &p, hipStream_t stream)
-{
-    return launch_own<NP, TM, NSL, NP == 3>(p, stream);
 }
 
 }  // namespace

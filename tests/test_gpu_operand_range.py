@@ -1,5 +1,6 @@
-"""Operands anywhere in the range of fp32, through the kernels that cut operands in bf16 pieces: an infinity or a NaN of
-one channel stays out of the others.
+"""Operands anywhere in the range of fp32: what three bf16 pieces per operand have to carry, through every kernel
+that cuts operands.  Subnormal and nearly subnormal values keep all their bits, products just below 2^128 are
+finite, an infinity times a subnormal is an infinity, and an infinity or a NaN of one channel stays out of the others.
 """
 import numpy as np
 import pytest
@@ -59,6 +60,75 @@ class _Kernel:
         dy = a.reshape(B, G, M // G, -1)
         return torch.stack([sum(dy[n, g] @ u[n, g].t().contiguous() for n in range(B)) for g in range(G)]).reshape(
             M, C // G, k, k).numpy()
+
+
+KERNELS = {
+    "patch_rows_shared": _Kernel("fwd", (2, 48, 9, 33, 3, 1, 1), "igemm_patch16_kernel<48x128,4>", patch=True),
+    "patch_64": _Kernel("fwd", (2, 16, 13, 72, 3, 1, 1), "igemm_patch_kernel<64x128,4>", patch=True),
+    "patch_bwd_data": _Kernel("bd", (1, 64, 27, 32, 5, 2, 1), "igemm_patch_kernel<64x128,5>", patch=True),
+    "band_64": _Kernel("bw", (4, 24, 14, 64, 5, 2, 1), "igemm_kernel<64x144,band4>", resident=2),
+    "band_128": _Kernel("bw", (5, 20, 27, 72, 3, 1, 1), "igemm_kernel<128x144,band8>", resident=2),
+    "pieces_16": _Kernel("fwd", (76, 20, 34, 8, 3, 0, 1), "igemm_kernel<16x128,4r-,pieces>"),
+    "pieces_128": _Kernel("fwd", (53, 29, 24, 113, 3, 0, 1), "igemm_kernel<128x128,4r-,pieces>"),
+    "pieces_filters_in_place": _Kernel("bd", (25, 512, 14, 32, 1, 0, 1), "igemm_kernel<128x128,rr-,pieces>"),
+}
+
+
+def _one_per_reduction(shape, rng, scale):
+    """Filters (or inputs) with few non-zeros, so that sums are a handful of products."""
+    t = np.zeros(shape, np.float32)
+    flat = t.reshape(shape[0], -1)
+    for r in range(shape[0]):
+        c = rng.integers(0, flat.shape[1], size=3)
+        flat[r, c] = (rng.uniform(1, 2, size=3) * scale).astype(np.float32)
+    return t
+
+
+@pytest.mark.parametrize("kernel", list(KERNELS))
+@pytest.mark.parametrize("ea,eb", [(-140, 100), (-149, 120), (-125, 40), (-60, -68), (62.9, 63), (90, -100)])
+def test_products_of_extreme_operands(kernel, ea, eb):
+    """a around 2^ea times a few b around 2^eb: at most 3 * B products a sum, so fp32 multiply-adds are within
+    (products + 1) * 2^-24 of the exact sum (plus half of the smallest subnormal); results beyond 2^128 are infinite on both sides."""
+    k = KERNELS[kernel]
+    rng = np.random.default_rng(sum(map(ord, kernel)))
+    sa, sb = k.tensors()
+    a = (rng.uniform(1, 2, size=sa) * 2.0 ** ea).astype(np.float32)
+    if k.which == "bw":          # few non-zero pixels of x: as many products a sum
+        b = np.zeros(sb, np.float32)
+        b[0, :, sb[2] // 2, sb[3] // 2] = rng.uniform(1, 2, size=sb[1]) * 2.0 ** (eb - 1)
+    else:
+        b = _one_per_reduction(sb, rng, 2.0 ** (eb - 1))
+    if k.which == "bd":          # a column of the filters adds up over all rows
+        b[1:] = 0
+    ref = k.exact(a, b)
+    got = k.run(a, b)
+    fits = np.abs(ref) < 2.0 ** 127.9
+    assert fits.any() and np.isfinite(got[fits]).all()
+    bound = 5 * 2.0 ** -24 * np.abs(ref[fits]) + 2.0 ** -149
+    assert (np.abs(got[fits] - ref[fits]) <= bound).all(), np.max(np.abs(got[fits] - ref[fits]) / np.maximum(np.abs(ref[fits]), 2.0 ** -149))
+
+
+@pytest.mark.parametrize("kernel", list(KERNELS))
+def test_infinities_and_nan(kernel):
+    """One infinity of each sign and one NaN among positive operands, subnormal ones among them (an infinity times
+    2^-140 is an infinity), all others finite: every output is what 64-bit arithmetic gives, finite ones as near as fp32
+    sums of one sign are (K * 2^-24)."""
+    k = KERNELS[kernel]
+    rng = np.random.default_rng(9)
+    sa, sb = k.tensors()
+    a, b = (rng.uniform(0.5, 1.5, size=s).astype(np.float32) for s in (sa, sb))
+    tiny = rng.integers(0, b.size, size=b.size // 8)
+    b.reshape(-1)[tiny] = np.float32(2.0 ** -140)
+    n, c, h, w = sa
+    a[0, 1, h // 2, w // 2] = np.inf
+    a[n - 1, c // 2, 0, 0] = -np.inf
+    a[n // 2, c - 1, h - 1, w - 1] = np.nan
+    ref, got = k.exact(a, b), k.run(a, b)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+    ok = np.isfinite(ref)
+    terms = {"fwd": sb[1] * sb[2] * sb[3], "bd": sa[1] * sb[2] * sb[3], "bw": sa[0] * sa[2] * sa[3]}[k.which]
+    assert ok.any() and (np.abs(got[ok] - ref[ok]) <= terms * 2.0 ** -24 * np.abs(ref[ok])).all()
 
 
 @pytest.mark.parametrize("math", [cg.CG_MATH_FP32, cg.CG_MATH_BF16, cg.CG_MATH_BF16X3])
