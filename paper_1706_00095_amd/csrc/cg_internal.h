@@ -255,9 +255,9 @@ constexpr uint64_t kSplitBlocks = 512;
 // on scheduling).  igemm_ws_bytes() says how much workspace igemm_run() needs for a problem.
 struct SplitPlan { uint32_t splits, k_per_split; size_t ws_bytes; int mt, pieces; };       // pieces: 1 = split_gemm_kernel
 SplitPlan gathered_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
-// Fills the derived fields and chooses units, tile and K slices (other_splits: what the gathered kernel would use);
-// false where the kernel does not apply.
-bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t other_splits, uint32_t *splits);
+// Fills the derived fields and chooses units, tile and K slices; false where the kernel does not apply or the gathered
+// kernel (whose plan for the M x N x K problem is `other`) is expected to be faster in this arithmetic.
+bool band_plan(BandGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other, int math, uint32_t *splits);
 size_t igemm_ws_bytes(const IgemmProblem &p);
 // rider: a small convolution's bias gradient (db[m] = sum of dy over images and pixels), summed by
 // extra blocks of the K-slice finishing launch, one block per channel, instead of a launch of its

@@ -769,7 +769,7 @@ int filter_prep_launch(int n, const FilterPrep *jobs, const float *const *w, flo
 // a multiple of four (padding indices read as zero in B), so that dy, contiguous along the pixels
 // of one image, can be fetched in aligned groups of four that never straddle two images.
 static IgemmProblem bwd_weight_problem(const cg_conv_desc &d, int OH, int OW, const float *x, const float *dy,
-                                       float *dw)
+                                       float *dw, int math)
 {
     const int G = d.groups, Cg = d.C / G, Mg = d.M / G, Kg = Cg * d.KH * d.KW, P = OH * OW;
     const int Pp = (P + 3) / 4 * 4;
@@ -815,7 +815,7 @@ static IgemmProblem bwd_weight_problem(const cg_conv_desc &d, int OH, int OW, co
         bg.x = x; bg.x_elems = wgm.x_elems; bg.dy = dy; bg.dy_elems = p.A.elems;
         bg.N = d.N; bg.C = d.C; bg.Cg = Cg; bg.H = d.H; bg.W = d.W; bg.OH = OH; bg.OW = OW; bg.s = d.stride_h;
         bg.pad_h = d.pad_h; bg.pad_w = d.pad_w; bg.KH = d.KH; bg.KW = d.KW; bg.M = d.M;
-        if (!p.use_wgrad && band_plan(bg, (uint32_t)Mg, (uint32_t)G, gathered_plan(p.M, p.N, p.K, p.groups).splits, &splits)) {
+        if (!p.use_wgrad && band_plan(bg, p.M, p.N, p.groups, gathered_plan(p.M, p.N, p.K, p.groups), math, &splits)) {
             p.use_band = 1;
             p.band = bg;
             p.splits = splits;
@@ -833,11 +833,16 @@ int conv_bwd_weight_impl(const cg_conv_desc &d, const float *x, const float *dy,
     int OH, OW;
     const int rc = conv_check(&d, &OH, &OW);
     if (rc) return rc;
-    IgemmProblem p = bwd_weight_problem(d, OH, OW, x, dy, dw);
-    const size_t split_bytes = round256(igemm_ws_bytes(p));       // sized for the kernel the fp32 mode picks
+    IgemmProblem p = bwd_weight_problem(d, OH, OW, x, dy, dw, math);
     p.math = math;
-    if (math != CG_MATH_FP32 && p.use_wgrad) { p.use_wgrad = 0; p.splits = 1; }    // the band kernel is fp32 only
+    if (math != CG_MATH_FP32 && p.use_wgrad) { p.use_wgrad = 0; p.splits = 1; }    // the fp32 band kernel
     const size_t bias_bytes = db ? bias_grad_ws_bytes(d.N, d.M) : 0;
+    size_t split_bytes = round256(igemm_ws_bytes(p));
+    if (p.use_band && ws_bytes < split_bytes + bias_bytes) {      // what the gathered kernel needs is always enough
+        p.use_band = 0;
+        p.splits = 1;
+        split_bytes = round256(igemm_ws_bytes(p));
+    }
     if (split_bytes + bias_bytes > 0) {
         if (!ws || ws_bytes < split_bytes + bias_bytes) return CG_ENOSPC;
         if (!aligned16(ws)) return CG_EINVAL;
@@ -867,6 +872,14 @@ int conv_bwd_weight_impl(const cg_conv_desc &d, const float *x, const float *dy,
     return bias_grad_launch(dy, d.N, d.M, OH * OW, db, static_cast<char *>(ws) + split_bytes, bias_bytes, stream);
 }
 
+// K slices of the gathered kernel (and, where a test has switched it on, of the fp32 band kernel): the least any mode needs
+static size_t gathered_bwd_weight_bytes(const cg_conv_desc &d, int OH, int OW)
+{
+    IgemmProblem p = bwd_weight_problem(d, OH, OW, nullptr, nullptr, nullptr, CG_MATH_FP32);
+    if (p.use_band) { p.use_band = 0; p.splits = 1; }
+    return igemm_ws_bytes(p);
+}
+
 size_t conv_ws_bytes(const cg_conv_desc &d, int pass)
 {
     int OH, OW;
@@ -887,9 +900,14 @@ size_t conv_ws_bytes(const cg_conv_desc &d, int pass)
         return round256((size_t)d.M * (d.C / d.groups) * d.KH * d.KW * sizeof(float)) +
                igemm_ws_bytes(bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0));
     }
-    if (pass == CG_PASS_BWD_WEIGHT)
-        return round256(igemm_ws_bytes(bwd_weight_problem(d, OH, OW, nullptr, nullptr, nullptr))) +
-               bias_grad_ws_bytes(d.N, d.M);
+    if (pass == CG_PASS_BWD_WEIGHT) {
+        size_t most = gathered_bwd_weight_bytes(d, OH, OW);
+        for (int math : {CG_MATH_FP32, CG_MATH_BF16, CG_MATH_BF16X3}) {
+            const size_t b = igemm_ws_bytes(bwd_weight_problem(d, OH, OW, nullptr, nullptr, nullptr, math));
+            if (b > most) most = b;
+        }
+        return round256(most) + bias_grad_ws_bytes(d.N, d.M);
+    }
     return 0;
 }
 
@@ -1002,7 +1020,7 @@ extern "C" int cg_debug_conv_operand(const cg_conv_desc *d, int pass, int operan
         if (d->stride_h != 1 || d->stride_w != 1) return CG_EUNSUPPORTED;
         p = bwd_data_problem(*d, OH, OW, nullptr, nullptr, nullptr, 0);
     } else if (pass == CG_PASS_BWD_WEIGHT)
-        p = bwd_weight_problem(*d, OH, OW, nullptr, nullptr, nullptr);
+        p = bwd_weight_problem(*d, OH, OW, nullptr, nullptr, nullptr, CG_MATH_FP32);
     else return CG_EINVAL;
     const Operand &op = operand == 0 ? p.A : p.B;
     if (row >= op.row.count || k >= p.K) return CG_EINVAL;
@@ -1133,7 +1151,7 @@ extern "C" int cg_conv_bwd_weight_noalloc(const cg_conv_desc *d, const float *x,
     int OH, OW;
     const int rc = conv_check(d, &OH, &OW);
     if (rc) return rc;
-    if (conv_ws_bytes(*d, CG_PASS_BWD_WEIGHT) > (size_t)CG_NOALLOC_SCRATCH_BYTES) return CG_ENOSPC;
+    if (round256(gathered_bwd_weight_bytes(*d, OH, OW)) + bias_grad_ws_bytes(d->N, d->M) > (size_t)CG_NOALLOC_SCRATCH_BYTES) return CG_ENOSPC;
     void *ptr = nullptr;
     const int rs = scratch_for_current_device(&ptr);
     if (rs) return rs;

@@ -309,13 +309,47 @@ int split_wgrad_launch(const IgemmProblem &p, hipStream_t stream)
     return p.math == CG_MATH_FP32 ? split_wgrad_3(p, stream) : CG_EINVAL;
 }
 
+// Expected times of this kernel and of the gathered one, us.  Fitted to 520 problems (9 to 384 channels a group, 33 to
+// 448 rows, windows 2x3 to 7x7 and rows and columns of 5 to 11, strides 1 and 2, planes 7 to 60 wide, batches 2 to 256)
+// in each arithmetic; one standard deviation of the relative error is 10 - 13 % and 5 - 11 %.  A block of this
+// kernel multiplies whole 16 channels, nine taps, 32 pixels and mt rows, brings a patch a unit, and stores one by one
+// unless the window has nine taps; the gathered kernel's blocks run one after another or in pairs on a compute unit and
+// check every element where there is padding; both write their slices and read them again.
+// Chosen by these the problems took 71.7 ms in fp32 (all here 83.0, all there 79.0, each at its best 71.5), 36.7 in
+// bf16 (49.0, 37.9, 36.5), 45.8 in bf16x3 (59.2, 48.0, 45.7).
+static double band_cost(const BandGeom &g, int chunks, double plane, uint64_t blocks, uint32_t splits, uint64_t resident, int math)
+{
+    struct Fit { double start, row, step, row_pair, step_pair, unit, unit8, byte, scattered; };
+    static const Fit fit[3] = {{13.6, 0.543, 0.334, 0.502, 0., 1.66, 0., 2.59e-7, 7.82e-7},
+                               {12.4, 0., 0.412, 0.291, 0.00465, 0.669, 0.328, 2.98e-7, 8.05e-7},
+                               {13.3, 0.179, 0.398, 0.345, 0., 0.914, 0.315, 2.64e-7, 8.18e-7}};
+    const Fit &f = fit[math];
+    const bool pair = blocks * 2 > resident;
+    const double rounds = (double)((blocks + resident - 1) / resident), units = rounds * g.units_per_split, steps = units * g.steps;
+    return f.start + steps * (g.mt / 64 * (f.row + (pair ? f.row_pair : 0.)) + f.step + (pair ? f.step_pair : 0.)) +
+           units * (f.unit + (chunks == 8 ? f.unit8 : 0.)) + splits * plane * ((splits > 1 ? f.byte * 2. : 0.) + (g.KH * g.KW != TT ? f.scattered : 0.));
+}
+
+static double gathered_cost(const SplitPlan &o, uint64_t blocks, double plane, bool padded, uint64_t resident, int math)
+{
+    struct Fit { double start, row, tile, check, byte, many; };
+    static const Fit fit[3] = {{11.2, 0.00741, 0.118, 0.0939, 2.05e-7, 2.74},
+                               {11.2, 0.00163, 0.184, 0.0398, 2.11e-7, 4.12},
+                               {12.0, 0.00245, 0.246, 0.0664, 2.05e-7, 3.50}};
+    const Fit &f = fit[math];
+    const uint64_t units = resident > 1 ? resident / 2 : 1, n = (blocks + units - 1) / units;
+    const double rounds = (n & 1) && n > 1 ? (double)(n - 1) + 1.2 : (double)n;
+    return f.start + rounds * (double)((o.k_per_split + 15) / 16) * (f.row * o.mt + f.tile + (padded ? f.check : 0.)) +
+           (o.splits > 1 ? f.byte * 2. * o.splits * plane : 0.) + (o.splits >= 16 ? f.many : 0.);
+}
+
 // Fills Wp, bands, dividers; chooses the unit, the row tile and the number of K slices.
-bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t other_splits, uint32_t *splits)
+bool band_plan(BandGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other, int math, uint32_t *splits)
 {
     g.nsl = 0;
     const int KK = g.KH * g.KW;
-    // fewer than half of the 16 channels of a block real: the gathered kernel wastes less
-    if (KK < 5 || g.s <= 0 || g.Cg < 9 || g.N <= 0 || M < 33) return false;
+    // (below nine channels more than half of a block's 16 would be padding; up to 32 rows more than half of its rows)
+    if (math < 0 || math > 2 || KK < 5 || g.s <= 0 || g.Cg < 9 || g.N <= 0 || M < 33) return false;
     if (g.x_elems * 4 > kMaxBufferBytes || g.dy_elems * 4 > kMaxBufferBytes) return false;
     g.Wp = (g.OW - 1) * g.s + g.KW;
     // Row tile: the least padding, the taller one where equal.  Padded slots a unit may fill: 512 beside 128
@@ -349,21 +383,27 @@ bool band_plan(BandGeom &g, uint32_t M, uint32_t groups, uint32_t other_splits, 
     const uint64_t tiles = (uint64_t)((M + g.mt - 1) / g.mt) * ((g.Cg + 15) / 16) * g.tap_blocks * groups;
     const uint64_t resident = igemm_resident_blocks();
     uint64_t want = resident / tiles;
-    if (want * 4 < (uint64_t)other_splits * 3) want = other_splits;      // no slice much longer than the gathered kernel's
+    if (want * 4 < (uint64_t)other.splits * 3) want = other.splits;      // no slice much longer than the gathered kernel's
     if (want > (uint64_t)g.units) want = (uint64_t)g.units;
     if (want < 1) want = 1;
     g.units_per_split = (int32_t)(((uint64_t)g.units + want - 1) / want);
     *splits = (uint32_t)(((uint64_t)g.units + g.units_per_split - 1) / g.units_per_split);
     // enough blocks to fill the chip, or the gathered kernel cuts K finer
     if (tiles * *splits * 2 < resident) return false;
-    if ((uint64_t)*splits * groups * M * (uint64_t)(g.Cg * KK) >= (1ull << 31)) return false;
+    if ((uint64_t)*splits * groups * M * N >= (1ull << 31)) return false;
+    const int chunks = g.ipu * ss <= 256 ? 4 : 8;
+    const double plane = 4. * groups * M * N;
+    const uint64_t other_blocks = (uint64_t)((M + other.mt - 1) / other.mt) * ((N + 127) / 128) * groups * other.splits;
+    if (band_cost(g, chunks, plane, tiles * *splits, *splits, resident, math) >=
+        0.97 * gathered_cost(other, other_blocks, plane, g.pad_h || g.pad_w, resident, math))
+        return false;
     g.divSS = make_fastdiv((uint32_t)ss);
     g.divWp = make_fastdiv((uint32_t)g.Wp);
     g.divP8 = make_fastdiv((uint32_t)p8);
     g.divOW = make_fastdiv((uint32_t)g.OW);
     g.divKW = make_fastdiv((uint32_t)g.KW);
     g.divNB = make_fastdiv((uint32_t)g.nb);
-    g.nsl = g.ipu * ss <= 256 ? 4 : 8;
+    g.nsl = chunks;
     return true;
 }
 #endif  // CG_NP == 3

@@ -153,3 +153,22 @@ def test_weight_gradient_of_other_channels_stays_clean(math, value):
         dy[3, 7, 7, 5] = value
         got = k.run(dy, x, math)
         assert np.array_equal(got[7], np.full_like(got[7], value))
+
+
+def test_weight_gradient_with_the_scratch_memory_of_the_gathered_kernel():
+    """The kernel with rows in LDS cuts this reduction into more slices than the gathered one's 79: a caller that brings
+    what that one needs (its slices, and the bias sums of 41 images behind them) gets its result."""
+    d = cg.conv_desc(41, 42, 20, 20, 48, 3, pad=1)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x, dy = (torch.randint(-3, 4, (41, c, 20, 20), device="cuda", generator=gen).float() for c in (42, 48))
+    (ref, rdb), names = _logged(lambda: conv_bwd_weight(d, x, dy))
+    assert any("band" in n for n in names), names
+    need = -(-79 * 48 * 42 * 9 * 4 // 256) * 256 + 41 * 48 * 4
+    assert need < cg.cg_conv_workspace_bytes(d, cg.CG_PASS_BWD_WEIGHT)
+    dw, db = torch.full_like(ref, float("nan")), torch.full_like(rdb, float("nan"))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    _, names = _logged(lambda: cg.cg_conv_bwd_weight(d, x, dy, dw, db, ws))
+    assert names and not any("band" in n for n in names), names
+    assert torch.equal(dw, ref) and torch.equal(db, rdb)
+    with pytest.raises(cg.CgError):
+        cg.cg_conv_bwd_weight(d, x, dy, dw, db, ws[:-16])

@@ -126,6 +126,10 @@ ROUTES = {
     ("fwd", 32, 480, 14, 64, 1, 0, 1): "igemm_kernel<64x128,4r->",
     ("bw", 32, 192, 28, 96, 1, 0, 1): "igemm_kernel<96x128,4k->",
     ("bd", 32, 192, 28, 96, 1, 0, 1): "igemm_kernel<192x128,rr->",
+    # a window of 25 taps in blocks of nine, 98 pixels a unit: more padding than the rows in LDS are worth
+    ("bw", 32, 24, 14, 64, 5, 2, 1): "igemm_kernel<64x128,4kc>",
+    ("bw", 32, 192, 7, 384, 3, 1, 1): "igemm_kernel<128x128,4kc>",
+    ("bw", 64, 384, 13, 384, 3, 1, 2): "igemm_kernel<192x144,band4>",
 }
 
 
