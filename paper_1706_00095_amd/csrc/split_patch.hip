@@ -371,36 +371,27 @@ int patch_launch(const IgemmProblem &p, hipStream_t stream)
     // rows for 48).  The reduced modes have 64-row tiles only.
     if (p.M <= 48 && p.math == CG_MATH_FP32) return patch_launch_tiles(p, (int)(p.M + 15) / 16 * 16, stream);
     int mt = patch_mt(p.M, p.N, p.groups);
-    // Two blocks are resident per compute unit, so blocks run in rounds of g_resident_blocks that
-    // start and end together.  When the last round would be less than three quarters full, the
-    // pixel tiles of the whole rounds go out as one launch and the rest as a second launch of
-    // 64-row tiles: three or two small blocks in place of a large one fill the compute units that
-    // the short round would leave idle (676 blocks of 192 rows: 512 + 492 of 64 rows).  Forward only:
-    // backward-data shares the GPU with backward-weight on another stream, whose blocks already
-    // fill those compute units, and a second dependent launch then only delays it (measured).
-    // Backward-data (mirrored taps) in the same situation takes 64-row tiles for the whole launch: three
-    // of those blocks fit a compute unit, and twice or three times as many, shorter blocks quantise
-    // better (676 blocks of 192 rows = 1.32 rounds of 512; 2028 of 64 rows = 2.64 rounds of 768).
-    // Alone on the GPU: conv4-shaped 0.516 -> 0.461 ms, conv5-shaped 0.352 -> 0.315 ms at B = 256 (a
-    // one-stream step 11.17 -> 10.82 ms); beside backward-weight on another stream, whose blocks fill the
-    // short round anyway, the step was 0.07 ms slower with it, so a caller that runs such a stream says
-    // so (beside_other_stream) and keeps the large tiles.
-    if (mt > 64 && p.patch.tile_count == 0 && p.patch.flip && p.patch.nsl == 4 && !p.beside_other_stream) {
-        const uint32_t rb = igemm_resident_blocks();
-        const uint64_t blocks = (uint64_t)patch_pixel_tiles(p) * ((p.M + mt - 1) / mt) * p.groups;
-        const uint32_t rest = (uint32_t)(blocks % rb);
-        if (blocks / rb >= 1 && rest > 0 && rest < rb * 3 / 4) mt = 64;
-    }
-    if (mt > 64 && p.patch.tile_count == 0 && !p.patch.flip) {
-        const uint32_t g_resident_blocks = igemm_resident_blocks();
-        const uint32_t px = patch_pixel_tiles(p), per_px = ((p.M + mt - 1) / mt) * p.groups;
-        const uint64_t blocks = (uint64_t)px * per_px;
-        const uint32_t rounds = (uint32_t)(blocks / g_resident_blocks);
-        const uint32_t rest = (uint32_t)(blocks - (uint64_t)rounds * g_resident_blocks);
-        const uint32_t px_main = rounds * g_resident_blocks / per_px;
+    // Two blocks are resident per compute unit, so blocks run in rounds of igemm_resident_blocks() that
+    // start and end together.  What a short last round leaves idle is won back in two ways; times with / without, us:
+    // - forward, fp32: the pixel tiles of the whole rounds go out as one launch and the rest as a second launch of
+    //   64-row tiles.  192-row tiles: 192 rows, 1728 indices, 1.32 rounds 303 / 315; 160 rows, 1296, 1.11 rounds 223 / 253;
+    //   320 rows, 2800, 2.09 rounds 726 / 772.  128-row tiles only for a rest of a few blocks (1.04 and 1.14 rounds 0.97;
+    //   1.3 - 1.5, 2.1 - 2.5, 4.3 rounds 1.03 - 1.06).  One and two pieces: 1.03 - 1.08 nearly always, so not there.
+    //   Not backward-data: it shares the GPU with backward-weight on another stream, whose blocks already
+    //   fill those compute units.
+    // - backward-data (mirrored taps), one and two pieces, 128-row tiles: 64-row tiles for the whole launch (112 rows, 1344
+    //   indices, 1.12 rounds, two pieces 106 / 118; 336 rows 1.63 rounds 162 / 172).  192-row tiles lose by it (1.02 - 1.08),
+    //   and three pieces do (256 rows, 3456 indices, 1.32 rounds 498 / 450; 192 rows 346 / 316).  A caller that runs another
+    //   stream beside it says so (beside_other_stream) and keeps the large tiles.
+    const uint32_t rb = igemm_resident_blocks(), px = patch_pixel_tiles(p), per_px = ((p.M + mt - 1) / mt) * p.groups;
+    const uint64_t blocks = (uint64_t)px * per_px;
+    const uint32_t rounds = (uint32_t)(blocks / rb), rest = (uint32_t)(blocks - (uint64_t)rounds * rb);
+    const bool short_round = mt > 64 && p.patch.tile_count == 0 && rounds >= 1 && rest > 0 && rest < rb * 3 / 4;
+    if (short_round && p.patch.flip && p.patch.nsl == 4 && !p.beside_other_stream && p.math != CG_MATH_FP32 && mt == 128) mt = 64;
+    else if (short_round && !p.patch.flip && p.math == CG_MATH_FP32 && (mt == 192 || rest <= 80)) {
+        const uint32_t px_main = rounds * rb / per_px;
         const uint32_t tail_blocks = (px - px_main) * ((p.M + 63) / 64) * p.groups;
-        if (rounds >= 1 && rest > 0 && rest < g_resident_blocks * 3 / 4 && px_main > 0 && px_main < px &&
-            tail_blocks <= g_resident_blocks) {
+        if (px_main > 0 && px_main < px && tail_blocks <= rb) {
             IgemmProblem a = p, b = p;
             a.patch.tile0 = 0;
             a.patch.tile_count = px_main;
@@ -437,10 +428,16 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
     g.divWp = make_fastdiv((uint32_t)g.Wp);
     g.divRfull = make_fastdiv((uint32_t)g.Rfull);
     g.divKW = make_fastdiv((uint32_t)g.KW);
-    // The kernel has no K slices, and a block alone on a compute unit waits for its own loads: below 256
-    // tiles of 64 rows the gathered kernel, cut along K, is faster (32 images of 14x14, 128 rows: 98 tiles,
-    // 79 us here, 54 there; 64 images of 13x13, two groups of 192 rows: 510 tiles, 98 us here, 147 there).
-    if ((uint64_t)((M + 63) / 64) * ((N + 127) / 128) * groups * 2 < g_patch_min_tiles.load(std::memory_order_relaxed)) return false;
+    // The kernel has no K slices, and a block alone on a compute unit waits for its own loads: with few tiles the
+    // gathered kernel, cut along K, is faster, the more so the longer the reduction.  fp32, tiles of 64 rows, times there /
+    // here (285 problems, 3x3 and 5x5 windows): below 256 tiles 0.5 - 1.3; 256 - 384 tiles 0.98 - 1.6 up to 1200 indices,
+    // 0.64 - 1.0 beyond for most; 384 - 640 tiles 1.0 - 1.7 below 3200 indices, 0.8 - 1.0 beyond; from 640 tiles 1.0 - 2.2.  Up
+    // to 48 rows (waves share the rows and split the steps) 0.9 - 2.6 from 200 tiles; more rows and fewer than 128 indices
+    // 0.79 - 0.98 whatever the tiles.
+    const uint64_t T = (uint64_t)((M + 63) / 64) * ((N + 127) / 128) * groups, lim = g_patch_min_tiles.load(std::memory_order_relaxed);
+    const uint32_t K = g.Cred * (uint32_t)KK;
+    const bool enough = M <= 48 ? T * 5 >= lim * 2 : K < 128 ? false : T * 4 >= lim * 5 || (T * 4 >= lim * 3 && K < 3200) || (T * 2 >= lim && K <= 1200);
+    if (lim > 1 && !enough) return false;
     // The largest patch any block needs: a fragment read reaches (KH-1)*Wp + KW-1 beyond sigma, and
     // sigma + that stays below the slot count of the block's segments, which is what is counted.
     auto slots = [&](uint32_t n0, uint32_t n1) {

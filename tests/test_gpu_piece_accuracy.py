@@ -130,6 +130,9 @@ ROUTES = {
     ("bw", 32, 24, 14, 64, 5, 2, 1): "igemm_kernel<64x128,4kc>",
     ("bw", 32, 192, 7, 384, 3, 1, 1): "igemm_kernel<128x128,4kc>",
     ("bw", 64, 384, 13, 384, 3, 1, 2): "igemm_kernel<192x144,band4>",
+    # 340 tiles of 64 rows, 3456 indices: cut along K; 510 tiles and 1728: raw rows
+    ("bd", 64, 256, 13, 384, 3, 1, 1): "igemm_kernel<256x128,4rc>",
+    ("bd", 64, 384, 13, 384, 3, 1, 2): "igemm_patch_kernel<64x128,4>",
 }
 
 
