@@ -23,6 +23,15 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_BF16_MFMA_TFLOPS = 2500.0
+
+
+def fp32_peak(kernel):
+    """What a fp32-mode matrix kernel of the launch log can reach: the gathered kernels multiply in the fp32
+    instruction; those that cut operands in three bf16 pieces take six dense bf16 products for one."""
+    fp32_instruction = kernel.startswith(("igemm_kernel", "igemm_wgrad_kernel")) and "pieces" not in kernel and "band" not in kernel
+    return PEAK_FP32_MFMA_TFLOPS if fp32_instruction else PEAK_BF16_MFMA_TFLOPS / 6
+
+
 PEAK_HBM_GBS = 8000.0
 # context only (other hardware, full AlexNet on ImageNet, paper Table 1): seconds per iteration, B=256
 PAPER_ALEXNET_S_PER_ITER = {"P100": 0.1, "K80": 0.9, "KNL": 0.6, "CPU": 2.0}
@@ -360,8 +369,8 @@ def kernel_rooflines(agg, steps, traffic):
     dom_name, dom = max(mm.items(), key=lambda kv: kv[1]["ms"])
     achieved = dom["flops"] / dom["ms"] / 1e9       # TFLOP/s over that kernel's own launches
     t = traffic.get(dom_name)
-    roofline = dict(bound="mfma", achieved=achieved, peak=PEAK_FP32_MFMA_TFLOPS, unit="TFLOP/s",
-                    frac=achieved / PEAK_FP32_MFMA_TFLOPS,
+    roofline = dict(bound="mfma", achieved=achieved, peak=fp32_peak(dom_name), unit="TFLOP/s",
+                    frac=achieved / fp32_peak(dom_name),
                     traffic=(t["fetch_bytes"] + t["write_bytes"]) if t else None, kernel=dom_name,
                     avg_launch_ms=dom["ms"] / dom["launches"], launches_per_step=dom["launches"] / steps,
                     flops_per_launch=dom["flops"] / dom["launches"])
@@ -377,8 +386,9 @@ def kernel_rooflines(agg, steps, traffic):
                   frac=upd_bytes / upd_ms / 1e6 / PEAK_HBM_GBS,
                   traffic=(t["fetch_bytes"] + t["write_bytes"]) if t else None, kernel=upd_name,
                   bytes_per_launch=upd_bytes / n_upd, avg_launch_ms=upd_ms / n_upd, launches_per_step=n_upd / steps)
-    totals = dict(tflops=all_flops / all_ms / 1e9, ms_per_step=all_ms / steps,
-                  frac=all_flops / all_ms / 1e9 / PEAK_FP32_MFMA_TFLOPS, flops_per_step=all_flops / steps)
+    floor_ms = sum(a["flops"] / fp32_peak(k) for k, a in mm.items()) / 1e9      # every kernel at its own peak
+    totals = dict(tflops=all_flops / all_ms / 1e9, ms_per_step=all_ms / steps, floor_ms_per_step=floor_ms / steps,
+                  frac=floor_ms / all_ms, flops_per_step=all_flops / steps)
     return roofline, update, totals
 
 
@@ -519,7 +529,7 @@ def main():
         if roofline_excl["kernel"] in agg:
             a = agg[roofline_excl["kernel"]]
             roofline = dict(roofline, kernel=roofline_excl["kernel"], achieved=a["flops"] / a["ms"] / 1e9,
-                            frac=a["flops"] / a["ms"] / 1e9 / PEAK_FP32_MFMA_TFLOPS,
+                            peak=roofline_excl["peak"], frac=a["flops"] / a["ms"] / 1e9 / roofline_excl["peak"],
                             avg_launch_ms=a["ms"] / a["launches"], launches_per_step=a["launches"] / inst_steps,
                             flops_per_launch=a["flops"] / a["launches"], traffic=roofline_excl["traffic"])
         if args.kernel_table:
@@ -600,7 +610,7 @@ def main():
         "update_roofline": update_excl if update_excl else update_roofline,
         "update_roofline_three_stream_pass" if not args.serial else "update_roofline_instrumented_pass": update_roofline,
         "whole_step_matrix_core": {"tflops": totals["flops_per_step"] / (ms_per_step * 1e-3) / 1e12,
-                                   "frac": totals["flops_per_step"] / (ms_per_step * 1e-3) / 1e12 / PEAK_FP32_MFMA_TFLOPS,
+                                   "frac": totals["floor_ms_per_step"] / ms_per_step,
                                    "what": "algorithmic FLOP of all matrix-core launches of a step / wall time of the step "
                                            "(glue layers and updates included in the time)"},
         "matrix_core_kernels_exclusive": totals_excl,

@@ -13,9 +13,10 @@
 extern "C" {
 #endif
 
-/* Test hook: forward and stride-1 backward-data convolutions with enough
- * output tiles to fill the chip without cutting the reduction (512 by default)
- * run a kernel that stages raw image rows instead of gathered im2col tiles;
+/* Test hook: forward and backward-data convolutions with enough output tiles
+ * for the length of their reduction (lines of 0.4, 0.5, 0.75 and 1.25 times this
+ * number of 64-row tiles, 512 by default; 1 takes every shape that fits) run a
+ * kernel that stages raw image rows instead of gathered im2col tiles;
  * tests lower the threshold so that small shapes the oracle can check element
  * by element take that path too.  Process-wide. */
 int cg_debug_patch_min_tiles(int tiles);
@@ -27,10 +28,9 @@ int cg_debug_patch_min_tiles(int tiles);
 int cg_debug_resident_blocks(int blocks);
 
 /* Switch for an alternative backward-weight kernel that stages bands of raw
- * image rows in LDS (convolutions with at least nine taps).  Off by default:
- * alone on the GPU it is a few percent faster than the gathered kernel at the
- * 3x3 AlexNet shapes, but beside the backward-data kernels of the three-stream
- * schedule the whole iteration is slower with it.  on = 1 selects it where it
+ * image rows in LDS and multiplies in the fp32 matrix instructions (convolutions
+ * with at least nine taps).  Off by default: the kernel that cuts such rows in
+ * bf16 pieces is faster.  on = 1 selects it where it
  * applies, so that tests can compare the two.  Process-wide. */
 int cg_debug_band_kernel(int on);
 

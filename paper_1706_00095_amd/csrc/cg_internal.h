@@ -117,7 +117,7 @@ struct Operand {
 // (tap t = ky*KW + kx, channel c), tap-major, with Cred % 16 == 0 channels per group; element
 // (pixel, t, c) is src[img][group*Cred + c][oy*s + oy0 + py(t)][ox*s + ox0 + px(t)] or zero outside
 // the Hs x Ws plane, where (py, px) = (ky, kx) in forward and (KH-1-ky, KW-1-kx) in backward-data.
-// The kernel keeps, per block of 128 pixels and 16 channels, the padded source rows those pixels'
+// The kernel keeps, per block of 128 pixels and 32 channels, the padded source rows those pixels'
 // windows touch in LDS and reads each tap's operand fragment from there at a per-tap offset.
 struct PatchGeom {
     const float *src;
@@ -131,7 +131,7 @@ struct PatchGeom {
     int32_t Rfull;            // slots of a whole image: ((OHo-1)*s + KH) * Wp
     int32_t flip;             // 0: (py, px) = (ky, kx); 1: mirrored taps
     FastDiv divP, divOW, divWp, divRfull, divKW;
-    int32_t nsl;              // 64-slot chunks per channel the kernel instance stages (4 or 5); 0 = not usable
+    int32_t nsl;              // 64-slot chunks per channel the kernel instance stages (4, 5 or 6); 0 = not usable
     int32_t tiles_per_img;    // 0: blocks own 128 consecutive pixels across image boundaries; > 0: every image is
                               // cut into this many blocks of its own (smaller patches for large images)
     FastDiv divTpi;

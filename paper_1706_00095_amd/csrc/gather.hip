@@ -407,7 +407,7 @@ __global__ __launch_bounds__(256, 2) void igemm_kernel(const IgemmProblem p)
 // colbase fixed per lane for the whole kernel, sigma computed per K-tile for the eight pixels a
 // lane half multiplies.  dy arrives in K-tiles of 16 consecutive pixels of the band (aligned quads;
 // what a quad reads beyond the band's last pixel meets B values forced to zero).  Pipeline and
-// waits as in the patch kernel above: A ring of NSTA stages, the patch double buffered, the next
+// waits: A ring of NSTA stages as in igemm_kernel, the patch double buffered, the next
 // unit's patch loads issued during the current unit's first K-tile (a unit has >= 5 K-tiles).
 
 template <int WM, int WN, int TM, int TN, int NSTA, int CPB, int NSL>

@@ -1,8 +1,7 @@
-// Planning of the dense contractions: which kernel, which tile, how many K slices; the kernels that
-// add the slices and the bias gradient; and the fp32 band kernel for backward-weight.
+// Planning of the dense contractions: which kernel, which tile, how many K slices; and the kernels that
+// add the slices and the bias gradient.
 #include <atomic>
 #include <cstdio>
-#include <cstdlib>
 #include "cg_internal.h"
 #include "igemm_device.h"
 
@@ -80,7 +79,17 @@ int pick_mt(uint32_t M, uint32_t N, uint32_t groups, uint32_t K = 0)
 // all others.  Its blocks have one step of 32 indices in flight, the gathered kernel three or four K-tiles of 16: short
 // and small problems, and backward-weight, whose long reduction is cut into slices, belong there (1x1 layers
 // of 32 images of 28x28 forward 17.8 us there, 21.7 here; 375 x 336 with 5772 indices 46.5, 66.7).
-// PIECES_RULES
+// The lines, from 620 problems a mode; times there / here:
+// - at most 16 rows (a 32-row tile wastes half): from 180 indices and 600 blocks 0.98 - 1.29, median 1.1 (one and two
+//   pieces 1.1 - 1.5); fewer blocks only where the reduction is very long (4096 indices and more 1.04 - 1.1).
+// - 1x1 backward-data, whose filters are read across (a load per element on both sides there): few padded rows, a
+//   short reduction, 150 blocks and more: fp32 1.1 - 1.6; at 256 indices one and two pieces 0.83 - 0.9, so they end
+//   before.  192 rows (a quarter padding) 0.8 - 0.9, two rounds of 256 rows 0.97.
+// - images with few padded rows in fp32, enough blocks times indices: 0.98 - 1.46, median 1.1; whole multiples of 128 rows
+//   suit both (0.93 - 1.14), more padding suits the 192- and 96-row tiles there (0.7 - 1.0); one and two pieces 0.7 - 1.24.
+// - fully-connected forward and backward-data in fp32 from 108 images: 1.0 - 1.3 (256 images, 9216 -> 4096 159.6 / 151.0 us,
+//   4096 -> 4096 backward-data 79.5 / 69.1); 64 images 0.8 - 1.0.  Not where columns lie apart in memory (1x1 layers
+//   of planes of one pixel: 0.82).
 int pieces_mt(const IgemmProblem &p)
 {
     if (p.A.check || p.B.k.r1_lim) return 0;

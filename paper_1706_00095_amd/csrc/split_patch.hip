@@ -185,7 +185,8 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     block_sync_lds();
 
     // (the rows are cut in one piece in front of the products: cutting them behind the products of the step
-    // before, as split_gemm_kernel does, takes 24 more registers and spills)
+    // before, as split_gemm_kernel does, takes 24 more registers; the 192-row tiles already spill 18 to 98, most of them
+    // outside the steps, the others none)
     using Step = MmaStep<NP, TM, TN, TM >= 3 ? 1 : 2>;
     for (int grp = 0; grp < ngrp; ++grp) {
         const int ns = steps_of(grp);
@@ -461,8 +462,7 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
         const int64_t sl = slots(n0, (n0 + 127 < P - 1) ? n0 + 127 : P - 1);
         if (sl > amax) amax = sl;
     }
-    // six chunks (planes 56 wide with a 3x3 window: four pixel rows, 348 slots) leave room for 128-row
-    // tiles with a three-stage filter ring
+    // (six chunks: planes 56 wide with a 3x3 window, four pixel rows, 348 slots)
     if (amax > 6 * 64) return false;
     g.nsl = amax > 5 * 64 ? 6 : 5;
     g.tiles_per_img = (int32_t)((P + 127) / 128);

@@ -353,7 +353,7 @@ bool band_plan(BandGeom &g, uint32_t M, uint32_t N, uint32_t groups, const Split
     if (g.x_elems * 4 > kMaxBufferBytes || g.dy_elems * 4 > kMaxBufferBytes) return false;
     g.Wp = (g.OW - 1) * g.s + g.KW;
     // Row tile: the least padding, the taller one where equal.  Padded slots a unit may fill: 512 beside 128
-    // rows, 256 beside the others (192 rows: the raw values of 512 slots in flight spill; 64 rows: a block's
+    // rows, 256 beside the others (192 rows: the raw values of 512 slots in flight would spill, those of 256 spill 9; 64 rows: a block's
     // steps are short, and so should be the wait for its patch).  256 images of 13x13, us with 512 / 256:
     // 384 rows x 256 channels in tiles of 192 435 / 415, of 128 421 / 442; 192 rows in one tile 362 / 326.
     g.mt = M <= 64 ? 64 : (M + 191) / 192 * 192 <= (M + 127) / 128 * 128 ? 192 : 128;

@@ -13,7 +13,7 @@ def main():
     rows = [r for r in csv.DictReader(open(src)) if "cg::" in r["Name"]]
     total = sum(int(r["TotalDurationNs"]) for r in rows)
     with open(out, "w") as f:
-        f.write(f"# {title}\n# command (from the repository root on the MI355X box):\n#   {cmd}\n")
+        f.write(f"# {title}\n# command (from the repository root, on an MI355X):\n#   {cmd}\n")
         f.write("# source: rocprofv3's <prefix>_kernel_stats.csv; the library's kernels only (torch's fill / random-number\n")
         f.write("# kernels of the input set-up omitted); % is of the listed kernels' total time\n")
         f.write(f"{'kernel':96s} {'calls':>6s} {'total_ms':>10s} {'avg_us':>10s} {'min_us':>9s} {'max_us':>9s} {'%':>6s}\n")

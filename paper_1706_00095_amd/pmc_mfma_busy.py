@@ -10,7 +10,8 @@ Per kernel label (the labels of pmc_traffic.py), over the matrix-core launches o
             which a compute unit has a wave (the rest: rounds of blocks that do not fill the chip, start-up);
   mfma    = SQ_VALU_MFMA_BUSY_CYCLES / (4 x SQ_BUSY_CU_CYCLES): share of that time in which the matrix
             pipeline of a SIMD is executing;
-  product = mfma busy over the whole duration, to compare with the launch's TFLOP/s over the 157.3 peak.
+  product = mfma busy over the whole duration, to compare with the launch's TFLOP/s over its peak (157.3 for the
+            fp32 instruction; a sixth of the dense bf16 rate where fp32 operands are cut in three bf16 pieces).
 """
 import collections
 import csv
@@ -27,7 +28,7 @@ def main():
     per = collections.defaultdict(dict)
     name = {}
     for r in csv.DictReader(open(counters)):
-        if "cg::igemm" not in r["Kernel_Name"]:
+        if "cg::igemm" not in r["Kernel_Name"] and "cg::split_" not in r["Kernel_Name"]:
             continue
         per[r["Dispatch_Id"]][r["Counter_Name"]] = float(r["Counter_Value"])
         name[r["Dispatch_Id"]] = label(r["Kernel_Name"])
@@ -39,7 +40,7 @@ def main():
         a[0] += 1; a[1] += dur[did]; a[2] += c["SQ_BUSY_CU_CYCLES"]; a[3] += c["SQ_VALU_MFMA_BUSY_CYCLES"]
     with open(out, "w") as f:
         f.write("# Matrix-pipeline occupancy of the matrix-core kernels (hardware counters, one run)\n")
-        f.write("# command (from the repository root on the MI355X box):\n")
+        f.write("# command (from the repository root, on an MI355X):\n")
         f.write("#   rocprofv3 --pmc SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES --kernel-trace --output-format csv "
                 f"-d gpurun_out/pmc_m -o m -- python3 bench.py {args}\n")
         f.write("#   python3 paper_1706_00095_amd/pmc_mfma_busy.py <counter csv> <kernel trace csv> <this file> '<args>'\n")

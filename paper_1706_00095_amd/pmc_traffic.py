@@ -28,15 +28,22 @@ COPY_BYTES = 256 << 20
 
 def label(name):
     name = name.replace("(anonymous namespace)::", "").replace("void ", "")
-    math = {"0": "", "1": ",bf16", "2": ",bf16x3"}      # last template argument of the two big kernels: the arithmetic
-    m = re.match(r"cg::igemm_patch_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (\d+), (\d)>", name)
+    math = {"0": "", "1": ",bf16", "2": ",bf16x3"}      # last template argument of the gathered kernel: the arithmetic
+    pieces = {3: "", 2: ",bf16x3", 1: ",bf16"}          # first template argument of the kernels that cut operands
+    m = re.match(r"cg::split_patch_kernel<(\d+), (\d+), (\d+), (\d+), (\d+)>", name)
     if m:
-        wm, _, tm, _, _, nsl = map(int, m.groups()[:6])
-        return f"igemm_patch_kernel<{wm * tm * 32}x128,{nsl}{math[m.group(7)]}>"
-    m = re.match(r"cg::igemm_patch16_kernel<(\d+), (\d+), (\d+)>", name)
+        np_, tm, wm, wk, nsl = map(int, m.groups())
+        return f"igemm_patch{'16' if wk == 2 else ''}_kernel<{wm * tm * 16}x128,{nsl}{pieces[np_]}>"
+    m = re.match(r"cg::split_wgrad_kernel<(\d+), (\d+), (\d+)>", name)
     if m:
-        tm, _, nsl = map(int, m.groups())
-        return f"igemm_patch16_kernel<{tm * 16}x128,{nsl}>"
+        np_, tm, nsl = map(int, m.groups())
+        return f"igemm_kernel<{64 * tm}x144,band{nsl}{pieces[np_]}>"
+    m = re.match(r"cg::split_gemm_kernel<(\d+), (\d+), (\d+), cg::LoadA<\d+, (\d)>, cg::(\w+)<\d+(?:, (\w+))?", name)
+    if m:
+        np_, tm, wm = (int(m.group(i)) for i in (1, 2, 3))
+        code = {"LoadBK": "4", "LoadBRows": "r"}[m.group(5)]
+        return (f"igemm_kernel<{wm * tm * 16}x128,{'4' if m.group(4) == '1' else 'r'}{code}"
+                f"{'c' if m.group(6) == 'true' else '-'},pieces{pieces[np_]}>")
     m = re.match(r"cg::igemm_wgrad_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (\d+), (\d+)>", name)
     if m:
         wm, _, tm, _, _, cpb, nsl = map(int, m.groups())
@@ -96,7 +103,7 @@ def main():
               open(out_json, "w"), indent=1)
     with open(out_txt, "w") as o:
         o.write("# HBM traffic per kernel launch (bytes fetched from / written to memory behind L2), mean over the launches of a label\n")
-        o.write("# commands (from the repository root on the MI355X box), one counter per run:\n")
+        o.write("# commands (from the repository root, on an MI355X), one counter per run:\n")
         o.write(f"#   rocprofv3 --pmc FETCH_SIZE --kernel-trace --output-format csv -d {os.path.dirname(fpath)} -o f -- python3 bench.py {args}\n")
         o.write(f"#   rocprofv3 --pmc WRITE_SIZE --kernel-trace --output-format csv -d {os.path.dirname(wpath)} -o w -- python3 bench.py {args}\n")
         o.write(f"#   python3 paper_1706_00095_amd/pmc_traffic.py {fpath} {wpath} <json> <txt> '<args>'\n")
