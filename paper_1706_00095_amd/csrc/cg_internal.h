@@ -173,6 +173,10 @@ struct BandGeom {
     FastDiv divSS, divWp, divP8, divOW, divKW, divNB;       // slots of an image's band; octets of its pixels
 };
 
+// A small convolution's bias gradient (db[m] = sum of dy over images and pixels), summed by extra blocks of
+// another launch, one block per channel, instead of a launch of its own.
+struct BiasRider { const float *dy; int N, M, P; float *db; };
+
 // C[m][n] = sum_k A(m,k) * B(n,k)   (+ bias), for `groups` independent problems, the K range
 // optionally cut into `splits` slices whose partial results go to consecutive output planes.
 struct IgemmProblem {
@@ -201,6 +205,8 @@ struct IgemmProblem {
     int math;                 // CG_MATH_FP32, CG_MATH_BF16 or CG_MATH_BF16X3: what the matrix instructions multiply in
     int mt;                   // row-tile height igemm_run has planned the K slices for (0: igemm_launch chooses)
     int pieces;               // operands in bf16 pieces (split_gemm_kernel) instead of the gathered kernel
+    int direct;               // waves of direct_kernel's blocks (direct_choice), 0 = another kernel
+    BiasRider rider;          // direct_kernel: a bias gradient that rides in the launch (dy NULL: none)
     int beside_other_stream;  // the caller runs matrix kernels on another stream meanwhile (tile choice of the patch kernel)
     // at most one of the three is set, and names the geometry in use
     int use_patch;            // B is described by `patch` (and A is the matching tap-major matrix); B unused
@@ -228,6 +234,14 @@ void patch_set_min_tiles(uint32_t t);
 int split_patch_launch(const IgemmProblem &p, hipStream_t stream);      // problems with a patch (igemm_launch dispatches)
 int split_wgrad_launch(const IgemmProblem &p, hipStream_t stream);      // use_band (igemm_launch dispatches)
 int split_wgrad_3(const IgemmProblem &p, hipStream_t stream);
+// direct_kernel: how many waves a problem gets (0: the gathered kernel, whose plan is `other`, is expected to be faster;
+// other NULL: there is none, and the answer is never 0 unless the kernel cannot run it), its launch
+int direct_launch(const IgemmProblem &p, bool a_quads, hipStream_t stream);
+// What igemm_run would refuse the scratch memory of a gathered problem for.
+int igemm_scratch_check(const IgemmProblem &p, const void *ws, size_t ws_bytes);
+// Sets p.direct if direct_kernel runs p faster than the other kernels run `other`, the same sums from operands laid out
+// for those (NULL: p itself).
+bool igemm_take_direct(IgemmProblem &p, const IgemmProblem *other = nullptr);
 uint32_t igemm_resident_blocks();
 int igemm_launch(const IgemmProblem &p, hipStream_t stream);
 // igemm_kernel (gather.hip) in fp32, bf16, bf16x3 (igemm_launch dispatches).  am, bm: how an operand's elements are
@@ -258,11 +272,10 @@ SplitPlan gathered_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
 // Fills the derived fields and chooses units, tile and K slices; false where the kernel does not apply or the gathered
 // kernel (whose plan for the M x N x K problem is `other`) is expected to be faster in this arithmetic.
 bool band_plan(BandGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other, int math, uint32_t *splits);
+int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, bool other_copies);
 size_t igemm_ws_bytes(const IgemmProblem &p);
-// rider: a small convolution's bias gradient (db[m] = sum of dy over images and pixels), summed by
-// extra blocks of the K-slice finishing launch, one block per channel, instead of a launch of its
-// own; *rider_taken says whether that happened (it does not when the problem runs without K slices).
-struct BiasRider { const float *dy; int N, M, P; float *db; };
+// rider: a bias gradient that may ride in the K-slice finishing launch or in direct_kernel's; *rider_taken says
+// whether that happened (it does not when a matrix kernel without either runs the problem).
 int igemm_run(const IgemmProblem &p, void *ws, size_t ws_bytes, hipStream_t stream, const BiasRider *rider = nullptr,
               bool *rider_taken = nullptr);
 // db[m] = sum over n and pixels of dy[n][m][pix]; two passes over `ws`, fixed order
@@ -296,7 +309,7 @@ struct FilterPrep {
     int Mg, Cg, KH, KW, sh, sw, Ah, Aw;
 };
 FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d);
-FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d);
+FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math);
 size_t conv_filter_prep_max_floats(const cg_conv_desc &d);      // upper bound of either copy, for sizing
 // n copies, eight per launch: job i reads w[i] and writes dst[i] (16-byte aligned, jobs[i].floats floats)
 int filter_prep_launch(int n, const FilterPrep *jobs, const float *const *w, float *const *dst, hipStream_t stream);

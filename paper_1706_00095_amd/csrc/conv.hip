@@ -193,102 +193,6 @@ __global__ __launch_bounds__(256) void bwd_data_strided_kernel(const cg_conv_des
     }
 }
 
-// Backward-data for strides > 1, by stride phase.  The input pixels with (ih mod s_h, iw mod s_w) =
-// (rh, rw) all see the same filter taps, kh = kh0 + s_h*a and kw = kw0 + s_w*b, and reach dy at
-// oh = ih' + qh - a, ow = iw' + qw - b for ih = s_h*ih' + rh: a stride-1 correlation of dy with the
-// sub-sampled filter.  A block owns one phase, 16 x 16 of its pixels, one image and CT input
-// channels of one group; it walks the group's output channels 16 at a time, with the dy window of
-// the tile (zeros outside dy) and the phase's taps of the 16 filters (zeros for taps a phase does
-// not have) staged in LDS, and every thread accumulates its pixel for the CT channels over a fixed
-// AM x AM sweep, AM = the most taps per dimension any phase has.
-// Made for few input channels per group (the first layer of a net: 3), where a matrix-core tile
-// would multiply mostly padding; more channels take several blocks, each re-reading dy.  Plain
-// vector arithmetic: about a third of the issued instructions are useful multiply-adds (the 11x11
-// stride-4 layer at B = 256: 4.9 ms, 11 TFLOP/s; variants that shared the dy window between the
-// phases of a block were slower, this kernel is bound by instruction issue, not by memory).
-constexpr int PH_T = 16;          // tile edge in phase pixels
-constexpr int PH_MC = 16;         // output channels per LDS stage
-
-template <int CT, int AM>
-__global__ __launch_bounds__(256) void bwd_data_phase_kernel(const cg_conv_desc d, int OH, int OW,
-                                                             const float *__restrict__ dy,
-                                                             const float *__restrict__ w, float *__restrict__ dx,
-                                                             const float *__restrict__ gate, int accumulate, int tiles_x,
-                                                             int chunks)
-{
-    constexpr int WT = PH_T + AM - 1, TAPS = AM * AM, TP = (TAPS + 3) / 4 * 4;
-    __shared__ float dys[PH_MC * WT * WT];
-    __shared__ __align__(16) float wsm[PH_MC * CT * TP];
-    const int Cg = d.C / d.groups, Mg = d.M / d.groups, KK = d.KH * d.KW;
-    const int tile_y = blockIdx.x / tiles_x, tile_x = blockIdx.x % tiles_x;
-    const int rh = blockIdx.y / d.stride_w, rw = blockIdx.y % d.stride_w;
-    int z = blockIdx.z;
-    const int chunk = z % chunks; z /= chunks;
-    const int g = z % d.groups, n = z / d.groups;
-    const int c0 = chunk * CT;
-    // taps and dy displacement of this phase
-    const int kh0 = (rh + d.pad_h) % d.stride_h, kw0 = (rw + d.pad_w) % d.stride_w;
-    const int qh = (rh + d.pad_h) / d.stride_h, qw = (rw + d.pad_w) / d.stride_w;
-    const int ty = threadIdx.x / PH_T, tx = threadIdx.x % PH_T;
-    const int oh_base = tile_y * PH_T + qh - (AM - 1), ow_base = tile_x * PH_T + qw - (AM - 1);
-    float acc[CT];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) acc[c] = 0.f;
-    for (int m0 = 0; m0 < Mg; m0 += PH_MC) {
-        const int mc = min(PH_MC, Mg - m0);
-        __syncthreads();
-        for (int i = threadIdx.x; i < PH_MC * WT * WT; i += 256) {
-            const int ml = i / (WT * WT), r = i - ml * (WT * WT), wy = r / WT, wx = r - wy * WT;
-            const int oh = oh_base + wy, ow = ow_base + wx;
-            float v = 0.f;
-            if (ml < mc && (unsigned)oh < (unsigned)OH && (unsigned)ow < (unsigned)OW)
-                v = dy[(((size_t)n * d.M + g * Mg + m0 + ml) * OH + oh) * OW + ow];
-            dys[i] = v;
-        }
-        for (int i = threadIdx.x; i < PH_MC * CT * TP; i += 256) {
-            const int ml = i / (CT * TP), r = i - ml * (CT * TP), c = r / TP, t = r - c * TP;
-            const int kh = kh0 + (t / AM) * d.stride_h, kw = kw0 + (t % AM) * d.stride_w;
-            float v = 0.f;
-            if (ml < mc && c0 + c < Cg && t < TAPS && kh < d.KH && kw < d.KW)
-                v = w[((size_t)(g * Mg + m0 + ml) * Cg + c0 + c) * KK + kh * d.KW + kw];
-            wsm[i] = v;
-        }
-        __syncthreads();
-#pragma unroll 2
-        for (int ml = 0; ml < PH_MC; ++ml) {          // channels beyond mc are staged as zeros
-            const float *dp = dys + ml * (WT * WT) + (ty + AM - 1) * WT + (tx + AM - 1);
-            float v[TP];
-#pragma unroll
-            for (int t = 0; t < TP; ++t)              // a tap the phase does not have reads nothing (its weight is 0)
-                v[t] = (t < TAPS && kh0 + (t / AM) * d.stride_h < d.KH && kw0 + (t % AM) * d.stride_w < d.KW)
-                           ? dp[-(t / AM) * WT - (t % AM)] : 0.f;
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                const float4 *wq = reinterpret_cast<const float4 *>(wsm + (ml * CT + c) * TP);
-#pragma unroll
-                for (int t4 = 0; t4 < TP / 4; ++t4) {
-                    const float4 q = wq[t4];
-                    acc[c] += v[4 * t4] * q.x;
-                    acc[c] += v[4 * t4 + 1] * q.y;
-                    acc[c] += v[4 * t4 + 2] * q.z;
-                    acc[c] += v[4 * t4 + 3] * q.w;
-                }
-            }
-        }
-    }
-    const int ih = (tile_y * PH_T + ty) * d.stride_h + rh, iw = (tile_x * PH_T + tx) * d.stride_w + rw;
-    if (ih < d.H && iw < d.W) {
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            if (c0 + c >= Cg) continue;
-            const size_t i = (((size_t)n * d.C + g * Cg + c0 + c) * d.H + ih) * d.W + iw;
-            float v = acc[c];
-            if (gate && !(gate[i] > 0.f)) v = 0.f;
-            dx[i] = accumulate ? dx[i] + v : v;
-        }
-    }
-}
-
 }  // namespace
 
 int conv_check(const cg_conv_desc *d, int *OH, int *OW)
@@ -483,6 +387,17 @@ static IgemmProblem bwd_data_problem(const cg_conv_desc &d, int OH, int OW, cons
     return p;
 }
 
+// The same for direct_kernel, which reads the filters where they are: A(c, (m, kh, kw)) = w[m][c][kh][kw].
+static IgemmProblem bwd_data_direct_problem(const cg_conv_desc &d, int OH, int OW, const float *dy, const float *w, float *dx, int accumulate)
+{
+    const int Cg = d.C / d.groups, Mg = d.M / d.groups, KK = d.KH * d.KW;
+    IgemmProblem p = bwd_data_problem(d, OH, OW, dy, w, dx, accumulate);
+    p.A.row = linear_map((uint32_t)Cg, KK);
+    p.A.k = split_map((uint32_t)Mg * KK, KK, Cg * KK, 1);
+    p.A.lanes_k = 0;
+    return p;
+}
+
 // Backward-data of a convolution with stride (sh, sw) > 1 as ONE stride-1 problem on the matrix
 // cores.  Write an input row as ih + ph = sh*i + rh (cell i, phase rh < sh).  Only the taps
 // kh = rh + sh*a reach it, from output row oh = i - a, so
@@ -495,14 +410,14 @@ static IgemmProblem bwd_data_problem(const cg_conv_desc &d, int OH, int OW, cons
 // stride 4) becomes 48 rows x 864 reduction indices, of which 121/144 multiply a real tap.
 struct StridedGeom { int sh, sw, Ah, Aw, Ch, Cw, R, Kp; uint32_t Np; };
 
-static bool strided_geom(const cg_conv_desc &d, StridedGeom &s)
+static bool strided_geom(const cg_conv_desc &d, StridedGeom &s, int min_rows = 8)
 {
     s.sh = d.stride_h; s.sw = d.stride_w;
     s.Ah = (d.KH + s.sh - 1) / s.sh; s.Aw = (d.KW + s.sw - 1) / s.sw;
     s.Ch = (d.H - 1 + d.pad_h) / s.sh + 1; s.Cw = (d.W - 1 + d.pad_w) / s.sw + 1;
     const int64_t R = (int64_t)(d.C / d.groups) * s.sh * s.sw, Kp = (int64_t)(d.M / d.groups) * s.Ah * s.Aw;
     const int64_t Np = (int64_t)d.N * s.Ch * s.Cw;
-    if (R < 8 || R >= (1 << 20) || Kp >= (1 << 28) || Np >= (1ll << 30) || R * Kp * d.groups >= (1ll << 29)) return false;
+    if (R < min_rows || R >= (1 << 20) || Kp >= (1 << 28) || Np >= (1ll << 30) || R * Kp * d.groups >= (1ll << 29)) return false;
     s.R = (int)R; s.Kp = (int)Kp; s.Np = (uint32_t)Np;
     return true;
 }
@@ -564,6 +479,32 @@ static IgemmProblem bwd_data_strided_problem(const cg_conv_desc &d, const Stride
     return p;
 }
 
+// The same for direct_kernel: A((c, rh, rw), (m, a, b)) = w[m][c][rh + sh*a][rw + sw*b], nothing beyond the window.
+static IgemmProblem bwd_data_strided_direct_problem(const cg_conv_desc &d, const StridedGeom &sg, int OH, int OW, const float *dy,
+                                                    const float *w, float *dx, int accumulate)
+{
+    const int Cg = d.C / d.groups, Mg = d.M / d.groups, KK = d.KH * d.KW;
+    IgemmProblem p = bwd_data_strided_problem(d, sg, OH, OW, dy, w, dx, accumulate);
+    p.A.row = IndexMap{};
+    p.A.row.count = (uint32_t)sg.R;
+    p.A.row.d1 = make_fastdiv((uint32_t)sg.sh * sg.sw);
+    p.A.row.d2 = make_fastdiv((uint32_t)sg.sw);
+    p.A.row.s1 = KK; p.A.row.s2 = d.KW; p.A.row.s3 = 1;
+    p.A.row.sa = 1; p.A.row.sb = 1;
+    p.A.k = IndexMap{};
+    p.A.k.count = (uint32_t)sg.Kp;
+    p.A.k.d1 = make_fastdiv((uint32_t)sg.Ah * sg.Aw);
+    p.A.k.d2 = make_fastdiv((uint32_t)sg.Aw);
+    p.A.k.s1 = Cg * KK; p.A.k.s2 = sg.sh * d.KW; p.A.k.s3 = sg.sw;
+    p.A.k.sa = sg.sh; p.A.k.sb = sg.sw;
+    p.A.limA = d.KH; p.A.limB = d.KW;
+    p.A.check = 1;
+    p.A.gstride = (int64_t)Mg * Cg * KK;
+    p.A.elems = (uint64_t)d.M * Cg * KK;
+    p.A.lanes_k = 0;
+    return p;
+}
+
 // dy as the patch operand of that problem: cells are the pixels, the taps are mirrored
 static bool bwd_data_strided_patch(const cg_conv_desc &d, const StridedGeom &sg, int OH, int OW, const float *dy,
                                    IgemmProblem &p)
@@ -611,6 +552,15 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         p.gate = gate;
         p.math = math;
         const bool patch = bwd_data_strided_patch(d, sg, OH, OW, dy, p);
+        if (!patch) {
+            IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
+            pd.gate = gate;
+            pd.math = math;
+            if (igemm_take_direct(pd, &p)) {
+                const int rs = igemm_scratch_check(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes);
+                return rs ? rs : igemm_launch(pd, stream);
+            }
+        }
         if (!prepared) {
             const int rc2 = strided_filters(w, wt, d, sg, patch ? 1 : 0, stream);
             if (rc2) return rc2;
@@ -619,35 +569,15 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
     }
     if ((d.stride_h != 1 || d.stride_w != 1) && math != CG_MATH_FP32) return CG_EUNSUPPORTED;   // plain vector arithmetic below
     if (d.stride_h != 1 || d.stride_w != 1) {
-        // few rows (channels x phases): by stride phase, for at most four taps per dimension and phase
-        const int Cg = d.C / d.groups;
-        const int Ahm = (d.KH + d.stride_h - 1) / d.stride_h, Awm = (d.KW + d.stride_w - 1) / d.stride_w;
-        const int am = Ahm > Awm ? Ahm : Awm;
-        const int th = ((d.H + d.stride_h - 1) / d.stride_h + PH_T - 1) / PH_T;
-        const int tw = ((d.W + d.stride_w - 1) / d.stride_w + PH_T - 1) / PH_T;
-        const int ct = Cg >= 4 ? 4 : Cg;
-        const int chunks = (Cg + ct - 1) / ct;
-        const uint64_t gz = (uint64_t)d.N * d.groups * chunks;
-        if (am <= 4 && d.stride_h * d.stride_w <= 65535 && gz <= 65535) {
-            const dim3 grid((unsigned)(th * tw), (unsigned)(d.stride_h * d.stride_w), (unsigned)gz);
-#define CG_PHASE(CT_, AM_)                                                                                            \
-    hipLaunchKernelGGL((bwd_data_phase_kernel<CT_, AM_>), grid, dim3(256), 0, stream, d, OH, OW, dy, w, dx, gate,      \
-                       accumulate, tw, chunks)
-#define CG_PHASE_AM(CT_)                                                                                              \
-    do {                                                                                                              \
-        if (am == 1) CG_PHASE(CT_, 1);                                                                                \
-        else if (am == 2) CG_PHASE(CT_, 2);                                                                           \
-        else if (am == 3) CG_PHASE(CT_, 3);                                                                           \
-        else CG_PHASE(CT_, 4);                                                                                        \
-    } while (0)
-            if (ct == 4) CG_PHASE_AM(4);
-            else if (ct == 3) CG_PHASE_AM(3);
-            else if (ct == 2) CG_PHASE_AM(2);
-            else CG_PHASE_AM(1);
-#undef CG_PHASE_AM
-#undef CG_PHASE
-            CG_HIP_TRY(hipGetLastError());
-            return CG_OK;
+        // Fewer than eight (channel, phase) rows: direct_kernel (B = 16, 86x95, 504 -> 1 channels, 3x3 stride 2: 51 us; plain
+        // vector code by stride phase took 290), but for dimensions its index maps do not cover
+        if (strided_geom(d, sg, 1)) {
+            IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
+            pd.gate = gate;
+            if ((pd.direct = direct_choice(pd, false, nullptr, false)) != 0) {
+                const int rc2 = igemm_launch(pd, stream);
+                if (rc2 != CG_EUNSUPPORTED) return rc2;
+            }
         }
         const size_t total = (size_t)d.N * d.C * d.H * d.W;
         const unsigned blocks = (unsigned)((total + 255) / 256 < 65536 ? (total + 255) / 256 : 65536);
@@ -677,15 +607,24 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         }
     }
     const bool in_place = bwd_data_reads_filters_in_place(d);
+    IgemmProblem p = bwd_data_problem(d, OH, OW, dy, in_place ? w : wuse, dx, accumulate);
+    p.gate = gate;
+    p.math = math;
+    if (!in_place) {
+        IgemmProblem pd = bwd_data_direct_problem(d, OH, OW, dy, w, dx, accumulate);
+        pd.gate = gate;
+        pd.math = math;
+        if (igemm_take_direct(pd, &p)) {
+            const int rs = igemm_scratch_check(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes);
+            return rs ? rs : igemm_launch(pd, stream);
+        }
+    }
     if (!in_place && !prepared) {
         const size_t total = (size_t)d.M * Cg * KK;
         const unsigned blocks = (unsigned)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
         hipLaunchKernelGGL(transpose_filters_kernel, dim3(blocks), dim3(256), 0, stream, w, wt, G, Mg, Cg, KK);
         CG_HIP_TRY(hipGetLastError());
     }
-    IgemmProblem p = bwd_data_problem(d, OH, OW, dy, in_place ? w : wuse, dx, accumulate);
-    p.gate = gate;
-    p.math = math;
     return igemm_run(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
 }
 
@@ -702,7 +641,7 @@ FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d)
     return f;
 }
 
-FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d)
+FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math)
 {
     FilterPrep f{};
     int OH, OW;
@@ -711,7 +650,11 @@ FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d)
     StridedGeom sg;
     if ((d.stride_h != 1 || d.stride_w != 1) && strided_geom(d, sg)) {
         IgemmProblem p = bwd_data_strided_problem(d, sg, OH, OW, nullptr, nullptr, nullptr, 0);
-        f.kind = bwd_data_strided_patch(d, sg, OH, OW, nullptr, p) ? CG_PREP_STRIDED_TAPS : CG_PREP_STRIDED_ROWS;
+        const bool patch = bwd_data_strided_patch(d, sg, OH, OW, nullptr, p);
+        IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, nullptr, nullptr, nullptr, 0);
+        p.math = pd.math = math;
+        if (!patch && igemm_take_direct(pd, &p)) return f;
+        f.kind = patch ? CG_PREP_STRIDED_TAPS : CG_PREP_STRIDED_ROWS;
         f.sh = sg.sh; f.sw = sg.sw; f.Ah = sg.Ah; f.Aw = sg.Aw;
         f.floats = (size_t)d.groups * sg.R * sg.Kp;
         return f;
@@ -719,8 +662,12 @@ FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d)
     if (d.stride_h != 1 || d.stride_w != 1) return f;            // the vector kernels read w itself
     IgemmProblem pp = bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
     if (bwd_data_patch(d, OH, OW, nullptr, pp)) f.kind = CG_PREP_PERMUTE_BWD;
-    else if (!bwd_data_reads_filters_in_place(d)) f.kind = CG_PREP_TRANSPOSE;
-    else return f;
+    else if (!bwd_data_reads_filters_in_place(d)) {
+        IgemmProblem pd = bwd_data_direct_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
+        pp.math = pd.math = math;
+        if (igemm_take_direct(pd, &pp)) return f;
+        f.kind = CG_PREP_TRANSPOSE;
+    } else return f;
     f.floats = (size_t)d.M * f.Cg * d.KH * d.KW;
     return f;
 }

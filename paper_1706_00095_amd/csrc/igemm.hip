@@ -217,7 +217,7 @@ int igemm_launch(const IgemmProblem &p0, hipStream_t stream)
     if (p.splits > 1 && (p.k_per_split % KT != 0)) return CG_EINVAL;
     if ((uint64_t)p.k_per_split * p.splits < p.K || (uint64_t)p.k_per_split * (p.splits - 1) >= p.K) return CG_EINVAL;
     if (p.bias_mode && !p.bias) return CG_EINVAL;
-    if (p.A.check) return CG_EUNSUPPORTED;
+    if (p.A.check && !p.direct) return CG_EUNSUPPORTED;
     p.A.shift = p.B.shift = 0;
     int rc = normalise_operand(p.A, p.groups);
     if (rc) return rc;
@@ -227,6 +227,7 @@ int igemm_launch(const IgemmProblem &p0, hipStream_t stream)
     if (!p.A.check) { p.A.limA = p.A.limB = 1; }
     if (!p.B.check) { p.B.limA = p.B.limB = 1; }
 
+    if (p.direct) return direct_launch(p, quad_ok(p.A, p.K), stream);
     const int mt = p.mt ? p.mt : pick_mt(p.M, p.N, p.groups, p.K);
     // how an operand's elements are fetched: 0 rows along the lanes, 1 k along the lanes, 2 aligned quads of k
     const int am = quad_ok(p.A, p.K) ? 2 : p.A.lanes_k ? 1 : 0;
@@ -278,47 +279,6 @@ struct FinishArgs {
     uint32_t finish_blocks;
 };
 
-typedef float f4u_b __attribute__((ext_vector_type(4), aligned(4)));
-
-// Sum of dy[n][m][0..P) over the images n_beg..n_end-1, by one block; thread 0 returns it.
-// The (image, group of four pixels) pairs are spread over the threads, each moving 16 bytes
-// (4-byte aligned: planes of an odd pixel count start anywhere) with four loads in flight.
-__device__ __forceinline__ float bias_channel_sum(const float *__restrict__ dy, int M, int P, int m, int n_beg, int n_end,
-                                                  FastDiv divQP)
-{
-    const uint32_t QP = divQP.d, total = (uint32_t)(n_end - n_beg) * QP;
-    float s = 0.f;
-    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += 256 * 4) {
-        f4u_b v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t i = i0 + u * 256;
-            v[u] = f4u_b{0.f, 0.f, 0.f, 0.f};
-            if (i < total) {
-                const uint32_t n = fdiv(i, divQP), qd = i - n * QP;
-                const float *src = dy + ((size_t)(n_beg + (int)n) * M + m) * P + 4 * qd;
-                const int rem = P - 4 * (int)qd;
-                if (rem >= 4) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f4u_b *>(src));
-                else {
-                    v[u].x = src[0];
-                    if (rem > 1) v[u].y = src[1];
-                    if (rem > 2) v[u].z = src[2];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) s += (v[u].x + v[u].y) + (v[u].z + v[u].w);
-    }
-    __shared__ float red[256];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    return red[0];
-}
-
 // C = (sum over the K slices) + bias, written through the problem's output map.  With few slices a
 // thread adds them in slice order.  With many (ROWS = 8) a block owns 32 consecutive elements, its
 // 8 thread rows add interleaved slices (row r: slices r, r+8, ...), and the 8 row sums are added
@@ -327,22 +287,8 @@ __device__ __forceinline__ float bias_channel_sum(const float *__restrict__ dy, 
 __device__ __forceinline__ void finish_store(const FinishArgs &a, uint32_t i, float s)
 {
     const uint32_t g = fdiv(i, a.divMN), rem = i - g * a.divMN.d;
-    const uint32_t m = fdiv(rem, a.divN), n = rem - m * a.divN.d;
-    if (a.bias_mode == 1) s += a.bias[(int64_t)g * a.bias_gstride + m];
-    else if (a.bias_mode == 2) s += a.bias[(int64_t)g * a.bias_gstride + n];
-    if (a.relu) s = fmaxf(s, 0.f);
-    const Info ci = map_info(a.c_col, n);
-    int32_t in_group = (int32_t)m * a.c_row_stride + ci.off;
-    if (a.c_scatter) {
-        const Info ri = map_info(a.c_row, m);
-        if (!((uint32_t)(ri.a + ci.a) < a.c_limA && (uint32_t)(ri.b + ci.b) < a.c_limB)) return;
-        in_group = ri.off + ci.off;
-    }
-    const int64_t idx = (int64_t)g * a.c_gstride + in_group;
-    if (a.gate && !(a.gate[idx] > 0.f)) s = 0.f;
-    float *dst = a.c_ptr + idx;
-    if (a.accumulate) s += *dst;
-    *dst = s;
+    const uint32_t m = fdiv(rem, a.divN);
+    store_element(a, g, m, rem - m * a.divN.d, s);
 }
 
 // AHEAD: a thread's next eight loads are in flight together (under a condition each, where fewer are left).  It pays
@@ -353,7 +299,8 @@ template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_fi
 {
     if (a.r_dy && blockIdx.x >= a.finish_blocks) {       // a rider block: one channel of the bias gradient
         const int m = (int)(blockIdx.x - a.finish_blocks);
-        const float s = bias_channel_sum(a.r_dy, a.rM, a.rP, m, 0, a.rN, a.r_divQP);
+        __shared__ float red[256];
+        const float s = bias_channel_sum(a.r_dy, a.rM, a.rP, m, 0, a.rN, a.r_divQP, red);
         if (threadIdx.x == 0) a.r_db[m] = s;
         return;
     }
@@ -464,9 +411,41 @@ size_t igemm_ws_bytes(const IgemmProblem &p)
     return gathered_plan(p.M, p.N, p.K, p.groups).ws_bytes;
 }
 
+bool igemm_take_direct(IgemmProblem &p, const IgemmProblem *other)
+{
+    const IgemmProblem &o = other ? *other : p;
+    p.direct = 0;
+    // (what split_gemm_kernel runs is added up from short sums of exact products: closer to 64 bits than the fp32 instruction)
+    if (p.math != CG_MATH_FP32 || pieces_mt(o)) return false;
+    const SplitPlan pl = plan_split(o);
+    p.direct = direct_choice(p, quad_ok(p.A, p.K), &pl, o.A.lanes_k && !p.A.lanes_k);
+    return p.direct != 0;
+}
+
+int igemm_scratch_check(const IgemmProblem &p, const void *ws, size_t ws_bytes)
+{
+    const SplitPlan pl = plan_split(p);
+    if (pl.splits <= 1) return CG_OK;
+    if (!ws || ws_bytes < pl.ws_bytes) return CG_ENOSPC;
+    return aligned16(ws) ? CG_OK : CG_EINVAL;
+}
+
 int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t stream, const BiasRider *rider, bool *rider_taken)
 {
     if (rider_taken) *rider_taken = false;
+    const bool ride = rider && rider->dy && rider->db && rider->M > 0 && rider->M <= 65536 &&
+                      (uint64_t)rider->N * (uint64_t)((rider->P + 3) / 4) < (1ull << 31);
+    if (!p0.use_patch && !p0.use_wgrad && !p0.use_band) {
+        IgemmProblem p = p0;
+        if (igemm_take_direct(p)) {
+            const int rc = igemm_scratch_check(p0, ws, ws_bytes);        // a call is refused for the same reasons whichever kernel runs it
+            if (rc) return rc;
+            p.splits = 1; p.k_per_split = p.K;
+            if (ride) p.rider = *rider;
+            if (rider_taken) *rider_taken = ride;
+            return igemm_launch(p, stream);
+        }
+    }
     const SplitPlan pl = p0.use_patch   ? SplitPlan{1, p0.K, 0, 0, 0}
                          : p0.use_wgrad || p0.use_band ? SplitPlan{p0.splits, p0.K, (size_t)(p0.splits > 1 ? p0.splits : 0) * p0.groups * p0.M * p0.N * sizeof(float), 0, 0}
                                         : plan_split(p0);
@@ -502,8 +481,7 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
     a.accumulate = p0.accumulate; a.relu = p0.relu; a.gate = p0.gate;
     a.total = p0.groups * p0.M * p0.N;
     unsigned riders = 0;
-    if (rider && rider->dy && rider->db && rider->M > 0 && rider->M <= 65536 &&
-        (uint64_t)rider->N * (uint64_t)((rider->P + 3) / 4) < (1ull << 31)) {
+    if (ride) {
         a.r_dy = rider->dy; a.rN = rider->N; a.rM = rider->M; a.rP = rider->P; a.r_db = rider->db;
         a.r_divQP = make_fastdiv((uint32_t)(rider->P + 3) / 4);
         riders = (unsigned)rider->M;
@@ -531,14 +509,13 @@ namespace {
 // block (m, s) sums the samples of slice s; the slices are added afterwards in slice order.
 // The (image, group of four pixels) pairs of the slice are spread over the threads, each moving
 // 16 bytes (4-byte aligned: planes of an odd pixel count start anywhere) with four loads in flight.
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-
 __global__ __launch_bounds__(256) void bias_grad_partial_kernel(const float *__restrict__ dy, int N, int M, int P,
                                                                 int n_per, FastDiv divQP, float *__restrict__ part)
 {
     const int m = blockIdx.x, sl = blockIdx.y;
     const int n_beg = sl * n_per, n_end = min(N, n_beg + n_per);
-    const float s = bias_channel_sum(dy, M, P, m, n_beg, n_end, divQP);
+    __shared__ float red[256];
+    const float s = bias_channel_sum(dy, M, P, m, n_beg, n_end, divQP, red);
     if (threadIdx.x == 0) part[(size_t)sl * M + m] = s;
 }
 

@@ -307,5 +307,66 @@ __device__ __forceinline__ void store_columns(const IgemmProblem &p, const v4f (
     else store_columns_impl<TM, TN, false>(p, acc, g, sp, mw, nw, n_end, lane);
 }
 
+// One element of C by itself: bias, rectifier, gate, accumulation, the output map (P: IgemmProblem, or the arguments
+// of the kernel that adds the K slices).
+template <class P> __device__ __forceinline__ void store_element(const P &a, uint32_t g, uint32_t m, uint32_t n, float s)
+{
+    if (a.bias_mode == 1) s += a.bias[(int64_t)g * a.bias_gstride + m];
+    else if (a.bias_mode == 2) s += a.bias[(int64_t)g * a.bias_gstride + n];
+    if (a.relu) s = fmaxf(s, 0.f);
+    const Info ci = map_info(a.c_col, n);
+    int32_t in_group = (int32_t)m * a.c_row_stride + ci.off;
+    if (a.c_scatter) {
+        const Info ri = map_info(a.c_row, m);
+        if (!((uint32_t)(ri.a + ci.a) < a.c_limA && (uint32_t)(ri.b + ci.b) < a.c_limB)) return;
+        in_group = ri.off + ci.off;
+    }
+    const int64_t idx = (int64_t)g * a.c_gstride + in_group;
+    if (a.gate && !(a.gate[idx] > 0.f)) s = 0.f;
+    float *dst = a.c_ptr + idx;
+    if (a.accumulate) s += *dst;
+    *dst = s;
+}
+
+// Sum of dy[n][m][0..P) over the images n_beg..n_end-1, by one block (a power of two of threads, `red` a float each);
+// thread 0 returns it.
+// The (image, group of four pixels) pairs are spread over the threads, each moving 16 bytes
+// (4-byte aligned: planes of an odd pixel count start anywhere) with four loads in flight.
+__device__ __forceinline__ float bias_channel_sum(const float *__restrict__ dy, int M, int P, int m, int n_beg, int n_end,
+                                                  FastDiv divQP, float *red)
+{
+    const uint32_t QP = divQP.d, total = (uint32_t)(n_end - n_beg) * QP;
+    const uint32_t T = blockDim.x;
+    float s = 0.f;
+    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += T * 4) {
+        f4u v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t i = i0 + u * T;
+            v[u] = f4u{0.f, 0.f, 0.f, 0.f};
+            if (i < total) {
+                const uint32_t n = fdiv(i, divQP), qd = i - n * QP;
+                const float *src = dy + ((size_t)(n_beg + (int)n) * M + m) * P + 4 * qd;
+                const int rem = P - 4 * (int)qd;
+                if (rem >= 4) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f4u *>(src));
+                else {
+                    v[u].x = src[0];
+                    if (rem > 1) v[u].y = src[1];
+                    if (rem > 2) v[u].z = src[2];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += (v[u].x + v[u].y) + (v[u].z + v[u].w);
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = (int)T / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    return red[0];
+}
+
 }  // namespace
 }  // namespace cg

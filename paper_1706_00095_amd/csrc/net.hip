@@ -430,7 +430,7 @@ extern "C" int cg_train_step(cg_net *net, const float *x, const int32_t *labels,
             }
             const int s0 = ly.d.inputs[0];
             if (ly.needs_grad && s0 >= 0 && net->layers[s0].needs_grad) {
-                const FilterPrep b = conv_bwd_data_filter_prep(ly.conv);
+                const FilterPrep b = conv_bwd_data_filter_prep(ly.conv, math);
                 if (b.kind != CG_PREP_NONE) {
                     ly.prep_bd = base + ly.prep_bd_off;
                     jobs.push_back(b); jw.push_back(ly.w); jd.push_back(base + ly.prep_bd_off);
