@@ -114,7 +114,7 @@ struct Operand {
 
 // Operand B of a convolution seen as raw image patches instead of gathered im2col rows.  The N
 // rows of B are output pixels (img, oy, ox) of a grid OHo x OWo; the reduction index is
-// (tap t = ky*KW + kx, channel c), tap-major, with Cred % 16 == 0 channels per group; element
+// (tap t = ky*KW + kx, channel c), tap-major, with Cred channels per group (zeros up to the next multiple of 16); element
 // (pixel, t, c) is src[img][group*Cred + c][oy*s + oy0 + py(t)][ox*s + ox0 + px(t)] or zero outside
 // the Hs x Ws plane, where (py, px) = (ky, kx) in forward and (KH-1-ky, KW-1-kx) in backward-data.
 // The kernel keeps, per block of 128 pixels and 32 channels, the padded source rows those pixels'
@@ -274,6 +274,8 @@ SplitPlan gathered_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
 bool band_plan(BandGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other, int math, uint32_t *splits);
 int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, bool other_copies);
 size_t igemm_ws_bytes(const IgemmProblem &p);
+// Does split_gemm_kernel run this gathered problem in tiles of 128 rows?
+bool igemm_in_pieces(const IgemmProblem &p);
 // rider: a bias gradient that may ride in the K-slice finishing launch or in direct_kernel's; *rider_taken says
 // whether that happened (it does not when a matrix kernel without either runs the problem).
 int igemm_run(const IgemmProblem &p, void *ws, size_t ws_bytes, hipStream_t stream, const BiasRider *rider = nullptr,
@@ -308,7 +310,7 @@ struct FilterPrep {
     size_t floats;
     int Mg, Cg, KH, KW, sh, sw, Ah, Aw;
 };
-FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d);
+FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d, int math);
 FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math);
 size_t conv_filter_prep_max_floats(const cg_conv_desc &d);      // upper bound of either copy, for sizing
 // n copies, eight per launch: job i reads w[i] and writes dst[i] (16-byte aligned, jobs[i].floats floats)

@@ -13,6 +13,7 @@ namespace cg {
 namespace {
 
 size_t round256(size_t v) { return (v + 255) / 256 * 256; }
+__host__ __device__ inline int padded16(int c) { return (c + 15) / 16 * 16; }
 
 // input pixel grid seen through the filter: index (n, oh, ow) -> window origin in x
 IndexMap window_origin_map(const cg_conv_desc &d, int OH, int OW)
@@ -57,7 +58,8 @@ __device__ __forceinline__ float transpose_filters_elem(const float *__restrict_
 }
 
 // Filters as the patch kernel multiplies with them: dst[g][t][c / 16][r][c % 16], t = kh*KW + kw (units of
-// 16 reduction indices, all rows of a unit contiguous: a wave's load is).  c runs over a multiple of 16.
+// 16 reduction indices, all rows of a unit contiguous: a wave's load is).  c runs over the next multiple of 16, zeros
+// behind the last channel.
 // Forward (bwd = 0): r = output channel, c = input channel: dst = w[g*Mg + r][c][t].
 // Backward-data (bwd = 1): r = input channel, c = output channel: dst = w[g*Mg + c][r][t].
 __device__ __forceinline__ float permute_filters_elem(const float *__restrict__ w, size_t i, int Mg, int Cg, int KK, int bwd)
@@ -65,11 +67,11 @@ __device__ __forceinline__ float permute_filters_elem(const float *__restrict__ 
     const int R = bwd ? Cg : Mg, Cr = bwd ? Mg : Cg;
     size_t q = i / 16;
     const int r = (int)(q % R); q /= R;
-    const int c = (int)(q % (Cr / 16)) * 16 + (int)(i % 16); q /= Cr / 16;
+    const int U = (Cr + 15) / 16, c = (int)(q % U) * 16 + (int)(i % 16); q /= U;
     const int t = (int)(q % KK);
     const int g = (int)(q / KK);
     const int m = bwd ? c : r, ci = bwd ? r : c;
-    return w[(((size_t)g * Mg + m) * Cg + ci) * KK + t];
+    return c >= Cr ? 0.f : w[(((size_t)g * Mg + m) * Cg + ci) * KK + t];
 }
 
 // Filters as the matrix of strided backward-data (see bwd_data_strided_problem): row (c, rh, rw),
@@ -85,13 +87,14 @@ __device__ __forceinline__ float strided_filters_elem(const float *__restrict__ 
     if (tap_major) {
         q = i / 16;
         row = (int)(q % R); q /= R;
-        m = (int)(q % (Mg / 16)) * 16 + (int)(i % 16); q /= Mg / 16;
+        const int U = (Mg + 15) / 16;
+        m = (int)(q % U) * 16 + (int)(i % 16); q /= U;
         t = (int)(q % T); q /= T;
     } else { t = (int)(i % T); q = i / T; m = (int)(q % Mg); q /= Mg; row = (int)(q % R); q /= R; }
     const int g = (int)q;
     const int rw = row % sw, rh = (row / sw) % sh, c = row / (sw * sh);
     const int kh = rh + sh * (t / Aw), kw = rw + sw * (t % Aw);
-    return (kh < KH && kw < KW) ? w[(((size_t)g * Mg + m) * Cg + c) * KH * KW + kh * KW + kw] : 0.f;
+    return (kh < KH && kw < KW && m < Mg) ? w[(((size_t)g * Mg + m) * Cg + c) * KH * KW + kh * KW + kw] : 0.f;
 }
 
 __global__ __launch_bounds__(256) void transpose_filters_kernel(const float *__restrict__ w, float *__restrict__ wt,
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(256) void transpose_filters_kernel(const float *__r
 __global__ __launch_bounds__(256) void permute_filters_kernel(const float *__restrict__ w, float *__restrict__ dst,
                                                               int G, int Mg, int Cg, int KK, int bwd)
 {
-    const size_t total = (size_t)G * Mg * Cg * KK;
+    const size_t total = bwd ? (size_t)G * Cg * padded16(Mg) * KK : (size_t)G * Mg * padded16(Cg) * KK;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256)
         dst[i] = permute_filters_elem(w, i, Mg, Cg, KK, bwd);
 }
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(256) void strided_filters_kernel(const float *__res
                                                               int G, int Mg, int Cg, int KH, int KW, int sh, int sw,
                                                               int Ah, int Aw, int tap_major)
 {
-    const size_t total = (size_t)G * (Cg * sh * sw) * (Ah * Aw) * Mg;
+    const size_t total = (size_t)G * (Cg * sh * sw) * (Ah * Aw) * (tap_major ? padded16(Mg) : Mg);
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256)
         dst[i] = strided_filters_elem(w, i, Mg, Cg, KH, KW, sh, sw, Ah, Aw, tap_major);
 }
@@ -255,7 +258,7 @@ static bool fwd_patch(const cg_conv_desc &d, int OH, int OW, const float *x, Ige
     g.gstride = (int64_t)Cg * d.H * d.W;
     g.Cred = (uint32_t)Cg; g.Hs = d.H; g.Ws = d.W; g.chan_stride = d.H * d.W; g.img_stride = d.C * d.H * d.W;
     g.OHo = OH; g.OWo = OW; g.s = d.stride_h; g.oy0 = -d.pad_h; g.ox0 = -d.pad_w; g.KH = d.KH; g.KW = d.KW; g.flip = 0;
-    if (!patch_plan(g, (uint32_t)(d.M / G), (uint32_t)d.N * OH * OW, (uint32_t)G)) return false;
+    if (!patch_plan(g, (uint32_t)(d.M / G), (uint32_t)d.N * OH * OW, (uint32_t)G) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
     p.patch = g; p.use_patch = 1;
     return true;
 }
@@ -270,14 +273,14 @@ static bool bwd_data_patch(const cg_conv_desc &d, int OH, int OW, const float *d
     g.Cred = (uint32_t)Mg; g.Hs = OH; g.Ws = OW; g.chan_stride = OH * OW; g.img_stride = d.M * OH * OW;
     g.OHo = d.H; g.OWo = d.W; g.s = 1; g.oy0 = d.pad_h - (d.KH - 1); g.ox0 = d.pad_w - (d.KW - 1);
     g.KH = d.KH; g.KW = d.KW; g.flip = 1;
-    if (!patch_plan(g, (uint32_t)(d.C / G), (uint32_t)d.N * d.H * d.W, (uint32_t)G)) return false;
+    if (!patch_plan(g, (uint32_t)(d.C / G), (uint32_t)d.N * d.H * d.W, (uint32_t)G) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
     p.patch = g; p.use_patch = 1;
     return true;
 }
 
 static int permute_filters(const float *w, float *dst, int G, int Mg, int Cg, int KK, int bwd, hipStream_t stream)
 {
-    const size_t total = (size_t)G * Mg * Cg * KK;
+    const size_t total = bwd ? (size_t)G * Cg * padded16(Mg) * KK : (size_t)G * Mg * padded16(Cg) * KK;
     const unsigned blocks = (unsigned)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
     hipLaunchKernelGGL(permute_filters_kernel, dim3(blocks), dim3(256), 0, stream, w, dst, G, Mg, Cg, KK, bwd);
     CG_HIP_TRY(hipGetLastError());
@@ -297,6 +300,16 @@ static void tap_major_filters(IgemmProblem &p, const float *m, int rows, int K, 
     p.A.lanes_k = 1;
 }
 
+// bytes of the rearranged filters the patch kernel multiplies with
+static size_t fwd_copy_bytes(const cg_conv_desc &d)
+{
+    return round256((size_t)d.M * padded16(d.C / d.groups) * d.KH * d.KW * sizeof(float));
+}
+static size_t bwd_copy_bytes(const cg_conv_desc &d)
+{
+    return round256((size_t)d.C * padded16(d.M / d.groups) * d.KH * d.KW * sizeof(float));
+}
+
 static bool math_ok(int math) { return math == CG_MATH_FP32 || math == CG_MATH_BF16 || math == CG_MATH_BF16X3; }
 
 int conv_fwd_impl(const cg_conv_desc &d, const float *x, const float *w, const float *bias, float *y, void *ws,
@@ -314,16 +327,17 @@ int conv_fwd_impl(const cg_conv_desc &d, const float *x, const float *w, const f
     IgemmProblem p = fwd_problem(d, OH, OW, x, w, bias, y, y_img_stride);
     p.relu = relu;
     p.math = math;
-    if (fwd_patch(d, OH, OW, x, p)) {
+    const size_t wt_bytes = fwd_copy_bytes(d);
+    // (a copy with padded channels is dropped where the workspace has no room for it)
+    if (fwd_patch(d, OH, OW, x, p) && (d.C / d.groups % 16 == 0 || (ws && ws_bytes >= wt_bytes) || (p.use_patch = 0))) {
         const int G = d.groups, Cg = d.C / G, Mg = d.M / G, KK = d.KH * d.KW;
-        const size_t wt_bytes = round256((size_t)d.M * Cg * KK * sizeof(float));
         if (!ws || ws_bytes < wt_bytes) return CG_ENOSPC;
         if (!aligned16(ws)) return CG_EINVAL;
         if (!prepared) {
             const int rc2 = permute_filters(w, static_cast<float *>(ws), G, Mg, Cg, KK, 0, stream);
             if (rc2) return rc2;
         }
-        tap_major_filters(p, prepared ? prepared : static_cast<const float *>(ws), Mg, Cg * KK, (uint64_t)d.M * Cg * KK);
+        tap_major_filters(p, prepared ? prepared : static_cast<const float *>(ws), Mg, padded16(Cg) * KK, (uint64_t)d.M * padded16(Cg) * KK);
         return igemm_run(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
     }
     return igemm_run(p, ws, ws_bytes, stream);
@@ -516,16 +530,22 @@ static bool bwd_data_strided_patch(const cg_conv_desc &d, const StridedGeom &sg,
     g.Cred = (uint32_t)Mg; g.Hs = OH; g.Ws = OW; g.chan_stride = OH * OW; g.img_stride = d.M * OH * OW;
     g.OHo = sg.Ch; g.OWo = sg.Cw; g.s = 1; g.oy0 = -(sg.Ah - 1); g.ox0 = -(sg.Aw - 1);
     g.KH = sg.Ah; g.KW = sg.Aw; g.flip = 1;
-    if (!patch_plan(g, (uint32_t)sg.R, sg.Np, (uint32_t)G)) return false;
+    if (!patch_plan(g, (uint32_t)sg.R, sg.Np, (uint32_t)G) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
     p.patch = g; p.use_patch = 1;
     return true;
 }
+
+static uint64_t copy_elems(const cg_conv_desc &d, const StridedGeom &sg)
+{
+    return (uint64_t)d.groups * sg.R * padded16(d.M / d.groups) * sg.Ah * sg.Aw;
+}
+static size_t strided_copy_bytes(const cg_conv_desc &d, const StridedGeom &sg) { return round256((size_t)copy_elems(d, sg) * sizeof(float)); }
 
 static int strided_filters(const float *w, float *dst, const cg_conv_desc &d, const StridedGeom &sg, int tap_major,
                            hipStream_t stream)
 {
     const int G = d.groups;
-    const size_t total = (size_t)G * sg.R * sg.Kp;
+    const size_t total = tap_major ? (size_t)copy_elems(d, sg) : (size_t)G * sg.R * sg.Kp;
     const unsigned blocks = (unsigned)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
     hipLaunchKernelGGL(strided_filters_kernel, dim3(blocks), dim3(256), 0, stream, w, dst, G, d.M / G, d.C / G, d.KH, d.KW,
                        sg.sh, sg.sw, sg.Ah, sg.Aw, tap_major);
@@ -551,7 +571,9 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         IgemmProblem p = bwd_data_strided_problem(d, sg, OH, OW, dy, prepared ? prepared : wt, dx, accumulate);
         p.gate = gate;
         p.math = math;
-        const bool patch = bwd_data_strided_patch(d, sg, OH, OW, dy, p);
+        const size_t copy = strided_copy_bytes(d, sg);
+        const bool patch = bwd_data_strided_patch(d, sg, OH, OW, dy, p) && (ws_bytes >= copy || (p.use_patch = 0));
+        if (patch) tap_major_filters(p, p.A.ptr, sg.R, padded16(d.M / d.groups) * sg.Ah * sg.Aw, copy_elems(d, sg));
         if (!patch) {
             IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
             pd.gate = gate;
@@ -565,6 +587,7 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
             const int rc2 = strided_filters(w, wt, d, sg, patch ? 1 : 0, stream);
             if (rc2) return rc2;
         }
+        if (patch) return igemm_run(p, nullptr, 0, stream);
         return igemm_run(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
     }
     if ((d.stride_h != 1 || d.stride_w != 1) && math != CG_MATH_FP32) return CG_EUNSUPPORTED;   // plain vector arithmetic below
@@ -597,13 +620,14 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         pp.gate = gate;
         pp.math = math;
         pp.beside_other_stream = beside_other_stream ? 1 : 0;
-        if (bwd_data_patch(d, OH, OW, dy, pp)) {
+        const size_t copy = bwd_copy_bytes(d);
+        if (bwd_data_patch(d, OH, OW, dy, pp) && ws_bytes >= copy) {
             if (!prepared) {
                 const int rc2 = permute_filters(w, wt, G, Mg, Cg, KK, 1, stream);
                 if (rc2) return rc2;
             }
-            tap_major_filters(pp, wuse, Cg, Mg * KK, (uint64_t)d.M * Cg * KK);
-            return igemm_run(pp, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
+            tap_major_filters(pp, wuse, Cg, padded16(Mg) * KK, (uint64_t)d.C * padded16(Mg) * KK);
+            return igemm_run(pp, static_cast<char *>(ws) + copy, ws_bytes - copy, stream);
         }
     }
     const bool in_place = bwd_data_reads_filters_in_place(d);
@@ -628,16 +652,17 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
     return igemm_run(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
 }
 
-FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d)
+FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d, int math)
 {
     FilterPrep f{};
     int OH, OW;
     if (conv_check(&d, &OH, &OW)) return f;
     IgemmProblem p = fwd_problem(d, OH, OW, nullptr, nullptr, nullptr, nullptr);
+    p.math = math;
     if (!fwd_patch(d, OH, OW, nullptr, p)) return f;
     f.kind = CG_PREP_PERMUTE_FWD;
     f.Mg = d.M / d.groups; f.Cg = d.C / d.groups; f.KH = d.KH; f.KW = d.KW;
-    f.floats = (size_t)d.M * f.Cg * d.KH * d.KW;
+    f.floats = (size_t)d.M * padded16(f.Cg) * d.KH * d.KW;
     return f;
 }
 
@@ -650,34 +675,39 @@ FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math)
     StridedGeom sg;
     if ((d.stride_h != 1 || d.stride_w != 1) && strided_geom(d, sg)) {
         IgemmProblem p = bwd_data_strided_problem(d, sg, OH, OW, nullptr, nullptr, nullptr, 0);
+        p.math = math;
         const bool patch = bwd_data_strided_patch(d, sg, OH, OW, nullptr, p);
         IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, nullptr, nullptr, nullptr, 0);
-        p.math = pd.math = math;
+        pd.math = math;
         if (!patch && igemm_take_direct(pd, &p)) return f;
         f.kind = patch ? CG_PREP_STRIDED_TAPS : CG_PREP_STRIDED_ROWS;
         f.sh = sg.sh; f.sw = sg.sw; f.Ah = sg.Ah; f.Aw = sg.Aw;
-        f.floats = (size_t)d.groups * sg.R * sg.Kp;
+        f.floats = patch ? (size_t)copy_elems(d, sg) : (size_t)d.groups * sg.R * sg.Kp;
         return f;
     }
     if (d.stride_h != 1 || d.stride_w != 1) return f;            // the vector kernels read w itself
     IgemmProblem pp = bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
-    if (bwd_data_patch(d, OH, OW, nullptr, pp)) f.kind = CG_PREP_PERMUTE_BWD;
-    else if (!bwd_data_reads_filters_in_place(d)) {
+    pp.math = math;
+    f.floats = (size_t)d.M * f.Cg * d.KH * d.KW;
+    if (bwd_data_patch(d, OH, OW, nullptr, pp)) {
+        f.kind = CG_PREP_PERMUTE_BWD;
+        f.floats = (size_t)d.C * padded16(f.Mg) * d.KH * d.KW;
+    } else if (!bwd_data_reads_filters_in_place(d)) {
         IgemmProblem pd = bwd_data_direct_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
-        pp.math = pd.math = math;
+        pd.math = math;
         if (igemm_take_direct(pd, &pp)) return f;
         f.kind = CG_PREP_TRANSPOSE;
-    } else return f;
-    f.floats = (size_t)d.M * f.Cg * d.KH * d.KW;
+    }
     return f;
 }
 
 size_t conv_filter_prep_max_floats(const cg_conv_desc &d)
 {
-    size_t m = (size_t)d.M * (d.C / d.groups) * d.KH * d.KW;
+    const size_t fwd = (size_t)d.M * padded16(d.C / d.groups), bwd = (size_t)d.C * padded16(d.M / d.groups);
+    size_t m = (fwd > bwd ? fwd : bwd) * d.KH * d.KW;
     StridedGeom sg;
     if ((d.stride_h != 1 || d.stride_w != 1) && strided_geom(d, sg)) {
-        const size_t s2 = (size_t)d.groups * sg.R * sg.Kp;
+        const size_t s2 = (size_t)copy_elems(d, sg);
         if (s2 > m) m = s2;
     }
     return m;
@@ -833,19 +863,28 @@ size_t conv_ws_bytes(const cg_conv_desc &d, int pass)
     if (conv_check(&d, &OH, &OW)) return 0;
     if (pass == CG_PASS_FWD) {
         IgemmProblem p = fwd_problem(d, OH, OW, nullptr, nullptr, nullptr, nullptr);
-        if (fwd_patch(d, OH, OW, nullptr, p)) return round256((size_t)d.M * (d.C / d.groups) * d.KH * d.KW * sizeof(float));
-        return igemm_ws_bytes(p);
+        const size_t gathered = igemm_ws_bytes(p);
+        p.math = CG_MATH_BF16;                   // (the mode in which most problems take the patch kernel)
+        if (!fwd_patch(d, OH, OW, nullptr, p)) return gathered;
+        const size_t copy = fwd_copy_bytes(d);
+        return d.C / d.groups % 16 == 0 || copy > gathered ? copy : gathered;
     }
     if (pass == CG_PASS_BWD_DATA) {
         StridedGeom sg;
         if ((d.stride_h != 1 || d.stride_w != 1) && strided_geom(d, sg)) {
             IgemmProblem p = bwd_data_strided_problem(d, sg, OH, OW, nullptr, nullptr, nullptr, 0);
-            bwd_data_strided_patch(d, sg, OH, OW, nullptr, p);
-            return round256((size_t)d.groups * sg.R * sg.Kp * sizeof(float)) + igemm_ws_bytes(p);
+            const size_t gathered = round256((size_t)d.groups * sg.R * sg.Kp * sizeof(float)) + igemm_ws_bytes(p);
+            p.math = CG_MATH_BF16;
+            if (!bwd_data_strided_patch(d, sg, OH, OW, nullptr, p)) return gathered;
+            const size_t copy = strided_copy_bytes(d, sg);
+            return d.M / d.groups % 16 == 0 || copy > gathered ? copy : gathered;
         }
         if (d.stride_h != 1 || d.stride_w != 1) return 0;
-        return round256((size_t)d.M * (d.C / d.groups) * d.KH * d.KW * sizeof(float)) +
-               igemm_ws_bytes(bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0));
+        IgemmProblem p = bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
+        const size_t gathered = round256((size_t)d.M * (d.C / d.groups) * d.KH * d.KW * sizeof(float)) + igemm_ws_bytes(p);
+        p.math = CG_MATH_BF16;
+        const size_t copy = bwd_data_patch(d, OH, OW, nullptr, p) ? bwd_copy_bytes(d) : 0;
+        return copy > gathered ? copy : gathered;
     }
     if (pass == CG_PASS_BWD_WEIGHT) {
         size_t most = gathered_bwd_weight_bytes(d, OH, OW);

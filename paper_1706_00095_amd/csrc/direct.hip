@@ -291,9 +291,10 @@ int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, b
     // A gathered from dy or from rows of a matrix beside a B that runs along k as well: neighbouring lanes lie far apart, and
     // beyond a few hundred indices the loads take longer than the second launch (181 x 68 with 2048 indices 35.3 / 12.9)
     if (p.B.lanes_k && p.K > 768) return 0;
-    // Forward's filters lie the way the gathered kernel likes them, and from about 0.38 GFLOP on what is gained (13 problems,
-    // 0.96 - 1.47, median 1.1; below 98 problems, 1.35) is within the fit's error
-    if (other && a_quads && 2. * p.M * (double)p.N * p.K * p.groups > 0.375e9) return 0;
+    // Where the gathered kernel needs no copy of the filters either (forward, 1x1 backward-data): from about 0.38 GFLOP on what
+    // is gained is within the fit's error (13 forward problems 0.96 - 1.47, median 1.1; below 98 problems, 1.35), and long rows
+    // of pixels suit its loaders (35 x 55575 with 243 indices 50.3 / 27.7)
+    if (other && !other_copies && 2. * p.M * (double)p.N * p.K * p.groups > 0.375e9) return 0;
     const uint64_t tiles = (uint64_t)((p.N + NT - 1) / NT) * ((p.M + MT - 1) / MT) * p.groups;
     if (tiles >= (1u << 30)) return 0;
     int best = 0;

@@ -411,6 +411,8 @@ size_t igemm_ws_bytes(const IgemmProblem &p)
     return gathered_plan(p.M, p.N, p.K, p.groups).ws_bytes;
 }
 
+bool igemm_in_pieces(const IgemmProblem &p) { return pieces_mt(p) == 128; }
+
 bool igemm_take_direct(IgemmProblem &p, const IgemmProblem *other)
 {
     const IgemmProblem &o = other ? *other : p;

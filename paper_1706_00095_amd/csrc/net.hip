@@ -423,7 +423,7 @@ extern "C" int cg_train_step(cg_net *net, const float *x, const int32_t *labels,
             Layer &ly = net->layers[i];
             if (ly.d.kind != CG_LAYER_CONV) continue;
             ly.prep_fwd = ly.prep_bd = nullptr;
-            const FilterPrep f = conv_fwd_filter_prep(ly.conv);
+            const FilterPrep f = conv_fwd_filter_prep(ly.conv, math);
             if (f.kind != CG_PREP_NONE) {
                 ly.prep_fwd = base + ly.prep_fwd_off;
                 jobs.push_back(f); jw.push_back(ly.w); jd.push_back(base + ly.prep_fwd_off);

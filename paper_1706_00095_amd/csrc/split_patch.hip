@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WM, wn = (wave / WM) % WN, wk = wave / (WM * WN);
     const uint32_t m0 = blockIdx.y * MT, g = blockIdx.z;
-    const int KK = pg.KH * pg.KW, ncb16 = (int)(pg.Cred / 16), ngrp = (ncb16 + 1) / 2;
+    const int KK = pg.KH * pg.KW, ncb16 = (int)(pg.Cred + 15) / 16, ngrp = (ncb16 + 1) / 2;
     // this block's pixels n0..n1
     const uint32_t P = pg.divP.d;
     uint32_t n0, n1;
@@ -134,10 +134,10 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     float pr[NSL][8];
     auto load_chunk = [&](auto EC, int grp) {
         constexpr int e = decltype(EC)::value;
-        const bool live = grp * 2 + (wave >> 1) < ncb16;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const uint32_t soff = live ? (uint32_t)((grp * 32 + wave * 8 + t) * pg.chan_stride) * 4u : OOB_K;
+            const int c = grp * 32 + wave * 8 + t;
+            const uint32_t soff = c < (int)pg.Cred ? (uint32_t)(c * pg.chan_stride) * 4u : OOB_K;
             pr[e][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrcB, voff[e], soff, 0));
         }
     };
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int c = 16 * cb + 4 * q + v;
-                        const uint32_t at = ok ? (uint32_t)(img + c * pg.chan_stride + sy * pg.Ws + sx) * 4u : OOB_K;
+                        const uint32_t at = ok && c < (int)pg.Cred ? (uint32_t)(img + c * pg.chan_stride + sy * pg.Ws + sx) * 4u : OOB_K;
                         b[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrcB, at, 0, 0));
                     }
 #pragma unroll
@@ -293,7 +293,8 @@ int launch_cfg(const IgemmProblem &p, hipStream_t stream)
     int rec = -1;
     if (prof_on()) {
         char name[64];
-        snprintf(name, sizeof name, NP == 1 ? "igemm_patch%s_kernel<%dx128,%d,bf16>" : NP == 2 ? "igemm_patch%s_kernel<%dx128,%d,bf16x3>" : "igemm_patch%s_kernel<%dx128,%d>",
+        if (p.patch.Cred % 16) snprintf(name, sizeof name, NP == 1 ? "igemm_kernel<%dx128,patch%d,pieces,bf16>" : NP == 2 ? "igemm_kernel<%dx128,patch%d,pieces,bf16x3>" : "igemm_kernel<%dx128,patch%d,pieces>", MT, NSL);
+        else snprintf(name, sizeof name, NP == 1 ? "igemm_patch%s_kernel<%dx128,%d,bf16>" : NP == 2 ? "igemm_patch%s_kernel<%dx128,%d,bf16x3>" : "igemm_patch%s_kernel<%dx128,%d>",
                  WK == 2 && NP == 3 ? "16" : "", MT, NSL);
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }
@@ -417,8 +418,9 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
 {
     g.nsl = 0;
     const int KK = g.KH * g.KW;
-    if (g.Cred == 0 || g.Cred % 16 || KK < 5 || g.s <= 0 || g.OHo <= 0 || g.OWo <= 0) return false;
+    if (g.Cred == 0 || KK < 4 || g.s <= 0 || g.OHo <= 0 || g.OWo <= 0) return false;
     if (g.src_elems * 4 > kMaxBufferBytes || N >= (1u << 30)) return false;
+    if (g.Cred % 16 && (uint64_t)M * groups * ((g.Cred + 15) / 16 * 16) * (uint64_t)KK * 4 > kMaxBufferBytes) return false;     // its filter copy
     g.Wp = (g.OWo - 1) * g.s + g.KW;
     const int64_t rfull = (int64_t)((g.OHo - 1) * g.s + g.KH) * g.Wp;
     if (rfull >= (1 << 24)) return false;
@@ -439,6 +441,18 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
     const uint32_t K = g.Cred * (uint32_t)KK;
     const bool enough = M <= 48 ? T * 5 >= lim * 2 : K < 128 ? false : T * 4 >= lim * 5 || (T * 4 >= lim * 3 && K < 3200) || (T * 2 >= lim && K <= 1200);
     if (lim > 1 && !enough) return false;
+    // Channels that are no multiple of 16 (zeros are multiplied for the rest) and windows of four taps (a patch is worth
+    // little there).  1300 problems in fp32, 260 in each of the other modes, the other kernels' time over this one's: as far as
+    // the lines below take them 0.87 - 2.4, geometric mean 1.3, and 1.5 in the other modes; left out: fewer tiles 0.16 - 1.7,
+    // most below 0.9; tiles x indices below 200 000 or fewer than 200 indices 0.55 - 1.2; more than 25 % zeros 0.6 - 1.5; two and
+    // three taps, and five in a row, 0.2 - 1.04; four taps of up to 16 rows, whose tiles in one and two pieces are 64 rows,
+    // 0.6 - 1.28.  (A problem that split_gemm_kernel runs in tiles of 128 rows stays there, see the callers: 0.8 - 1.2, and its
+    // shorter sums are closer to 64 bits.)  The error against 64 bits is 0.15 to 1.0 of what it was.
+    const bool padded = g.Cred % 16 != 0;
+    if (lim > 1 && (padded || KK == 4)) {
+        const uint64_t zeros = (g.Cred + 15) / 16 * 16 * 100ull;
+        if (T * K < 200000 || K < 200 || KK == 5 || (KK == 4 && M <= 16) || (M <= 48 ? T < 250 : T < 400 || zeros > g.Cred * 125ull)) return false;
+    }
     // The largest patch any block needs: a fragment read reaches (KH-1)*Wp + KW-1 beyond sigma, and
     // sigma + that stays below the slot count of the block's segments, which is what is counted.
     auto slots = [&](uint32_t n0, uint32_t n1) {
@@ -464,8 +478,9 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
     }
     // (six chunks: planes 56 wide with a 3x3 window, four pixel rows, 348 slots)
     if (amax > 6 * 64) return false;
-    g.nsl = amax > 5 * 64 ? 6 : 5;
     g.tiles_per_img = (int32_t)((P + 127) / 128);
+    if (lim > 1 && (padded || KK == 4) && P * 4 < (uint32_t)g.tiles_per_img * 128 * 3) return false;       // mostly empty blocks
+    g.nsl = amax > 5 * 64 ? 6 : 5;
     g.divTpi = make_fastdiv((uint32_t)g.tiles_per_img);
     return true;
 }
@@ -478,12 +493,12 @@ int split_patch_launch(const IgemmProblem &p, hipStream_t stream)
     if (p.bias_mode && !p.bias) return CG_EINVAL;
     if (p.math != CG_MATH_FP32 && p.math != CG_MATH_BF16 && p.math != CG_MATH_BF16X3) return CG_EINVAL;
     const PatchGeom &g = p.patch;
-    if (!g.src || !aligned16(g.src) || g.nsl < 4 || g.nsl > 6 || p.splits != 1 || g.Cred % 16 ||
+    if (!g.src || !aligned16(g.src) || g.nsl < 4 || g.nsl > 6 || p.splits != 1 || g.Cred == 0 ||
         p.K != g.Cred * (uint32_t)(g.KH * g.KW))
         return CG_EINVAL;
-    // the filter copy holds M rows of K floats per group, and byte offsets into it stay below the marks
+    // the filter copy holds M rows of K floats (channels padded to 16) per group, and byte offsets into it stay below the marks
     // that stand for "out of range"
-    if (p.A.elems * 4 > kMaxBufferBytes || (uint64_t)p.A.gstride * p.groups > p.A.elems || (uint64_t)p.M * p.K > (uint64_t)p.A.gstride)
+    if (p.A.elems * 4 > kMaxBufferBytes || (uint64_t)p.A.gstride * p.groups > p.A.elems || (uint64_t)p.M * ((g.Cred + 15) / 16 * 16) * (uint64_t)(g.KH * g.KW) > (uint64_t)p.A.gstride)
         return CG_EUNSUPPORTED;
     return patch_launch(p, stream);
 }
