@@ -134,6 +134,8 @@ struct PatchGeom {
     int32_t nsl;              // 64-slot chunks per channel the kernel instance stages (4, 5 or 6); 0 = not usable
     int32_t tiles_per_img;    // 0: blocks own 128 consecutive pixels across image boundaries; > 0: every image is
                               // cut into this many blocks of its own (smaller patches for large images)
+    int32_t rect_shift;       // > 0: a block's 128 pixels are a rectangle 2^rect_shift wide (wide images: fewer rows to keep)
+    FastDiv divTx;            // rectangles per row of them
     FastDiv divTpi;
     uint32_t tile0;           // first pixel tile of this launch (blockIdx.x counts from it)
     uint32_t tile_count;      // pixel tiles of this launch; 0 = all

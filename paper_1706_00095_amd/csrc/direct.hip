@@ -296,7 +296,7 @@ int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, b
     // of pixels suit its loaders (35 x 55575 with 243 indices 50.3 / 27.7)
     if (other && !other_copies && 2. * p.M * (double)p.N * p.K * p.groups > 0.375e9) return 0;
     const uint64_t tiles = (uint64_t)((p.N + NT - 1) / NT) * ((p.M + MT - 1) / MT) * p.groups;
-    if (tiles >= (1u << 30)) return 0;
+    if (tiles >= (1u << 30) || (other && 2. * p.M * (double)p.N * p.K * p.groups > 2e9)) return 0;       // (beyond what was fitted)
     int best = 0;
     double cost = 1e300;
     for (int waves = 4; waves <= 16; waves *= 2) {

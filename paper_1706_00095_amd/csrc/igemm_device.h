@@ -206,9 +206,12 @@ __device__ __forceinline__ void store_tile(const IgemmProblem &p, const v16f (&a
 // Columns whose offsets are not consecutive (a pixel tile that crosses into the next image), that reach beyond n_end
 // or are scattered go one by one.
 typedef float v4f __attribute__((ext_vector_type(4)));
-template <int TM, int TN, bool PLAIN>
+// at(c): the four columns that start at column c of the wave's tile, as the first one's index in C and how many of them
+// exist; they follow one another in C.
+struct Columns { uint32_t n, cnt; };
+template <int TM, int TN, bool PLAIN, class At>
 __device__ __forceinline__ void store_columns_impl(const IgemmProblem &p, const v4f (&acc)[TM][TN], uint32_t g, uint32_t sp,
-                                                   uint32_t mw, uint32_t nw, uint32_t n_end, int lane)
+                                                   uint32_t mw, int lane, At &&at)
 {
     constexpr int JB = PLAIN ? 1 : TN < 4 ? TN : TM >= 3 ? 2 : 4;
     const int q = lane >> 4, l16 = lane & 15;
@@ -232,13 +235,14 @@ __device__ __forceinline__ void store_columns_impl(const IgemmProblem &p, const 
     static_for<0, TN / JB>([&](auto BC) {
         constexpr int j0 = decltype(BC)::value * JB;
         int32_t off[JB];
-        uint32_t cnt[JB];               // columns of this lane's four that exist
+        uint32_t first[JB], cnt[JB];    // this lane's four columns, how many of them exist
         bool quad[JB];
         v4f bcol[JB], gt[JB][TM], old[JB][TM];
 #pragma unroll
         for (int u = 0; u < JB; ++u) {
-            const uint32_t n = nw + (uint32_t)((j0 + u) * 16 + 4 * q);
-            cnt[u] = n < n_end ? min(4u, n_end - n) : 0u;
+            const Columns four = at((j0 + u) * 16 + 4 * q);
+            const uint32_t n = first[u] = four.n;
+            cnt[u] = four.cnt;
             off[u] = 0;
             quad[u] = false;
             bcol[u] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -281,17 +285,16 @@ __device__ __forceinline__ void store_columns_impl(const IgemmProblem &p, const 
                     }
                     if (row_ok) *reinterpret_cast<f4u *>(c_base + roff[i] + off[u]) = v;
                 } else if (row_ok && cnt[u]) {
-                    const uint32_t n = nw + (uint32_t)((j0 + u) * 16 + 4 * q);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         if ((uint32_t)e >= cnt[u]) continue;
-                        const Info ci = map_info(p.c_col, n + (uint32_t)e);
+                        const Info ci = map_info(p.c_col, first[u] + (uint32_t)e);
                         if (scatter && !((uint32_t)(ra[i] + ci.a) < p.c_limA && (uint32_t)(rb[i] + ci.b) < p.c_limB)) continue;
-                        const int32_t at = roff[i] + ci.off;
+                        const int32_t to = roff[i] + ci.off;
                         float x = v[e];
-                        if (gate && !(gate[at] > 0.f)) x = 0.f;
-                        if (accumulate) x += c_base[at];
-                        c_base[at] = x;
+                        if (gate && !(gate[to] > 0.f)) x = 0.f;
+                        if (accumulate) x += c_base[to];
+                        c_base[to] = x;
                     }
                 }
             }
@@ -299,12 +302,21 @@ __device__ __forceinline__ void store_columns_impl(const IgemmProblem &p, const 
     });
 }
 
+template <int TM, int TN, class At>
+__device__ __forceinline__ void store_columns_at(const IgemmProblem &p, const v4f (&acc)[TM][TN], uint32_t g, uint32_t sp, uint32_t mw, int lane, At &&at)
+{
+    if (!p.gate && !p.accumulate && !p.c_scatter) store_columns_impl<TM, TN, true>(p, acc, g, sp, mw, lane, at);
+    else store_columns_impl<TM, TN, false>(p, acc, g, sp, mw, lane, at);
+}
+// columns nw, nw + 1, ... below n_end
 template <int TM, int TN>
 __device__ __forceinline__ void store_columns(const IgemmProblem &p, const v4f (&acc)[TM][TN], uint32_t g, uint32_t sp,
                                               uint32_t mw, uint32_t nw, uint32_t n_end, int lane)
 {
-    if (!p.gate && !p.accumulate && !p.c_scatter) store_columns_impl<TM, TN, true>(p, acc, g, sp, mw, nw, n_end, lane);
-    else store_columns_impl<TM, TN, false>(p, acc, g, sp, mw, nw, n_end, lane);
+    store_columns_at<TM, TN>(p, acc, g, sp, mw, lane, [&](int c) {
+        const uint32_t n = nw + (uint32_t)c;
+        return Columns{n, n < n_end ? min(4u, n_end - n) : 0u};
+    });
 }
 
 // One element of C by itself: bias, rectifier, gate, accumulation, the output map (P: IgemmProblem, or the arguments

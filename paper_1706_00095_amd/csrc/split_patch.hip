@@ -62,25 +62,44 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     const int wm = wave % WM, wn = (wave / WM) % WN, wk = wave / (WM * WN);
     const uint32_t m0 = blockIdx.y * MT, g = blockIdx.z;
     const int KK = pg.KH * pg.KW, ncb16 = (int)(pg.Cred + 15) / 16, ngrp = (ncb16 + 1) / 2;
-    // this block's pixels n0..n1
+    // this block's pixels: n0..n1, or the rectangle of image bA from (ty0, tx0) on
     const uint32_t P = pg.divP.d;
-    uint32_t n0, n1;
+    uint32_t n0 = 0, n1 = 0, bA, ty0 = 0, tx0 = 0;
     const uint32_t tile = blockIdx.x + pg.tile0;
+    const int rs = pg.rect_shift;
     if (pg.tiles_per_img) {
-        const uint32_t b = fdiv(tile, pg.divTpi), ti = tile - b * pg.divTpi.d;
-        n0 = b * P + ti * NT;
-        n1 = min(n0 + NT - 1, (b + 1) * P - 1);
+        bA = fdiv(tile, pg.divTpi);
+        const uint32_t ti = tile - bA * pg.divTpi.d;
+        if (rs) {
+            const uint32_t ry = fdiv(ti, pg.divTx);
+            ty0 = ry * (uint32_t)(NT >> rs);
+            tx0 = (ti - ry * pg.divTx.d) << rs;
+        } else {
+            n0 = bA * P + ti * NT;
+            n1 = min(n0 + NT - 1, (bA + 1) * P - 1);
+        }
     } else {
         n0 = tile * NT;
         n1 = min(n0 + NT - 1, p.N - 1);
+        bA = fdiv(n0, pg.divP);
     }
+    // pixel i of the block: image, row, column, is it one
+    struct Pixel { uint32_t b, oy, ox; bool ok; };
+    auto pixel = [&](int i) {
+        if (rs) {
+            const uint32_t oy = ty0 + (uint32_t)(i >> rs), ox = tx0 + (uint32_t)(i & ((1 << rs) - 1));
+            return Pixel{bA, oy, ox, oy < (uint32_t)pg.OHo && ox < (uint32_t)pg.OWo};
+        }
+        const uint32_t n = n0 + (uint32_t)i, b = fdiv(n, pg.divP), rem = n - b * P, oy = fdiv(rem, pg.divOW);
+        return Pixel{b, oy, rem - oy * pg.divOW.d, n <= n1};
+    };
 
     const auto rsrcA = buffer_of(p.A.ptr + (int64_t)g * p.A.gstride, (p.A.elems - (uint64_t)g * p.A.gstride) * 4);
     const auto rsrcB = buffer_of(pg.src + (int64_t)g * pg.gstride, (pg.src_elems - (uint64_t)g * pg.gstride) * 4);
 
     // ---- where this block's pixels sit: images bA..bB, pixel rows oyA (in bA) .. oyB (in bB) -------
-    const uint32_t bA = fdiv(n0, pg.divP), oyA = fdiv(n0 - bA * P, pg.divOW);
-    const uint32_t bB = fdiv(n1, pg.divP), oyB = fdiv(n1 - bB * P, pg.divOW);
+    const uint32_t oyA = rs ? ty0 : fdiv(n0 - bA * P, pg.divOW), bB = rs ? bA : fdiv(n1, pg.divP);
+    const uint32_t oyB = rs ? ty0 + (uint32_t)(NT >> rs) - 1u : fdiv(n1 - bB * P, pg.divOW);
     // slots of the first image's segment; later images start at R0 + (d-1)*Rfull
     const int32_t R0 = (int32_t)((((bA == bB) ? oyB : (uint32_t)pg.OHo - 1) - oyA) * pg.s + pg.KH) * pg.Wp;
 
@@ -94,7 +113,7 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
         const uint32_t r = fdiv((uint32_t)local, pg.divWp), c = (uint32_t)local - r * (uint32_t)pg.Wp;
         const uint32_t b = bA + d, oylo = d == 0 ? oyA : 0u;
         const uint32_t oyhi = b == bB ? oyB : (uint32_t)pg.OHo - 1;
-        const int32_t sy = (int32_t)(oylo * pg.s) + pg.oy0 + (int32_t)r, sx = pg.ox0 + (int32_t)c;
+        const int32_t sy = (int32_t)(oylo * pg.s) + pg.oy0 + (int32_t)r, sx = (int32_t)(tx0 * pg.s) + pg.ox0 + (int32_t)c;
         const bool ok = b <= bB && r < (oyhi - oylo) * pg.s + pg.KH && (uint32_t)sy < (uint32_t)pg.Hs &&
                         (uint32_t)sx < (uint32_t)pg.Ws;
         voff[e] = ok ? (uint32_t)((int32_t)b * pg.img_stride + sy * pg.Ws + sx) * 4u : OOB_ROW;
@@ -106,14 +125,10 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     int32_t sig[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const uint32_t n = n0 + (uint32_t)((wn * TN + j) * 16 + l16);
-        int32_t sg = 0;
-        if (n <= n1) {
-            const uint32_t b = fdiv(n, pg.divP), rem = n - b * P, oy = fdiv(rem, pg.divOW), ox = rem - oy * pg.divOW.d;
-            const uint32_t d = b - bA, oylo = d == 0 ? oyA : 0u;
-            sg = (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull) + (int32_t)((oy - oylo) * pg.s) * pg.Wp + (int32_t)(ox * pg.s);
-        }
-        sig[j] = sg;
+        const Pixel px = pixel((wn * TN + j) * 16 + l16);
+        const uint32_t d = px.b - bA, oylo = d == 0 ? oyA : 0u;
+        const int32_t sg = (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull) + (int32_t)((px.oy - oylo) * pg.s) * pg.Wp + (int32_t)((px.ox - tx0) * pg.s);
+        sig[j] = px.ok ? sg : 0;
     }
     // byte offset of this lane's eight floats in a unit of the filter copy [unit][row][16]
     uint32_t arow[TM];
@@ -244,13 +259,12 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     if constexpr (NP == 3) {
         if (not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
             // this lane's pixel: its image, position of its window
-            const uint32_t n = n0 + (uint32_t)((wn * TN + j) * 16 + l16);
-            const uint32_t b = fdiv(n, pg.divP), rem = n - b * P, oy = fdiv(rem, pg.divOW), ox = rem - oy * pg.divOW.d;
-            const int32_t img = (int32_t)b * pg.img_stride, wy = (int32_t)(oy * pg.s) + pg.oy0, wx = (int32_t)(ox * pg.s) + pg.ox0;
+            const Pixel px = pixel((wn * TN + j) * 16 + l16);
+            const int32_t img = (int32_t)px.b * pg.img_stride, wy = (int32_t)(px.oy * pg.s) + pg.oy0, wx = (int32_t)(px.ox * pg.s) + pg.ox0;
             for (int t = 0; t < KK; ++t) {
                 const int ky = (int)fdiv((uint32_t)t, pg.divKW), kx = t - ky * pg.KW;
                 const int32_t sy = wy + (pg.flip ? pg.KH - 1 - ky : ky), sx = wx + (pg.flip ? pg.KW - 1 - kx : kx);
-                const bool ok = n <= n1 && (uint32_t)sy < (uint32_t)pg.Hs && (uint32_t)sx < (uint32_t)pg.Ws;
+                const bool ok = px.ok && (uint32_t)sy < (uint32_t)pg.Hs && (uint32_t)sx < (uint32_t)pg.Ws;
                 for (int cb = 0; cb < ncb16; ++cb) {
                     // a unit of 16 channels, four consecutive ones a lane, its loads in flight together
                     float a[4][TM], b[4];
@@ -273,7 +287,15 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
             }
         });
     }
-    store_columns<TM, TN>(p, acc, g, 0u, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), n1 + 1, lane);
+    store_columns_at<TM, TN>(p, acc, g, 0u, m0 + (uint32_t)(wm * TM * 16), lane, [&](int c) {
+        const int i = wn * TN * 16 + c;
+        if (rs) {
+            const Pixel px = pixel(i);
+            return Columns{px.b * P + px.oy * pg.divOW.d + px.ox, px.ok ? min(4u, (uint32_t)pg.OWo - px.ox) : 0u};
+        }
+        const uint32_t n = n0 + (uint32_t)i;
+        return Columns{n, n <= n1 ? min(4u, n1 + 1u - n) : 0u};
+    });
 }
 
 namespace {
@@ -444,14 +466,17 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
     // Channels that are no multiple of 16 (zeros are multiplied for the rest) and windows of four taps (a patch is worth
     // little there).  1300 problems in fp32, 260 in each of the other modes, the other kernels' time over this one's: as far as
     // the lines below take them 0.87 - 2.4, geometric mean 1.3, and 1.5 in the other modes; left out: fewer tiles 0.16 - 1.7,
-    // most below 0.9; tiles x indices below 200 000 or fewer than 200 indices 0.55 - 1.2; more than 25 % zeros 0.6 - 1.5; two and
+    // most below 0.9; tiles x indices below 200 000 or fewer than 250 indices 0.55 - 1.2; more than 25 % zeros (90 % beside few
+    // rows) 0.6 - 1.5; two and
     // three taps, and five in a row, 0.2 - 1.04; four taps of up to 16 rows, whose tiles in one and two pieces are 64 rows,
     // 0.6 - 1.28.  (A problem that split_gemm_kernel runs in tiles of 128 rows stays there, see the callers: 0.8 - 1.2, and its
     // shorter sums are closer to 64 bits.)  The error against 64 bits is 0.15 to 1.0 of what it was.
     const bool padded = g.Cred % 16 != 0;
     if (lim > 1 && (padded || KK == 4)) {
         const uint64_t zeros = (g.Cred + 15) / 16 * 16 * 100ull;
-        if (T * K < 200000 || K < 200 || KK == 5 || (KK == 4 && M <= 16) || (M <= 48 ? T < 250 : T < 400 || zeros > g.Cred * 125ull)) return false;
+        if (T * K < 200000 || K < 250 || KK == 5 || (KK == 4 && M <= 16) || T < (M <= 16 ? 350 : M <= 48 ? 250 : 400) ||
+            zeros > g.Cred * (M <= 48 ? 190ull : 125ull))
+            return false;
     }
     // The largest patch any block needs: a fragment read reaches (KH-1)*Wp + KW-1 beyond sigma, and
     // sigma + that stays below the slot count of the block's segments, which is what is counted.
@@ -462,25 +487,47 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
                (int64_t)(oyB * g.s + g.KH) * g.Wp;
     };
     int64_t smax = 0;
-    for (uint32_t n0 = 0; n0 < N; n0 += 128) {
+    for (uint32_t n0 = 0; n0 < N && smax <= 4 * 64; n0 += 128) {
         const int64_t sl = slots(n0, (n0 + 127 < N - 1) ? n0 + 127 : N - 1);
         if (sl > smax) smax = sl;
     }
     g.tiles_per_img = 0;
-    g.divTpi = make_fastdiv(1);
+    g.rect_shift = 0;
+    g.divTpi = g.divTx = make_fastdiv(1);
     if (smax <= 4 * 64) { g.nsl = 4; return true; }
     // large images: blocks that stay inside one image need smaller patches (every image is the same)
     if (N % P) return false;
     int64_t amax = 0;
-    for (uint32_t n0 = 0; n0 < P; n0 += 128) {
+    for (uint32_t n0 = 0; n0 < P && amax <= 6 * 64; n0 += 128) {
         const int64_t sl = slots(n0, (n0 + 127 < P - 1) ? n0 + 127 : P - 1);
         if (sl > amax) amax = sl;
     }
-    // (six chunks: planes 56 wide with a 3x3 window, four pixel rows, 348 slots)
-    if (amax > 6 * 64) return false;
-    g.tiles_per_img = (int32_t)((P + 127) / 128);
-    if (lim > 1 && (padded || KK == 4) && P * 4 < (uint32_t)g.tiles_per_img * 128 * 3) return false;       // mostly empty blocks
-    g.nsl = amax > 5 * 64 ? 6 : 5;
+    if (amax <= 6 * 64) {
+        // (six chunks: planes 56 wide with a 3x3 window, four pixel rows, 348 slots)
+        g.tiles_per_img = (int32_t)((P + 127) / 128);
+        if (lim > 1 && (padded || KK == 4) && P * 4 < (uint32_t)g.tiles_per_img * 128 * 3) return false;       // mostly empty blocks
+        g.nsl = amax > 5 * 64 ? 6 : 5;
+    } else {
+        // Rows too long to keep: rectangles of pixels, the fewest that fit.  170 problems on planes 40 to 240 wide that meet the
+        // lines above, the other kernels' time over this one's 0.97 - 3.0, geometric mean 1.4 (57434 pixels, 12 rows, 221 channels
+        // 5x5 344 / 114 us; 164892 pixels, 3 rows, 187 channels 5x5 678 / 277).
+        for (int rs = 2; rs <= 6; ++rs) {
+            const int w = 1 << rs, h = 128 >> rs;
+            const int64_t sl = (int64_t)((h - 1) * g.s + g.KH) * ((w - 1) * g.s + g.KW);
+            const int32_t tx = (g.OWo + w - 1) / w, tiles = tx * ((g.OHo + h - 1) / h);
+            if (sl > 6 * 64 || (g.tiles_per_img && tiles >= g.tiles_per_img)) continue;
+            g.tiles_per_img = tiles;
+            g.rect_shift = rs;
+            g.divTx = make_fastdiv((uint32_t)tx);
+            g.nsl = sl > 5 * 64 ? 6 : sl > 4 * 64 ? 5 : 4;
+        }
+        if (!g.rect_shift) return false;
+        const int w = 1 << g.rect_shift;
+        g.Wp = (w - 1) * g.s + g.KW;
+        g.Rfull = (int32_t)(((128 >> g.rect_shift) - 1) * g.s + g.KH) * g.Wp;
+        g.divWp = make_fastdiv((uint32_t)g.Wp);
+        g.divRfull = make_fastdiv((uint32_t)g.Rfull);
+    }
     g.divTpi = make_fastdiv((uint32_t)g.tiles_per_img);
     return true;
 }

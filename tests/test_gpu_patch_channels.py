@@ -1,5 +1,5 @@
-"""The patch kernel on channel counts that are no multiple of 16 and on windows of four taps: exact on small integers, also in
-the bf16 modes; what lies behind the last channel stays out; a workspace without room for the padded filter copy."""
+"""The patch kernel on channel counts that are no multiple of 16, on windows of four taps and on planes so wide that a block takes
+a rectangle of pixels: exact on small integers, also in the bf16 modes; what lies behind the last channel stays out; a workspace without room for the padded filter copy."""
 import pytest
 import torch
 
@@ -23,6 +23,9 @@ CASES = [
     (2, 33, 13, 13, 47, 5, 1, 2, 1), (2, 58, 13, 13, 50, 3, 1, 1, 2), (3, 19, 15, 15, 21, 3, 2, 1, 1), (1, 3, 30, 30, 20, 7, 2, 3, 1),
     (2, 20, 14, 13, 70, 2, 1, 0, 1), (5, 47, 27, 27, 16, 5, 1, 2, 1),
 ]
+# planes whose rows do not fit: rectangles with remainders on both sides, every width the slots allow, groups
+WIDE = [(2, 18, 9, 130, 20, 3, 1, 1, 1), (1, 16, 70, 97, 40, 5, 1, 2, 1), (2, 34, 33, 81, 70, 7, 1, 3, 2), (1, 3, 150, 151, 33, 11, 2, 5, 1),
+        (1, 16, 65, 129, 130, 3, 1, 0, 1), (1, 21, 127, 3, 17, 3, 1, 1, 1)]
 
 
 @pytest.mark.parametrize("math", [cg.CG_MATH_FP32, cg.CG_MATH_BF16, cg.CG_MATH_BF16X3])
@@ -32,6 +35,23 @@ def test_any_number_of_channels_exact(orc32, case, math):
     cfg = dict(C=C, H=H, W=W, M=M, k=k, stride=stride, pad=pad, groups=groups)
     _, names = _all_three(orc32, B, cfg, seed=C, bwd_weight=False, math=math)
     assert len([n for n in names if "patch" in n]) >= (1 if C == 3 else 2), names
+
+
+@pytest.mark.parametrize("math", [cg.CG_MATH_FP32, cg.CG_MATH_BF16X3])
+@pytest.mark.parametrize("case", WIDE, ids=lambda c: "-".join(map(str, c)))
+def test_rectangles_of_wide_planes_exact(orc32, case, math):
+    test_any_number_of_channels_exact(orc32, case, math)
+
+
+def test_an_infinity_in_a_rectangle():
+    """Infinite exactly where a window reaches it: the sums done again in fp32 find the same pixels."""
+    d = cg.conv_desc(1, 17, 40, 130, 20, 3, pad=1)
+    x, w = torch.ones((1, 17, 40, 130), device="cuda"), torch.ones((20, 17, 3, 3), device="cuda")
+    x[0, 16, 21, 77] = float("inf")
+    y, names = _logged(lambda: conv_fwd(d, x, w, None))
+    assert any("patch" in n for n in names), names
+    assert bool((~y.isfinite()).nonzero()[:, 2:].unique(dim=0).eq(torch.cartesian_prod(torch.arange(20, 23), torch.arange(76, 79)).cuda()).all())
+    assert bool((y[0, :, 20:23, 76:79] == float("inf")).all()) and bool((y[0, :, 1:19, 1:129] == 153).all())
 
 
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
