@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libcg.so")
 # (source, object name, extra flags): the matrix kernels are compiled once per number of bf16 pieces
 SOURCES = [(f"{s}.hip", f"{s}{n}.o", [f"-DCG_NP={n}"]) for n in (3, 2, 1) for s in ("split_gemm", "split_patch", "split_wgrad")] + [
     ("gather.hip", f"gather{m}.o", [f"-DCG_MATH={m}"]) for m in (0, 1, 2)] + [
-    (f"{s}.hip", f"{s}.o", []) for s in ("igemm", "direct", "layers", "conv", "sgd", "net", "api")]
+    (f"{s}.hip", f"{s}.o", []) for s in ("igemm", "direct", "stem", "layers", "conv", "sgd", "net", "api")]
 COMMON = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -175,6 +175,26 @@ struct BandGeom {
     FastDiv divSS, divWp, divP8, divOW, divKW, divNB;       // slots of an image's band; octets of its pixels
 };
 
+// Forward convolutions of few input channels (stem.hip): tiles of Tw x Th pixels, whose source rows a block keeps in LDS in
+// pieces, the window's columns in quads of four.
+struct StemGeom {
+    const float *x;
+    uint64_t x_elems;
+    int32_t N, C, Cg, H, W, OH, OW, s, pad_h, pad_w, KH, KW;
+    int32_t Tw, Th;
+    int32_t Rr, Wp;           // source rows of a tile, values kept of each
+    int32_t copies;           // of the rows, each shifted by some columns, so that every window starts on 8 bytes of one: 1, 2, 4
+    int32_t copy_values, plane_values;       // values of a copy, of a piece (all copies)
+    int32_t nquads;           // channels * window rows * quads
+    int32_t units;            // tiles of all images
+    int32_t mt;               // rows of a block
+    int32_t table_bytes, lds_bytes;
+    const float *copy;        // the filters in pieces (stem_filters_word)
+    uint64_t copy_floats;
+    FastDiv divTx, divTpi, divTw, divHalf, divKH, divKW, divQuads;
+};
+constexpr int kStemLds = 80 * 1024;          // two blocks a compute unit
+
 // A small convolution's bias gradient (db[m] = sum of dy over images and pixels), summed by extra blocks of
 // another launch, one block per channel, instead of a launch of its own.
 struct BiasRider { const float *dy; int N, M, P; float *db; };
@@ -236,6 +256,9 @@ void patch_set_min_tiles(uint32_t t);
 int split_patch_launch(const IgemmProblem &p, hipStream_t stream);      // problems with a patch (igemm_launch dispatches)
 int split_wgrad_launch(const IgemmProblem &p, hipStream_t stream);      // use_band (igemm_launch dispatches)
 int split_wgrad_3(const IgemmProblem &p, hipStream_t stream);
+// stem.hip
+uint64_t stem_copy_floats(int Mg, int Cg, int KH, int KW);        // of one group's filters in pieces
+int stem_fwd_launch(const IgemmProblem &p, const StemGeom &g, hipStream_t stream);
 // direct_kernel: how many waves a problem gets (0: the gathered kernel, whose plan is `other`, is expected to be faster;
 // other NULL: there is none, and the answer is never 0 unless the kernel cannot run it), its launch
 int direct_launch(const IgemmProblem &p, bool a_quads, hipStream_t stream);
@@ -275,6 +298,8 @@ SplitPlan gathered_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
 // kernel (whose plan for the M x N x K problem is `other`) is expected to be faster in this arithmetic.
 bool band_plan(BandGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other, int math, uint32_t *splits);
 int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, bool other_copies);
+// false where the kernel does not apply or the gathered one (plan `other`) is expected to be faster
+bool stem_fwd_plan(StemGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other);
 size_t igemm_ws_bytes(const IgemmProblem &p);
 // Does split_gemm_kernel run this gathered problem in tiles of 128 rows?
 bool igemm_in_pieces(const IgemmProblem &p);
@@ -306,7 +331,7 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
                        bool beside_other_stream = false);
 // Which rearranged copy of its filters a pass needs (kind CG_PREP_NONE: it reads w itself), and how
 // many floats the copy has.  The answer follows the same kernel choice the pass itself makes.
-enum { CG_PREP_NONE = 0, CG_PREP_TRANSPOSE, CG_PREP_PERMUTE_FWD, CG_PREP_PERMUTE_BWD, CG_PREP_STRIDED_TAPS, CG_PREP_STRIDED_ROWS };
+enum { CG_PREP_NONE = 0, CG_PREP_TRANSPOSE, CG_PREP_PERMUTE_FWD, CG_PREP_PERMUTE_BWD, CG_PREP_STRIDED_TAPS, CG_PREP_STRIDED_ROWS, CG_PREP_PIECES };
 struct FilterPrep {
     int kind;
     size_t floats;

@@ -7,6 +7,7 @@
 // one is the first step of every turn in Fig. 3).
 #include <mutex>
 #include "cg_internal.h"
+#include "split_device.h"
 
 namespace cg {
 
@@ -97,6 +98,29 @@ __device__ __forceinline__ float strided_filters_elem(const float *__restrict__ 
     return (kh < KH && kw < KW && m < Mg) ? w[(((size_t)g * Mg + m) * Cg + c) * KH * KW + kh * KW + kw] : 0.f;
 }
 
+// Filters in three bf16 pieces, as a lane of stem_fwd_kernel multiplies with them: word i of
+// dst[g][row / 16][step][piece][lane][4], two bf16 a word: lane (q, l) of a step holds row l's quads 8 * step + 2q and + 1, quad
+// t being columns 4j .. 4j+3 of window row t / quads of (channel, ky); zeros where there is no column, quad or row.
+__device__ __forceinline__ float stem_filters_word(const float *__restrict__ w, size_t i, int Mg, int Cg, int KH, int KW)
+{
+    const int Q = (KW + 3) / 4, nq = Cg * KH * Q, ns = (nq + 7) / 8, RT = (Mg + 15) / 16;
+    const int word = (int)(i % 4), lane = (int)(i / 4 % 64), piece = (int)(i / 256 % 3);
+    size_t u = i / 768;
+    const int s = (int)(u % ns); u /= ns;
+    const int rt = (int)(u % RT), g = (int)(u / RT), r = rt * 16 + lane % 16, t = 8 * s + 2 * (lane / 16) + word / 2, kx = 4 * (t % Q) + 2 * (word % 2);
+    const float *row = w + (((size_t)g * Mg + r) * Cg * KH + t / Q) * KW + kx;
+    const bool ok = r < Mg && t < nq;
+    uint32_t pc[3];
+    split_pair<3>(ok && kx < KW ? row[0] : 0.f, ok && kx + 1 < KW ? row[1] : 0.f, pc);
+    return __uint_as_float(piece == 0 ? pc[0] : piece == 1 ? pc[1] : pc[2]);
+}
+
+__global__ __launch_bounds__(256) void stem_filters_kernel(const float *__restrict__ w, float *__restrict__ dst, size_t total, int Mg, int Cg, int KH, int KW)
+{
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256)
+        dst[i] = stem_filters_word(w, i, Mg, Cg, KH, KW);
+}
+
 __global__ __launch_bounds__(256) void transpose_filters_kernel(const float *__restrict__ w, float *__restrict__ wt,
                                                                 int G, int Mg, int Cg, int KK)
 {
@@ -151,6 +175,7 @@ __global__ __launch_bounds__(256) void prepare_filters_kernel(const PrepTable t)
         if (i >= jb.total) break;
         float v;
         if (jb.kind == CG_PREP_TRANSPOSE) v = transpose_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH * jb.KW);
+        else if (jb.kind == CG_PREP_PIECES) v = stem_filters_word(jb.w, i, jb.Mg, jb.Cg, jb.KH, jb.KW);
         else if (jb.kind == CG_PREP_PERMUTE_FWD) v = permute_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH * jb.KW, 0);
         else if (jb.kind == CG_PREP_PERMUTE_BWD) v = permute_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH * jb.KW, 1);
         else v = strided_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH, jb.KW, jb.sh, jb.sw, jb.Ah, jb.Aw,
@@ -263,6 +288,17 @@ static bool fwd_patch(const cg_conv_desc &d, int OH, int OW, const float *x, Ige
     return true;
 }
 
+// Does the kernel for few input channels run the forward pass?  g: its geometry.
+static bool fwd_stem(const cg_conv_desc &d, int OH, int OW, const float *x, const IgemmProblem &p, StemGeom &g)
+{
+    if (d.stride_h != d.stride_w || p.math != CG_MATH_FP32 || igemm_in_pieces(p)) return false;
+    g = StemGeom{};
+    g.x = x; g.x_elems = (uint64_t)d.N * d.C * d.H * d.W;
+    g.N = d.N; g.C = d.C; g.Cg = d.C / d.groups; g.H = d.H; g.W = d.W; g.OH = OH; g.OW = OW; g.s = d.stride_h;
+    g.pad_h = d.pad_h; g.pad_w = d.pad_w; g.KH = d.KH; g.KW = d.KW;
+    return stem_fwd_plan(g, p.M, p.N, p.groups, gathered_plan(p.M, p.N, p.K, p.groups));
+}
+
 // dy as the patch operand of backward-data at stride 1 (pixels = input positions, mirrored taps)
 static bool bwd_data_patch(const cg_conv_desc &d, int OH, int OW, const float *dy, IgemmProblem &p)
 {
@@ -339,6 +375,19 @@ int conv_fwd_impl(const cg_conv_desc &d, const float *x, const float *w, const f
         }
         tap_major_filters(p, prepared ? prepared : static_cast<const float *>(ws), Mg, padded16(Cg) * KK, (uint64_t)d.M * padded16(Cg) * KK);
         return igemm_run(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
+    }
+    StemGeom sg;
+    if (fwd_stem(d, OH, OW, x, p, sg) && ws && ws_bytes >= sg.copy_floats * sizeof(float) && aligned16(ws)) {
+        const int rs = igemm_scratch_check(p, ws, ws_bytes);
+        if (rs) return rs;
+        sg.copy = prepared ? prepared : static_cast<const float *>(ws);
+        if (!prepared) {
+            const unsigned blocks = (unsigned)((sg.copy_floats + 255) / 256 < 4096 ? (sg.copy_floats + 255) / 256 : 4096);
+            hipLaunchKernelGGL(stem_filters_kernel, dim3(blocks), dim3(256), 0, stream, w, static_cast<float *>(ws), (size_t)sg.copy_floats, d.M / d.groups,
+                               d.C / d.groups, d.KH, d.KW);
+            CG_HIP_TRY(hipGetLastError());
+        }
+        return stem_fwd_launch(p, sg, stream);
     }
     return igemm_run(p, ws, ws_bytes, stream);
 }
@@ -659,7 +708,14 @@ FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d, int math)
     if (conv_check(&d, &OH, &OW)) return f;
     IgemmProblem p = fwd_problem(d, OH, OW, nullptr, nullptr, nullptr, nullptr);
     p.math = math;
-    if (!fwd_patch(d, OH, OW, nullptr, p)) return f;
+    StemGeom sg;
+    if (!fwd_patch(d, OH, OW, nullptr, p)) {
+        if (!fwd_stem(d, OH, OW, nullptr, p, sg)) return f;
+        f.kind = CG_PREP_PIECES;
+        f.Mg = d.M / d.groups; f.Cg = d.C / d.groups; f.KH = d.KH; f.KW = d.KW;
+        f.floats = (size_t)sg.copy_floats;
+        return f;
+    }
     f.kind = CG_PREP_PERMUTE_FWD;
     f.Mg = d.M / d.groups; f.Cg = d.C / d.groups; f.KH = d.KH; f.KW = d.KW;
     f.floats = (size_t)d.M * padded16(f.Cg) * d.KH * d.KW;
@@ -705,6 +761,10 @@ size_t conv_filter_prep_max_floats(const cg_conv_desc &d)
 {
     const size_t fwd = (size_t)d.M * padded16(d.C / d.groups), bwd = (size_t)d.C * padded16(d.M / d.groups);
     size_t m = (fwd > bwd ? fwd : bwd) * d.KH * d.KW;
+    int OH, OW;
+    StemGeom st;
+    if (conv_check(&d, &OH, &OW) == CG_OK && fwd_stem(d, OH, OW, nullptr, fwd_problem(d, OH, OW, nullptr, nullptr, nullptr, nullptr), st) && st.copy_floats > m)
+        m = (size_t)st.copy_floats;
     StridedGeom sg;
     if ((d.stride_h != 1 || d.stride_w != 1) && strided_geom(d, sg)) {
         const size_t s2 = (size_t)copy_elems(d, sg);
@@ -864,8 +924,10 @@ size_t conv_ws_bytes(const cg_conv_desc &d, int pass)
     if (pass == CG_PASS_FWD) {
         IgemmProblem p = fwd_problem(d, OH, OW, nullptr, nullptr, nullptr, nullptr);
         const size_t gathered = igemm_ws_bytes(p);
+        StemGeom sg;
+        const size_t stem = fwd_stem(d, OH, OW, nullptr, p, sg) ? (size_t)sg.copy_floats * sizeof(float) : 0;
         p.math = CG_MATH_BF16;                   // (the mode in which most problems take the patch kernel)
-        if (!fwd_patch(d, OH, OW, nullptr, p)) return gathered;
+        if (!fwd_patch(d, OH, OW, nullptr, p)) return stem > gathered ? stem : gathered;
         const size_t copy = fwd_copy_bytes(d);
         return d.C / d.groups % 16 == 0 || copy > gathered ? copy : gathered;
     }
