@@ -10,8 +10,8 @@
 // (and with them events): up to eight of them, or a million parameters, per launch.
 //
 // Within a layer's turn backward-data and backward-weight are independent and run side by side
-// (backward-weight on a third stream owned by the net); the update waits for both, because it
-// overwrites the model that backward-data still reads.
+// (backward-weight on a third stream owned by the net, but for very small layers of small nets); the update waits for both,
+// because it overwrites the model that backward-data still reads.
 #include <atomic>
 #include <new>
 #include <vector>
@@ -405,6 +405,7 @@ extern "C" int cg_train_step(cg_net *net, const float *x, const int32_t *labels,
     // of one fill the compute units the other's last wave of blocks leaves idle.
     hipStream_t S2 = serial ? S0 : net->wgrad_stream;
     hipEvent_t last_wgrad = nullptr;
+    bool on_third = false;                       // the third stream has work that no event has been recorded behind yet
     const int B = net->B;
     auto act = [&](int i) -> const float * { return i < 0 ? x : base + net->layers[i].act_off; };
     int rc = CG_OK;
@@ -519,17 +520,27 @@ extern "C" int cg_train_step(cg_net *net, const float *x, const int32_t *labels,
     std::vector<int> pend;
     size_t pend_params = 0;
     constexpr long long kBatchParams = 1ll << 20;
+    // A dependency between two streams costs the host 10 us (an event recorded on one and waited for on the other; a launch
+    // 3.3), more than a small turn takes on the GPU, and a net of few layers does not let the host run ahead: there backward-weight
+    // of less than 20 MFLOP stays on the compute stream (the 3-convolution net at B = 8 120 -> 101 us a step).  Nets of many
+    // layers are not bound by the host (142 layers at B = 2 2375 us as it is, 2463 so).
+    int turns = 0;
+    for (const Layer &ly : net->layers) turns += ly.n_params ? 1 : 0;
+    const double beside_from = turns <= 8 ? 2e7 : 0.;
     auto flush_updates = [&]() -> int {
         if (pend.empty()) return CG_OK;
         Layer &last = net->layers[pend.back()];
         if (!serial) {
             // the update overwrites the models backward-data reads and consumes the gradients
             // backward-weight writes: it waits for both streams, which run the layers in turn order
-            CG_HIP_TRY(hipEventRecord(last.ev_grad, S2));
+            if (on_third) {
+                CG_HIP_TRY(hipEventRecord(last.ev_grad, S2));
+                CG_HIP_TRY(hipStreamWaitEvent(S1, last.ev_grad, 0));
+                last_wgrad = last.ev_grad;
+                on_third = false;
+            }
             CG_HIP_TRY(hipEventRecord(last.ev_bd, S0));
-            CG_HIP_TRY(hipStreamWaitEvent(S1, last.ev_grad, 0));
             CG_HIP_TRY(hipStreamWaitEvent(S1, last.ev_bd, 0));
-            last_wgrad = last.ev_grad;
         }
         float *w[8], *v[8];
         const float *g[8];
@@ -584,20 +595,25 @@ extern "C" int cg_train_step(cg_net *net, const float *x, const int32_t *labels,
         switch (d.kind) {
         case CG_LAYER_CONV:
         case CG_LAYER_FC: {
-            if (!serial) {
+            const int IN = ly.inC * ly.inH * ly.inW;
+            const double work = d.kind == CG_LAYER_CONV ? 2. * B * (double)ly.n_weights * ly.H * ly.W : 2. * B * (double)ly.n_weights;
+            const bool beside = !serial && work >= beside_from;
+            if (beside) {
                 CG_HIP_TRY(hipEventRecord(ly.ev_dy, S0));
                 CG_HIP_TRY(hipStreamWaitEvent(S2, ly.ev_dy, 0));
+                on_third = true;
             }
-            const int IN = ly.inC * ly.inH * ly.inW;
+            hipStream_t SW = beside ? S2 : S0;
+            void *const scratch_w = beside ? scratch2 : scratch;
             if (d.kind == CG_LAYER_CONV)
                 // without a backward-data pass of its own (a first layer) the compute stream is idle during this
                 // turn: the bias sums go there, beside the weight gradient; the update waits for both streams
                 // (their partial sums in the compute stream's own scratch region: the other region may still be
                 // read by an earlier layer's weight-gradient kernels, which only the third stream orders)
-                rc = conv_bwd_weight_impl(ly.conv, in, dy, ly.g, ly.g + ly.n_weights, scratch2, scratch_bytes, S2, math,
-                                          (!serial && !want_dx) ? S0 : nullptr, scratch, scratch_bytes);
+                rc = conv_bwd_weight_impl(ly.conv, in, dy, ly.g, ly.g + ly.n_weights, scratch_w, scratch_bytes, SW, math,
+                                          (beside && !want_dx) ? S0 : nullptr, scratch, scratch_bytes);
             else
-                rc = fc_bwd_weight_impl(B, IN, d.fc_out, in, dy, ly.g, ly.g + ly.n_weights, scratch2, scratch_bytes, S2, math);
+                rc = fc_bwd_weight_impl(B, IN, d.fc_out, in, dy, ly.g, ly.g + ly.n_weights, scratch_w, scratch_bytes, SW, math);
             if (rc == CG_OK && want_dx) {
                 if (d.kind == CG_LAYER_CONV)
                     // (true: the tile choice made for the three-stream schedule, in the one-stream schedule as well,
