@@ -261,7 +261,7 @@ uint64_t stem_copy_floats(int Mg, int Cg, int KH, int KW);        // of one grou
 int stem_fwd_launch(const IgemmProblem &p, const StemGeom &g, hipStream_t stream);
 // direct_kernel: how many waves a problem gets (0: the gathered kernel, whose plan is `other`, is expected to be faster;
 // other NULL: there is none, and the answer is never 0 unless the kernel cannot run it), its launch
-int direct_launch(const IgemmProblem &p, bool a_quads, hipStream_t stream);
+int direct_launch(const IgemmProblem &p, bool a_quads, bool b_quads, hipStream_t stream);
 // What igemm_run would refuse the scratch memory of a gathered problem for.
 int igemm_scratch_check(const IgemmProblem &p, const void *ws, size_t ws_bytes);
 // Sets p.direct if direct_kernel runs p faster than the other kernels run `other`, the same sums from operands laid out
@@ -298,6 +298,8 @@ SplitPlan gathered_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t groups);
 // kernel (whose plan for the M x N x K problem is `other`) is expected to be faster in this arithmetic.
 bool band_plan(BandGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other, int math, uint32_t *splits);
 int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, bool other_copies);
+// The same for a problem that is cut into K slices: its slices here, added up afterwards.
+int direct_for_slices(const IgemmProblem &p, bool a_quads);
 // false where the kernel does not apply or the gathered one (plan `other`) is expected to be faster
 bool stem_fwd_plan(StemGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other);
 size_t igemm_ws_bytes(const IgemmProblem &p);

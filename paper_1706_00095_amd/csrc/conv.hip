@@ -824,6 +824,10 @@ static IgemmProblem bwd_weight_problem(const cg_conv_desc &d, int OH, int OW, co
     p.B.k.count = (uint32_t)d.N * Pp;
     p.B.k.d1 = make_fastdiv((uint32_t)Pp);
     p.B.k.r1_lim = (uint32_t)P;
+    if (bwd_data_reads_filters_in_place(d)) {           // a 1x1 window at stride 1: x lies along the pixels as dy does
+        p.B.k = split_map((uint32_t)d.N * Pp, Pp, d.C * P, 1);
+        p.B.k.r1_lim = (uint32_t)P;
+    }
     p.B.limA = d.H; p.B.limB = d.W;
     p.B.gstride = (int64_t)Cg * d.H * d.W;
     p.B.elems = (uint64_t)d.N * d.C * d.H * d.W;

@@ -25,7 +25,7 @@ constexpr int TM = 1, TN = 2, MT = 16 * TM, NT = 16 * TN;
 constexpr int TABLE = 64;                    // reduction indices whose offsets a wave works out at a time
 constexpr int STEP = 32;                     // reduction indices in registers at a time, twice (this step's, the next one's)
 
-enum { AD_WORDS = 0, AD_CHECKED = 1, AD_QUADS = 2 };
+enum { AD_WORDS = 0, AD_CHECKED = 1, AD_QUADS = 2 };      // how an operand is loaded: element by element, where the window has one, aligned quads of k
 
 // byte offset of an index of an operand, and its window coordinates
 struct Entry { uint32_t off; int32_t a, b; };
@@ -41,8 +41,29 @@ __device__ __forceinline__ float ldw(__amdgpu_buffer_rsrc_t r, uint32_t voff)
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, 0));
 }
 
+// One element of C by itself: bias, rectifier, gate, accumulation, the output map.
+__device__ __forceinline__ void store_element(const IgemmProblem &a, uint32_t g, uint32_t m, uint32_t n, float s)
+{
+    if (a.bias_mode == 1) s += a.bias[(int64_t)g * a.bias_gstride + m];
+    else if (a.bias_mode == 2) s += a.bias[(int64_t)g * a.bias_gstride + n];
+    if (a.relu) s = fmaxf(s, 0.f);
+    const Info ci = map_info(a.c_col, n);
+    int32_t in_group = (int32_t)m * a.c_row_stride + ci.off;
+    if (a.c_scatter) {
+        const Info ri = map_info(a.c_row, m);
+        if (!((uint32_t)(ri.a + ci.a) < a.c_limA && (uint32_t)(ri.b + ci.b) < a.c_limB)) return;
+        in_group = ri.off + ci.off;
+    }
+    const int64_t idx = (int64_t)g * a.c_gstride + in_group;
+    if (a.gate && !(a.gate[idx] > 0.f)) s = 0.f;
+    float *dst = a.c_ptr + idx;
+    if (a.accumulate) s += *dst;
+    *dst = s;
+}
+
 // offsets of TABLE reduction indices of one wave: B's offset and window coordinates, A's likewise where it has them
-template <int AKIND, bool BCHECK> struct Table {
+template <int AKIND, int BKIND> struct Table {
+    static constexpr bool BCHECK = BKIND == AD_CHECKED;
     static constexpr int COLS = 1 + (BCHECK ? 2 : 0) + (AKIND == AD_QUADS ? 0 : AKIND == AD_CHECKED ? 3 : 1);
     static constexpr int WORDS = COLS * TABLE;
     static constexpr int BA = 1, BB = 2, AO = BCHECK ? 3 : 1, AA = AO + 1, AB = AO + 2;
@@ -52,30 +73,31 @@ template <int AKIND, bool BCHECK> struct Table {
 
 struct DirectArgs {
     IgemmProblem p;
-    FastDiv divNT, divMT;                    // column tiles, row tiles
+    FastDiv divNT, divMT, divG;              // column tiles, row tiles, groups
     uint32_t tiles, k_per_wave;
     BiasRider rider;                         // blocks behind the tiles: a channel of a convolution's bias gradient each
     FastDiv divQP;
 };
 
-template <int AKIND, bool BCHECK>
+template <int AKIND, int BKIND>
 __global__ __launch_bounds__(1024) void direct_kernel(const DirectArgs d)
 {
-    using T = Table<AKIND, BCHECK>;
+    using T = Table<AKIND, BKIND>;
+    constexpr bool BCHECK = BKIND == AD_CHECKED;
     constexpr int LS = NT + 4;
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     const IgemmProblem &p = d.p;
     if (blockIdx.x >= d.tiles) {
         const int m = (int)(blockIdx.x - d.tiles);
-        const float s = bias_channel_sum(d.rider.dy, d.rider.M, d.rider.P, m, 0, d.rider.N, d.divQP, reinterpret_cast<float *>(smem));
+        const float s = bias_channel_sum(d.rider.dy, d.rider.M, d.rider.P, m, 0, d.rider.N, d.divQP, blockDim.x, reinterpret_cast<float *>(smem));
         if (threadIdx.x == 0) d.rider.db[m] = s;
         return;
     }
     const int lane = threadIdx.x & 63, q = lane >> 4, l16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t r = fdiv(blockIdx.x, d.divNT), g = fdiv(r, d.divMT);
-    const uint32_t m0 = (r - g * d.divMT.d) * MT, n0 = (blockIdx.x - r * d.divNT.d) * NT;
-    const uint32_t kbeg = (uint32_t)wave * d.k_per_wave, kend = min(p.K, kbeg + d.k_per_wave);
+    const uint32_t r = fdiv(blockIdx.x, d.divNT), gs = fdiv(r, d.divMT), sp = fdiv(gs, d.divG), g = gs - sp * d.divG.d;
+    const uint32_t m0 = (r - gs * d.divMT.d) * MT, n0 = (blockIdx.x - r * d.divNT.d) * NT;
+    const uint32_t kbeg = sp * p.k_per_split + (uint32_t)wave * d.k_per_wave, kend = min(min(p.K, (sp + 1) * p.k_per_split), kbeg + d.k_per_wave);
     const int ns = kbeg < kend ? (int)((kend - kbeg + STEP - 1) / STEP) : 0;
 
     const int64_t fa = (int64_t)g * p.A.gstride + p.A.shift, fb = (int64_t)g * p.B.gstride + p.B.shift;
@@ -147,6 +169,15 @@ __global__ __launch_bounds__(1024) void direct_kernel(const DirectArgs d)
                     }
             }
             const v4u bo = four(s, h, 0);
+            if constexpr (BKIND == AD_QUADS) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rB, brow[j] + bo[0], 0, 0);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) bv[b][h][j][t] = __uint_as_float((uint32_t)v[t]);
+                }
+                continue;
+            }
             v4u ba{}, bb{};
             if constexpr (BCHECK) { ba = four(s, h, T::BA); bb = four(s, h, T::BB); }
 #pragma unroll
@@ -173,12 +204,17 @@ __global__ __launch_bounds__(1024) void direct_kernel(const DirectArgs d)
 #pragma unroll
         for (int h = 0; h < STEP / 16; ++h) {
             if constexpr (AKIND == AD_QUADS) {
-                // what a quad holds behind the last index (of the reduction, of a run) may be anything; B is zero there
+                // what a quad holds behind the last index (of the reduction, of a run) may be anything; an element of B is zero there
                 const v4u bo = four(s, h, 0);
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
                     for (int i = 0; i < TM; ++i) av[b][h][i][t] = bo[t] < OOB_K ? av[b][h][i][t] : 0.f;
+                if constexpr (BKIND == AD_QUADS)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) bv[b][h][j][t] = bo[t] < OOB_K ? bv[b][h][j][t] : 0.f;
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -220,23 +256,25 @@ __global__ __launch_bounds__(1024) void direct_kernel(const DirectArgs d)
         if (m >= p.M || n >= p.N) continue;
         float s = red[row * LS + col];
         for (int w = 1; w < waves; ++w) s += red[(w * MT + (int)row) * LS + (int)col];
-        store_element(p, g, m, n, s);
+        if (p.splits > 1) p.c_ptr[(int64_t)g * p.c_gstride + (int64_t)sp * p.c_split_stride + (int64_t)m * p.c_row_stride + n] = s;
+        else store_element(p, g, m, n, s);
     }
 }
 
 namespace {
 
-template <int AKIND, bool BCHECK> int launch_cfg(const IgemmProblem &p, int waves, const BiasRider *rider, hipStream_t stream)
+template <int AKIND, int BKIND> int launch_cfg(const IgemmProblem &p, int waves, const BiasRider *rider, hipStream_t stream)
 {
     DirectArgs d{};
     d.p = p;
     const uint32_t nt = (p.N + NT - 1) / NT, mt = (p.M + MT - 1) / MT;
-    const uint64_t tiles = (uint64_t)nt * mt * p.groups;
+    const uint64_t tiles = (uint64_t)nt * mt * p.groups * p.splits;
     if (tiles >= (1u << 30)) return CG_EUNSUPPORTED;
     d.tiles = (uint32_t)tiles;
     d.divNT = make_fastdiv(nt);
     d.divMT = make_fastdiv(mt);
-    d.k_per_wave = ((p.K + waves - 1) / waves + 15) / 16 * 16;
+    d.divG = make_fastdiv(p.groups);
+    d.k_per_wave = ((p.k_per_split + waves - 1) / waves + 15) / 16 * 16;
     unsigned riders = 0;
     if (rider) {
         d.rider = *rider;
@@ -249,16 +287,16 @@ template <int AKIND, bool BCHECK> int launch_cfg(const IgemmProblem &p, int wave
         snprintf(name, sizeof name, "igemm_kernel<%dx%d,direct%d>", MT, NT, waves);
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }
-    const size_t tab = (size_t)waves * 2 * Table<AKIND, BCHECK>::WORDS * 4, sums = (size_t)waves * MT * (NT + 4) * 4;
+    const size_t tab = (size_t)waves * 2 * Table<AKIND, BKIND>::WORDS * 4, sums = (size_t)waves * MT * (NT + 4) * 4;
     size_t lds = tab > sums ? tab : sums;
     if (riders && lds < 4096) lds = 4096;                       // a rider block adds up one float a thread
     static std::atomic<bool> attr_set{false};
     if (lds > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<AKIND, BCHECK>),
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<AKIND, BKIND>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 16 * MT * (NT + 4) * 4));
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((direct_kernel<AKIND, BCHECK>), dim3((unsigned)tiles + riders), dim3((unsigned)waves * 64), lds, stream, d);
+    hipLaunchKernelGGL((direct_kernel<AKIND, BKIND>), dim3((unsigned)tiles + riders), dim3((unsigned)waves * 64), lds, stream, d);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
@@ -313,16 +351,29 @@ int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, b
     return cost < 0.9 * there ? best : 0;
 }
 
+// Sums over pixels (both operands run along k) of few columns: a 128-column tile of the gathered kernel is mostly padding, here
+// the columns fit one tile of 32.  190 problems, times there / here: up to 32 columns 1.05 - 3.2 (16 x 4 with 3 836 300 indices 417 /
+// 132 us, 394 x 1 with 124 768 178 / 95), 33 - 43 columns 0.6 - 1.5; more columns with few tiles and indices (the launch and a block's
+// start are what counts) 1.0 - 1.34 up to 140 000 tiles x indices, 0.85 - 1.0 to 280 000, 0.4 - 0.9 beyond.  Four waves; eight and
+// sixteen 0.5 - 1.0 of that.  Error against 64 bits 0.25 to 0.75 of the gathered kernel's.
+int direct_for_slices(const IgemmProblem &p, bool a_quads)
+{
+    if (p.math != CG_MATH_FP32 || !p.B.lanes_k || !a_quads) return 0;
+    const uint64_t tiles = (uint64_t)((p.N + NT - 1) / NT) * ((p.M + MT - 1) / MT) * p.groups;
+    return p.N <= 32 || tiles * p.K <= 140000 ? 4 : 0;
+}
+
 // (normalised by igemm_launch)
-int direct_launch(const IgemmProblem &p, bool a_quads, hipStream_t stream)
+int direct_launch(const IgemmProblem &p, bool a_quads, bool b_quads, hipStream_t stream)
 {
     const int waves = p.direct;
     const BiasRider *rider = p.rider.dy ? &p.rider : nullptr;
     if (waves != 4 && waves != 8 && waves != 16) return CG_EINVAL;
     const bool bc = p.B.check != 0;
-    if (p.A.check) return bc ? launch_cfg<AD_CHECKED, true>(p, waves, rider, stream) : launch_cfg<AD_CHECKED, false>(p, waves, rider, stream);
-    if (a_quads) return bc ? launch_cfg<AD_QUADS, true>(p, waves, rider, stream) : launch_cfg<AD_QUADS, false>(p, waves, rider, stream);
-    return bc ? launch_cfg<AD_WORDS, true>(p, waves, rider, stream) : launch_cfg<AD_WORDS, false>(p, waves, rider, stream);
+    if (b_quads) return a_quads && !bc ? launch_cfg<AD_QUADS, AD_QUADS>(p, waves, rider, stream) : CG_EINVAL;
+    if (p.A.check) return bc ? launch_cfg<AD_CHECKED, AD_CHECKED>(p, waves, rider, stream) : launch_cfg<AD_CHECKED, AD_WORDS>(p, waves, rider, stream);
+    if (a_quads) return bc ? launch_cfg<AD_QUADS, AD_CHECKED>(p, waves, rider, stream) : launch_cfg<AD_QUADS, AD_WORDS>(p, waves, rider, stream);
+    return bc ? launch_cfg<AD_WORDS, AD_CHECKED>(p, waves, rider, stream) : launch_cfg<AD_WORDS, AD_WORDS>(p, waves, rider, stream);
 }
 
 }  // namespace cg

@@ -227,7 +227,7 @@ int igemm_launch(const IgemmProblem &p0, hipStream_t stream)
     if (!p.A.check) { p.A.limA = p.A.limB = 1; }
     if (!p.B.check) { p.B.limA = p.B.limB = 1; }
 
-    if (p.direct) return direct_launch(p, quad_ok(p.A, p.K), stream);
+    if (p.direct) return direct_launch(p, quad_ok(p.A, p.K), quad_ok(p.A, p.K) && quad_ok(p.B, p.K), stream);
     const int mt = p.mt ? p.mt : pick_mt(p.M, p.N, p.groups, p.K);
     // how an operand's elements are fetched: 0 rows along the lanes, 1 k along the lanes, 2 aligned quads of k
     const int am = quad_ok(p.A, p.K) ? 2 : p.A.lanes_k ? 1 : 0;
@@ -284,11 +284,28 @@ struct FinishArgs {
 // 8 thread rows add interleaved slices (row r: slices r, r+8, ...), and the 8 row sums are added
 // in row order.  Either way the association is fixed by the number of slices alone, so the result
 // does not depend on scheduling.
+// (Written out here and in direct.hip: through one shared template the compiler orders this kernel's index arithmetic
+// otherwise, and the pass after the backward weights of 64 images, 13 x 13, 384 -> 384 channels, 3 x 3, two groups, takes
+// 23.7 us, not 21.9.)
 __device__ __forceinline__ void finish_store(const FinishArgs &a, uint32_t i, float s)
 {
     const uint32_t g = fdiv(i, a.divMN), rem = i - g * a.divMN.d;
-    const uint32_t m = fdiv(rem, a.divN);
-    store_element(a, g, m, rem - m * a.divN.d, s);
+    const uint32_t m = fdiv(rem, a.divN), n = rem - m * a.divN.d;
+    if (a.bias_mode == 1) s += a.bias[(int64_t)g * a.bias_gstride + m];
+    else if (a.bias_mode == 2) s += a.bias[(int64_t)g * a.bias_gstride + n];
+    if (a.relu) s = fmaxf(s, 0.f);
+    const Info ci = map_info(a.c_col, n);
+    int32_t in_group = (int32_t)m * a.c_row_stride + ci.off;
+    if (a.c_scatter) {
+        const Info ri = map_info(a.c_row, m);
+        if (!((uint32_t)(ri.a + ci.a) < a.c_limA && (uint32_t)(ri.b + ci.b) < a.c_limB)) return;
+        in_group = ri.off + ci.off;
+    }
+    const int64_t idx = (int64_t)g * a.c_gstride + in_group;
+    if (a.gate && !(a.gate[idx] > 0.f)) s = 0.f;
+    float *dst = a.c_ptr + idx;
+    if (a.accumulate) s += *dst;
+    *dst = s;
 }
 
 // AHEAD: a thread's next eight loads are in flight together (under a condition each, where fewer are left).  It pays
@@ -300,7 +317,7 @@ template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_fi
     if (a.r_dy && blockIdx.x >= a.finish_blocks) {       // a rider block: one channel of the bias gradient
         const int m = (int)(blockIdx.x - a.finish_blocks);
         __shared__ float red[256];
-        const float s = bias_channel_sum(a.r_dy, a.rM, a.rP, m, 0, a.rN, a.r_divQP, red);
+        const float s = bias_channel_sum(a.r_dy, a.rM, a.rP, m, 0, a.rN, a.r_divQP, 256u, red);
         if (threadIdx.x == 0) a.r_db[m] = s;
         return;
     }
@@ -468,6 +485,7 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
     p.c_scatter = 0;
     p.bias = nullptr; p.bias_mode = 0; p.accumulate = 0; p.relu = 0; p.gate = nullptr;
     p.splits = pl.splits; p.k_per_split = pl.k_per_split; p.mt = pl.mt; p.pieces = pl.pieces;
+    if (!p0.use_wgrad && !p0.use_band && !pl.pieces) p.direct = direct_for_slices(p0, quad_ok(p0.A, p0.K));
     const int rc = igemm_launch(p, stream);
     if (rc) return rc;
     FinishArgs a{};
@@ -517,7 +535,7 @@ __global__ __launch_bounds__(256) void bias_grad_partial_kernel(const float *__r
     const int m = blockIdx.x, sl = blockIdx.y;
     const int n_beg = sl * n_per, n_end = min(N, n_beg + n_per);
     __shared__ float red[256];
-    const float s = bias_channel_sum(dy, M, P, m, n_beg, n_end, divQP, red);
+    const float s = bias_channel_sum(dy, M, P, m, n_beg, n_end, divQP, 256u, red);
     if (threadIdx.x == 0) part[(size_t)sl * M + m] = s;
 }
 

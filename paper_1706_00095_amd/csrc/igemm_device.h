@@ -319,36 +319,14 @@ __device__ __forceinline__ void store_columns(const IgemmProblem &p, const v4f (
     });
 }
 
-// One element of C by itself: bias, rectifier, gate, accumulation, the output map (P: IgemmProblem, or the arguments
-// of the kernel that adds the K slices).
-template <class P> __device__ __forceinline__ void store_element(const P &a, uint32_t g, uint32_t m, uint32_t n, float s)
-{
-    if (a.bias_mode == 1) s += a.bias[(int64_t)g * a.bias_gstride + m];
-    else if (a.bias_mode == 2) s += a.bias[(int64_t)g * a.bias_gstride + n];
-    if (a.relu) s = fmaxf(s, 0.f);
-    const Info ci = map_info(a.c_col, n);
-    int32_t in_group = (int32_t)m * a.c_row_stride + ci.off;
-    if (a.c_scatter) {
-        const Info ri = map_info(a.c_row, m);
-        if (!((uint32_t)(ri.a + ci.a) < a.c_limA && (uint32_t)(ri.b + ci.b) < a.c_limB)) return;
-        in_group = ri.off + ci.off;
-    }
-    const int64_t idx = (int64_t)g * a.c_gstride + in_group;
-    if (a.gate && !(a.gate[idx] > 0.f)) s = 0.f;
-    float *dst = a.c_ptr + idx;
-    if (a.accumulate) s += *dst;
-    *dst = s;
-}
-
-// Sum of dy[n][m][0..P) over the images n_beg..n_end-1, by one block (a power of two of threads, `red` a float each);
+// Sum of dy[n][m][0..P) over the images n_beg..n_end-1, by one block (T threads, a power of two; `red` a float each);
 // thread 0 returns it.
 // The (image, group of four pixels) pairs are spread over the threads, each moving 16 bytes
 // (4-byte aligned: planes of an odd pixel count start anywhere) with four loads in flight.
 __device__ __forceinline__ float bias_channel_sum(const float *__restrict__ dy, int M, int P, int m, int n_beg, int n_end,
-                                                  FastDiv divQP, float *red)
+                                                  FastDiv divQP, uint32_t T, float *red)
 {
     const uint32_t QP = divQP.d, total = (uint32_t)(n_end - n_beg) * QP;
-    const uint32_t T = blockDim.x;
     float s = 0.f;
     for (uint32_t i0 = threadIdx.x; i0 < total; i0 += T * 4) {
         f4u v[4];

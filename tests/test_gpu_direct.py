@@ -35,6 +35,31 @@ def test_direct_kernel_exact(orc32, name):
         assert len(names) == 1 and "direct" in names[0], (p, names)
 
 
+# sums over pixels cut into slices: 1x1 windows at stride 1 (both operands in quads) and others, planes of a multiple of four pixels
+# and not, up to 32 columns and few tiles of more
+SLICED = [(3, 1, 40, 41, 17, 1, 1, 0, 1), (5, 32, 21, 23, 33, 1, 1, 0, 1), (6, 14, 20, 20, 10, 1, 1, 0, 2), (4, 3, 37, 29, 20, 3, 1, 1, 1), (2, 3, 60, 51, 16, 3, 2, 0, 1),
+          (3, 4, 31, 30, 11, 5, 1, 2, 1), (9, 40, 14, 15, 12, 1, 1, 0, 1)]
+
+
+@pytest.mark.parametrize("case", SLICED, ids=lambda c: "-".join(map(str, c)))
+def test_sliced_sums_over_pixels_exact(orc32, case):
+    B, C, H, W, M, k, stride, pad, groups = case
+    _, names = _all_three(orc32, B, dict(C=C, H=H, W=W, M=M, k=k, stride=stride, pad=pad, groups=groups), seed=C, fwd=False, bwd_data=False)
+    assert names == ["igemm_kernel<16x32,direct4>"], names
+
+
+def test_quads_on_both_sides_stop_at_an_image():
+    """1x1 windows over 33 pixels an image: what a quad of either operand holds behind an image's last pixel is another channel's."""
+    d = cg.conv_desc(40, 5, 3, 11, 6, 1)
+    x, dy = torch.ones((40, 5, 3, 11), device="cuda"), torch.ones((40, 6, 3, 11), device="cuda")
+    x[:, 2], dy[:, 3] = float("inf"), float("nan")
+    dw, db = conv_bwd_weight(d, x, dy)
+    dw = dw.reshape(6, 5)
+    keep = torch.tensor([[m != 3 and c != 2 for c in range(5)] for m in range(6)], device="cuda")
+    assert bool((dw[keep] == 1320).all()) and not bool(dw[~keep].isfinite().any())
+    assert bool((db[[0, 1, 2, 4, 5]] == 1320).all()) and bool(db[3].isnan())
+
+
 def test_what_lies_behind_a_reduction_stays_out():
     """NaN in the next row's first filter values and in the pixels behind an image's last ones: 27 indices and 35 pixels are no
     whole quads, and what a quad holds beyond them belongs to another sum."""
