@@ -395,8 +395,13 @@ int dropout_launch(const float *x, const uint8_t *mask, float *y, const float *g
 // per_sample: B floats of scratch
 int softmax_ce_launch(const float *z, const int32_t *labels, float *loss, float *dz, float *per_sample, int B, int C,
                       hipStream_t st);
-// dst[n][c_off + c][hw] = src[n][c][hw]  (forward of a channel concat) or the reverse slice copy
-int concat_copy_launch(const float *src, float *dst, int N, int Csrc, int Cdst, int c_off, int HW, int to_concat,
-                       int accumulate, const float *gate, hipStream_t st);
+// dst[n][c_off + c][hw] = src[n][c][hw]  (forward of a channel concat)
+int concat_copy_launch(const float *src, float *dst, int N, int Csrc, int Cdst, int c_off, int HW, hipStream_t st);
+// one channel slice of a concat whose gradient goes to the layer it came from (dst null: that layer wants none)
+struct ConcatSlice { float *dst; int c, c_off, gated, accumulate; };
+constexpr int CONCAT_SLICES = 4;           // inputs a layer can have
+// the slices of one concat, in channel order; C * HW is below 2^29 (cg_net_create)
+int concat_grad_launch(const float *dy, const float *y, int N, int C, int HW, const ConcatSlice *slices, int n_slices,
+                       hipStream_t st);
 
 }  // namespace cg

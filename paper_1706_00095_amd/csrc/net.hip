@@ -500,7 +500,7 @@ extern "C" int cg_train_step(cg_net *net, const float *x, const int32_t *labels,
                 int c, h, w;
                 in_shape(*net, d.inputs[k], &c, &h, &w);
                 const bool in_place = d.inputs[k] >= 0 && net->layers[d.inputs[k]].in_concat == i;
-                if (!in_place) rc = concat_copy_launch(act(d.inputs[k]), out, B, c, ly.C, c_off, ly.H * ly.W, 1, 0, nullptr, S0);
+                if (!in_place) rc = concat_copy_launch(act(d.inputs[k]), out, B, c, ly.C, c_off, ly.H * ly.W, S0);
                 c_off += c;
             }
             break;
@@ -652,22 +652,27 @@ extern "C" int cg_train_step(cg_net *net, const float *x, const int32_t *labels,
             if (want_dx) rc = dropout_launch(dy, masks[i], dx, gate, in_elems, d.drop_p, accum, S0);
             break;
         case CG_LAYER_CONCAT: {
+            ConcatSlice slices[CONCAT_SLICES];
             int c_off = 0;
-            for (int k = 0; k < d.n_inputs && rc == CG_OK; ++k) {
+            for (int k = 0; k < d.n_inputs; ++k) {
                 int c, h, w;
                 in_shape(*net, d.inputs[k], &c, &h, &w);
                 const int sk = d.inputs[k];
+                ConcatSlice s{nullptr, c, c_off, 0, 0};
                 if (sk >= 0 && net->layers[sk].needs_grad) {
                     const int t = concat_target(i, sk);
                     Layer &T = net->layers[t];
                     // through a folded rectifier: gated by the rectifier's output, which is this
                     // layer's own output slice
-                    rc = concat_copy_launch(dy, base + T.grad_off, B, c, ly.C, c_off, ly.H * ly.W, 0,
-                                            T.grad_written ? 1 : 0, t != sk ? base + ly.act_off : nullptr, S0);
+                    s.dst = base + T.grad_off;
+                    s.gated = t != sk;
+                    s.accumulate = T.grad_written ? 1 : 0;
                     T.grad_written = true;
                 }
+                slices[k] = s;
                 c_off += c;
             }
+            rc = concat_grad_launch(dy, base + ly.act_off, B, ly.C, ly.H * ly.W, slices, d.n_inputs, S0);
             break;
         }
         default: break;
