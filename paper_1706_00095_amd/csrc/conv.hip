@@ -741,7 +741,7 @@ FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math)
         f.floats = patch ? (size_t)copy_elems(d, sg) : (size_t)d.groups * sg.R * sg.Kp;
         return f;
     }
-    if (d.stride_h != 1 || d.stride_w != 1) return f;            // the vector kernels read w itself
+    if (d.stride_h != 1 || d.stride_w != 1) return f;            // fewer than eight (channel, phase) rows: w itself is read
     IgemmProblem pp = bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
     pp.math = math;
     f.floats = (size_t)d.M * f.Cg * d.KH * d.KW;
