@@ -10,8 +10,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcg.so")
-# (source, object name, extra flags): the matrix kernels are compiled once per number of bf16 pieces
-SOURCES = [(f"{s}.hip", f"{s}{n}.o", [f"-DCG_NP={n}"]) for n in (3, 2, 1) for s in ("split_gemm", "split_patch", "split_wgrad")] + [
+# (source, object name, extra flags): the matrix kernels are compiled once per number of bf16 pieces, the patch kernel
+# for scattered rows and for others
+SOURCES = [("split_patch.hip", f"split_patch{n}{'s' * s}.o", [f"-DCG_NP={n}", f"-DCG_SCATTER={s}"]) for n in (3, 2, 1) for s in (0, 1)] + [
+    (f"{s}.hip", f"{s}{n}.o", [f"-DCG_NP={n}"]) for n in (3, 2, 1) for s in ("split_gemm", "split_wgrad")] + [
     ("gather.hip", f"gather{m}.o", [f"-DCG_MATH={m}"]) for m in (0, 1, 2)] + [
     (f"{s}.hip", f"{s}.o", []) for s in ("igemm", "direct", "stem", "layers", "conv", "sgd", "net", "api")]
 COMMON = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",

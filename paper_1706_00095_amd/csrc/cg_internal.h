@@ -199,6 +199,14 @@ constexpr int kStemLds = 80 * 1024;          // two blocks a compute unit
 // another launch, one block per channel, instead of a launch of its own.
 struct BiasRider { const float *dy; int N, M, P; float *db; };
 
+// Backward-data of a strided convolution: dy and the filters themselves.  The matrix problem has zeros for taps that a
+// stride phase does not have, and an infinity times zero is a NaN, so sums that are not finite are done again from the taps that
+// exist (sum_of_taps).
+struct StridedTaps {
+    const float *dy, *w;      // w NULL: not such a problem
+    int32_t OH, OW, M, Mg, Cg, KH, KW, sh, sw, bf16;
+};
+
 // C[m][n] = sum_k A(m,k) * B(n,k)   (+ bias), for `groups` independent problems, the K range
 // optionally cut into `splits` slices whose partial results go to consecutive output planes.
 struct IgemmProblem {
@@ -239,6 +247,7 @@ struct IgemmProblem {
         BandGeom band;
         WgradGeom wgrad;
     };
+    StridedTaps taps;         // with c_scatter (read by code that hardly ever runs: behind everything else)
 };
 
 // Fills the derived fields of a patch description (Wp, Rfull, dividers) and decides whether the

@@ -485,6 +485,11 @@ static bool strided_geom(const cg_conv_desc &d, StridedGeom &s, int min_rows = 8
     return true;
 }
 
+static StridedTaps strided_taps(const cg_conv_desc &d, int OH, int OW, const float *dy, const float *w, int math)
+{
+    return StridedTaps{dy, w, OH, OW, d.M, d.M / d.groups, d.C / d.groups, d.KH, d.KW, d.stride_h, d.stride_w, math == CG_MATH_BF16};
+}
+
 static IgemmProblem bwd_data_strided_problem(const cg_conv_desc &d, const StridedGeom &sg, int OH, int OW, const float *dy,
                                              const float *wt, float *dx, int accumulate)
 {
@@ -620,6 +625,7 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         IgemmProblem p = bwd_data_strided_problem(d, sg, OH, OW, dy, prepared ? prepared : wt, dx, accumulate);
         p.gate = gate;
         p.math = math;
+        p.taps = strided_taps(d, OH, OW, dy, w, math);
         const size_t copy = strided_copy_bytes(d, sg);
         const bool patch = bwd_data_strided_patch(d, sg, OH, OW, dy, p) && (ws_bytes >= copy || (p.use_patch = 0));
         if (patch) tap_major_filters(p, p.A.ptr, sg.R, padded16(d.M / d.groups) * sg.Ah * sg.Aw, copy_elems(d, sg));
@@ -627,6 +633,7 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
             IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
             pd.gate = gate;
             pd.math = math;
+            pd.taps = p.taps;
             if (igemm_take_direct(pd, &p)) {
                 const int rs = igemm_scratch_check(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes);
                 return rs ? rs : igemm_launch(pd, stream);
@@ -646,6 +653,7 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         if (strided_geom(d, sg, 1)) {
             IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
             pd.gate = gate;
+            pd.taps = strided_taps(d, OH, OW, dy, w, math);
             if ((pd.direct = direct_choice(pd, false, nullptr, false)) != 0) {
                 const int rc2 = igemm_launch(pd, stream);
                 if (rc2 != CG_EUNSUPPORTED) return rc2;

@@ -42,16 +42,20 @@ __device__ __forceinline__ float ldw(__amdgpu_buffer_rsrc_t r, uint32_t voff)
 }
 
 // One element of C by itself: bias, rectifier, gate, accumulation, the output map.
-__device__ __forceinline__ void store_element(const IgemmProblem &a, uint32_t g, uint32_t m, uint32_t n, float s)
+template <bool SCATTER> __device__ __forceinline__ void store_element(const IgemmProblem &a, uint32_t g, uint32_t m, uint32_t n, float s)
 {
     if (a.bias_mode == 1) s += a.bias[(int64_t)g * a.bias_gstride + m];
     else if (a.bias_mode == 2) s += a.bias[(int64_t)g * a.bias_gstride + n];
     if (a.relu) s = fmaxf(s, 0.f);
     const Info ci = map_info(a.c_col, n);
     int32_t in_group = (int32_t)m * a.c_row_stride + ci.off;
-    if (a.c_scatter) {
+    if constexpr (SCATTER) {
         const Info ri = map_info(a.c_row, m);
         if (!((uint32_t)(ri.a + ci.a) < a.c_limA && (uint32_t)(ri.b + ci.b) < a.c_limB)) return;
+        if (!__builtin_isfinite(s)) {
+            const auto &f = first_argument<IgemmProblem>();
+            s = sum_of_taps(f.taps, f.c_row, f.c_col, g, m, n);
+        }
         in_group = ri.off + ci.off;
     }
     const int64_t idx = (int64_t)g * a.c_gstride + in_group;
@@ -78,6 +82,8 @@ struct DirectArgs {
     BiasRider rider;                         // blocks behind the tiles: a channel of a convolution's bias gradient each
     FastDiv divQP;
 };
+
+static_assert(offsetof(DirectArgs, p) == 0, "the problem is the start of a kernel's arguments");
 
 template <int AKIND, int BKIND>
 __global__ __launch_bounds__(1024) void direct_kernel(const DirectArgs d)
@@ -257,7 +263,7 @@ __global__ __launch_bounds__(1024) void direct_kernel(const DirectArgs d)
         float s = red[row * LS + col];
         for (int w = 1; w < waves; ++w) s += red[(w * MT + (int)row) * LS + (int)col];
         if (p.splits > 1) p.c_ptr[(int64_t)g * p.c_gstride + (int64_t)sp * p.c_split_stride + (int64_t)m * p.c_row_stride + n] = s;
-        else store_element(p, g, m, n, s);
+        else store_element<AKIND == AD_CHECKED>(p, g, m, n, s);       // (strided backward-data)
     }
 }
 

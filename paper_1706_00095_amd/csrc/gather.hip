@@ -390,7 +390,8 @@ __global__ __launch_bounds__(256, 2) void igemm_kernel(const IgemmProblem p)
     // the padding tiles still in flight write into this block's LDS: let them finish before it is released
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();            // every wave has read its last fragments: the stages are free for the epilogue
-    store_tile<TM, TN>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 32), n0 + (uint32_t)(wn * TN * 32), p.N, lane,
+    // (scattered rows: strided backward-data, whose columns are an image's cells under a window)
+    store_tile<TM, TN, std::is_same_v<LB, RowsLoader<NT, true>>>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 32), n0 + (uint32_t)(wn * TN * 32), p.N, lane,
                        smem + wave * EpiLds<TN>::FLOATS);
 }
 
@@ -592,7 +593,7 @@ __global__ __launch_bounds__(256, 2) void igemm_wgrad_kernel(const IgemmProblem 
     // the padding tiles still in flight write into this block's LDS: let them finish before it is released
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();            // every wave has read its last fragments: the stages are free for the epilogue
-    store_tile<TM, TN>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 32), n0 + (uint32_t)(wn * TN * 32), p.N, lane,
+    store_tile<TM, TN, false>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 32), n0 + (uint32_t)(wn * TN * 32), p.N, lane,
                        smem + wave * EpiLds<TN>::FLOATS);
 }
 

@@ -1,5 +1,6 @@
 // Planning of the dense contractions: which kernel, which tile, how many K slices; and the kernels that
 // add the slices and the bias gradient.
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include "cg_internal.h"
@@ -218,6 +219,7 @@ int igemm_launch(const IgemmProblem &p0, hipStream_t stream)
     if ((uint64_t)p.k_per_split * p.splits < p.K || (uint64_t)p.k_per_split * (p.splits - 1) >= p.K) return CG_EINVAL;
     if (p.bias_mode && !p.bias) return CG_EINVAL;
     if (p.A.check && !p.direct) return CG_EUNSUPPORTED;
+    if (p.c_scatter && (!p.taps.dy || !p.taps.w || (p.direct ? !p.A.check : !p.B.check || p.B.lanes_k))) return CG_EINVAL;
     p.A.shift = p.B.shift = 0;
     int rc = normalise_operand(p.A, p.groups);
     if (rc) return rc;
@@ -259,8 +261,7 @@ struct FinishArgs {
     float *c_ptr;
     int32_t c_row_stride;
     IndexMap c_col;
-    int c_scatter;
-    IndexMap c_row;
+    IndexMap c_row;           // SCATTER only
     uint32_t c_limA, c_limB;
     int64_t c_gstride;
     const float *bias;
@@ -277,6 +278,7 @@ struct FinishArgs {
     FastDiv r_divQP;
     float *r_db;
     uint32_t finish_blocks;
+    StridedTaps taps;
 };
 
 // C = (sum over the K slices) + bias, written through the problem's output map.  With few slices a
@@ -287,7 +289,7 @@ struct FinishArgs {
 // (Written out here and in direct.hip: through one shared template the compiler orders this kernel's index arithmetic
 // otherwise, and the pass after the backward weights of 64 images, 13 x 13, 384 -> 384 channels, 3 x 3, two groups, takes
 // 23.7 us, not 21.9.)
-__device__ __forceinline__ void finish_store(const FinishArgs &a, uint32_t i, float s)
+template <bool SCATTER> __device__ __forceinline__ void finish_store(const FinishArgs &a, uint32_t i, float s)
 {
     const uint32_t g = fdiv(i, a.divMN), rem = i - g * a.divMN.d;
     const uint32_t m = fdiv(rem, a.divN), n = rem - m * a.divN.d;
@@ -296,9 +298,13 @@ __device__ __forceinline__ void finish_store(const FinishArgs &a, uint32_t i, fl
     if (a.relu) s = fmaxf(s, 0.f);
     const Info ci = map_info(a.c_col, n);
     int32_t in_group = (int32_t)m * a.c_row_stride + ci.off;
-    if (a.c_scatter) {
+    if constexpr (SCATTER) {
         const Info ri = map_info(a.c_row, m);
         if (!((uint32_t)(ri.a + ci.a) < a.c_limA && (uint32_t)(ri.b + ci.b) < a.c_limB)) return;
+        if (!__builtin_isfinite(s)) {
+            const auto &f = first_argument<FinishArgs>();
+            s = sum_of_taps(f.taps, f.c_row, f.c_col, g, m, n);
+        }
         in_group = ri.off + ci.off;
     }
     const int64_t idx = (int64_t)g * a.c_gstride + in_group;
@@ -312,7 +318,7 @@ __device__ __forceinline__ void finish_store(const FinishArgs &a, uint32_t i, fl
 // where a thread has many; whole passes, us, plain / ahead: one thread per element, 2 slices 33.8 / 39.8, 3 slices
 // 26.9 / 28.4, 7 slices 16.1 / 15.0, 13 slices 16.1 / 14.4; eight rows of threads, 32 slices 44.8 / 49.4, 49 slices 15.3 / 14.0,
 // 64 slices 113.8 / 109.2, 512 slices 55.6 / 44.9.
-template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_finish_kernel(const FinishArgs a)
+template <int ROWS, bool AHEAD, bool SCATTER> __global__ __launch_bounds__(256) void splitk_finish_kernel(const FinishArgs a)
 {
     if (a.r_dy && blockIdx.x >= a.finish_blocks) {       // a rider block: one channel of the bias gradient
         const int m = (int)(blockIdx.x - a.finish_blocks);
@@ -335,7 +341,7 @@ template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_fi
                 for (int u = 0; u < 8; ++u)
                     if (k0 + u < a.splits) s += v[u];
             }
-            finish_store(a, i, s);
+            finish_store<SCATTER>(a, i, s);
         }
         return;
     }
@@ -362,7 +368,7 @@ template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_fi
             s = part[0][el];
 #pragma unroll
             for (int k = 1; k < 8; ++k) s += part[k][el];
-            finish_store(a, i, s);
+            finish_store<SCATTER>(a, i, s);
         }
         __syncthreads();
     }
@@ -493,7 +499,8 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
     a.plane = p.c_split_stride;
     a.splits = (int)pl.splits;
     a.c_ptr = p0.c_ptr; a.c_row_stride = p0.c_row_stride; a.c_col = p0.c_col; a.c_gstride = p0.c_gstride;
-    a.c_scatter = p0.c_scatter; a.c_row = p0.c_row; a.c_limA = p0.c_limA; a.c_limB = p0.c_limB;
+    a.c_row = p0.c_row; a.c_limA = p0.c_limA; a.c_limB = p0.c_limB;
+    a.taps = p0.taps;
     a.bias = p0.bias; a.bias_mode = p0.bias_mode; a.bias_gstride = p0.bias_gstride;
     a.M = p0.M; a.N = p0.N;
     a.divN = make_fastdiv(p0.N);
@@ -507,17 +514,17 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
         riders = (unsigned)rider->M;
         if (rider_taken) *rider_taken = true;
     }
-    if (pl.splits >= 16) {
-        const unsigned blocks = (a.total + 31) / 32 < 65536 ? (a.total + 31) / 32 : 65536;
-        a.finish_blocks = blocks;
-        if (pl.splits >= 40) hipLaunchKernelGGL((splitk_finish_kernel<8, true>), dim3(blocks + riders), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((splitk_finish_kernel<8, false>), dim3(blocks + riders), dim3(256), 0, stream, a);
-    } else {
-        const unsigned blocks = (a.total + 255) / 256 < 16384 ? (a.total + 255) / 256 : 16384;
-        a.finish_blocks = blocks;
-        if (pl.splits >= 6) hipLaunchKernelGGL((splitk_finish_kernel<1, true>), dim3(blocks + riders), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((splitk_finish_kernel<1, false>), dim3(blocks + riders), dim3(256), 0, stream, a);
-    }
+    const bool rows = pl.splits >= 16;
+    const unsigned blocks = rows ? std::min((a.total + 31) / 32, 65536u) : std::min((a.total + 255) / 256, 16384u);
+    a.finish_blocks = blocks;
+    auto launch = [&](auto *kernel) { hipLaunchKernelGGL(kernel, dim3(blocks + riders), dim3(256), 0, stream, a); };
+    auto pick = [&](auto SC) {
+        constexpr bool scatter = decltype(SC)::value;
+        if (rows) pl.splits >= 40 ? launch(&splitk_finish_kernel<8, true, scatter>) : launch(&splitk_finish_kernel<8, false, scatter>);
+        else pl.splits >= 6 ? launch(&splitk_finish_kernel<1, true, scatter>) : launch(&splitk_finish_kernel<1, false, scatter>);
+    };
+    if (p0.c_scatter) pick(std::true_type{});
+    else pick(std::false_type{});
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
 }

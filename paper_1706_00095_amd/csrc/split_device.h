@@ -69,19 +69,6 @@ template <int NP> __device__ __forceinline__ void split8(const float (&f)[8], v4
     for (int t = 0; t < 4; ++t) split8_pair<NP>(f, t, pc);
 }
 
-// Does any lane of the wave hold a sum that is an infinity or a NaN?
-template <int TM, int TN> __device__ __forceinline__ bool not_finite(const v4f (&acc)[TM][TN])
-{
-    float z = 0.f;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) z = fmaf(acc[i][j][e], 0.f, z);
-    return __builtin_expect(__any(!(z == 0.f)), 0);
-}
-
 // The sums of a wave's tile that are not finite, again, by fp32 matrix instructions from the operands themselves, one
 // column tile after the other: for_k(j, add) calls add(a, b) with four reduction indices at a time, one per lane / 16
 // (a[i], b: of row 16 i + lane % 16 and of column 16 j + lane % 16).  What infinities, NaN and sums beyond 2^80

@@ -274,7 +274,8 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
             }
         });
     }
-    store_columns<TM, TN>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), p.N, lane);
+    // (scattered rows: strided backward-data, whose columns are an image's cells under a window)
+    store_columns<TM, TN, std::is_same_v<LB, LoadBRows<1, true>> || std::is_same_v<LB, LoadBRows<2, true>>>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), p.N, lane);
 }
 
 namespace {

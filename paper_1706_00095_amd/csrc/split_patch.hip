@@ -48,7 +48,8 @@ template <int NP, int NSL> struct PatchLds {
 
 // WM x WN x WK waves: rows x pixels x steps (WK = 2: two waves share a tile, each takes every other
 // step, and their sums meet in LDS at the end: for row counts too small to give each wave its own).
-template <int NP, int TM, int WM, int WK, int NSL>
+// SCATTER: strided backward-data (c_scatter).
+template <int NP, int TM, int WM, int WK, int NSL, bool SCATTER>
 __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem p)
 {
     constexpr int WN = 4 / (WM * WK), TN = 128 / (16 * WN), MT = WM * TM * 16, NT = 128;
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
             }
         });
     }
-    store_columns_at<TM, TN>(p, acc, g, 0u, m0 + (uint32_t)(wm * TM * 16), lane, [&](int c) {
+    store_columns_at<TM, TN, SCATTER>(p, acc, g, 0u, m0 + (uint32_t)(wm * TM * 16), lane, [&](int c) {
         const int i = wn * TN * 16 + c;
         if (rs) {
             const Pixel px = pixel(i);
@@ -324,11 +325,11 @@ int launch_cfg(const IgemmProblem &p, hipStream_t stream)
     static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_patch_kernel<NP, TM, WM, WK, NSL>),
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_patch_kernel<NP, TM, WM, WK, NSL, CG_SCATTER>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((split_patch_kernel<NP, TM, WM, WK, NSL>), grid, dim3(256), lds, stream, p);
+    hipLaunchKernelGGL((split_patch_kernel<NP, TM, WM, WK, NSL, CG_SCATTER>), grid, dim3(256), lds, stream, p);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
@@ -348,27 +349,30 @@ template <int NP, int NSL> int launch_tiles(const IgemmProblem &p, int mt, hipSt
 
 }  // namespace
 
-// This file is compiled once per number of pieces (CG_NP), in parallel.
-#define CG_CAT_(a, b) a##b
-#define CG_CAT(a, b) CG_CAT_(a, b)
-int CG_CAT(split_patch_tiles_, CG_NP)(const IgemmProblem &p, int mt, hipStream_t stream)
+// This file is compiled once per number of pieces (CG_NP), for scattered rows (CG_SCATTER) and for others, in parallel.
+#define CG_CAT_(a, b, c, d) a##b##c##d
+#define CG_CAT(a, b, c, d) CG_CAT_(a, b, c, d)
+int CG_CAT(split_patch_tiles_, CG_NP, _, CG_SCATTER)(const IgemmProblem &p, int mt, hipStream_t stream)
 {
     if (p.patch.nsl == 4) return launch_tiles<CG_NP, 4>(p, mt, stream);
     if (p.patch.nsl == 5) return launch_tiles<CG_NP, 5>(p, mt, stream);
     return launch_tiles<CG_NP, 6>(p, mt, stream);
 }
 
-#if CG_NP == 3
-int split_patch_tiles_1(const IgemmProblem &p, int mt, hipStream_t stream);
-int split_patch_tiles_2(const IgemmProblem &p, int mt, hipStream_t stream);
+#if CG_NP == 3 && !CG_SCATTER
+int split_patch_tiles_1_0(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_1_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_2_0(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_2_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_3_1(const IgemmProblem &p, int mt, hipStream_t stream);
 
 namespace {
 
 int patch_launch_tiles(const IgemmProblem &p, int mt, hipStream_t stream)
 {
-    if (p.math == CG_MATH_BF16) return split_patch_tiles_1(p, mt, stream);
-    if (p.math == CG_MATH_BF16X3) return split_patch_tiles_2(p, mt, stream);
-    return split_patch_tiles_3(p, mt, stream);
+    if (p.math == CG_MATH_BF16) return p.c_scatter ? split_patch_tiles_1_1(p, mt, stream) : split_patch_tiles_1_0(p, mt, stream);
+    if (p.math == CG_MATH_BF16X3) return p.c_scatter ? split_patch_tiles_2_1(p, mt, stream) : split_patch_tiles_2_0(p, mt, stream);
+    return p.c_scatter ? split_patch_tiles_3_1(p, mt, stream) : split_patch_tiles_3_0(p, mt, stream);
 }
 
 // Row-tile height.  Two blocks are resident per compute unit (an odd one out runs alone and a little
@@ -541,7 +545,7 @@ int split_patch_launch(const IgemmProblem &p, hipStream_t stream)
     if (p.math != CG_MATH_FP32 && p.math != CG_MATH_BF16 && p.math != CG_MATH_BF16X3) return CG_EINVAL;
     const PatchGeom &g = p.patch;
     if (!g.src || !aligned16(g.src) || g.nsl < 4 || g.nsl > 6 || p.splits != 1 || g.Cred == 0 ||
-        p.K != g.Cred * (uint32_t)(g.KH * g.KW))
+        p.K != g.Cred * (uint32_t)(g.KH * g.KW) || (p.c_scatter && (!p.taps.dy || !p.taps.w)))
         return CG_EINVAL;
     // the filter copy holds M rows of K floats (channels padded to 16) per group, and byte offsets into it stay below the marks
     // that stand for "out of range"

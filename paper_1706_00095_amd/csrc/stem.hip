@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs args)
             for (int v = 0; v < 4; ++v) add(a[v], b[v]);
         }
     });
-    store_columns_at<TM, TN>(p, acc, gr, 0u, m0 + (uint32_t)(wm * TM * 16), lane, [&](int c) {
+    store_columns_at<TM, TN, false>(p, acc, gr, 0u, m0 + (uint32_t)(wm * TM * 16), lane, [&](int c) {
         const Pixel px = pixel(wn * TN * 16 + c);
         return Columns{(uint32_t)((t.n * g.OH + px.oy) * g.OW + px.ox), px.ok ? (uint32_t)min(4, min(g.OW - px.ox, g.Tw - (px.ox - t.tx0))) : 0u};
     });
