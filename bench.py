@@ -26,9 +26,9 @@ PEAK_BF16_MFMA_TFLOPS = 2500.0
 
 
 def fp32_peak(kernel):
-    """What a fp32-mode matrix kernel of the launch log can reach: the gathered kernels multiply in the fp32
-    instruction; those that cut operands in three bf16 pieces take six dense bf16 products for one."""
-    fp32_instruction = kernel.startswith(("igemm_kernel", "igemm_wgrad_kernel")) and "pieces" not in kernel and "band" not in kernel
+    """What a fp32-mode matrix kernel of the launch log can reach: the gathered kernels and the small-tile kernel multiply
+    in the fp32 instruction; those that cut operands in three bf16 pieces take six dense bf16 products for one."""
+    fp32_instruction = kernel.startswith(("igemm_kernel", "igemm_direct_kernel", "igemm_wgrad_kernel")) and "pieces" not in kernel and "band" not in kernel
     return PEAK_FP32_MFMA_TFLOPS if fp32_instruction else PEAK_BF16_MFMA_TFLOPS / 6
 
 

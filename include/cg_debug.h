@@ -34,6 +34,12 @@ int cg_debug_resident_blocks(int blocks);
  * applies, so that tests can compare the two.  Process-wide. */
 int cg_debug_band_kernel(int on);
 
+/* Switch for the kernel that runs small fp32 contractions in one launch (on by
+ * default).  on = 0 leaves them to the kernels for larger ones, and backward-data
+ * of strided convolutions with fewer than eight (channel, stride phase) pairs per
+ * group to plain vector code, so that tests can run small shapes on both.  Process-wide. */
+int cg_debug_direct_kernel(int on);
+
 /* Measurement aid: dst[0..bytes) = src[0..bytes) by a plain kernel (16-byte
  * aligned device pointers, bytes % 16 == 0): a dispatch of known HBM traffic to
  * scale hardware-counter readings of the other kernels by. */

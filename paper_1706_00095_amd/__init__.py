@@ -26,7 +26,7 @@ EXPORTS = [
     "cg_conv_out_shape", "cg_conv_workspace_bytes", "cg_conv_fwd", "cg_conv_bwd_data", "cg_conv_bwd_weight", "cg_conv_bwd_weight_noalloc",
     "cg_conv_fwd_math", "cg_conv_bwd_data_math", "cg_conv_bwd_weight_math",
     "cg_grad_reduce_sgd", "cg_grad_reduce_sgd_multi", "cg_grad_reduce_sgd_tree", "cg_grad_reduce_sgd_tree_multi", "cg_net_create", "cg_net_destroy", "cg_net_param_count", "cg_net_layer_fused", "cg_net_bind",
-    "cg_net_workspace_bytes", "cg_train_step", "cg_net_tensor", "cg_net_tensor_image_stride", "cg_strerror", "cg_version", "cg_last_hip_error", "cg_debug_conv_operand", "cg_debug_copy", "cg_debug_stream", "cg_debug_mfma_loop", "cg_debug_launch_count", "cg_debug_fuse_lrn_pool", "cg_debug_patch_min_tiles", "cg_debug_resident_blocks", "cg_debug_band_kernel",
+    "cg_net_workspace_bytes", "cg_train_step", "cg_net_tensor", "cg_net_tensor_image_stride", "cg_strerror", "cg_version", "cg_last_hip_error", "cg_debug_conv_operand", "cg_debug_copy", "cg_debug_stream", "cg_debug_mfma_loop", "cg_debug_launch_count", "cg_debug_fuse_lrn_pool", "cg_debug_patch_min_tiles", "cg_debug_resident_blocks", "cg_debug_band_kernel", "cg_debug_direct_kernel",
     "cg_profile_enable", "cg_profile_count", "cg_profile_get",
 ]
 
@@ -244,6 +244,10 @@ def cg_debug_patch_min_tiles(tiles):
 
 def cg_debug_resident_blocks(blocks):
     _check(lib().cg_debug_resident_blocks(int(blocks)), "cg_debug_resident_blocks")
+
+
+def cg_debug_direct_kernel(on):
+    _check(lib().cg_debug_direct_kernel(int(bool(on))), "cg_debug_direct_kernel")
 
 
 def cg_debug_band_kernel(on):

@@ -256,6 +256,7 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups);
 // The same for backward-weight: fills Wp, bands, dividers, chooses the staging and the number of K
 // slices (p.splits, units_per_split); returns true if the band kernel can run the problem.
 bool wgrad_plan(WgradGeom &g, uint32_t M, uint32_t N, uint32_t groups, uint32_t images, uint32_t *splits);
+void direct_set_enabled(int on);    // tests run small shapes on the kernels for larger ones
 void wgrad_set_enabled(int on);     // tests compare the band kernel with the gathered one
 // smallest number of C tiles for which the patch kernel is chosen (512; tests lower it)
 void patch_set_resident_blocks(uint32_t blocks);

@@ -1096,6 +1096,12 @@ extern "C" int cg_debug_band_kernel(int on)
     return CG_OK;
 }
 
+extern "C" int cg_debug_direct_kernel(int on)
+{
+    direct_set_enabled(on);
+    return CG_OK;
+}
+
 extern "C" int cg_debug_patch_min_tiles(int tiles)
 {
     if (tiles < 1) return CG_EINVAL;

@@ -290,7 +290,7 @@ template <int AKIND, int BKIND> int launch_cfg(const IgemmProblem &p, int waves,
     int rec = -1;
     if (prof_on()) {
         char name[64];
-        snprintf(name, sizeof name, "igemm_kernel<%dx%d,direct%d>", MT, NT, waves);
+        snprintf(name, sizeof name, "igemm_direct_kernel<%dx%d,%c%c>", MT, NT, "rc4"[AKIND], "rc4"[BKIND]);
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }
     const size_t tab = (size_t)waves * 2 * Table<AKIND, BKIND>::WORDS * 4, sums = (size_t)waves * MT * (NT + 4) * 4;
@@ -329,9 +329,12 @@ static double direct_cost(const IgemmProblem &p, bool a_quads, uint64_t tiles, i
     return f.start + f.step * steps + all * (f.load + (p.B.check ? f.check : 0.)) + f.wave * simd;
 }
 
+static std::atomic<int> g_enabled{1};
+void direct_set_enabled(int on) { g_enabled.store(on ? 1 : 0, std::memory_order_relaxed); }
+
 int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, bool other_copies)
 {
-    if (p.math != CG_MATH_FP32) return 0;
+    if (p.math != CG_MATH_FP32 || !g_enabled.load(std::memory_order_relaxed)) return 0;
     // A gathered from dy or from rows of a matrix beside a B that runs along k as well: neighbouring lanes lie far apart, and
     // beyond a few hundred indices the loads take longer than the second launch (181 x 68 with 2048 indices 35.3 / 12.9)
     if (p.B.lanes_k && p.K > 768) return 0;
@@ -364,7 +367,7 @@ int direct_choice(const IgemmProblem &p, bool a_quads, const SplitPlan *other, b
 // sixteen 0.5 - 1.0 of that.  Error against 64 bits 0.25 to 0.75 of the gathered kernel's.
 int direct_for_slices(const IgemmProblem &p, bool a_quads)
 {
-    if (p.math != CG_MATH_FP32 || !p.B.lanes_k || !a_quads) return 0;
+    if (p.math != CG_MATH_FP32 || !p.B.lanes_k || !a_quads || !g_enabled.load(std::memory_order_relaxed)) return 0;
     const uint64_t tiles = (uint64_t)((p.N + NT - 1) / NT) * ((p.M + MT - 1) / MT) * p.groups;
     return p.N <= 32 || tiles * p.K <= 140000 ? 4 : 0;
 }

@@ -316,8 +316,7 @@ int launch_cfg(const IgemmProblem &p, hipStream_t stream)
     int rec = -1;
     if (prof_on()) {
         char name[64];
-        if (p.patch.Cred % 16) snprintf(name, sizeof name, NP == 1 ? "igemm_kernel<%dx128,patch%d,pieces,bf16>" : NP == 2 ? "igemm_kernel<%dx128,patch%d,pieces,bf16x3>" : "igemm_kernel<%dx128,patch%d,pieces>", MT, NSL);
-        else snprintf(name, sizeof name, NP == 1 ? "igemm_patch%s_kernel<%dx128,%d,bf16>" : NP == 2 ? "igemm_patch%s_kernel<%dx128,%d,bf16x3>" : "igemm_patch%s_kernel<%dx128,%d>",
+        snprintf(name, sizeof name, NP == 1 ? "igemm_patch%s_kernel<%dx128,%d,bf16>" : NP == 2 ? "igemm_patch%s_kernel<%dx128,%d,bf16x3>" : "igemm_patch%s_kernel<%dx128,%d>",
                  WK == 2 && NP == 3 ? "16" : "", MT, NSL);
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }

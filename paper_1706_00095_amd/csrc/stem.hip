@@ -235,7 +235,7 @@ template <int TM, int WM> int launch_fwd(const StemArgs &a, hipStream_t stream)
     int rec = -1;
     if (prof_on()) {
         char name[64];
-        snprintf(name, sizeof name, "igemm_kernel<%dx%d,rows,pieces>", MT, a.g.Tw * a.g.Th);
+        snprintf(name, sizeof name, "igemm_stem_kernel<%d>", MT);
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }
     hipLaunchKernelGGL((stem_fwd_kernel<TM, WM>), grid, dim3(256), (size_t)a.g.lds_bytes, stream, a);

@@ -25,7 +25,7 @@ from test_oracle_net import _small_alexnet_like
 pytestmark = pytest.mark.gpu
 MODES = {"bf16": (cg.CG_MATH_BF16, 2e-2), "bf16x3": (cg.CG_MATH_BF16X3, 1e-4)}
 SGD = (0.01, 0.9, 5e-4, 1.0)
-# backward-data of these exists in fp32 only (fewer than 8 (channel, stride phase) rows: vector kernels)
+# backward-data of these exists in fp32 only (fewer than 8 (channel, stride phase) rows)
 FP32_ONLY_BWD_DATA = {"phase_s2_c1", "phase_s3_c2_g2", "eleven_s2_c1"}
 
 

@@ -24,8 +24,7 @@ pytestmark = pytest.mark.gpu
 EXTRA_SHAPES = {
     # strided backward-data as a stride-1 problem with 6 x 6 taps and 8 rows (2 channels x 4 phases)
     "eleven_s2": (2, dict(C=4, H=29, M=8, k=11, stride=2, pad=3, groups=2)),
-    # fewer than 8 (channel, phase) rows: backward-data by stride phase, and, with more than four taps per
-    # dimension and phase, by the one-thread-per-element kernel
+    # fewer than 8 (channel, phase) rows, up to two and up to six taps per dimension and phase
     "phase_s2_c1": (3, dict(C=1, H=17, M=12, k=3, stride=2, pad=1, groups=1)),
     "phase_s3_c2_g2": (2, dict(C=2, H=20, M=6, k=5, stride=3, pad=2, groups=2)),
     "eleven_s2_c1": (2, dict(C=2, H=29, M=8, k=11, stride=2, pad=3, groups=2)),
@@ -87,19 +86,28 @@ def _all_three(orc32, B, cfg, seed, fwd=True, bwd_data=True, bwd_weight=True, ma
     return d, names
 
 
+@pytest.mark.parametrize("small", [True, False], ids=["", "without_small_tiles"])
 @pytest.mark.parametrize("name", list(SHAPES) + list(EXTRA_SHAPES))
-def test_gathered_and_strided_kernels_exact(orc32, name):
+def test_gathered_and_strided_kernels_exact(orc32, name, small):
+    """small = False: the shapes that run in one launch of small tiles run on the gathered kernel (backward-data of fewer
+    than eight (channel, phase) rows in plain vector code, which logs no launch)."""
     B, cfg = {**SHAPES, **EXTRA_SHAPES}[name]
     if name.startswith("strided_patch"):
         cg.cg_debug_patch_min_tiles(1)
+    cg.cg_debug_direct_kernel(small)
     try:
         d, names = _all_three(orc32, B, cfg, seed=sum(map(ord, name)))
     finally:
         cg.cg_debug_patch_min_tiles(512)
+        cg.cg_debug_direct_kernel(True)
+    few_rows = d.stride_h > 1 and d.C // d.groups * d.stride_h * d.stride_w < 8
     if name.startswith("strided_patch"):
         assert len([n for n in names if n.startswith("igemm_patch")]) >= 1, names
+    elif not small:
+        assert len(names) == (2 if few_rows else 3) and all(n.startswith("igemm_kernel<") for n in names), names
     else:
-        assert all(n.startswith("igemm_kernel") for n in names), names
+        assert len(names) == 3 and all(n.startswith(("igemm_kernel<", "igemm_direct_kernel<")) for n in names), names
+        assert not few_rows or names[1].startswith("igemm_direct_kernel<"), names
     if name.startswith("splitk"):
         # the reduction over pixels was cut: partial planes in the workspace, added by a second kernel
         bias_bytes = 4 * d.M * min(d.N, -(-2048 // d.M))
@@ -145,8 +153,7 @@ def patch_path():
 def test_patch_kernels_exact(orc32, patch_path, name):
     B, cfg = PATCH_SHAPES[name]
     d, names = _all_three(orc32, B, cfg, seed=sum(map(ord, name)), bwd_data=cfg["stride"] == 1, bwd_weight=False)
-    # forward always; backward-data where the output channels of a group (its reduction) come in blocks of 16
-    expect = 1 + (1 if cfg["stride"] == 1 and (cfg["M"] // cfg["groups"]) % 16 == 0 else 0)
+    expect = 1 + (1 if cfg["stride"] == 1 else 0)
     assert len([n for n in names if n.startswith("igemm_patch")]) == expect, names
     if cfg["M"] <= 48:
         assert any(n.startswith("igemm_patch16_kernel") for n in names), names
@@ -176,12 +183,14 @@ def test_patch_kernel_six_chunks_exact(orc32, patch_path, B, C, M, W):
 def test_band_kernel_exact(orc32, name):
     B, cfg = BAND_SHAPES[name]
     cg.cg_debug_band_kernel(True)
+    cg.cg_debug_direct_kernel(False)
     try:
         d, names = _all_three(orc32, B, cfg, seed=sum(map(ord, name)), fwd=False, bwd_data=False)
     finally:
         cg.cg_debug_band_kernel(False)
+        cg.cg_debug_direct_kernel(True)
     # one shape's last band of rows is shorter than the band kernel's pipeline needs: the gathered kernel takes it
-    family = "igemm_kernel" if name == "b3x3_s2_p1" else "igemm_wgrad_kernel"
+    family = "igemm_kernel<" if name == "b3x3_s2_p1" else "igemm_wgrad_kernel"
     assert names and all(n.startswith(family) for n in names), names
 
 

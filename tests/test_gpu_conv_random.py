@@ -1,7 +1,7 @@
 """Randomised differential test of the three convolution passes: 48 seeded descriptors with
 independent kernel heights and widths, strides and paddings per axis, groups and ragged sizes, each
-run through the default kernel choice and again with the thresholds lowered that normally keep
-the raw-row (patch) kernels and the two-launch forward for large problems.  Reference: the CPU
+run through the default kernel choice, without the kernel for small contractions, and with the thresholds lowered
+that normally keep the raw-row (patch) kernels and the two-launch forward for large problems.  Reference: the CPU
 oracle's direct loops; tolerance as everywhere, max-abs-relative <= 1e-3."""
 import numpy as np
 import pytest
@@ -46,12 +46,14 @@ def _tensors(c, seed):
     return x, w, b, dy
 
 
-@pytest.fixture(params=["default", "low_thresholds"])
+@pytest.fixture(params=["default", "without_small_tiles", "low_thresholds"])
 def thresholds(request):
     if request.param == "low_thresholds":
         cg.cg_debug_patch_min_tiles(1)
         cg.cg_debug_resident_blocks(3)
+    cg.cg_debug_direct_kernel(request.param != "without_small_tiles")
     yield request.param
+    cg.cg_debug_direct_kernel(True)
     cg.cg_debug_patch_min_tiles(512)
     cg.cg_debug_resident_blocks(512)
 

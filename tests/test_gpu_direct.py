@@ -32,7 +32,7 @@ def test_direct_kernel_exact(orc32, name):
     cfg = dict(C=C, H=H, W=W, M=M, k=k, stride=stride, pad=pad, groups=groups)
     for p in passes.split():
         _, names = _all_three(orc32, B, cfg, seed=len(name), fwd=p == "fwd", bwd_data=p == "bd", bwd_weight=p == "bw")
-        assert len(names) == 1 and "direct" in names[0], (p, names)
+        assert len(names) == 1 and names[0].startswith("igemm_direct_kernel<"), (p, names)
 
 
 # sums over pixels cut into slices: 1x1 windows at stride 1 (both operands in quads) and others, planes of a multiple of four pixels
@@ -45,7 +45,10 @@ SLICED = [(3, 1, 40, 41, 17, 1, 1, 0, 1), (5, 32, 21, 23, 33, 1, 1, 0, 1), (6, 1
 def test_sliced_sums_over_pixels_exact(orc32, case):
     B, C, H, W, M, k, stride, pad, groups = case
     _, names = _all_three(orc32, B, dict(C=C, H=H, W=W, M=M, k=k, stride=stride, pad=pad, groups=groups), seed=C, fwd=False, bwd_data=False)
-    assert names == ["igemm_kernel<16x32,direct4>"], names
+    # (slices: a workspace for more than the partial sums of the bias gradient)
+    assert names in (["igemm_direct_kernel<16x32,44>"], ["igemm_direct_kernel<16x32,4r>"], ["igemm_direct_kernel<16x32,4c>"]), names
+    d = cg.conv_desc(B, C, H, W, M, k, stride=stride, pad=pad, groups=groups)
+    assert cg.cg_conv_workspace_bytes(d, cg.CG_PASS_BWD_WEIGHT) >= 2 * M * C // groups * k * k * 4
 
 
 def test_quads_on_both_sides_stop_at_an_image():

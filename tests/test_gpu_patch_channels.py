@@ -34,7 +34,7 @@ def test_any_number_of_channels_exact(orc32, case, math):
     B, C, H, W, M, k, stride, pad, groups = case
     cfg = dict(C=C, H=H, W=W, M=M, k=k, stride=stride, pad=pad, groups=groups)
     _, names = _all_three(orc32, B, cfg, seed=C, bwd_weight=False, math=math)
-    assert len([n for n in names if "patch" in n]) >= (1 if C == 3 else 2), names
+    assert len([n for n in names if "igemm_patch" in n]) >= (1 if C == 3 else 2), names
 
 
 @pytest.mark.parametrize("math", [cg.CG_MATH_FP32, cg.CG_MATH_BF16X3])
@@ -49,7 +49,7 @@ def test_an_infinity_in_a_rectangle():
     x, w = torch.ones((1, 17, 40, 130), device="cuda"), torch.ones((20, 17, 3, 3), device="cuda")
     x[0, 16, 21, 77] = float("inf")
     y, names = _logged(lambda: conv_fwd(d, x, w, None))
-    assert any("patch" in n for n in names), names
+    assert any("igemm_patch" in n for n in names), names
     assert bool((~y.isfinite()).nonzero()[:, 2:].unique(dim=0).eq(torch.cartesian_prod(torch.arange(20, 23), torch.arange(76, 79)).cuda()).all())
     assert bool((y[0, :, 20:23, 76:79] == float("inf")).all()) and bool((y[0, :, 1:19, 1:129] == 153).all())
 
@@ -60,7 +60,7 @@ def test_the_next_groups_channels_stay_out(value):
     d = cg.conv_desc(2, 10, 13, 13, 14, 3, pad=1, groups=2)
     x, w = torch.ones((2, 10, 13, 13), device="cuda"), torch.ones((14, 5, 3, 3), device="cuda")
     (ref, names) = _logged(lambda: conv_fwd(d, x, w, None).clone())
-    assert any("patch" in n for n in names), names
+    assert any("igemm_patch" in n for n in names), names
     x[:, 5:] = value
     y = conv_fwd(d, x, w, None)
     assert torch.equal(y[:, :7], ref[:, :7]) and not bool(y[:, 7:].isfinite().any())
@@ -84,7 +84,7 @@ def test_workspace_of_the_other_kernels_is_enough(which):
     p = cg.CG_PASS_FWD if which == "fwd" else cg.CG_PASS_BWD_DATA
     need = cg.cg_conv_workspace_bytes(d, p)
     _, names = _logged(lambda: run(out, torch.empty(need, dtype=torch.uint8, device="cuda")))
-    assert any("patch" in n for n in names), names
+    assert any("igemm_patch" in n for n in names), names
     ref = out.clone()
     cg.cg_debug_patch_min_tiles(512)
     less = cg.cg_conv_workspace_bytes(d, p)
@@ -92,5 +92,5 @@ def test_workspace_of_the_other_kernels_is_enough(which):
     cg.cg_debug_patch_min_tiles(1)
     out.fill_(float("nan"))
     _, names = _logged(lambda: run(out, torch.empty(less, dtype=torch.uint8, device="cuda")))
-    assert not any("patch" in n for n in names), names
+    assert not any("igemm_patch" in n for n in names), names
     assert torch.equal(out, ref)

@@ -17,11 +17,11 @@ FP32, BF16, X3 = cg.CG_MATH_FP32, cg.CG_MATH_BF16, cg.CG_MATH_BF16X3
 
 # (B, C, H, W, M, k, stride, pad, groups), arithmetics, what the kernel's name holds, thresholds lowered
 CASES = {
-    "4_rows": ((2, 1, 21, 18, 12, 3, 2, 1, 1), [FP32], "direct", {}),
-    "4_rows_depthwise": ((2, 6, 15, 14, 6, 3, 2, 1, 6), [FP32], "direct", {}),
-    "phases_without_taps": ((2, 1, 13, 13, 9, 1, 2, 0, 1), [FP32], "direct", {}),
-    "12_rows": ((2, 3, 21, 18, 12, 3, 2, 1, 1), [FP32], "direct", {}),
-    "54_rows_without_taps": ((2, 6, 11, 11, 9, 1, 3, 0, 1), [FP32], "direct", {}),
+    "4_rows": ((2, 1, 21, 18, 12, 3, 2, 1, 1), [FP32], "igemm_direct_kernel", {}),
+    "4_rows_depthwise": ((2, 6, 15, 14, 6, 3, 2, 1, 6), [FP32], "igemm_direct_kernel", {}),
+    "phases_without_taps": ((2, 1, 13, 13, 9, 1, 2, 0, 1), [FP32], "igemm_direct_kernel", {}),
+    "12_rows": ((2, 3, 21, 18, 12, 3, 2, 1, 1), [FP32], "igemm_direct_kernel", {}),
+    "54_rows_without_taps": ((2, 6, 11, 11, 9, 1, 3, 0, 1), [FP32], "igemm_direct_kernel", {}),
     "gathered_12_rows": ((2, 3, 21, 18, 12, 3, 2, 1, 1), [BF16, X3], "igemm_kernel<32x128", {}),
     "gathered_96_rows": ((2, 24, 21, 18, 12, 3, 2, 1, 1), [BF16, X3], "igemm_kernel<", {}),
     "gathered_200_rows": ((2, 50, 33, 40, 12, 3, 2, 1, 1), [BF16, X3], "igemm_kernel<", {}),
@@ -33,10 +33,10 @@ CASES = {
     "pieces_16": ((50, 3, 80, 80, 46, 3, 2, 1, 1), [FP32, BF16, X3], "igemm_kernel<16x128,4rc,pieces", {}),
     "pieces_128": ((32, 27, 79, 79, 60, 3, 2, 1, 1), [FP32], "igemm_kernel<128x128,4rc,pieces", {}),
     "slices_2_pieces_128": ((16, 27, 79, 79, 64, 3, 2, 1, 1), [FP32], "igemm_kernel<128x128,4rc,pieces", {}),
-    "patch_48_rows": ((2, 3, 51, 51, 32, 11, 4, 2, 1), [FP32, BF16, X3], "patch", dict(tiles=1)),
-    "patch_32_rows": ((3, 16, 23, 23, 64, 5, 2, 2, 2), [FP32, BF16, X3], "patch", dict(tiles=1)),
-    "patch_192_rows": ((9, 48, 26, 26, 20, 5, 2, 2, 1), [FP32, BF16, X3], "patch", dict(tiles=1, resident=2)),
-    "patch_120_rows_wide": ((1, 30, 40, 260, 17, 5, 2, 2, 1), [FP32, BF16, X3], "patch", dict(tiles=1)),
+    "patch_48_rows": ((2, 3, 51, 51, 32, 11, 4, 2, 1), [FP32, BF16, X3], "igemm_patch", dict(tiles=1)),
+    "patch_32_rows": ((3, 16, 23, 23, 64, 5, 2, 2, 2), [FP32, BF16, X3], "igemm_patch", dict(tiles=1)),
+    "patch_192_rows": ((9, 48, 26, 26, 20, 5, 2, 2, 1), [FP32, BF16, X3], "igemm_patch", dict(tiles=1, resident=2)),
+    "patch_120_rows_wide": ((1, 30, 40, 260, 17, 5, 2, 2, 1), [FP32, BF16, X3], "igemm_patch", dict(tiles=1)),
 }
 
 
@@ -72,7 +72,7 @@ def test_only_windows_that_hold_it(name, math):
         cg.cg_debug_resident_blocks(512)
     assert len(names) == 1 and kernel in names[0], names
     # the matrix kernel, the copy of the filters before it, the sum of its slices behind it
-    assert cg.cg_debug_launch_count() - before == (1 if kernel == "direct" else 3 if "slices" in name else 2)
+    assert cg.cg_debug_launch_count() - before == (1 if kernel == "igemm_direct_kernel" else 3 if "slices" in name else 2)
     ref = _exact(dy, w, H, W, stride, pad, groups)
     assert np.isfinite(ref).any() and not np.isfinite(ref).all()
     assert np.array_equal(got, ref, equal_nan=True), np.argwhere(~((got == ref) | (np.isnan(got) & np.isnan(ref))))[:4]
