@@ -28,7 +28,7 @@ def main():
     per = collections.defaultdict(dict)
     name = {}
     for r in csv.DictReader(open(counters)):
-        if "cg::igemm" not in r["Kernel_Name"] and "cg::split_" not in r["Kernel_Name"]:
+        if not any(k in r["Kernel_Name"] for k in ("cg::igemm", "cg::split_", "cg::stem_fwd", "cg::direct_")):
             continue
         per[r["Dispatch_Id"]][r["Counter_Name"]] = float(r["Counter_Value"])
         name[r["Dispatch_Id"]] = label(r["Kernel_Name"])

@@ -34,6 +34,12 @@ def label(name):
     if m:
         np_, tm, wm, wk, nsl = map(int, m.groups())
         return f"igemm_patch{'16' if wk == 2 else ''}_kernel<{wm * tm * 16}x128,{nsl}{pieces[np_]}>"
+    m = re.match(r"cg::stem_fwd_kernel<(\d+), (\d+)>", name)
+    if m:
+        return f"igemm_stem_kernel<{16 * int(m.group(1)) * int(m.group(2))}>"
+    m = re.match(r"cg::direct_kernel<(\d), (\d)>", name)
+    if m:
+        return f"igemm_direct_kernel<16x32,{'rc4'[int(m.group(1))]}{'rc4'[int(m.group(2))]}>"
     m = re.match(r"cg::split_wgrad_kernel<(\d+), (\d+), (\d+)>", name)
     if m:
         np_, tm, nsl = map(int, m.groups())
