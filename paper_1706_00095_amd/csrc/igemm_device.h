@@ -226,14 +226,14 @@ __device__ __forceinline__ void store_slabs(const IgemmProblem &p, Turn &&turn, 
 // Does any lane of the wave hold a sum that is an infinity or a NaN?
 template <class Tile, int TM, int TN> __device__ __forceinline__ bool not_finite(const Tile (&acc)[TM][TN])
 {
-    float z = 0.f;
+    float z[4] = {};            // (a chain of its own for every fourth element: an addition waits for the one before it)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < (int)(sizeof(Tile) / 4); ++e) z = fmaf(acc[i][j][e], 0.f, z);
-    return __builtin_expect(__any(!(z == 0.f)), 0);
+            for (int e = 0; e < (int)(sizeof(Tile) / 4); ++e) z[e % 4] = fmaf(acc[i][j][e], 0.f, z[e % 4]);
+    return __builtin_expect(__any(!((z[0] + z[1]) + (z[2] + z[3]) == 0.f)), 0);
 }
 
 // wave tiles of 32x32 accumulators.  SCATTER: the kernel instance runs problems with c_scatter.  (Only the second look at their

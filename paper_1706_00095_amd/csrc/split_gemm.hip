@@ -247,8 +247,11 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
         step(std::integral_constant<int, 0>{}, s);
         if (s + 1 < ns) step(std::integral_constant<int, 1>{}, s + 1);
     }
+    // scattered rows: strided backward-data, whose columns are an image's cells under a window; its sums are looked at when
+    // they are stored, but for those of a slice
+    constexpr bool SCATTER = std::is_same_v<LB, LoadBRows<1, true>> || std::is_same_v<LB, LoadBRows<2, true>>;
     if constexpr (NP == 3) {
-        if (not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
+        if (!(SCATTER && p.c_scatter) && not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
             const uint32_t col = n0 + (uint32_t)((wn * TN + j) * 16 + l16);
             const Info r = map_info(p.B.row, col);
             const uint32_t boff = col < p.N ? (uint32_t)r.off * 4u : OOB_ROW;
@@ -274,8 +277,7 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
             }
         });
     }
-    // (scattered rows: strided backward-data, whose columns are an image's cells under a window)
-    store_columns<TM, TN, std::is_same_v<LB, LoadBRows<1, true>> || std::is_same_v<LB, LoadBRows<2, true>>>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), p.N, lane);
+    store_columns<TM, TN, SCATTER>(p, acc, g, sp, m0 + (uint32_t)(wm * TM * 16), n0 + (uint32_t)(wn * TN * 16), p.N, lane);
 }
 
 namespace {

@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] += ex[(i * TN + j) * 64 + lane];
     }
-    if constexpr (NP == 3) {
+    if constexpr (NP == 3 && !SCATTER) {          // (scattered sums are looked at when they are stored)
         if (not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
             // this lane's pixel: its image, position of its window
             const Pixel px = pixel((wn * TN + j) * 16 + l16);
