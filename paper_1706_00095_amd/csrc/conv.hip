@@ -184,40 +184,48 @@ __global__ __launch_bounds__(256) void prepare_filters_kernel(const PrepTable t)
     }
 }
 
-// General-stride backward-data, gather form, one thread per dx element.  Only the taps with
-// (ih + p - kh) divisible by the stride contribute.
-__global__ __launch_bounds__(256) void bwd_data_strided_kernel(const cg_conv_desc d, int OH, int OW,
-                                                               const float *__restrict__ dy,
-                                                               const float *__restrict__ w, float *__restrict__ dx,
-                                                               const float *__restrict__ gate, int accumulate)
+// General-stride backward-data, gather form, one thread per dx element: the taps of the element's stride phase, four output
+// channels at a time.  dy reads as zero outside its plane, as everywhere.
+struct GatherArgs {
+    cg_conv_desc d;
+    int OH, OW;
+    const float *dy, *w, *gate;
+    float *dx;
+    int accumulate;
+    FastDiv divW, divH, divC, divCg, divSh, divSw;
+};
+
+__global__ __launch_bounds__(256) void bwd_data_strided_kernel(const GatherArgs a)
 {
-    const int Cg = d.C / d.groups, Mg = d.M / d.groups;
-    const size_t total = (size_t)d.N * d.C * d.H * d.W;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const int iw = (int)(i % d.W);
-        size_t r = i / d.W;
-        const int ih = (int)(r % d.H); r /= d.H;
-        const int c = (int)(r % d.C);
-        const int n = (int)(r / d.C);
-        const int g = c / Cg, cl = c - g * Cg;
-        float s = 0.f;
-        const int kh0 = (ih + d.pad_h) % d.stride_h, kw0 = (iw + d.pad_w) % d.stride_w;
-        for (int ml = 0; ml < Mg; ++ml) {
-            const int m = g * Mg + ml;
-            const float *wp = w + ((size_t)m * Cg + cl) * d.KH * d.KW;
-            const float *yp = dy + ((size_t)n * d.M + m) * OH * OW;
-            for (int kh = kh0; kh < d.KH; kh += d.stride_h) {
-                const int oh = (ih + d.pad_h - kh) / d.stride_h;
-                if (ih + d.pad_h - kh < 0 || oh >= OH) continue;
-                for (int kw = kw0; kw < d.KW; kw += d.stride_w) {
-                    const int ow = (iw + d.pad_w - kw) / d.stride_w;
-                    if (iw + d.pad_w - kw < 0 || ow >= OW) continue;
-                    s += yp[oh * OW + ow] * wp[kh * d.KW + kw];
+    const cg_conv_desc &d = a.d;
+    const int Cg = d.C / d.groups, Mg = d.M / d.groups, KK = d.KH * d.KW, P = a.OH * a.OW;
+    const uint32_t total = (uint32_t)d.N * d.C * d.H * d.W;
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+        const uint32_t q = fdiv(i, a.divW), r = fdiv(q, a.divH), n = fdiv(r, a.divC), c = r - n * d.C, g = fdiv(c, a.divCg);
+        const uint32_t y = q - r * d.H + d.pad_h, x = i - q * d.W + d.pad_w;
+        const int oh0 = (int)fdiv(y, a.divSh), ow0 = (int)fdiv(x, a.divSw), kh0 = (int)y - oh0 * d.stride_h, kw0 = (int)x - ow0 * d.stride_w;
+        const float *yp = a.dy + (size_t)(n * d.M + g * Mg) * P, *wp = a.w + ((size_t)g * Mg * Cg + (c - g * Cg)) * KK;
+        float s[4] = {};
+        auto channels = [&](auto UC) {
+            constexpr int U = decltype(UC)::value;
+            for (int kh = kh0, oh = oh0; kh < d.KH; kh += d.stride_h, --oh)
+                for (int kw = kw0, ow = ow0; kw < d.KW; kw += d.stride_w, --ow) {
+                    const bool ok = (uint32_t)oh < (uint32_t)a.OH && (uint32_t)ow < (uint32_t)a.OW;
+                    float v[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] = ok ? yp[u * P + oh * a.OW + ow] : 0.f;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) s[u] = fmaf(v[u], wp[u * Cg * KK + kh * d.KW + kw], s[u]);
                 }
-            }
-        }
-        if (gate && !(gate[i] > 0.f)) s = 0.f;
-        dx[i] = accumulate ? dx[i] + s : s;
+            yp += U * P;
+            wp += U * Cg * KK;
+        };
+        int m = 0;
+        for (; m + 4 <= Mg; m += 4) channels(std::integral_constant<int, 4>{});
+        for (; m < Mg; ++m) channels(std::integral_constant<int, 1>{});
+        float out = (s[0] + s[1]) + (s[2] + s[3]);
+        if (a.gate && !(a.gate[i] > 0.f)) out = 0.f;
+        a.dx[i] = a.accumulate ? a.dx[i] + out : out;
     }
 }
 
@@ -646,11 +654,15 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         if (patch) return igemm_run(p, nullptr, 0, stream);
         return igemm_run(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
     }
-    if ((d.stride_h != 1 || d.stride_w != 1) && math != CG_MATH_FP32) return CG_EUNSUPPORTED;   // plain vector arithmetic below
+    if ((d.stride_h != 1 || d.stride_w != 1) && math != CG_MATH_FP32) return CG_EUNSUPPORTED;   // fewer than eight rows: fp32 only
     if (d.stride_h != 1 || d.stride_w != 1) {
-        // Fewer than eight (channel, phase) rows: direct_kernel (B = 16, 86x95, 504 -> 1 channels, 3x3 stride 2: 51 us; plain
-        // vector code by stride phase took 290), but for dimensions its index maps do not cover
-        if (strided_geom(d, sg, 1)) {
+        // Fewer than eight (channel, phase) rows of a group fill less than half of a matrix tile.  What a matrix tile takes hardly
+        // depends on them, what a thread per element takes goes with rows times indices, and up to 288 of these the
+        // latter is faster: 700 problems, direct_kernel's time over this one's at 2 - 7 rows 1.15 - 6.6, median 2.2 (64 images of 28x28,
+        // 256 channels in as many groups, 3x3 stride 2: 326 / 32 us; by stride phase, as it once was, 234); beyond, 0.4 - 1.1 with
+        // 5 to 7 rows, 0.6 - 1.5 with fewer, and down to 0.1 from a thousand indices on (16 images of 86x95, 504 -> 1 channels,
+        // 3x3 stride 2: 51 us; by stride phase 290).  Dimensions that direct_kernel's index maps do not cover end here too.
+        if (strided_geom(d, sg, 1) && (int64_t)sg.R * sg.Kp > 288) {
             IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
             pd.gate = gate;
             pd.taps = strided_taps(d, OH, OW, dy, w, math);
@@ -659,10 +671,11 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
                 if (rc2 != CG_EUNSUPPORTED) return rc2;
             }
         }
+        const GatherArgs a{d, OH, OW, dy, w, gate, dx, accumulate, make_fastdiv((uint32_t)d.W), make_fastdiv((uint32_t)d.H), make_fastdiv((uint32_t)d.C),
+                           make_fastdiv((uint32_t)(d.C / d.groups)), make_fastdiv((uint32_t)d.stride_h), make_fastdiv((uint32_t)d.stride_w)};
         const size_t total = (size_t)d.N * d.C * d.H * d.W;
         const unsigned blocks = (unsigned)((total + 255) / 256 < 65536 ? (total + 255) / 256 : 65536);
-        hipLaunchKernelGGL(bwd_data_strided_kernel, dim3(blocks), dim3(256), 0, stream, d, OH, OW, dy, w, dx, gate,
-                           accumulate);
+        hipLaunchKernelGGL(bwd_data_strided_kernel, dim3(blocks), dim3(256), 0, stream, a);
         CG_HIP_TRY(hipGetLastError());
         return CG_OK;
     }

@@ -89,8 +89,9 @@ def _all_three(orc32, B, cfg, seed, fwd=True, bwd_data=True, bwd_weight=True, ma
 @pytest.mark.parametrize("small", [True, False], ids=["", "without_small_tiles"])
 @pytest.mark.parametrize("name", list(SHAPES) + list(EXTRA_SHAPES))
 def test_gathered_and_strided_kernels_exact(orc32, name, small):
-    """small = False: the shapes that run in one launch of small tiles run on the gathered kernel (backward-data of fewer
-    than eight (channel, phase) rows in plain vector code, which logs no launch)."""
+    """small = False: the shapes that run in one launch of small tiles run on the gathered kernel.  Backward-data of fewer
+    than eight (channel, phase) rows runs one thread per element then, and with up to 288 rows times indices in any case; that logs
+    no launch."""
     B, cfg = {**SHAPES, **EXTRA_SHAPES}[name]
     if name.startswith("strided_patch"):
         cg.cg_debug_patch_min_tiles(1)
@@ -100,14 +101,14 @@ def test_gathered_and_strided_kernels_exact(orc32, name, small):
     finally:
         cg.cg_debug_patch_min_tiles(512)
         cg.cg_debug_direct_kernel(True)
-    few_rows = d.stride_h > 1 and d.C // d.groups * d.stride_h * d.stride_w < 8
+    s, rows, taps = d.stride_h, d.C // d.groups * d.stride_h * d.stride_w, d.M // d.groups * -(-d.KH // d.stride_h) * -(-d.KW // d.stride_w)
+    few_rows = s > 1 and rows < 8 and (not small or rows * taps <= 288)
     if name.startswith("strided_patch"):
         assert len([n for n in names if n.startswith("igemm_patch")]) >= 1, names
     elif not small:
         assert len(names) == (2 if few_rows else 3) and all(n.startswith("igemm_kernel<") for n in names), names
     else:
-        assert len(names) == 3 and all(n.startswith(("igemm_kernel<", "igemm_direct_kernel<")) for n in names), names
-        assert not few_rows or names[1].startswith("igemm_direct_kernel<"), names
+        assert len(names) == (2 if few_rows else 3) and all(n.startswith(("igemm_kernel<", "igemm_direct_kernel<")) for n in names), names
     if name.startswith("splitk"):
         # the reduction over pixels was cut: partial planes in the workspace, added by a second kernel
         bias_bytes = 4 * d.M * min(d.N, -(-2048 // d.M))

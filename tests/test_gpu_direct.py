@@ -21,7 +21,7 @@ CASES = {
     "planes_of_odd_pixels": ((4, 9, 5, 7, 21, 3, 1, 1, 1), "fwd bd bw"),
     "stride_2": ((5, 19, 13, 11, 37, 5, 2, 1, 1), "fwd bd bw"),
     "stride_beyond_window": ((2, 6, 11, 11, 9, 1, 3, 0, 1), "fwd bd bw"),
-    "fewer_than_8_rows": ((2, 1, 21, 18, 12, 3, 2, 1, 1), "bd"),
+    "fewer_than_8_rows": ((2, 1, 21, 18, 40, 3, 2, 1, 1), "bd"),
     "fewer_than_8_rows_11x11": ((2, 2, 29, 29, 8, 11, 2, 3, 2), "bd"),
 }
 
