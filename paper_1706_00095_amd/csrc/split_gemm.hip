@@ -156,7 +156,7 @@ __device__ __forceinline__ Rsrc rsrc_of(const Operand &op, uint32_t g)
 
 }  // namespace
 
-template <int NP, int TM, int WM, class LA, class LB>
+template <int NP, int TM, int WM, class LA, class LB, bool SCATTER>
 __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(const IgemmProblem p)
 {
     constexpr int WAVES = WM == 8 ? 8 : 4, WN = WAVES / WM, TN = 128 / (16 * WN), MT = WM * TM * 16, NT = 128, NU = 8 / WAVES;
@@ -247,11 +247,8 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
         step(std::integral_constant<int, 0>{}, s);
         if (s + 1 < ns) step(std::integral_constant<int, 1>{}, s + 1);
     }
-    // scattered rows: strided backward-data, whose columns are an image's cells under a window; its sums are looked at when
-    // they are stored, but for those of a slice
-    constexpr bool SCATTER = std::is_same_v<LB, LoadBRows<1, true>> || std::is_same_v<LB, LoadBRows<2, true>>;
-    if constexpr (NP == 3) {
-        if (!(SCATTER && p.c_scatter) && not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
+    if constexpr (NP == 3 && !SCATTER) {          // (scattered sums are looked at when they are stored)
+        if (not_finite(acc)) sums_in_fp32(acc, [&](int j, auto &&add) {
             const uint32_t col = n0 + (uint32_t)((wn * TN + j) * 16 + l16);
             const Info r = map_info(p.B.row, col);
             const uint32_t boff = col < p.N ? (uint32_t)r.off * 4u : OOB_ROW;
@@ -282,7 +279,7 @@ __global__ __launch_bounds__(WM == 8 ? 512 : 256, 2) void split_gemm_kernel(cons
 
 namespace {
 
-template <int NP, int TM, int WM, class LA, class LB>
+template <int NP, int TM, int WM, class LA, class LB, bool SCATTER>
 int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
 {
     constexpr int MT = WM * TM * 16;
@@ -298,11 +295,11 @@ int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
     static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
     static std::atomic<bool> attr_set{false};      // raising the dynamic-LDS limit: once per kernel (repeating it is harmless)
     if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_gemm_kernel<NP, TM, WM, LA, LB>),
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_gemm_kernel<NP, TM, WM, LA, LB, SCATTER>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((split_gemm_kernel<NP, TM, WM, LA, LB>), grid, dim3(WM == 8 ? 512 : 256), lds, stream, p);
+    hipLaunchKernelGGL((split_gemm_kernel<NP, TM, WM, LA, LB, SCATTER>), grid, dim3(WM == 8 ? 512 : 256), lds, stream, p);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
@@ -310,16 +307,16 @@ int launch_cfg(const IgemmProblem &p, const char *modes, hipStream_t stream)
 
 // At most one block a compute unit: eight waves of 16 rows instead of four of 32, so that two share a
 // SIMD (a lone wave issues a step's instructions one after the other: 2.3 us a step).
-template <int AK, template <int> class LB, bool ROWS16, bool WAVES8>
+template <int AK, template <int> class LB, bool ROWS16, bool WAVES8, bool SCATTER = false>
 int launch_rows(const IgemmProblem &p, int mt, const char *modes, hipStream_t stream)
 {
     if constexpr (ROWS16) {
-        if (mt == 16) return launch_cfg<CG_NP, 1, 1, LoadA<1, AK>, LB<2>>(p, modes, stream);
+        if (mt == 16) return launch_cfg<CG_NP, 1, 1, LoadA<1, AK>, LB<2>, SCATTER>(p, modes, stream);
     }
     if (mt != 128) return CG_EUNSUPPORTED;
     if constexpr (WAVES8) if ((uint64_t)((p.N + 127) / 128) * ((p.M + 127) / 128) * p.groups * p.splits <= 256)
-        return launch_cfg<CG_NP, 1, 8, LoadA<1, AK>, LB<1>>(p, modes, stream);
-    return launch_cfg<CG_NP, 2, 4, LoadA<2, AK>, LB<2>>(p, modes, stream);
+        return launch_cfg<CG_NP, 1, 8, LoadA<1, AK>, LB<1>, SCATTER>(p, modes, stream);
+    return launch_cfg<CG_NP, 2, 4, LoadA<2, AK>, LB<2>, SCATTER>(p, modes, stream);
 }
 template <int NU> using BRowsCheck = LoadBRows<NU, true>;
 template <int NU> using BRowsPlain = LoadBRows<NU, false>;
@@ -339,6 +336,8 @@ int CG_CAT(split_gemm_, CG_NP)(const IgemmProblem &p, int mt, bool a_quads, bool
     if (!a_lin || p.B.k.r1_lim) return CG_EUNSUPPORTED;
     // (padding means an image, and images get 128 rows only where there are blocks for more than one a compute unit)
     if (b_quads) return a_quads && b_lin && !bc ? launch_rows<A_QUAD, LoadBK, false, true>(p, mt, modes, stream) : CG_EUNSUPPORTED;
+    // (scattered rows: strided backward-data, whose columns are an image's cells under a window)
+    if (p.c_scatter) return a_quads && bc ? launch_rows<A_QUAD, BRowsCheck, true, false, true>(p, mt, modes, stream) : CG_EUNSUPPORTED;
     if (a_quads)
         return bc ? launch_rows<A_QUAD, BRowsCheck, true, false>(p, mt, modes, stream)
                   : launch_rows<A_QUAD, BRowsPlain, true, true>(p, mt, modes, stream);
