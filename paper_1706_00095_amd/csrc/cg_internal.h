@@ -130,6 +130,7 @@ struct PatchGeom {
     int32_t Wp;               // padded patch width: (OWo-1)*s + KW
     int32_t Rfull;            // slots of a whole image: ((OHo-1)*s + KH) * Wp
     int32_t flip;             // 0: (py, px) = (ky, kx); 1: mirrored taps
+    uint32_t taps, tap_slots; // of every tap_slots taps that are multiplied, this many exist on average (strided backward-data)
     FastDiv divP, divOW, divWp, divRfull, divKW;
     int32_t nsl;              // 64-slot chunks per channel the kernel instance stages (4, 5 or 6); 0 = not usable
     int32_t tiles_per_img;    // 0: blocks own 128 consecutive pixels across image boundaries; > 0: every image is
@@ -252,7 +253,8 @@ struct IgemmProblem {
 
 // Fills the derived fields of a patch description (Wp, Rfull, dividers) and decides whether the
 // patch kernel can run it for N output pixels and M rows: sets g.nsl, returns true if usable.
-bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups);
+bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups, int math);
+bool patch_forced();                // a test has taken the lines out
 // The same for backward-weight: fills Wp, bands, dividers, chooses the staging and the number of K
 // slices (p.splits, units_per_split); returns true if the band kernel can run the problem.
 bool wgrad_plan(WgradGeom &g, uint32_t M, uint32_t N, uint32_t groups, uint32_t images, uint32_t *splits);

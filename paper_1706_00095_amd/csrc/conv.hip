@@ -5,6 +5,7 @@
 // Backward-weight:  dW[m][(c,kh,kw)]  = sum_{(n,oh,ow)} dY[m][(n,oh,ow)] * X(n,c,oh*s-p+kh,ow*s-p+kw)
 // (section 2.1: forward propagation, backward propagation, gradient on the weights; the last
 // one is the first step of every turn in Fig. 3).
+#include <algorithm>
 #include <mutex>
 #include "cg_internal.h"
 #include "split_device.h"
@@ -291,7 +292,8 @@ static bool fwd_patch(const cg_conv_desc &d, int OH, int OW, const float *x, Ige
     g.gstride = (int64_t)Cg * d.H * d.W;
     g.Cred = (uint32_t)Cg; g.Hs = d.H; g.Ws = d.W; g.chan_stride = d.H * d.W; g.img_stride = d.C * d.H * d.W;
     g.OHo = OH; g.OWo = OW; g.s = d.stride_h; g.oy0 = -d.pad_h; g.ox0 = -d.pad_w; g.KH = d.KH; g.KW = d.KW; g.flip = 0;
-    if (!patch_plan(g, (uint32_t)(d.M / G), (uint32_t)d.N * OH * OW, (uint32_t)G) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
+    g.taps = g.tap_slots = 1;
+    if (!patch_plan(g, (uint32_t)(d.M / G), (uint32_t)d.N * OH * OW, (uint32_t)G, p.math) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
     p.patch = g; p.use_patch = 1;
     return true;
 }
@@ -305,21 +307,6 @@ static bool fwd_stem(const cg_conv_desc &d, int OH, int OW, const float *x, cons
     g.N = d.N; g.C = d.C; g.Cg = d.C / d.groups; g.H = d.H; g.W = d.W; g.OH = OH; g.OW = OW; g.s = d.stride_h;
     g.pad_h = d.pad_h; g.pad_w = d.pad_w; g.KH = d.KH; g.KW = d.KW;
     return stem_fwd_plan(g, p.M, p.N, p.groups, gathered_plan(p.M, p.N, p.K, p.groups));
-}
-
-// dy as the patch operand of backward-data at stride 1 (pixels = input positions, mirrored taps)
-static bool bwd_data_patch(const cg_conv_desc &d, int OH, int OW, const float *dy, IgemmProblem &p)
-{
-    const int G = d.groups, Mg = d.M / G;
-    PatchGeom g{};
-    g.src = dy; g.src_elems = (uint64_t)d.N * d.M * OH * OW;
-    g.gstride = (int64_t)Mg * OH * OW;
-    g.Cred = (uint32_t)Mg; g.Hs = OH; g.Ws = OW; g.chan_stride = OH * OW; g.img_stride = d.M * OH * OW;
-    g.OHo = d.H; g.OWo = d.W; g.s = 1; g.oy0 = d.pad_h - (d.KH - 1); g.ox0 = d.pad_w - (d.KW - 1);
-    g.KH = d.KH; g.KW = d.KW; g.flip = 1;
-    if (!patch_plan(g, (uint32_t)(d.C / G), (uint32_t)d.N * d.H * d.W, (uint32_t)G) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
-    p.patch = g; p.use_patch = 1;
-    return true;
 }
 
 static int permute_filters(const float *w, float *dst, int G, int Mg, int Cg, int KK, int bwd, hipStream_t stream)
@@ -469,6 +456,33 @@ static IgemmProblem bwd_data_direct_problem(const cg_conv_desc &d, int OH, int O
     return p;
 }
 
+// Up to 16 rows, channels that are no multiple of 16 and 800 indices or more: where the small-tile kernel would run the problem
+// if the patch kernel did not, it is the faster one (patch kernel's time over its own 1.03 - 1.5, seven problems of 350 to 660
+// tiles; with fewer indices 0.85 - 1.4, twelve problems, median 0.98).
+static bool direct_before_patch(IgemmProblem &pd, const IgemmProblem &p, const PatchGeom &g)
+{
+    return p.M <= 16 && g.Cred % 16 && p.K >= 800 && !patch_forced() && igemm_take_direct(pd, &p);
+}
+
+// dy as the patch operand of backward-data at stride 1 (pixels = input positions, mirrored taps)
+static bool bwd_data_patch(const cg_conv_desc &d, int OH, int OW, const float *dy, IgemmProblem &p)
+{
+    const int G = d.groups, Mg = d.M / G;
+    PatchGeom g{};
+    g.src = dy; g.src_elems = (uint64_t)d.N * d.M * OH * OW;
+    g.gstride = (int64_t)Mg * OH * OW;
+    g.Cred = (uint32_t)Mg; g.Hs = OH; g.Ws = OW; g.chan_stride = OH * OW; g.img_stride = d.M * OH * OW;
+    g.OHo = d.H; g.OWo = d.W; g.s = 1; g.oy0 = d.pad_h - (d.KH - 1); g.ox0 = d.pad_w - (d.KW - 1);
+    g.KH = d.KH; g.KW = d.KW; g.flip = 1;
+    g.taps = g.tap_slots = 1;
+    if (!patch_plan(g, (uint32_t)(d.C / G), (uint32_t)d.N * d.H * d.W, (uint32_t)G, p.math) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
+    IgemmProblem pd = bwd_data_direct_problem(d, OH, OW, dy, nullptr, nullptr, 0);
+    pd.math = p.math;
+    if (direct_before_patch(pd, p, g)) return false;
+    p.patch = g; p.use_patch = 1;
+    return true;
+}
+
 // Backward-data of a convolution with stride (sh, sw) > 1 as ONE stride-1 problem on the matrix
 // cores.  Write an input row as ih + ph = sh*i + rh (cell i, phase rh < sh).  Only the taps
 // kh = rh + sh*a reach it, from output row oh = i - a, so
@@ -592,7 +606,11 @@ static bool bwd_data_strided_patch(const cg_conv_desc &d, const StridedGeom &sg,
     g.Cred = (uint32_t)Mg; g.Hs = OH; g.Ws = OW; g.chan_stride = OH * OW; g.img_stride = d.M * OH * OW;
     g.OHo = sg.Ch; g.OWo = sg.Cw; g.s = 1; g.oy0 = -(sg.Ah - 1); g.ox0 = -(sg.Aw - 1);
     g.KH = sg.Ah; g.KW = sg.Aw; g.flip = 1;
-    if (!patch_plan(g, (uint32_t)sg.R, sg.Np, (uint32_t)G) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
+    g.taps = (uint32_t)(d.KH * d.KW); g.tap_slots = (uint32_t)(sg.Ah * sg.sh * sg.Aw * sg.sw);
+    if (!patch_plan(g, (uint32_t)sg.R, sg.Np, (uint32_t)G, p.math) || (g.Cred % 16 && igemm_in_pieces(p))) return false;
+    IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, nullptr, nullptr, 0);
+    pd.math = p.math;
+    if (direct_before_patch(pd, p, g)) return false;
     p.patch = g; p.use_patch = 1;
     return true;
 }
@@ -951,20 +969,24 @@ size_t conv_ws_bytes(const cg_conv_desc &d, int pass)
         const size_t gathered = igemm_ws_bytes(p);
         StemGeom sg;
         const size_t stem = fwd_stem(d, OH, OW, nullptr, p, sg) ? (size_t)sg.copy_floats * sizeof(float) : 0;
+        IgemmProblem fp32 = p;
         p.math = CG_MATH_BF16;                   // (the mode in which most problems take the patch kernel)
         if (!fwd_patch(d, OH, OW, nullptr, p)) return stem > gathered ? stem : gathered;
         const size_t copy = fwd_copy_bytes(d);
-        return d.C / d.groups % 16 == 0 || copy > gathered ? copy : gathered;
+        if (d.C / d.groups % 16 == 0 && fwd_patch(d, OH, OW, nullptr, fp32)) return copy;
+        return std::max({copy, gathered, stem});
     }
     if (pass == CG_PASS_BWD_DATA) {
         StridedGeom sg;
         if ((d.stride_h != 1 || d.stride_w != 1) && strided_geom(d, sg)) {
             IgemmProblem p = bwd_data_strided_problem(d, sg, OH, OW, nullptr, nullptr, nullptr, 0);
             const size_t gathered = round256((size_t)d.groups * sg.R * sg.Kp * sizeof(float)) + igemm_ws_bytes(p);
+            IgemmProblem fp32 = p;
             p.math = CG_MATH_BF16;
             if (!bwd_data_strided_patch(d, sg, OH, OW, nullptr, p)) return gathered;
             const size_t copy = strided_copy_bytes(d, sg);
-            return d.M / d.groups % 16 == 0 || copy > gathered ? copy : gathered;
+            if (d.M / d.groups % 16 == 0 && bwd_data_strided_patch(d, sg, OH, OW, nullptr, fp32)) return copy;
+            return copy > gathered ? copy : gathered;
         }
         if (d.stride_h != 1 || d.stride_w != 1) return 0;
         IgemmProblem p = bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);

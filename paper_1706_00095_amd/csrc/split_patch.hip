@@ -437,9 +437,10 @@ int patch_launch(const IgemmProblem &p, hipStream_t stream)
 }  // namespace
 
 static std::atomic<uint32_t> g_patch_min_tiles{512};
+bool patch_forced() { return g_patch_min_tiles.load(std::memory_order_relaxed) <= 1; }
 void patch_set_min_tiles(uint32_t t) { g_patch_min_tiles.store(t, std::memory_order_relaxed); }
 
-bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
+bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups, int math)
 {
     g.nsl = 0;
     const int KK = g.KH * g.KW;
@@ -480,7 +481,29 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
         if (T * K < 200000 || K < 250 || KK == 5 || (KK == 4 && M <= 16) || T < (M <= 16 ? 350 : M <= 48 ? 250 : 400) ||
             zeros > g.Cred * (M <= 48 ? 190ull : 125ull))
             return false;
+        // strided backward-data, 17 to 48 rows: by the taps that exist (both kernels multiply the zeros of the others); see below
+        const uint64_t real = (uint64_t)K * g.taps / g.tap_slots;
+        if (math == CG_MATH_FP32 && g.taps < g.tap_slots && M > 16 && M <= 48 && (real < 270 || T * real < 140000 || zeros > g.Cred * 170ull)) return false;
     }
+    // Those problems again, fp32, 780 of them chosen around the lines; times there / here of what is taken out and of what stays:
+    // - strided backward-data, 17 to 48 rows: 0.74 - 1.2, 13 of 18 below 0.97 (35 -> 3 channels 11x11 stride 4, 80 images of
+    //   156x156, 79 / 88 us; 69 -> 3 7x7, 122 of 196x196, 135 / 171); what stays 0.95 - 1.9
+    // - what of a block's products is none of padding, here over there (`share`), is what the times follow where the other kernels
+    //   test no window (forward without padding) and a block is all rows: up to 48 rows and fewer than 700 indices they are within
+    //   15 % of it, with more indices 1.2 times it, with four taps 0.8 times it, with 25 and more 1.1 - 1.7 times it
+    // - more than 48 rows and fewer than 500 tiles: a share below 0.74 0.82 - 0.92 (54 -> 55 channels 3x3, 137 images of 20x22, 56 / 67 us;
+    //   26 -> 269 5x5, ten of 31x35, 63 / 69), above 1.05 - 1.6
+    // - four taps without padding, 49 to 100 rows, fewer than 500 indices 0.73 - 1.08, median 0.92; beyond 0.94 - 1.23
+    const bool few = M <= 48, inside = !g.flip && !g.oy0 && !g.ox0;
+    auto worth = [&](uint64_t pixel_tiles) {
+        if (lim <= 1 || math != CG_MATH_FP32 || (!padded && KK != 4)) return true;
+        if (inside && KK == 4 && !few && M <= 100 && K < 500) return false;
+        const double least = inside && few ? (KK == 4 ? 1.2 : KK >= 25 ? 0.7 : K < 700 ? 1. : 0.8) : !few && T < 500 ? 0.74 : 0.;
+        auto full = [&](uint32_t tile) { return (double)M / ((M + tile - 1) / tile * tile); };
+        const int there = M <= 16 && K >= 180 && T >= 600 ? 16 : gathered_plan(M, N, K, groups).mt;
+        const double here = full(few ? 16 : (uint32_t)patch_mt(M, N, groups)) * g.Cred / ((g.Cred + 15) / 16 * 16) * N / (pixel_tiles * 128.);
+        return here >= least * full((uint32_t)there);
+    };
     // The largest patch any block needs: a fragment read reaches (KH-1)*Wp + KW-1 beyond sigma, and
     // sigma + that stays below the slot count of the block's segments, which is what is counted.
     auto slots = [&](uint32_t n0, uint32_t n1) {
@@ -497,7 +520,7 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
     g.tiles_per_img = 0;
     g.rect_shift = 0;
     g.divTpi = g.divTx = make_fastdiv(1);
-    if (smax <= 4 * 64) { g.nsl = 4; return true; }
+    if (smax <= 4 * 64) { g.nsl = 4; return worth((N + 127) / 128); }
     // large images: blocks that stay inside one image need smaller patches (every image is the same)
     if (N % P) return false;
     int64_t amax = 0;
@@ -532,7 +555,7 @@ bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups)
         g.divRfull = make_fastdiv((uint32_t)g.Rfull);
     }
     g.divTpi = make_fastdiv((uint32_t)g.tiles_per_img);
-    return true;
+    return worth((uint64_t)(N / P) * g.tiles_per_img);
 }
 
 int split_patch_launch(const IgemmProblem &p, hipStream_t stream)
