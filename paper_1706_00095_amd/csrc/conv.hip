@@ -360,7 +360,8 @@ int conv_fwd_impl(const cg_conv_desc &d, const float *x, const float *w, const f
     p.math = math;
     const size_t wt_bytes = fwd_copy_bytes(d);
     // (a copy with padded channels is dropped where the workspace has no room for it)
-    if (fwd_patch(d, OH, OW, x, p) && (d.C / d.groups % 16 == 0 || (ws && ws_bytes >= wt_bytes) || (p.use_patch = 0))) {
+    const bool room = d.C / d.groups % 16 == 0 || (ws && ws_bytes >= wt_bytes), patch = room && fwd_patch(d, OH, OW, x, p);
+    if (patch) {
         const int G = d.groups, Cg = d.C / G, Mg = d.M / G, KK = d.KH * d.KW;
         if (!ws || ws_bytes < wt_bytes) return CG_ENOSPC;
         if (!aligned16(ws)) return CG_EINVAL;
@@ -653,7 +654,7 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         p.math = math;
         p.taps = strided_taps(d, OH, OW, dy, w, math);
         const size_t copy = strided_copy_bytes(d, sg);
-        const bool patch = bwd_data_strided_patch(d, sg, OH, OW, dy, p) && (ws_bytes >= copy || (p.use_patch = 0));
+        const bool patch = ws_bytes >= copy && bwd_data_strided_patch(d, sg, OH, OW, dy, p);
         if (patch) tap_major_filters(p, p.A.ptr, sg.R, padded16(d.M / d.groups) * sg.Ah * sg.Aw, copy_elems(d, sg));
         if (!patch) {
             IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
