@@ -294,14 +294,9 @@ template <int AKIND, int BKIND> int launch_cfg(const IgemmProblem &p, int waves,
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }
     const size_t tab = (size_t)waves * 2 * Table<AKIND, BKIND>::WORDS * 4, sums = (size_t)waves * MT * (NT + 4) * 4;
+    static_assert(16 * 2 * Table<AKIND, BKIND>::WORDS * 4 <= 64 * 1024 && 16 * MT * (NT + 4) * 4 <= 64 * 1024, "what a block of 16 waves gets without asking");
     size_t lds = tab > sums ? tab : sums;
     if (riders && lds < 4096) lds = 4096;                       // a rider block adds up one float a thread
-    static std::atomic<bool> attr_set{false};
-    if (lds > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<AKIND, BKIND>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 16 * MT * (NT + 4) * 4));
-        attr_set.store(true, std::memory_order_release);
-    }
     hipLaunchKernelGGL((direct_kernel<AKIND, BKIND>), dim3((unsigned)tiles + riders), dim3((unsigned)waves * 64), lds, stream, d);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
@@ -316,8 +311,8 @@ template <int AKIND, int BKIND> int launch_cfg(const IgemmProblem &p, int waves,
 // one another, and what the waves of a SIMD load adds up; there K-tiles of a block do, and a second launch adds K slices, a
 // first one makes a copy of the filters.  Chosen by these (below 0.9 of the other) forward became faster by 14 %,
 // backward-data by 45 %, backward-weight by 4 % in the mean, 7 of 660 passes slower than 0.97 (0.77 at worst); one at 9 us
-// is bound by the host.  Mean error against 64 bits 0.6 of the gathered kernel's: shorter chains, and never a longer one
-// than its K slices.
+// is bound by the host.  Mean error against 64 bits 0.6 of the gathered kernel's: a wave's chain is no longer than the larger of
+// its K slice and 144 indices (where there is such a plan).
 static double direct_cost(const IgemmProblem &p, bool a_quads, uint64_t tiles, int waves)
 {
     struct Fit { double start, step, load, check, wave; };
