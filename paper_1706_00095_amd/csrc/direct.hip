@@ -140,6 +140,9 @@ __global__ __launch_bounds__(1024) void direct_kernel(const DirectArgs d)
             to[T::AO * TABLE] = f.off;
             if constexpr (AKIND == AD_CHECKED) { to[T::AA * TABLE] = (uint32_t)f.a; to[T::AB * TABLE] = (uint32_t)f.b; }
         }
+        // other lanes of the wave read this: no instruction, but nothing moves across
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     };
     // the four consecutive indices of this lane in 16 of them: column c of the table
     auto four = [&](int s, int h, int c) {
