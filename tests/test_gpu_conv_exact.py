@@ -116,6 +116,13 @@ def test_gathered_and_strided_kernels_exact(orc32, name, small):
         assert planes >= (16 if "many" in name else 2), planes
 
 
+@pytest.mark.parametrize("C,groups", [(1, 1), (4, 2)])
+def test_strides_beyond_the_index_maps(orc32, C, groups):
+    """More than 2^20 (channel, phase) rows: backward-data by one thread per element, whatever the number of rows."""
+    d, names = _all_three(orc32, 2, dict(C=C, H=5, W=7, M=6, k=4, stride=1100, pad=1, groups=groups), seed=C)
+    assert len(names) == 2 and cg.cg_conv_workspace_bytes(d, cg.CG_PASS_BWD_DATA) == 0, names
+
+
 def test_small_layer_bias_gradient_rides_in_the_k_slice_launch(orc32):
     """Backward-weight of a small layer whose reduction is cut into K slices: two launches in all (the
     matrix kernel and the one that adds the slices, whose extra blocks sum the bias gradient), db exact;
