@@ -130,7 +130,6 @@ struct PatchGeom {
     int32_t Wp;               // padded patch width: (OWo-1)*s + KW
     int32_t Rfull;            // slots of a whole image: ((OHo-1)*s + KH) * Wp
     int32_t flip;             // 0: (py, px) = (ky, kx); 1: mirrored taps
-    uint32_t taps, tap_slots; // of every tap_slots taps that are multiplied, this many exist on average (strided backward-data)
     FastDiv divP, divOW, divWp, divRfull, divKW;
     int32_t nsl;              // 64-slot chunks per channel the kernel instance stages (4, 5 or 6); 0 = not usable
     int32_t tiles_per_img;    // 0: blocks own 128 consecutive pixels across image boundaries; > 0: every image is
@@ -140,6 +139,7 @@ struct PatchGeom {
     FastDiv divTpi;
     uint32_t tile0;           // first pixel tile of this launch (blockIdx.x counts from it)
     uint32_t tile_count;      // pixel tiles of this launch; 0 = all
+    uint32_t taps, tap_slots; // of every tap_slots taps that are multiplied, this many exist on average (strided backward-data)
 };
 
 // Backward-weight seen as  dw[m][(c,kh,kw)] = sum over pixels of dy[m][pix] * x[c][window of pix at (kh,kw)]
