@@ -272,7 +272,7 @@ int split_wgrad_3(const IgemmProblem &p, hipStream_t stream);
 uint64_t stem_copy_floats(int Mg, int Cg, int KH, int KW);        // of one group's filters in pieces
 int stem_fwd_launch(const IgemmProblem &p, const StemGeom &g, hipStream_t stream);
 // direct_kernel: how many waves a problem gets (0: the gathered kernel, whose plan is `other`, is expected to be faster;
-// other NULL: there is none, and the answer is never 0 unless the kernel cannot run it), its launch
+// other NULL: there is none, and the answer is 0 only if the kernel cannot run it or a test has turned it off), its launch
 int direct_launch(const IgemmProblem &p, bool a_quads, bool b_quads, hipStream_t stream);
 // What igemm_run would refuse the scratch memory of a gathered problem for.
 int igemm_scratch_check(const IgemmProblem &p, const void *ws, size_t ws_bytes);

@@ -1,9 +1,10 @@
 // Forward convolutions of few input channels (a net's first layer) on the bf16 matrix instructions, fp32 operands in
 // three pieces (split_device.h).
 //
-// What bounds it: the matrix pipe for about half of the time, and beside it what a block does before and after (bringing
-// its rows, storing), which two blocks a compute unit do not hide (256 images 3x227x227 -> 96, 11x11 stride 4: 446 us, of them
-// 227 for the products, 103 for the rows, 133 for the rest, 50 of those the output's way to memory).
+// What bounds it: the rows, the products and the stores of a block, one after the other, which two blocks a compute unit hide in
+// part; the matrix pipe executes 47 % of the time a unit has work (256 images 3x227x227 -> 96, 11x11 stride 4, one run: 440 us,
+// without 12 of the 13 steps of products 240, without the rows 369, without the stores 343, without products and rows 130).
+
 //
 // The gathered kernel loads every value of a window by an instruction of its own, 121 times a pixel and channel here, and
 // the patch kernel wants 16 channels.  So a block keeps the source rows of a rectangle of at most 128 pixels in LDS, cut into
@@ -282,8 +283,8 @@ int fwd_rows(uint32_t M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 48 ? 48 : M
 
 // Expected times, us, from 200 problems (1 to 8 channels, windows 1x3 to 11x11, strides 1, 2 and 4, planes of 64 to 227
 // pixels a side, up to 80 GFLOP): one standard deviation of the relative error is 22 % here and 28 % for the gathered
-// kernel.  A block here sets up, brings its rows and multiplies whole steps of 32 indices (a third more than there are in an
-// 11x11 window of 3 channels at most) for mt rows.  Chosen by these (below 0.85 of the other) 52 of them became faster by
+// kernel.  A block here sets up, brings its rows and multiplies whole steps of 32 indices (15 % more than there are in an
+// 11x11 window of 3 channels) for mt rows.  Chosen by these (below 0.85 of the other) 52 of them became faster by
 // 33 % in the mean, three slower than 0.97 (0.75 at worst).
 bool stem_fwd_plan(StemGeom &g, uint32_t M, uint32_t N, uint32_t groups, const SplitPlan &other)
 {
