@@ -22,13 +22,17 @@ from pmc_traffic import label
 CLOCK_GHZ, CUS, SIMDS = 2.4, 256, 4
 
 
+def is_matrix_kernel(name):
+    return any(k in name for k in ("cg::igemm", "cg::split_", "cg::stem_fwd", "cg::direct_")) and "splitk_finish" not in name
+
+
 def main():
     counters, trace, out, args = sys.argv[1:5]
     dur = {r["Dispatch_Id"]: int(r["End_Timestamp"]) - int(r["Start_Timestamp"]) for r in csv.DictReader(open(trace))}
     per = collections.defaultdict(dict)
     name = {}
     for r in csv.DictReader(open(counters)):
-        if not any(k in r["Kernel_Name"] for k in ("cg::igemm", "cg::split_", "cg::stem_fwd", "cg::direct_")):
+        if not is_matrix_kernel(r["Kernel_Name"]):
             continue
         per[r["Dispatch_Id"]][r["Counter_Name"]] = float(r["Counter_Value"])
         name[r["Dispatch_Id"]] = label(r["Kernel_Name"])

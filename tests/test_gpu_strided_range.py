@@ -43,7 +43,8 @@ CASES = {
 
 def _exact(dy, w, H, W, stride, pad, groups):
     k, (OH, OW) = w.shape[2], dy.shape[2:]
-    rest = tuple(n - ((o - 1) * stride - 2 * pad + k) for n, o in ((H, OH), (W, OW)))
+    stride, pad = ((v, v) if isinstance(v, int) else v for v in (stride, pad))
+    rest = tuple(n - ((o - 1) * s - 2 * p + k) for n, o, s, p in zip((H, W), (OH, OW), stride, pad))
     dy, w = torch.as_tensor(dy).double(), torch.as_tensor(w).double()
     return torch.nn.functional.conv_transpose2d(dy, w, stride=stride, padding=pad, output_padding=rest, groups=groups).numpy()
 
@@ -79,12 +80,25 @@ def test_only_windows_that_hold_it(name, math):
     assert np.array_equal(got, ref, equal_nan=True), np.argwhere(~((got == ref) | (np.isnan(got) & np.isnan(ref))))[:4]
 
 
-@pytest.mark.parametrize("flags", [0, cg.CG_STEP_BF16X3])
+@pytest.mark.parametrize("C,M,math", [(2, 7, FP32), (2, 60, FP32), (6, 7, FP32), (6, 7, BF16), (6, 7, X3)])
+@pytest.mark.parametrize("stride,pad", [((1, 3), (0, 2)), ((3, 1), (2, 0)), ((2, 3), (1, 0))])
+def test_strides_that_differ(C, M, math, stride, pad):
+    H, W, k, groups = 17, 20, 4, 2
+    d = cg.cg_conv_desc(2, C, H, W, M * groups, k, k, *stride, *pad, groups)
+    rng = np.random.default_rng(C + M)
+    dy, w = (rng.integers(1, 4, size=s).astype(np.float32) for s in ((2, M * groups) + tuple(cg.cg_conv_out_shape(d)), (M * groups, C // groups, k, k)))
+    _spoil(dy)
+    ref = _exact(dy, w, H, W, stride, pad, groups)
+    assert np.isfinite(ref).any() and not np.isfinite(ref).all()
+    assert np.array_equal(host(conv_bwd_data(d, dev(dy), dev(w), math)), ref, equal_nan=True)
+
+
+@pytest.mark.parametrize("C,flags", [(4, 0), (4, cg.CG_STEP_BF16X3), (1, 0)])
 @pytest.mark.parametrize("branches", [1, 2])
-def test_gate_and_accumulation(branches, flags):
+def test_gate_and_accumulation(branches, C, flags):
     """In a net: behind a rectifier, whose gate is applied on the way, and into a gradient that two strided layers share.  The
     infinite gradient comes from weights of the head that add up to 6e38 behind a channel whose output is zero."""
-    C, H, M, OH = 4, 9, 5, 5
+    H, M, OH = 9, 5, 5
     layers = [dict(kind="conv", inputs=[-1], M=C, k=1, stride=1, pad=0, groups=1), dict(kind="relu", inputs=[0])]
     layers += [dict(kind="conv", inputs=[1], M=M, k=3, stride=2, pad=1, groups=1) for _ in range(branches)]
     if branches == 2:
