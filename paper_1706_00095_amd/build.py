@@ -11,8 +11,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcg.so")
 # (source, object name, extra flags): the matrix kernels are compiled once per number of bf16 pieces, the patch kernel
-# for scattered rows and for others
-SOURCES = [("split_patch.hip", f"split_patch{n}{'s' * s}.o", [f"-DCG_NP={n}", f"-DCG_SCATTER={s}"]) for n in (3, 2, 1) for s in (0, 1)] + [
+# for scattered rows and for others, and in three pieces for filters in pieces and in fp32
+SOURCES = [("split_patch.hip", f"split_patch{n}{'s' * s}{'c' * c}.o", [f"-DCG_NP={n}", f"-DCG_SCATTER={s}", f"-DCG_CUT={c}"])
+           for n, s, c in ((3, 0, 0), (3, 1, 0), (3, 0, 1), (3, 1, 1), (2, 0, 1), (2, 1, 1), (1, 0, 1), (1, 1, 1))] + [
     (f"{s}.hip", f"{s}{n}.o", [f"-DCG_NP={n}"]) for n in (3, 2, 1) for s in ("split_gemm", "split_wgrad")] + [
     ("gather.hip", f"gather{m}.o", [f"-DCG_MATH={m}"]) for m in (0, 1, 2)] + [
     (f"{s}.hip", f"{s}.o", []) for s in ("igemm", "direct", "stem", "layers", "conv", "sgd", "net", "api")]

@@ -140,6 +140,7 @@ struct PatchGeom {
     uint32_t tile0;           // first pixel tile of this launch (blockIdx.x counts from it)
     uint32_t tile_count;      // pixel tiles of this launch; 0 = all
     uint32_t taps, tap_slots; // of every tap_slots taps that are multiplied, this many exist on average (strided backward-data)
+    int32_t filter_pieces;    // the filter copy holds this many bf16 pieces of each value; 0: fp32 values
 };
 
 // Backward-weight seen as  dw[m][(c,kh,kw)] = sum over pixels of dy[m][pix] * x[c][window of pix at (kh,kw)]
@@ -202,7 +203,7 @@ struct BiasRider { const float *dy; int N, M, P; float *db; };
 
 // Backward-data of a strided convolution: dy and the filters themselves.  The matrix problem has zeros for taps that a
 // stride phase does not have, and an infinity times zero is a NaN, so sums that are not finite are done again from the taps that
-// exist (sum_of_taps).
+// exist (sum_of_taps).  A problem whose filter copy holds pieces names the filters here too (w, Mg, Cg).
 struct StridedTaps {
     const float *dy, *w;      // w NULL: not such a problem
     int32_t OH, OW, M, Mg, Cg, KH, KW, sh, sw, bf16;
@@ -248,12 +249,14 @@ struct IgemmProblem {
         BandGeom band;
         WgradGeom wgrad;
     };
-    StridedTaps taps;         // with c_scatter (read by code that hardly ever runs: behind everything else)
+    StridedTaps taps;         // with c_scatter or filters in pieces (read by code that hardly ever runs: behind everything else)
 };
 
 // Fills the derived fields of a patch description (Wp, Rfull, dividers) and decides whether the
 // patch kernel can run it for N output pixels and M rows: sets g.nsl, returns true if usable.
 bool patch_plan(PatchGeom &g, uint32_t M, uint32_t N, uint32_t groups, int math);
+// Three pieces, and a workspace with room for them: is the kernel faster with filters cut beforehand than with fp32 ones?
+bool patch_wants_pieces(const IgemmProblem &p);
 bool patch_forced();                // a test has taken the lines out
 // The same for backward-weight: fills Wp, bands, dividers, chooses the staging and the number of K
 // slices (p.splits, units_per_split); returns true if the band kernel can run the problem.
@@ -350,6 +353,7 @@ struct FilterPrep {
     int kind;
     size_t floats;
     int Mg, Cg, KH, KW, sh, sw, Ah, Aw;
+    int pieces;               // PERMUTE_*, STRIDED_TAPS: bf16 pieces of each value (0: fp32 values)
 };
 FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d, int math);
 FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math);

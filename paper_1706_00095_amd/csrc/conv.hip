@@ -59,46 +59,6 @@ __device__ __forceinline__ float transpose_filters_elem(const float *__restrict_
     return w[(((size_t)g * Mg + ml) * Cg + c) * KK + kk];
 }
 
-// Filters as the patch kernel multiplies with them: dst[g][t][c / 16][r][c % 16], t = kh*KW + kw (units of
-// 16 reduction indices, all rows of a unit contiguous: a wave's load is).  c runs over the next multiple of 16, zeros
-// behind the last channel.
-// Forward (bwd = 0): r = output channel, c = input channel: dst = w[g*Mg + r][c][t].
-// Backward-data (bwd = 1): r = input channel, c = output channel: dst = w[g*Mg + c][r][t].
-__device__ __forceinline__ float permute_filters_elem(const float *__restrict__ w, size_t i, int Mg, int Cg, int KK, int bwd)
-{
-    const int R = bwd ? Cg : Mg, Cr = bwd ? Mg : Cg;
-    size_t q = i / 16;
-    const int r = (int)(q % R); q /= R;
-    const int U = (Cr + 15) / 16, c = (int)(q % U) * 16 + (int)(i % 16); q /= U;
-    const int t = (int)(q % KK);
-    const int g = (int)(q / KK);
-    const int m = bwd ? c : r, ci = bwd ? r : c;
-    return c >= Cr ? 0.f : w[(((size_t)g * Mg + m) * Cg + ci) * KK + t];
-}
-
-// Filters as the matrix of strided backward-data (see bwd_data_strided_problem): row (c, rh, rw),
-// reduction index (m, a, b) with filter tap kh = rh + sh*a, kw = rw + sw*b (zero where that tap
-// does not exist).  tap_major = 1: dst[g][t = a*Aw + b][m / 16][row][m % 16] (the patch kernel's order);
-// 0: dst[g][row][m][t] (the gathered kernel's).
-__device__ __forceinline__ float strided_filters_elem(const float *__restrict__ w, size_t i, int Mg, int Cg, int KH, int KW,
-                                                      int sh, int sw, int Ah, int Aw, int tap_major)
-{
-    const int R = Cg * sh * sw, T = Ah * Aw;
-    int m, t, row;
-    size_t q;
-    if (tap_major) {
-        q = i / 16;
-        row = (int)(q % R); q /= R;
-        const int U = (Mg + 15) / 16;
-        m = (int)(q % U) * 16 + (int)(i % 16); q /= U;
-        t = (int)(q % T); q /= T;
-    } else { t = (int)(i % T); q = i / T; m = (int)(q % Mg); q /= Mg; row = (int)(q % R); q /= R; }
-    const int g = (int)q;
-    const int rw = row % sw, rh = (row / sw) % sh, c = row / (sw * sh);
-    const int kh = rh + sh * (t / Aw), kw = rw + sw * (t % Aw);
-    return (kh < KH && kw < KW && m < Mg) ? w[(((size_t)g * Mg + m) * Cg + c) * KH * KW + kh * KW + kw] : 0.f;
-}
-
 // Filters in three bf16 pieces, as a lane of stem_fwd_kernel multiplies with them: word i of
 // dst[g][row / 16][step][piece][lane][4], two bf16 a word: lane (q, l) of a step holds row l's quads 8 * step + 2q and + 1, quad
 // t being columns 4j .. 4j+3 of window row t / quads of (channel, ky); zeros where there is no column, quad or row.
@@ -130,23 +90,6 @@ __global__ __launch_bounds__(256) void transpose_filters_kernel(const float *__r
         wt[i] = transpose_filters_elem(w, i, Mg, Cg, KK);
 }
 
-__global__ __launch_bounds__(256) void permute_filters_kernel(const float *__restrict__ w, float *__restrict__ dst,
-                                                              int G, int Mg, int Cg, int KK, int bwd)
-{
-    const size_t total = bwd ? (size_t)G * Cg * padded16(Mg) * KK : (size_t)G * Mg * padded16(Cg) * KK;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256)
-        dst[i] = permute_filters_elem(w, i, Mg, Cg, KK, bwd);
-}
-
-__global__ __launch_bounds__(256) void strided_filters_kernel(const float *__restrict__ w, float *__restrict__ dst,
-                                                              int G, int Mg, int Cg, int KH, int KW, int sh, int sw,
-                                                              int Ah, int Aw, int tap_major)
-{
-    const size_t total = (size_t)G * (Cg * sh * sw) * (Ah * Aw) * (tap_major ? padded16(Mg) : Mg);
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256)
-        dst[i] = strided_filters_elem(w, i, Mg, Cg, KH, KW, sh, sw, Ah, Aw, tap_major);
-}
-
 // The rearranged filters of several layers in one launch (a net prepares those of all its layers at
 // the start of an iteration): block b belongs to the job whose [first_block, ...) range holds it and
 // writes 1024 consecutive elements of that job's copy.
@@ -154,14 +97,63 @@ constexpr int kPrepJobs = 8;
 struct PrepJob {
     const float *w;
     float *dst;
-    int kind, Mg, Cg, KH, KW, sh, sw, Ah, Aw;
+    int kind, Mg, Cg, KH, KW, sh, sw, Ah, Aw, pieces;
     unsigned first_block;
-    unsigned long long total;
+    unsigned long long total;          // what the threads write: elements of the copy, or pairs of values in pieces
 };
 struct PrepTable {
     PrepJob j[kPrepJobs];
     int n;
 };
+
+__device__ __forceinline__ uint32_t prep_rows(const PrepJob &f)
+{
+    return (uint32_t)(f.kind == CG_PREP_PERMUTE_FWD ? f.Mg : f.kind == CG_PREP_PERMUTE_BWD ? f.Cg : f.Cg * f.sh * f.sw);
+}
+
+// Filters as the patch kernel multiplies with them: dst[g][t][c / 16][r][c % 16], t a tap (units of 16 reduction indices, all
+// rows of a unit contiguous: a wave's load is).  c runs over the next multiple of 16, zeros behind the last channel.
+// Forward: r = output channel, c = input channel, t = kh*KW + kw: dst = w[g*Mg + r][c][t].
+// Backward-data: r = input channel, c = output channel: dst = w[g*Mg + c][r][t].
+// Strided backward-data (see bwd_data_strided_problem): r = (input channel, rh, rw), c = output channel, t = a*Aw + b, with filter
+// tap kh = rh + sh*a, kw = rw + sw*b (zero where that tap does not exist).
+__device__ __forceinline__ float tap_major_value(const PrepJob &f, uint32_t unit, uint32_t r, uint32_t k)
+{
+    const bool fwd = f.kind == CG_PREP_PERMUTE_FWD, strided = f.kind == CG_PREP_STRIDED_TAPS;
+    const uint32_t Cr = (uint32_t)(fwd ? f.Cg : f.Mg), U = (Cr + 15) / 16, T = (uint32_t)(strided ? f.Ah * f.Aw : f.KH * f.KW);
+    const uint32_t gt = unit / U, c = (unit - gt * U) * 16 + k, g = gt / T, t = gt - g * T;
+    uint32_t ci = fwd ? c : r, tap = t;
+    bool ok = c < Cr;
+    if (strided) {
+        const uint32_t q = r / (uint32_t)f.sw, a = t / (uint32_t)f.Aw, kh = q % (uint32_t)f.sh + (uint32_t)f.sh * a,
+                       kw = r - q * (uint32_t)f.sw + (uint32_t)f.sw * (t - a * (uint32_t)f.Aw);
+        ci = q / (uint32_t)f.sh;
+        tap = kh * (uint32_t)f.KW + kw;
+        ok = ok && kh < (uint32_t)f.KH && kw < (uint32_t)f.KW;
+    }
+    return ok ? f.w[(((size_t)g * f.Mg + (fwd ? r : c)) * f.Cg + ci) * (size_t)(f.KH * f.KW) + tap] : 0.f;
+}
+
+// The same as the pieces they are multiplied in: dst[g][t][c / 16][piece][r][c % 16], bf16.  Pair i of values, all its pieces.
+template <int NP> __device__ __forceinline__ void cut_tap_major_pair(const PrepJob &f, uint32_t i)
+{
+    const uint32_t R = prep_rows(f), j = i % 8, q = i / 8, unit = q / R, r = q - unit * R;
+    uint32_t pc[NP], *dst = reinterpret_cast<uint32_t *>(f.dst) + ((size_t)unit * NP * R + r) * 8 + j;
+    split_pair<NP>(tap_major_value(f, unit, r, 2 * j), tap_major_value(f, unit, r, 2 * j + 1), pc);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) dst[(size_t)k * R * 8] = pc[k];
+}
+
+// Filters as the gathered kernel's matrix of strided backward-data: dst[g][r][c][t], as above.
+__device__ __forceinline__ float strided_rows_value(const PrepJob &f, uint32_t i)
+{
+    const uint32_t T = (uint32_t)(f.Ah * f.Aw), R = prep_rows(f);
+    const uint32_t q = i / T, t = i - q * T, u = q / (uint32_t)f.Mg, m = q - u * (uint32_t)f.Mg, g = u / R, r = u - g * R;
+    const uint32_t v = r / (uint32_t)f.sw, kh = v % (uint32_t)f.sh + (uint32_t)f.sh * (t / (uint32_t)f.Aw), kw = r % (uint32_t)f.sw + (uint32_t)f.sw * (t % (uint32_t)f.Aw);
+    return kh < (uint32_t)f.KH && kw < (uint32_t)f.KW
+               ? f.w[(((size_t)g * f.Mg + m) * f.Cg + v / (uint32_t)f.sh) * (size_t)(f.KH * f.KW) + kh * (uint32_t)f.KW + kw] : 0.f;
+}
+
 __global__ __launch_bounds__(256) void prepare_filters_kernel(const PrepTable t)
 {
     int ji = 0;
@@ -174,13 +166,17 @@ __global__ __launch_bounds__(256) void prepare_filters_kernel(const PrepTable t)
     for (int u = 0; u < 4; ++u) {
         const size_t i = base + (size_t)u * 256;
         if (i >= jb.total) break;
+        if (jb.pieces == 3) { cut_tap_major_pair<3>(jb, (uint32_t)i); continue; }
+        if (jb.pieces == 2) { cut_tap_major_pair<2>(jb, (uint32_t)i); continue; }
+        if (jb.pieces == 1) { cut_tap_major_pair<1>(jb, (uint32_t)i); continue; }
         float v;
         if (jb.kind == CG_PREP_TRANSPOSE) v = transpose_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH * jb.KW);
         else if (jb.kind == CG_PREP_PIECES) v = stem_filters_word(jb.w, i, jb.Mg, jb.Cg, jb.KH, jb.KW);
-        else if (jb.kind == CG_PREP_PERMUTE_FWD) v = permute_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH * jb.KW, 0);
-        else if (jb.kind == CG_PREP_PERMUTE_BWD) v = permute_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH * jb.KW, 1);
-        else v = strided_filters_elem(jb.w, i, jb.Mg, jb.Cg, jb.KH, jb.KW, jb.sh, jb.sw, jb.Ah, jb.Aw,
-                                      jb.kind == CG_PREP_STRIDED_TAPS ? 1 : 0);
+        else if (jb.kind == CG_PREP_STRIDED_ROWS) v = strided_rows_value(jb, (uint32_t)i);
+        else {
+            const uint32_t R = prep_rows(jb), q = (uint32_t)i / 16, unit = q / R;
+            v = tap_major_value(jb, unit, q - unit * R, (uint32_t)i % 16);
+        }
         jb.dst[i] = v;
     }
 }
@@ -309,27 +305,27 @@ static bool fwd_stem(const cg_conv_desc &d, int OH, int OW, const float *x, cons
     return stem_fwd_plan(g, p.M, p.N, p.groups, gathered_plan(p.M, p.N, p.K, p.groups));
 }
 
-static int permute_filters(const float *w, float *dst, int G, int Mg, int Cg, int KK, int bwd, hipStream_t stream)
-{
-    const size_t total = bwd ? (size_t)G * Cg * padded16(Mg) * KK : (size_t)G * Mg * padded16(Cg) * KK;
-    const unsigned blocks = (unsigned)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
-    hipLaunchKernelGGL(permute_filters_kernel, dim3(blocks), dim3(256), 0, stream, w, dst, G, Mg, Cg, KK, bwd);
-    CG_HIP_TRY(hipGetLastError());
-    return CG_OK;
-}
-
-// operand A = a plain row-major [rows][K] matrix per group
-static void tap_major_filters(IgemmProblem &p, const float *m, int rows, int K, uint64_t elems)
+// Operand A of the patch kernel = the copy at m that `f` describes, made from w.
+static void tap_major_filters(IgemmProblem &p, const FilterPrep &f, const float *m, const float *w)
 {
     p.A = Operand{};
     p.A.ptr = m;
-    p.A.row = linear_map((uint32_t)rows, K);
-    p.A.k = linear_map((uint32_t)K, 1);
-    p.A.limA = p.A.limB = 1;
-    p.A.gstride = (int64_t)rows * K;
-    p.A.elems = elems;
-    p.A.lanes_k = 1;
+    p.A.gstride = (int64_t)(f.floats / p.groups);
+    p.A.elems = f.floats;
+    p.patch.filter_pieces = f.pieces;
+    p.taps.w = w; p.taps.Mg = f.Mg; p.taps.Cg = f.Cg;
 }
+
+// Describes the copy of the filters that the patch kernel multiplies p with: `values` values.  In the reduced modes it always
+// holds pieces: they take no more room than the values.  Three take half as much again, so a copy into a workspace holds
+// them where the workspace has `room` bytes for them (a net's slots do), and where the kernel is the faster for it
+// (patch_wants_pieces).
+static void tap_major_copy(FilterPrep &f, uint64_t values, const IgemmProblem &p, size_t room)
+{
+    f.pieces = p.math == CG_MATH_BF16 ? 1 : p.math == CG_MATH_BF16X3 ? 2 : values * 6 <= kMaxBufferBytes && values * 6 <= room && patch_wants_pieces(p) ? 3 : 0;
+    f.floats = f.pieces ? (size_t)values / 2 * f.pieces : (size_t)values;
+}
+constexpr size_t kSlotRoom = ~(size_t)0;
 
 // bytes of the rearranged filters the patch kernel multiplies with
 static size_t fwd_copy_bytes(const cg_conv_desc &d)
@@ -339,6 +335,23 @@ static size_t fwd_copy_bytes(const cg_conv_desc &d)
 static size_t bwd_copy_bytes(const cg_conv_desc &d)
 {
     return round256((size_t)d.C * padded16(d.M / d.groups) * d.KH * d.KW * sizeof(float));
+}
+
+static FilterPrep fwd_patch_prep(const cg_conv_desc &d, const IgemmProblem &p, size_t room)
+{
+    FilterPrep f{};
+    f.kind = CG_PREP_PERMUTE_FWD;
+    f.Mg = d.M / d.groups; f.Cg = d.C / d.groups; f.KH = d.KH; f.KW = d.KW;
+    tap_major_copy(f, (uint64_t)d.M * padded16(f.Cg) * d.KH * d.KW, p, room);
+    return f;
+}
+static FilterPrep bwd_patch_prep(const cg_conv_desc &d, const IgemmProblem &p, size_t room)
+{
+    FilterPrep f{};
+    f.kind = CG_PREP_PERMUTE_BWD;
+    f.Mg = d.M / d.groups; f.Cg = d.C / d.groups; f.KH = d.KH; f.KW = d.KW;
+    tap_major_copy(f, (uint64_t)d.C * padded16(f.Mg) * d.KH * d.KW, p, room);
+    return f;
 }
 
 static bool math_ok(int math) { return math == CG_MATH_FP32 || math == CG_MATH_BF16 || math == CG_MATH_BF16X3; }
@@ -362,15 +375,16 @@ int conv_fwd_impl(const cg_conv_desc &d, const float *x, const float *w, const f
     // (a copy with padded channels is dropped where the workspace has no room for it)
     const bool room = d.C / d.groups % 16 == 0 || (ws && ws_bytes >= wt_bytes), patch = room && fwd_patch(d, OH, OW, x, p);
     if (patch) {
-        const int G = d.groups, Cg = d.C / G, Mg = d.M / G, KK = d.KH * d.KW;
         if (!ws || ws_bytes < wt_bytes) return CG_ENOSPC;
         if (!aligned16(ws)) return CG_EINVAL;
+        const FilterPrep f = fwd_patch_prep(d, p, prepared ? kSlotRoom : ws_bytes);
+        float *copy = static_cast<float *>(ws);
         if (!prepared) {
-            const int rc2 = permute_filters(w, static_cast<float *>(ws), G, Mg, Cg, KK, 0, stream);
+            const int rc2 = filter_prep_launch(1, &f, &w, &copy, stream);
             if (rc2) return rc2;
         }
-        tap_major_filters(p, prepared ? prepared : static_cast<const float *>(ws), Mg, padded16(Cg) * KK, (uint64_t)d.M * padded16(Cg) * KK);
-        return igemm_run(p, static_cast<char *>(ws) + wt_bytes, ws_bytes - wt_bytes, stream);
+        tap_major_filters(p, f, prepared ? prepared : copy, w);
+        return igemm_run(p, nullptr, 0, stream);
     }
     StemGeom sg;
     if (fwd_stem(d, OH, OW, x, p, sg) && ws && ws_bytes >= sg.copy_floats * sizeof(float) && aligned16(ws)) {
@@ -622,16 +636,16 @@ static uint64_t copy_elems(const cg_conv_desc &d, const StridedGeom &sg)
 }
 static size_t strided_copy_bytes(const cg_conv_desc &d, const StridedGeom &sg) { return round256((size_t)copy_elems(d, sg) * sizeof(float)); }
 
-static int strided_filters(const float *w, float *dst, const cg_conv_desc &d, const StridedGeom &sg, int tap_major,
-                           hipStream_t stream)
+// patch: in the patch kernel's order, else the gathered kernel's
+static FilterPrep strided_prep(const cg_conv_desc &d, const StridedGeom &sg, bool patch, const IgemmProblem &p, size_t room)
 {
-    const int G = d.groups;
-    const size_t total = tap_major ? (size_t)copy_elems(d, sg) : (size_t)G * sg.R * sg.Kp;
-    const unsigned blocks = (unsigned)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
-    hipLaunchKernelGGL(strided_filters_kernel, dim3(blocks), dim3(256), 0, stream, w, dst, G, d.M / G, d.C / G, d.KH, d.KW,
-                       sg.sh, sg.sw, sg.Ah, sg.Aw, tap_major);
-    CG_HIP_TRY(hipGetLastError());
-    return CG_OK;
+    FilterPrep f{};
+    f.kind = patch ? CG_PREP_STRIDED_TAPS : CG_PREP_STRIDED_ROWS;
+    f.Mg = d.M / d.groups; f.Cg = d.C / d.groups; f.KH = d.KH; f.KW = d.KW;
+    f.sh = sg.sh; f.sw = sg.sw; f.Ah = sg.Ah; f.Aw = sg.Aw;
+    f.floats = (size_t)d.groups * sg.R * sg.Kp;
+    if (patch) tap_major_copy(f, copy_elems(d, sg), p, room);
+    return f;
 }
 
 int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, float *dx, const float *gate, void *ws,
@@ -655,7 +669,8 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         p.taps = strided_taps(d, OH, OW, dy, w, math);
         const size_t copy = strided_copy_bytes(d, sg);
         const bool patch = ws_bytes >= copy && bwd_data_strided_patch(d, sg, OH, OW, dy, p);
-        if (patch) tap_major_filters(p, p.A.ptr, sg.R, padded16(d.M / d.groups) * sg.Ah * sg.Aw, copy_elems(d, sg));
+        const FilterPrep f = strided_prep(d, sg, patch, p, prepared ? kSlotRoom : ws_bytes);
+        if (patch) tap_major_filters(p, f, p.A.ptr, w);
         if (!patch) {
             IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, dy, w, dx, accumulate);
             pd.gate = gate;
@@ -667,7 +682,7 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
             }
         }
         if (!prepared) {
-            const int rc2 = strided_filters(w, wt, d, sg, patch ? 1 : 0, stream);
+            const int rc2 = filter_prep_launch(1, &f, &w, &wt, stream);
             if (rc2) return rc2;
         }
         if (patch) return igemm_run(p, nullptr, 0, stream);
@@ -711,12 +726,13 @@ int conv_bwd_data_impl(const cg_conv_desc &d, const float *dy, const float *w, f
         pp.beside_other_stream = beside_other_stream ? 1 : 0;
         const size_t copy = bwd_copy_bytes(d);
         if (bwd_data_patch(d, OH, OW, dy, pp) && ws_bytes >= copy) {
+            const FilterPrep f = bwd_patch_prep(d, pp, prepared ? kSlotRoom : ws_bytes);
             if (!prepared) {
-                const int rc2 = permute_filters(w, wt, G, Mg, Cg, KK, 1, stream);
+                const int rc2 = filter_prep_launch(1, &f, &w, &wt, stream);
                 if (rc2) return rc2;
             }
-            tap_major_filters(pp, wuse, Cg, padded16(Mg) * KK, (uint64_t)d.C * padded16(Mg) * KK);
-            return igemm_run(pp, static_cast<char *>(ws) + copy, ws_bytes - copy, stream);
+            tap_major_filters(pp, f, wuse, w);
+            return igemm_run(pp, nullptr, 0, stream);
         }
     }
     const bool in_place = bwd_data_reads_filters_in_place(d);
@@ -756,10 +772,7 @@ FilterPrep conv_fwd_filter_prep(const cg_conv_desc &d, int math)
         f.floats = (size_t)sg.copy_floats;
         return f;
     }
-    f.kind = CG_PREP_PERMUTE_FWD;
-    f.Mg = d.M / d.groups; f.Cg = d.C / d.groups; f.KH = d.KH; f.KW = d.KW;
-    f.floats = (size_t)d.M * padded16(f.Cg) * d.KH * d.KW;
-    return f;
+    return fwd_patch_prep(d, p, kSlotRoom);
 }
 
 FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math)
@@ -776,19 +789,14 @@ FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math)
         IgemmProblem pd = bwd_data_strided_direct_problem(d, sg, OH, OW, nullptr, nullptr, nullptr, 0);
         pd.math = math;
         if (!patch && igemm_take_direct(pd, &p)) return f;
-        f.kind = patch ? CG_PREP_STRIDED_TAPS : CG_PREP_STRIDED_ROWS;
-        f.sh = sg.sh; f.sw = sg.sw; f.Ah = sg.Ah; f.Aw = sg.Aw;
-        f.floats = patch ? (size_t)copy_elems(d, sg) : (size_t)d.groups * sg.R * sg.Kp;
-        return f;
+        return strided_prep(d, sg, patch, p, kSlotRoom);
     }
     if (d.stride_h != 1 || d.stride_w != 1) return f;            // fewer than eight (channel, phase) rows: w itself is read
     IgemmProblem pp = bwd_data_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
     pp.math = math;
     f.floats = (size_t)d.M * f.Cg * d.KH * d.KW;
-    if (bwd_data_patch(d, OH, OW, nullptr, pp)) {
-        f.kind = CG_PREP_PERMUTE_BWD;
-        f.floats = (size_t)d.C * padded16(f.Mg) * d.KH * d.KW;
-    } else if (!bwd_data_reads_filters_in_place(d)) {
+    if (bwd_data_patch(d, OH, OW, nullptr, pp)) return bwd_patch_prep(d, pp, kSlotRoom);
+    if (!bwd_data_reads_filters_in_place(d)) {
         IgemmProblem pd = bwd_data_direct_problem(d, OH, OW, nullptr, nullptr, nullptr, 0);
         pd.math = math;
         if (igemm_take_direct(pd, &pp)) return f;
@@ -800,14 +808,14 @@ FilterPrep conv_bwd_data_filter_prep(const cg_conv_desc &d, int math)
 size_t conv_filter_prep_max_floats(const cg_conv_desc &d)
 {
     const size_t fwd = (size_t)d.M * padded16(d.C / d.groups), bwd = (size_t)d.C * padded16(d.M / d.groups);
-    size_t m = (fwd > bwd ? fwd : bwd) * d.KH * d.KW;
+    size_t m = (fwd > bwd ? fwd : bwd) * d.KH * d.KW / 2 * 3;          // (three pieces of each value)
     int OH, OW;
     StemGeom st;
     if (conv_check(&d, &OH, &OW) == CG_OK && fwd_stem(d, OH, OW, nullptr, fwd_problem(d, OH, OW, nullptr, nullptr, nullptr, nullptr), st) && st.copy_floats > m)
         m = (size_t)st.copy_floats;
     StridedGeom sg;
     if ((d.stride_h != 1 || d.stride_w != 1) && strided_geom(d, sg)) {
-        const size_t s2 = (size_t)copy_elems(d, sg);
+        const size_t s2 = (size_t)copy_elems(d, sg) / 2 * 3;
         if (s2 > m) m = s2;
     }
     return m;
@@ -823,12 +831,12 @@ int filter_prep_launch(int n, const FilterPrep *jobs, const float *const *w, flo
             const FilterPrep &f = jobs[i];
             if (f.kind == CG_PREP_NONE || f.floats == 0) { ++i; continue; }
             if (!w[i] || !dst[i] || !aligned16(dst[i])) return CG_EINVAL;
-            const unsigned long long need = (f.floats + 1023) / 1024;
+            const unsigned long long items = f.pieces ? f.floats / f.pieces : f.floats, need = (items + 1023) / 1024;
             if (blocks + need >= (1ull << 31)) break;
             PrepJob &j = t.j[t.n++];
             j.w = w[i]; j.dst = dst[i]; j.kind = f.kind; j.Mg = f.Mg; j.Cg = f.Cg; j.KH = f.KH; j.KW = f.KW;
             j.sh = f.sh; j.sw = f.sw; j.Ah = f.Ah; j.Aw = f.Aw;
-            j.first_block = (unsigned)blocks; j.total = f.floats;
+            j.pieces = f.pieces; j.first_block = (unsigned)blocks; j.total = items;
             blocks += need;
             ++i;
         }

@@ -27,6 +27,7 @@ __device__ __forceinline__ void block_sync_lds()
 
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));      // eight bf16: one piece of eight values
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // Two fp32 values cut into NP bf16 pieces, most significant first, each piece the nearest even of what
 // the pieces before it left.  Three pieces hold 24 bits.  They are cut from the value times 2^24: the
@@ -44,13 +45,12 @@ template <int NP> __device__ __forceinline__ void split_pair(float x0, float x1,
     }
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        bf16x2 h;
-        h[0] = (__bf16)x0;
-        h[1] = (__bf16)x1;
-        pc[k] = __builtin_bit_cast(uint32_t, h);
+        pc[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
         if (k + 1 < NP) {
-            x0 -= (float)h[0];
-            x1 -= (float)h[1];
+            uint32_t h = pc[k];
+            asm("" : "+v"(h));             // both values from the pair: else each is converted once more on its own, 17 instructions
+            x0 -= __uint_as_float(h << 16);
+            x1 -= __uint_as_float(h & 0xffff0000u);
         }
     }
 }

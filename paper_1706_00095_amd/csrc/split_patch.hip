@@ -15,12 +15,16 @@
 //
 // What bounds it: the matrix pipe.  v_mfma_f32_16x16x32_bf16 rather than 32x32x16: on random operands
 // the former holds 1970 TFLOP/s, the latter 1700 (power; both 2450 on zeros), with the same LDS traffic
-// for the same wave tile.
+// for the same wave tile.  Power bounds the rest too: the clock stands at 2.0 GHz of 2.4 with the pipe 53 % busy, and what a
+// variant leaves out comes off the time whether or not it overlapped (256 images of 13x13, 256 -> 384 channels 3x3, 375 us: cutting
+// filters 55, bringing and cutting the patch 26, reading fragments 35, own sums 20).  So the filters come cut.
 //
 // Split of the work.  A block is four waves and 128 pixels; wave w owns 16*TM rows of its own and
 // ALL 128 pixels.  So the filters are shared by nobody and need no LDS: a lane fetches its eight
-// consecutive reduction indices of a row as two 16-byte loads straight from L2 (the filter copy is
-// laid out so that a wave's load is contiguous), and cuts them in registers, once per value.  The
+// consecutive reduction indices of a row straight from L2 (the filter copy is laid out so that a wave's load is
+// contiguous), a 16-byte load per piece, cut once by the kernel that makes the copy: every pixel tile cut the same values
+// again before (375 -> 346 us there; 5x5 of 48 rows 670 -> 568).  Where a workspace has no room for three pieces
+// (half as much again as the values) the copy is fp32, two loads, and a lane cuts its values in registers.  The
 // image patch is cut once per block, on its way into LDS, 32 channels at a time, as
 // [piece][octet of channels][slot][8 channels]: a lane's operand is then one 16-byte read per piece
 // whose address runs over consecutive slots, and one patch serves every tap.  There is no barrier
@@ -38,9 +42,14 @@ namespace cg {
 
 namespace {
 
-template <int NP, int NSL> struct PatchLds {
-    // in 16-byte units; behind the four octets of every piece lies one unit of zeros
-    static constexpr int SLOTS = NSL * 64, ZERO = 4 * SLOTS, PLANE = ZERO + 1;
+template <int NP, int TM, int WK, int NSL, bool CUT> struct PatchLds {
+    // In 16-byte units; behind the octets of every piece lies one unit of zeros.  Four octets of channels are a group's; where
+    // registers allow no third block and two more octets find room beside another block, the octets of the groups go round: a
+    // group's first two are stored while the group before is multiplied, and a wave holds 16 values on their way, not 32, which is
+    // what lets 192-row tiles take filters in pieces (256 images of 13x13, 3x3, two groups, 384 -> 384 channels, backward-data 331 -> 285 us
+    // with it; fp32 filters 310).  Beside fp32 filters it is no gain (310 / 321).
+    static constexpr bool RING = CUT && NSL == 4 && TM >= 2 && WK == 1;
+    static constexpr int OCTETS = RING ? 6 : 4, SLOTS = NSL * 64, ZERO = OCTETS * SLOTS, PLANE = ZERO + 1;
     static constexpr size_t BYTES = (size_t)NP * PLANE * 16;
 };
 
@@ -48,13 +57,14 @@ template <int NP, int NSL> struct PatchLds {
 
 // WM x WN x WK waves: rows x pixels x steps (WK = 2: two waves share a tile, each takes every other
 // step, and their sums meet in LDS at the end: for row counts too small to give each wave its own).
-// SCATTER: strided backward-data (c_scatter).
-template <int NP, int TM, int WM, int WK, int NSL, bool SCATTER>
+// SCATTER: strided backward-data (c_scatter).  CUT: the filter copy holds pieces, else fp32 (only with three pieces).
+template <int NP, int TM, int WM, int WK, int NSL, bool SCATTER, bool CUT>
 __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem p)
 {
     constexpr int WN = 4 / (WM * WK), TN = 128 / (16 * WN), MT = WM * TM * 16, NT = 128;
     static_assert(WM * WN * WK == 4 && TN % 2 == 0, "four waves");
-    using L = PatchLds<NP, NSL>;
+    static_assert(CUT || NP == 3, "fewer pieces take no more room than the values");
+    using L = PatchLds<NP, TM, WK, NSL, CUT>;
     extern __shared__ __attribute__((aligned(16))) v4u lds[];        // the pieces of the patch (PatchLds)
 
     const PatchGeom &pg = p.patch;
@@ -105,10 +115,11 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     const int32_t R0 = (int32_t)((((bA == bB) ? oyB : (uint32_t)pg.OHo - 1) - oyA) * pg.s + pg.KH) * pg.Wp;
 
     // global byte offset of every patch slot this lane loads (or out of range: padding, unused slots)
-    uint32_t voff[NSL];
+    const int chunk0 = L::RING ? 2 * (wave / 2) : 0;
+    uint32_t voff[L::RING ? 2 : NSL];
 #pragma unroll
-    for (int e = 0; e < NSL; ++e) {
-        const int32_t j = e * 64 + lane;
+    for (int e = 0; e < (L::RING ? 2 : NSL); ++e) {
+        const int32_t j = (chunk0 + e) * 64 + lane;
         const uint32_t d = j < R0 ? 0u : 1u + fdiv((uint32_t)(j - R0), pg.divRfull);
         const int32_t local = j - (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull);
         const uint32_t r = fdiv((uint32_t)local, pg.divWp), c = (uint32_t)local - r * (uint32_t)pg.Wp;
@@ -131,14 +142,16 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
         const int32_t sg = (d == 0 ? 0 : R0 + (int32_t)(d - 1) * pg.Rfull) + (int32_t)((px.oy - oylo) * pg.s) * pg.Wp + (int32_t)((px.ox - tx0) * pg.s);
         sig[j] = px.ok ? sg : 0;
     }
-    // byte offset of this lane's eight floats in a unit of the filter copy [unit][row][16]
+    // byte offset of this lane's eight values in a unit of the filter copy [unit][row][16], or in the first piece of
+    // [unit][piece][row][16]
+    constexpr uint32_t ROW_BYTES = CUT ? 32u : 64u;
     uint32_t arow[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const uint32_t row = m0 + (uint32_t)((wm * TM + i) * 16 + l16);
-        arow[i] = row < p.M ? row * 64u + (uint32_t)(q & 1) * 32u : OOB_ROW;
+        arow[i] = row < p.M ? row * ROW_BYTES + (uint32_t)(q & 1) * (ROW_BYTES / 2) : OOB_ROW;
     }
-    const uint32_t unit_bytes = p.M * 64u;      // unit = tap * ncb16 + 16-channel block
+    const uint32_t piece_bytes = p.M * ROW_BYTES, unit_bytes = piece_bytes * (CUT ? NP : 1);      // unit = tap * ncb16 + 16-channel block
 
     v4f acc[TM][TN];
 #pragma unroll
@@ -146,29 +159,39 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    // ---- patch: wave w brings channels 8w..8w+7 of a group, 64 slots at a time -----------------------
-    float pr[NSL][8];
-    auto load_chunk = [&](auto EC, int grp) {
+    // ---- patch: a wave brings eight channels of a group (an octet), 64 slots (a chunk) at a time: wave w all chunks of
+    // octet w, or, going round, chunks 2 * (w / 2) and the next of octet w % 2 and, once these are stored, of octet 2 + w % 2 -----
+    constexpr bool RING = L::RING;
+    constexpr int kStoreHalf = 3;               // of a group's steps, the one in front of which the next one's first half is stored
+    constexpr int NCH = RING ? 2 : NSL;         // chunks on their way at a time
+    float pr[NCH][8];
+    auto load_chunk = [&](auto EC, int grp, int half) {
         constexpr int e = decltype(EC)::value;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const int c = grp * 32 + wave * 8 + t;
+            const int c = grp * 32 + (RING ? half * 2 + wave % 2 : wave) * 8 + t;
             const uint32_t soff = c < (int)pg.Cred ? (uint32_t)(c * pg.chan_stride) * 4u : OOB_K;
             pr[e][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrcB, voff[e], soff, 0));
         }
     };
-    auto store_chunk = [&](auto EC) {
-        constexpr int e = decltype(EC)::value;
-        v4u pc[NP];
-        split8<NP>(pr[e], pc);
+    // plane of octet o of the group whose first one lies in plane `first`
+    auto plane_of = [&](int first, int o) { return RING && first + o >= L::OCTETS ? first + o - L::OCTETS : first + o; };
+    auto store_chunks = [&](int first, int half) {
+        const int at = plane_of(first, RING ? half * 2 + wave % 2 : wave) * L::SLOTS + chunk0 * 64 + lane;
 #pragma unroll
-        for (int k = 0; k < NP; ++k) lds[k * L::PLANE + wave * L::SLOTS + e * 64 + lane] = pc[k];
+        for (int e = 0; e < NCH; ++e) {
+            v4u pc[NP];
+            split8<NP>(pr[e], pc);
+#pragma unroll
+            for (int k = 0; k < NP; ++k) lds[k * L::PLANE + at + e * 64] = pc[k];
+        }
     };
 
     // ---- steps: (group, index); both units of a step and where they lie -------------------------------
     auto steps_of = [&](int grp) { return 2 * grp + 1 < ncb16 ? KK : (KK + 1) / 2; };
-    float ar[TM][8];
-    auto load_a = [&](int grp, int s) {
+    constexpr int AW = CUT ? NP : 2;            // 16-byte loads of a row: a piece each, or four fp32 values
+    using Rows = v4u[TM][AW];
+    auto load_a = [&](Rows &ar, int grp, int s) {
         uint32_t u0 = OOB_K, u1 = OOB_K;
         if (grp < ngrp) {
             if (2 * grp + 1 < ncb16) {
@@ -181,13 +204,12 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
         }
         const uint32_t u = second ? u1 : u0;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
+            const uint32_t at = CUT && u >= OOB_K ? OOB_K : arow[i] + u;        // (a piece's offset on top of both marks would wrap)
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, arow[i] + u + 16u * hf, 0, 0);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) ar[i][4 * hf + t] = __uint_as_float((uint32_t)v[t]);
-            }
+            for (int k = 0; k < AW; ++k)
+                ar[i][k] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, at + (CUT ? 0u : 16u * k), CUT ? k * piece_bytes : 0u, 0));
+        }
     };
     auto tap_slot = [&](int t) {                // slot displacement of tap t
         const int ky = (int)fdiv((uint32_t)t, pg.divKW), kx = t - ky * pg.KW;
@@ -195,50 +217,109 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
     };
 
     if (threadIdx.x < NP) lds[threadIdx.x * L::PLANE + L::ZERO] = v4u{0u, 0u, 0u, 0u};
-    static_for<0, NSL>([&](auto EC) { load_chunk(EC, 0); });
-    load_a(0, wk);
-    static_for<0, NSL>([&](auto EC) { store_chunk(EC); });
+    static_for<0, NCH>([&](auto EC) { load_chunk(EC, 0, 0); });
+    Rows ar;                                    // of the next step
+    load_a(ar, 0, wk);
+    store_chunks(0, 0);
+    if constexpr (RING) {
+        static_for<0, NCH>([&](auto EC) { load_chunk(EC, 0, 1); });
+        store_chunks(0, 1);
+    }
     block_sync_lds();
+    int first = 0;                              // plane of this group's first octet
 
-    // (the rows are cut in one piece in front of the products: cutting them behind the products of the step
-    // before, as split_gemm_kernel does, takes 24 more registers; the 192-row tiles already spill 18 to 98, most of them
-    // outside the steps, the others none)
     using Step = MmaStep<NP, TM, TN, TM >= 3 ? 1 : 2>;
-    for (int grp = 0; grp < ngrp; ++grp) {
-        const int ns = steps_of(grp);
-        const bool pair = 2 * grp + 1 < ncb16;
-        int ls = 0;
-        for (int s = wk; s < ns; s += WK, ++ls) {
-            v4u ap[TM][NP];
+    // the products of step s of a group with the rows in `ap`, everything for later steps being on its way
+    auto multiply = [&](int grp, int s, const v4u (&ap)[TM][NP]) {
+        // where the lane reads: slot displacement of its unit's tap, octet of its channels
+        int base;
+        int32_t mask = -1;
+        if (2 * grp + 1 < ncb16) base = tap_slot(s) + plane_of(first, q) * L::SLOTS;
+        else {
+            const int t0 = tap_slot(2 * s), t1 = tap_slot(min(2 * s + 1, KK - 1));
+            base = (second ? t1 : t0) + plane_of(first, q & 1) * L::SLOTS;
+            if (2 * s + 1 >= KK && second) { base = L::ZERO; mask = 0; }     // no second unit: zeros
+        }
+        auto read_b = [&](int j, v4u (&pc)[NP]) {
+            const int idx = (sig[j] & mask) + base;
 #pragma unroll
-            for (int i = 0; i < TM; ++i) split8<NP>(ar[i], ap[i]);
-            // a chunk of the next group's patch, then the next step's filters (so that waiting for those,
-            // one step from now, waits for nothing younger)
-            static_for<0, NSL>([&](auto EC) { if (ls == decltype(EC)::value) load_chunk(EC, grp + 1); });
-            if (s + WK < ns) load_a(grp, s + WK);
-            else load_a(grp + 1, wk);
-            // where the lane reads: slot displacement of its unit's tap, octet of its channels
-            int base;
-            int32_t mask = -1;
-            if (pair) base = tap_slot(s) + q * L::SLOTS;
-            else {
-                const int t0 = tap_slot(2 * s), t1 = tap_slot(min(2 * s + 1, KK - 1));
-                base = (second ? t1 : t0) + (q & 1) * L::SLOTS;
-                if (2 * s + 1 >= KK && second) { base = L::ZERO; mask = 0; }     // no second unit: zeros
+            for (int k = 0; k < NP; ++k) pc[k] = lds[idx + k * L::PLANE];
+        };
+        Step::run(ap, acc, read_b, typename Step::NoWork{});
+    };
+    // in front of a step's products: part of the next group's patch, then (by the caller) the next step's filters, so that
+    // waiting for those, one step from now, waits for nothing younger.  ls: steps this wave has made of the group
+    auto part_of_patch = [&](int grp, int ls) {
+        if constexpr (RING) {
+            if (ls == kStoreHalf && grp + 1 < ngrp) store_chunks(plane_of(first, 4), 0);
+            static_for<0, 2>([&](auto EC) {
+                constexpr int e = decltype(EC)::value;
+                if (ls == e) load_chunk(EC, grp + 1, 0);
+                if (ls == kStoreHalf + e) load_chunk(EC, grp + 1, 1);
+            });
+        } else static_for<0, NSL>([&](auto EC) { if (ls == decltype(EC)::value) load_chunk(EC, grp + 1, 0); });
+    };
+    // the group of which this wave has made ls steps is behind it
+    auto next_patch = [&](int grp, int ls) {
+        const int next = plane_of(first, 4);
+        if constexpr (RING) {
+            if (ls <= kStoreHalf) {             // (a short group)
+                static_for<0, 2>([&](auto EC) { if (ls <= decltype(EC)::value) load_chunk(EC, grp + 1, 0); });
+                store_chunks(next, 0);
             }
-            auto read_b = [&](int j, v4u (&pc)[NP]) {
-                const int idx = (sig[j] & mask) + base;
+            static_for<0, 2>([&](auto EC) { if (ls <= kStoreHalf + decltype(EC)::value) load_chunk(EC, grp + 1, 1); });
+        } else static_for<0, NSL>([&](auto EC) { if (ls <= decltype(EC)::value) load_chunk(EC, grp + 1, 0); });
+        block_sync_lds();                       // every wave is done with this group's patch
+        store_chunks(RING ? next : 0, RING ? 1 : 0);
+        block_sync_lds();
+        if constexpr (RING) first = next;
+    };
+    if constexpr (NP == 3) {
+        // (fp32 rows are cut in one piece in front of the products: cutting them behind the products of the step
+        // before, as split_gemm_kernel does, takes 24 more registers.  Two steps a turn with two sets of rows, as below, makes the
+        // 192-row tiles spill 200 registers and more: 308 -> 554 us for 256 images, 192 channels of 13x13, 192 rows, 3x3)
+        for (int grp = 0; grp < ngrp; ++grp) {
+            const int ns = steps_of(grp);
+            int ls = 0;
+            for (int s = wk; s < ns; s += WK, ++ls) {
+                v4u ap[TM][NP];
 #pragma unroll
-                for (int k = 0; k < NP; ++k) pc[k] = lds[idx + k * L::PLANE];
-            };
-            Step::run(ap, acc, read_b, typename Step::NoWork{});
+                for (int i = 0; i < TM; ++i) {
+                    if constexpr (CUT) {
+#pragma unroll
+                        for (int k = 0; k < NP; ++k) ap[i][k] = ar[i][k];
+                    } else {
+                        float f[8];
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) f[t] = __uint_as_float(ar[i][t / 4][t % 4]);
+                        split8<NP>(f, ap[i]);
+                    }
+                }
+                part_of_patch(grp, ls);
+                if (s + WK < ns) load_a(ar, grp, s + WK);
+                else load_a(ar, grp + 1, wk);
+                multiply(grp, s, ap);
+            }
+            if (grp + 1 < ngrp) next_patch(grp, ls);
         }
-        if (grp + 1 < ngrp) {
-            static_for<0, NSL>([&](auto EC) { if (ls <= decltype(EC)::value) load_chunk(EC, grp + 1); });
-            block_sync_lds();                   // every wave is done with this group's patch
-            static_for<0, NSL>([&](auto EC) { store_chunk(EC); });
-            block_sync_lds();
-        }
+    } else {
+        // two steps a turn, so that the rows on their way need not be moved to where the next step reads them
+        int grp = 0, s = wk, ls = 0;
+        auto step = [&](const Rows &cur, Rows &next) {
+            const bool last = s + WK >= steps_of(grp);
+            part_of_patch(grp, ls);
+            load_a(next, last ? grp + 1 : grp, last ? wk : s + WK);
+            multiply(grp, s, cur);
+            s += WK;
+            ++ls;
+            if (!last) return true;
+            if (grp + 1 < ngrp) next_patch(grp, ls);
+            s = wk;
+            ls = 0;
+            return ++grp < ngrp;
+        };
+        Rows other;
+        while (step(ar, other) && step(other, ar)) {}
     }
     if constexpr (WK == 2) {
         // the second wave's sums are added to the first's, which stores the tile
@@ -271,10 +352,20 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
                     float a[4][TM], b[4];
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
-                        const uint32_t row = m0 + (uint32_t)((wm * TM + i) * 16 + l16), unit = (uint32_t)(t * ncb16 + cb) * unit_bytes;
-                        const auto f = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, row < p.M ? row * 64u + unit + 16u * (uint32_t)q : OOB_K, 0, 0);
+                        const uint32_t row = m0 + (uint32_t)((wm * TM + i) * 16 + l16);
+                        if constexpr (CUT) {            // (the pieces may be infinite where the value is not)
+                            const StridedTaps &f = p.taps;
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) a[v][i] = __uint_as_float((uint32_t)f[v]);
+                            for (int v = 0; v < 4; ++v) {
+                                const int c = 16 * cb + 4 * q + v, m = pg.flip ? c : (int)row, ci = pg.flip ? (int)row : c;
+                                a[v][i] = row < p.M && c < (int)pg.Cred ? f.w[(((size_t)g * f.Mg + m) * f.Cg + ci) * KK + t] : 0.f;
+                            }
+                        } else {
+                            const uint32_t unit = (uint32_t)(t * ncb16 + cb) * unit_bytes;
+                            const auto f = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, row < p.M ? row * 64u + unit + 16u * (uint32_t)q : OOB_K, 0, 0);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) a[v][i] = __uint_as_float((uint32_t)f[v]);
+                        }
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
@@ -320,15 +411,15 @@ int launch_cfg(const IgemmProblem &p, hipStream_t stream)
                  WK == 2 && NP == 3 ? "16" : "", MT, NSL);
         rec = prof_begin(name, p.flops > 0 ? p.flops : 2.0 * p.M * (double)p.N * p.K * p.groups, 0.0, stream);
     }
-    constexpr size_t patch = PatchLds<NP, NSL>::BYTES, sums = WK == 2 ? (4 / (WM * WK)) * WM * TM * TN * 64 * 16 : 0, lds = patch > sums ? patch : sums;
+    constexpr size_t patch = PatchLds<NP, TM, WK, NSL, CG_CUT>::BYTES, sums = WK == 2 ? (4 / (WM * WK)) * WM * TM * TN * 64 * 16 : 0, lds = patch > sums ? patch : sums;
     static_assert(2 * lds <= 160 * 1024, "two blocks of this tile do not fit the LDS of a compute unit");
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_patch_kernel<NP, TM, WM, WK, NSL, CG_SCATTER>),
+        CG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&split_patch_kernel<NP, TM, WM, WK, NSL, CG_SCATTER, CG_CUT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((split_patch_kernel<NP, TM, WM, WK, NSL, CG_SCATTER>), grid, dim3(256), lds, stream, p);
+    hipLaunchKernelGGL((split_patch_kernel<NP, TM, WM, WK, NSL, CG_SCATTER, CG_CUT>), grid, dim3(256), lds, stream, p);
     prof_end(rec, stream);
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
@@ -348,30 +439,34 @@ template <int NP, int NSL> int launch_tiles(const IgemmProblem &p, int mt, hipSt
 
 }  // namespace
 
-// This file is compiled once per number of pieces (CG_NP), for scattered rows (CG_SCATTER) and for others, in parallel.
-#define CG_CAT_(a, b, c, d) a##b##c##d
-#define CG_CAT(a, b, c, d) CG_CAT_(a, b, c, d)
-int CG_CAT(split_patch_tiles_, CG_NP, _, CG_SCATTER)(const IgemmProblem &p, int mt, hipStream_t stream)
+// This file is compiled once per number of pieces (CG_NP), for scattered rows (CG_SCATTER) and for others, for filters in
+// pieces (CG_CUT) and, with three pieces, for fp32 ones, in parallel.
+#define CG_CAT_(a, b, c, d, e, f) a##b##c##d##e##f
+#define CG_CAT(a, b, c, d, e, f) CG_CAT_(a, b, c, d, e, f)
+int CG_CAT(split_patch_tiles_, CG_NP, _, CG_SCATTER, _, CG_CUT)(const IgemmProblem &p, int mt, hipStream_t stream)
 {
     if (p.patch.nsl == 4) return launch_tiles<CG_NP, 4>(p, mt, stream);
     if (p.patch.nsl == 5) return launch_tiles<CG_NP, 5>(p, mt, stream);
     return launch_tiles<CG_NP, 6>(p, mt, stream);
 }
 
-#if CG_NP == 3 && !CG_SCATTER
-int split_patch_tiles_1_0(const IgemmProblem &p, int mt, hipStream_t stream);
-int split_patch_tiles_1_1(const IgemmProblem &p, int mt, hipStream_t stream);
-int split_patch_tiles_2_0(const IgemmProblem &p, int mt, hipStream_t stream);
-int split_patch_tiles_2_1(const IgemmProblem &p, int mt, hipStream_t stream);
-int split_patch_tiles_3_1(const IgemmProblem &p, int mt, hipStream_t stream);
+#if CG_NP == 3 && !CG_SCATTER && !CG_CUT
+int split_patch_tiles_1_0_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_1_1_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_2_0_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_2_1_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_3_0_1(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_3_1_0(const IgemmProblem &p, int mt, hipStream_t stream);
+int split_patch_tiles_3_1_1(const IgemmProblem &p, int mt, hipStream_t stream);
 
 namespace {
 
 int patch_launch_tiles(const IgemmProblem &p, int mt, hipStream_t stream)
 {
-    if (p.math == CG_MATH_BF16) return p.c_scatter ? split_patch_tiles_1_1(p, mt, stream) : split_patch_tiles_1_0(p, mt, stream);
-    if (p.math == CG_MATH_BF16X3) return p.c_scatter ? split_patch_tiles_2_1(p, mt, stream) : split_patch_tiles_2_0(p, mt, stream);
-    return p.c_scatter ? split_patch_tiles_3_1(p, mt, stream) : split_patch_tiles_3_0(p, mt, stream);
+    if (p.math == CG_MATH_BF16) return p.c_scatter ? split_patch_tiles_1_1_1(p, mt, stream) : split_patch_tiles_1_0_1(p, mt, stream);
+    if (p.math == CG_MATH_BF16X3) return p.c_scatter ? split_patch_tiles_2_1_1(p, mt, stream) : split_patch_tiles_2_0_1(p, mt, stream);
+    if (p.patch.filter_pieces) return p.c_scatter ? split_patch_tiles_3_1_1(p, mt, stream) : split_patch_tiles_3_0_1(p, mt, stream);
+    return p.c_scatter ? split_patch_tiles_3_1_0(p, mt, stream) : split_patch_tiles_3_0_0(p, mt, stream);
 }
 
 // Row-tile height.  Two blocks are resident per compute unit (an odd one out runs alone and a little
@@ -435,6 +530,11 @@ int patch_launch(const IgemmProblem &p, hipStream_t stream)
 }
 
 }  // namespace
+
+// 192-row tiles have registers for a second set of pieces only where the patch goes round (PatchLds): 27x27 planes, 96 -> 192
+// channels 5x5, five chunks, 791 / 780 - 818 us (fp32 / pieces); 13x13, two groups, 384 -> 384 3x3, four chunks, 310 / 285.
+// Lower tiles take 6 to 18 % less with pieces.
+bool patch_wants_pieces(const IgemmProblem &p) { return p.M <= 48 || p.patch.nsl == 4 || patch_mt(p.M, p.N, p.groups) != 192; }
 
 static std::atomic<uint32_t> g_patch_min_tiles{512};
 bool patch_forced() { return g_patch_min_tiles.load(std::memory_order_relaxed) <= 1; }
@@ -567,15 +667,18 @@ int split_patch_launch(const IgemmProblem &p, hipStream_t stream)
     if (p.math != CG_MATH_FP32 && p.math != CG_MATH_BF16 && p.math != CG_MATH_BF16X3) return CG_EINVAL;
     const PatchGeom &g = p.patch;
     if (!g.src || !aligned16(g.src) || g.nsl < 4 || g.nsl > 6 || p.splits != 1 || g.Cred == 0 ||
-        p.K != g.Cred * (uint32_t)(g.KH * g.KW) || (p.c_scatter && (!p.taps.dy || !p.taps.w)))
+        p.K != g.Cred * (uint32_t)(g.KH * g.KW) || (p.c_scatter && (!p.taps.dy || !p.taps.w)) ||
+        (g.filter_pieces ? g.filter_pieces != (p.math == CG_MATH_BF16 ? 1 : p.math == CG_MATH_BF16X3 ? 2 : 3) || !p.taps.w : p.math != CG_MATH_FP32))
         return CG_EINVAL;
-    // the filter copy holds M rows of K floats (channels padded to 16) per group, and byte offsets into it stay below the marks
+    // the filter copy holds M rows of K values (channels padded to 16) per group, and byte offsets into it stay below the marks
     // that stand for "out of range"
-    if (p.A.elems * 4 > kMaxBufferBytes || (uint64_t)p.A.gstride * p.groups > p.A.elems || (uint64_t)p.M * ((g.Cred + 15) / 16 * 16) * (uint64_t)(g.KH * g.KW) > (uint64_t)p.A.gstride)
+    const uint64_t values = (uint64_t)p.M * ((g.Cred + 15) / 16 * 16) * (uint64_t)(g.KH * g.KW);
+    if (p.A.elems * 4 > kMaxBufferBytes || (uint64_t)p.A.gstride * p.groups > p.A.elems ||
+        (g.filter_pieces ? values / 2 * g.filter_pieces : values) > (uint64_t)p.A.gstride)
         return CG_EUNSUPPORTED;
     return patch_launch(p, stream);
 }
 
-#endif  // CG_NP == 3
+#endif  // CG_NP == 3 && !CG_SCATTER && !CG_CUT
 
 }  // namespace cg
