@@ -226,11 +226,13 @@ __global__ __launch_bounds__(TB) void maxpool_bwd_kernel(const float *__restrict
 // Planes too large for the LDS staging (beyond POOL_LDS input elements forward, POOL_LDS / 2
 // outputs backward): the same two gathers straight from global memory, one element per thread,
 // `bpp` blocks per plane.  Window order and tie-break are those of the staged kernels.
+template <int KT, int ST>
 __global__ __launch_bounds__(TB) void maxpool_fwd_direct_kernel(const float *__restrict__ x, float *__restrict__ y,
                                                                 int32_t *__restrict__ argmax, int H, int W, int OH,
-                                                                int OW, int k, int s, int p, uint32_t bpp,
+                                                                int OW, int k_rt, int s_rt, int p, uint32_t bpp,
                                                                 FastDiv divBpp, FastDiv divOW)
 {
+    const int k = KT ? KT : k_rt, s = ST ? ST : s_rt;
     const uint32_t pl = fdiv(blockIdx.x, divBpp), o = (blockIdx.x - pl * bpp) * TB + threadIdx.x;
     const uint32_t P = (uint32_t)(OH * OW);
     if (o >= P) return;
@@ -238,14 +240,35 @@ __global__ __launch_bounds__(TB) void maxpool_fwd_direct_kernel(const float *__r
     const float *xp = x + (size_t)pl * (uint32_t)(H * W);
     int best = -1;
     float bv = 0.f;
-    for (int kh = 0; kh < k; ++kh) {
-        const int ih = oh * s - p + kh;
-        if (ih < 0 || ih >= H) continue;
-        for (int kw = 0; kw < k; ++kw) {
-            const int iw = ow * s - p + kw;
-            if (iw < 0 || iw >= W) continue;
-            const float val = xp[ih * W + iw];
-            if (best < 0 || val > bv) { best = ih * W + iw; bv = val; }
+    if constexpr (KT > 0) {
+        // the window's loads in flight together, those beyond the plane from a place inside it (2048 planes of 112x112, 3x3 at
+        // stride 2: 53.5 -> 34.7 us)
+        float v[KT][KT];
+#pragma unroll
+        for (int kh = 0; kh < KT; ++kh)
+#pragma unroll
+            for (int kw = 0; kw < KT; ++kw) {
+                const int ih = min(max(oh * s - p + kh, 0), H - 1), iw = min(max(ow * s - p + kw, 0), W - 1);
+                v[kh][kw] = xp[ih * W + iw];
+            }
+#pragma unroll
+        for (int kh = 0; kh < KT; ++kh)
+#pragma unroll
+            for (int kw = 0; kw < KT; ++kw) {
+                const int ih = oh * s - p + kh, iw = ow * s - p + kw;
+                const bool in = ih >= 0 && ih < H && iw >= 0 && iw < W;
+                if (in && (best < 0 || v[kh][kw] > bv)) { best = ih * W + iw; bv = v[kh][kw]; }
+            }
+    } else {
+        for (int kh = 0; kh < k; ++kh) {
+            const int ih = oh * s - p + kh;
+            if (ih < 0 || ih >= H) continue;
+            for (int kw = 0; kw < k; ++kw) {
+                const int iw = ow * s - p + kw;
+                if (iw < 0 || iw >= W) continue;
+                const float val = xp[ih * W + iw];
+                if (best < 0 || val > bv) { best = ih * W + iw; bv = val; }
+            }
         }
     }
     y[(size_t)pl * P + o] = bv;
@@ -285,6 +308,83 @@ __global__ __launch_bounds__(TB) void maxpool_bwd_direct_kernel(const float *__r
         }
     if (!(gt > 0.f)) acc = 0.f;
     dx[at] = ACC ? old + acc : acc;
+}
+
+// The same gather for 3x3 windows at stride 2 where a plane of dx finds no room in LDS beside dy and the winners, a thread per cell
+// of 2 x 2 input elements: the (at most 2 x 2) windows that can cover any of them are read once, where a thread per element
+// reads up to four for itself.  Bound by HBM (dy, winners, gate, dx): 2048 planes of 112x112 118 us from LDS, an element a
+// thread; here 65.
+template <int ACC>
+__global__ __launch_bounds__(TB) void maxpool_bwd_cell_direct_kernel(const float *__restrict__ dy, const int32_t *__restrict__ argmax,
+                                                                     float *__restrict__ dx, const float *__restrict__ gate, uint32_t total,
+                                                                     int H, int W, int OH, int OW, int p, FastDiv divCells, FastDiv divCW)
+{
+    constexpr int KT = 3, ST = 2, NWC = 2;
+    const uint32_t i = blockIdx.x * TB + threadIdx.x;
+    if (i >= total) return;
+    const uint32_t pl = fdiv(i, divCells), cell = i - pl * divCells.d, ca = fdiv(cell, divCW), cb = cell - ca * divCW.d;
+    // the cell's elements are those whose padded coordinates are 2 ca, 2 ca + 1: all of them lie in windows ca - 1 and ca
+    const int ih0 = (int)ca * ST - p, iw0 = (int)cb * ST - p, oh0 = (int)ca - (KT - 1) / ST, ow0 = (int)cb - (KT - 1) / ST;
+    const int32_t *ap = argmax + (size_t)pl * (uint32_t)(OH * OW);
+    const float *gp = dy + (size_t)pl * (uint32_t)(OH * OW);
+    int32_t wa[NWC][NWC];
+    float wg[NWC][NWC];
+#pragma unroll
+    for (int a = 0; a < NWC; ++a)
+#pragma unroll
+        for (int b = 0; b < NWC; ++b) {
+            const int oh = oh0 + a, ow = ow0 + b;
+            const bool in = oh >= 0 && oh < OH && ow >= 0 && ow < OW;
+            const int o = in ? oh * OW + ow : 0;
+            const int32_t w = ap[o];
+            wa[a][b] = in ? w : -1;
+            wg[a][b] = gp[o];
+        }
+    const size_t at = (size_t)pl * (uint32_t)(H * W);
+    typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+    const bool c0 = iw0 >= 0, c1 = iw0 + 1 < W, both = c0 && c1;           // (a row's two elements move as one 8-byte access)
+    f2u gt[ST], old[ST];
+#pragma unroll
+    for (int r = 0; r < ST; ++r) {
+        const int ih = ih0 + r;
+        const size_t e = at + (size_t)(ih * W + iw0);
+        gt[r] = f2u{1.f, 1.f};
+        old[r] = f2u{0.f, 0.f};
+        if (ih < 0 || ih >= H) continue;
+        if (both) {
+            if (gate) gt[r] = *reinterpret_cast<const f2u *>(gate + e);
+            if (ACC) old[r] = *reinterpret_cast<const f2u *>(dx + e);
+        } else {
+            if (gate && c0) gt[r].x = gate[e];
+            if (gate && c1) gt[r].y = gate[e + 1];
+            if (ACC && c0) old[r].x = dx[e];
+            if (ACC && c1) old[r].y = dx[e + 1];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ST; ++r) {
+        const int ih = ih0 + r;
+        if (ih < 0 || ih >= H) continue;
+        const size_t e = at + (size_t)(ih * W + iw0);
+        f2u out;
+#pragma unroll
+        for (int c = 0; c < ST; ++c) {
+            const int32_t me = ih * W + iw0 + c;
+            float acc = 0.f;
+#pragma unroll
+            for (int a = 0; a < NWC; ++a)
+#pragma unroll
+                for (int b = 0; b < NWC; ++b)
+                    if (wa[a][b] == me) acc += wg[a][b];
+            if (!(gt[r][c] > 0.f)) acc = 0.f;
+            out[c] = ACC ? old[r][c] + acc : acc;
+        }
+        if (both) *reinterpret_cast<f2u *>(dx + e) = out;
+        else {
+            if (c0) dx[e] = out.x;
+            if (c1) dx[e + 1] = out.y;
+        }
+    }
 }
 
 // Backward for a window and stride known at compile time.  A thread owns a cell of ST x ST input
@@ -403,8 +503,19 @@ __device__ __forceinline__ float pow_neg(float sc, float beta)      // sc^-beta,
     return exp2f(-beta * log2f(sc));
 }
 
-constexpr int LRN_CH = 48;        // channels per chunk
+constexpr int LRN_CH = 48;        // channels per chunk, at most
 constexpr int LRN_V = 4;          // consecutive pixels per thread
+
+// What a thread owns: four pixels of an image, channels c0 .. c1-1.  Threads run along the groups of four pixels of a plane, the
+// chunks of an image, the images.
+struct LrnPart { int n, c0, c1, pix; bool ok; };
+struct LrnShape { int C, HW, ch; uint32_t total; FastDiv divQ, divChunks; };       // channels a chunk; threads; groups a plane, chunks
+__device__ __forceinline__ LrnPart lrn_part(const LrnShape &s)
+{
+    const uint32_t i = blockIdx.x * TB + threadIdx.x, u = fdiv(i, s.divQ), n = fdiv(u, s.divChunks);
+    const int c0 = (int)(u - n * s.divChunks.d) * s.ch;
+    return LrnPart{(int)n, c0, min(s.C, c0 + s.ch), (int)(i - u * s.divQ.d) * LRN_V, i < s.total};
+}
 
 // Four consecutive pixels of one channel plane move as one 16-byte access.  The planes of a tensor
 // with an odd pixel count start at any multiple of 4 bytes, which these accesses allow; the last
@@ -448,15 +559,13 @@ template <int ACC> __device__ __forceinline__ void px_store(float *__restrict__ 
 }
 
 template <int SIZE>
-__global__ __launch_bounds__(TB) void lrn_fwd_stream_kernel(const float *__restrict__ x, float *__restrict__ y, int C,
-                                                            int HW, int nchunk, float aos, float beta, float kappa)
+__global__ __launch_bounds__(TB) void lrn_fwd_stream_kernel(const float *__restrict__ x, float *__restrict__ y, const LrnShape sh,
+                                                            float aos, float beta, float kappa)
 {
     constexpr int half = (SIZE - 1) / 2;
-    const int pix = (blockIdx.x * TB + threadIdx.x) * LRN_V;
-    if (pix >= HW) return;
-    const int rem = HW - pix;
-    const int n = blockIdx.y / nchunk, c0 = (blockIdx.y % nchunk) * LRN_CH;
-    const int c1 = min(C, c0 + LRN_CH);
+    const LrnPart part = lrn_part(sh);
+    if (!part.ok) return;
+    const int C = sh.C, HW = sh.HW, n = part.n, c0 = part.c0, c1 = part.c1, pix = part.pix, rem = HW - pix;
     const float *xp = x + (size_t)n * C * HW + pix;
     float *yp = y + (size_t)n * C * HW + pix;
     Px4 win[SIZE];                 // x[c - half .. c - half + SIZE - 1] once the step's element has entered
@@ -490,15 +599,13 @@ __global__ __launch_bounds__(TB) void lrn_fwd_stream_kernel(const float *__restr
 // GATE: x is the output of a rectifier and dx the gradient with respect to that rectifier's input.
 template <int SIZE, int ACC, int GATE>
 __global__ __launch_bounds__(TB) void lrn_bwd_stream_kernel(const float *__restrict__ x, const float *__restrict__ dy,
-                                                            float *__restrict__ dx, int C, int HW, int nchunk,
+                                                            float *__restrict__ dx, const LrnShape sh,
                                                             float aos, float coef, float beta, float kappa)
 {
     constexpr int half = (SIZE - 1) / 2;
-    const int pix = (blockIdx.x * TB + threadIdx.x) * LRN_V;
-    if (pix >= HW) return;
-    const int rem = HW - pix;
-    const int n = blockIdx.y / nchunk, c0 = (blockIdx.y % nchunk) * LRN_CH;
-    const int c1 = min(C, c0 + LRN_CH);
+    const LrnPart part = lrn_part(sh);
+    if (!part.ok) return;
+    const int C = sh.C, HW = sh.HW, n = part.n, c0 = part.c0, c1 = part.c1, pix = part.pix, rem = HW - pix;
     const size_t img = (size_t)n * C * HW + pix;
     const float *xp = x + img, *gp = dy + img;
     float *dp = dx + img;
@@ -569,7 +676,7 @@ __global__ __launch_bounds__(TB) void lrn_bwd_stream_kernel(const float *__restr
 //             window order, as maxpool_bwd_kernel does) and feeds it to the LRN backward recurrence
 //             of lrn_bwd_stream_kernel.
 // The arithmetic is that of the separate kernels, operation for operation: same y, same winners.
-constexpr int LP_CH = 32;
+constexpr int LP_CH = 32;         // channels a block, at most (forward), always (backward)
 constexpr int LP_NP = 4;          // staged pooled elements per thread (at most LP_NP * TB a band)
 
 // LDS writes of this wave have landed, then the block's barrier.  Unlike __syncthreads() this does
@@ -585,7 +692,7 @@ __device__ __forceinline__ void lds_barrier()
 template <int SIZE, int KT, int ST, bool INSIDE>
 __global__ __launch_bounds__(TB) void lrn_pool_fwd_kernel(const float *__restrict__ x, float *__restrict__ yp,
                                                           int32_t *__restrict__ argmax, int C, int H, int W, int OH, int OW,
-                                                          int k_rt, int s_rt, int p, int nchunk, int nbands, int prb, float aos,
+                                                          int k_rt, int s_rt, int p, int ch, int nchunk, int nbands, int prb, float aos,
                                                           float beta, float kappa, FastDiv divOW)
 {
     const int k = KT ? KT : k_rt, s = ST ? ST : s_rt;
@@ -594,7 +701,7 @@ __global__ __launch_bounds__(TB) void lrn_pool_fwd_kernel(const float *__restric
     const int HW = H * W, P = OH * OW;
     int bi = blockIdx.x;
     const int band = bi % nbands; bi /= nbands;
-    const int n = bi / nchunk, c0 = (bi % nchunk) * LP_CH, c1 = min(C, c0 + LP_CH);
+    const int n = bi / nchunk, c0 = (bi % nchunk) * ch, c1 = min(C, c0 + ch);
     const int pr0 = band * prb, pr1 = min(OH, pr0 + prb);
     const int ih0 = max(0, pr0 * s - p), ih1 = min(H, (pr1 - 1) * s - p + k);
     const int base = ih0 * W, lim = ih1 * W;                 // the band's pixels in the plane
@@ -645,9 +752,12 @@ __global__ __launch_bounds__(TB) void lrn_pool_fwd_kernel(const float *__restric
                         if (val > bv) { best = org + kh * W + kw; bv = val; }
                     }
             } else {
+                constexpr int UN = KT ? KT : 1;
+#pragma unroll UN
                 for (int kh = 0; kh < k; ++kh) {
                     const int ih = oh * s - p + kh;
                     if (ih < 0 || ih >= H) continue;
+#pragma unroll UN
                     for (int kw = 0; kw < k; ++kw) {
                         const int iw = ow * s - p + kw;
                         if (iw < 0 || iw >= W) continue;
@@ -1083,8 +1193,12 @@ int maxpool_fwd_launch(const float *x, float *y, int32_t *argmax, int N, int C, 
     if (H * W > POOL_LDS) {        // an input plane does not fit the LDS staging
         const uint32_t bpp = ((uint32_t)(OH * OW) + TB - 1) / TB;
         if ((uint64_t)planes * bpp >= (1ull << 31)) return CG_EUNSUPPORTED;
-        hipLaunchKernelGGL(maxpool_fwd_direct_kernel, dim3(planes * bpp), dim3(TB), 0, st, x, y, argmax, H, W, OH, OW, k,
-                           s, p, bpp, make_fastdiv(bpp), make_fastdiv((uint32_t)OW));
+        auto launch = [&](auto *kernel) {
+            hipLaunchKernelGGL(kernel, dim3(planes * bpp), dim3(TB), 0, st, x, y, argmax, H, W, OH, OW, k, s, p, bpp,
+                               make_fastdiv(bpp), make_fastdiv((uint32_t)OW));
+        };
+        if (k == 3 && s == 2) launch(&maxpool_fwd_direct_kernel<3, 2>);
+        else launch(&maxpool_fwd_direct_kernel<0, 0>);
         CG_LAUNCH_CHECK();
     }
     const int ppb = pool_planes_per_block(OH * OW, H * W, POOL_LDS);
@@ -1109,9 +1223,21 @@ int maxpool_bwd_launch(const float *dy, const int32_t *argmax, float *dx, const 
     if (OH <= 0 || OW <= 0) return CG_EINVAL;
     if ((uint64_t)N * C >= (1ull << 31) || (uint64_t)H * W >= (1ull << 24)) return CG_EUNSUPPORTED;
     const uint32_t planes = (uint32_t)N * C;
+    auto cells = [&]() -> int {
+        const uint32_t cw = (uint32_t)(W + p + 1) / 2, per = cw * ((uint32_t)(H + p + 1) / 2);
+        if ((uint64_t)planes * per >= (1ull << 31)) return CG_EUNSUPPORTED;
+        auto launch = [&](auto *kernel) {
+            hipLaunchKernelGGL(kernel, dim3((planes * per + TB - 1) / TB), dim3(TB), 0, st, dy, argmax, dx, gate, planes * per, H, W,
+                               OH, OW, p, make_fastdiv(per), make_fastdiv(cw));
+        };
+        if (accumulate) launch(&maxpool_bwd_cell_direct_kernel<1>);
+        else launch(&maxpool_bwd_cell_direct_kernel<0>);
+        CG_LAUNCH_CHECK();
+    };
     if (OH * OW > POOL_LDS / 2) {  // dy and the winners of a plane do not fit the LDS staging
         const uint32_t bpp = ((uint32_t)(H * W) + TB - 1) / TB;
         if ((uint64_t)planes * bpp >= (1ull << 31)) return CG_EUNSUPPORTED;
+        if (k == 3 && s == 2) return cells();
         const FastDiv dB = make_fastdiv(bpp), dW = make_fastdiv((uint32_t)W), dS = make_fastdiv((uint32_t)s);
         if (accumulate)
             hipLaunchKernelGGL(maxpool_bwd_direct_kernel<1>, dim3(planes * bpp), dim3(TB), 0, st, dy, argmax, dx, gate, H, W,
@@ -1147,6 +1273,7 @@ int maxpool_bwd_launch(const float *dy, const int32_t *argmax, float *dx, const 
 #undef CG_POOL_CELL
         CG_LAUNCH_CHECK();
     }
+    if (k == 3 && s == 2) return cells();
     const int ppb = pool_planes_per_block(H * W, OH * OW, POOL_LDS / 2);
     const dim3 grid((planes + ppb - 1) / ppb);
     const size_t lds = 2 * (((size_t)ppb * OH * OW + 4 + 3) & ~(size_t)3) * sizeof(float);
@@ -1161,18 +1288,33 @@ int maxpool_bwd_launch(const float *dy, const int32_t *argmax, float *dx, const 
     CG_LAUNCH_CHECK();
 }
 
+// Channels of a chunk: a thread waits for its loads channel after channel, so small tensors take short chunks, whose windows'
+// halos are read again, until there are this many threads (six waves a SIMD).  Always a multiple of four: the loops are unrolled, and
+// which of a channel's products the compiler contracts with a sum goes with its place in the turn.  32 images, forward and backward, us: 64
+// channels of 56x56 (50 000 threads of 48 channels) 50.8 / 15.7 and 92.5 / 32.6 (6 channels a chunk; 8 the same), 192 channels of 56x56 (100 000)
+// backward 104 / 66; 800 000 threads 16.0, 32.9 and 69.  256 images of 96 channels of 55x55 (387 000 with 48) the same either way.
+constexpr uint64_t kLrnThreads = 400000;
+static LrnShape lrn_shape(int N, int C, int HW)
+{
+    const uint32_t q = (uint32_t)(HW + LRN_V - 1) / LRN_V;
+    int ch = LRN_CH;
+    while (ch > 8 && (uint64_t)N * q * (uint32_t)((C + ch - 1) / ch) < kLrnThreads) ch = ch > 12 ? ch / 2 : 8;
+    const uint32_t chunks = (uint32_t)((C + ch - 1) / ch);
+    return LrnShape{C, HW, ch, (uint32_t)N * chunks * q, make_fastdiv(q), make_fastdiv(chunks)};
+}
+
 int lrn_fwd_launch(const float *x, float *y, int N, int C, int HW, int size, float alpha, float beta, float kappa,
                    hipStream_t st)
 {
     if (size <= 0 || N <= 0 || C <= 0 || HW <= 0) return CG_EINVAL;
     const float aos = alpha / (float)size;
-    const int nchunk = (C + LRN_CH - 1) / LRN_CH;
-    const dim3 grid(((HW + LRN_V - 1) / LRN_V + TB - 1) / TB, (unsigned)(N * nchunk));
-    if (grid.y > 65535u && (size == 3 || size == 5 || size == 7)) return CG_EUNSUPPORTED;
+    if ((uint64_t)N * ((C + LRN_CH - 1) / LRN_CH) > 65535u && (size == 3 || size == 5 || size == 7)) return CG_EUNSUPPORTED;
+    const LrnShape sh = lrn_shape(N, C, HW);
+    const dim3 grid((sh.total + TB - 1) / TB);
     switch (size) {
-    case 3: hipLaunchKernelGGL(lrn_fwd_stream_kernel<3>, grid, dim3(TB), 0, st, x, y, C, HW, nchunk, aos, beta, kappa); break;
-    case 5: hipLaunchKernelGGL(lrn_fwd_stream_kernel<5>, grid, dim3(TB), 0, st, x, y, C, HW, nchunk, aos, beta, kappa); break;
-    case 7: hipLaunchKernelGGL(lrn_fwd_stream_kernel<7>, grid, dim3(TB), 0, st, x, y, C, HW, nchunk, aos, beta, kappa); break;
+    case 3: hipLaunchKernelGGL(lrn_fwd_stream_kernel<3>, grid, dim3(TB), 0, st, x, y, sh, aos, beta, kappa); break;
+    case 5: hipLaunchKernelGGL(lrn_fwd_stream_kernel<5>, grid, dim3(TB), 0, st, x, y, sh, aos, beta, kappa); break;
+    case 7: hipLaunchKernelGGL(lrn_fwd_stream_kernel<7>, grid, dim3(TB), 0, st, x, y, sh, aos, beta, kappa); break;
     default: {
         const size_t total = (size_t)N * C * HW;
         hipLaunchKernelGGL(lrn_fwd_kernel, dim3(grid_for(total)), dim3(TB), 0, st, x, y, total, C, HW, size, aos, beta,
@@ -1187,22 +1329,22 @@ int lrn_bwd_launch(const float *x, const float *dy, float *dx, int N, int C, int
 {
     if (size <= 0 || N <= 0 || C <= 0 || HW <= 0) return CG_EINVAL;
     const float aos = alpha / (float)size, coef = 2.f * alpha * beta / (float)size;
-    const int nchunk = (C + LRN_CH - 1) / LRN_CH;
-    const dim3 grid(((HW + LRN_V - 1) / LRN_V + TB - 1) / TB, (unsigned)(N * nchunk));
-    if (grid.y > 65535u && (size == 3 || size == 5 || size == 7)) return CG_EUNSUPPORTED;
+    if ((uint64_t)N * ((C + LRN_CH - 1) / LRN_CH) > 65535u && (size == 3 || size == 5 || size == 7)) return CG_EUNSUPPORTED;
+    const LrnShape sh = lrn_shape(N, C, HW);
+    const dim3 grid((sh.total + TB - 1) / TB);
 #define CG_LRN_BWD(SZ)                                                                                                \
     do {                                                                                                              \
         if (accumulate && gate)                                                                                       \
-            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 1, 1>), grid, dim3(TB), 0, st, x, dy, dx, C, HW, nchunk,    \
+            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 1, 1>), grid, dim3(TB), 0, st, x, dy, dx, sh,               \
                                aos, coef, beta, kappa);                                                               \
         else if (accumulate)                                                                                          \
-            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 1, 0>), grid, dim3(TB), 0, st, x, dy, dx, C, HW, nchunk,    \
+            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 1, 0>), grid, dim3(TB), 0, st, x, dy, dx, sh,               \
                                aos, coef, beta, kappa);                                                               \
         else if (gate)                                                                                                \
-            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 0, 1>), grid, dim3(TB), 0, st, x, dy, dx, C, HW, nchunk,    \
+            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 0, 1>), grid, dim3(TB), 0, st, x, dy, dx, sh,               \
                                aos, coef, beta, kappa);                                                               \
         else                                                                                                          \
-            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 0, 0>), grid, dim3(TB), 0, st, x, dy, dx, C, HW, nchunk,    \
+            hipLaunchKernelGGL((lrn_bwd_stream_kernel<SZ, 0, 0>), grid, dim3(TB), 0, st, x, dy, dx, sh,               \
                                aos, coef, beta, kappa);                                                               \
     } while (0)
     switch (size) {
@@ -1239,11 +1381,16 @@ int lrn_pool_fwd_launch(const float *x, float *y, int32_t *argmax, int N, int C,
 {
     if (!lrn_pool_fusable(C, H, W, size, k, s, p) || N <= 0) return CG_EUNSUPPORTED;
     const int OH = pool_out_size(H, k, s, p), OW = pool_out_size(W, k, s, p);
-    const int nchunk = (C + LP_CH - 1) / LP_CH;
     // bands of equal height, as few as fit
     int prb = lrn_pool_fwd_rows(W, k, s);
     const int nbands = (OH + prb - 1) / prb;
     prb = (OH + nbands - 1) / nbands;
+    if ((uint64_t)N * ((C + LP_CH - 1) / LP_CH) * nbands >= (1ull << 31)) return CG_EUNSUPPORTED;
+    // As above, by blocks: 32 images of 192 channels of 56x56 (768 blocks of 32 channels) 85.6 / 52.4 us (8 channels; 19 of that from
+    // the window's size at compile time, 2048 blocks 55.5), 256 of 96 channels of 55x55 and of 256 of 27x27 121 / 115 in the mean.
+    int ch = LP_CH;
+    while (ch > 4 && (uint64_t)N * ((C + ch - 1) / ch) * nbands < 4096) ch /= 2;
+    const int nchunk = (C + ch - 1) / ch;
     if ((uint64_t)N * nchunk * nbands >= (1ull << 31)) return CG_EUNSUPPORTED;
     const dim3 grid((unsigned)(N * nchunk * nbands));
     const size_t lds = 2 * (size_t)LRN_V * TB * sizeof(float);
@@ -1252,8 +1399,9 @@ int lrn_pool_fwd_launch(const float *x, float *y, int32_t *argmax, int N, int C,
     const bool inside = p == 0 && (OH - 1) * s + k <= H && (OW - 1) * s + k <= W;
 #define CG_LP_FWD(SZ, K_, S_, IN_)                                                                                    \
     hipLaunchKernelGGL((lrn_pool_fwd_kernel<SZ, K_, S_, IN_>), grid, dim3(TB), lds, st, x, y, argmax, C, H, W, OH, OW, k, \
-                       s, p, nchunk, nbands, prb, aos, beta, kappa, divOW)
+                       s, p, ch, nchunk, nbands, prb, aos, beta, kappa, divOW)
     if (size == 5 && k == 3 && s == 2 && inside) CG_LP_FWD(5, 3, 2, true);
+    else if (size == 5 && k == 3 && s == 2) CG_LP_FWD(5, 3, 2, false);
     else if (size == 5) CG_LP_FWD(5, 0, 0, false);
     else if (k == 3 && s == 2 && inside) CG_LP_FWD(3, 3, 2, true);
     else CG_LP_FWD(3, 0, 0, false);
