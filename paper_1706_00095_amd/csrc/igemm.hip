@@ -91,6 +91,9 @@ int pick_mt(uint32_t M, uint32_t N, uint32_t groups, uint32_t K = 0)
 // - fully-connected forward and backward-data in fp32 from 108 images: 1.0 - 1.3 (256 images, 9216 -> 4096 159.6 / 151.0 us,
 //   4096 -> 4096 backward-data 79.5 / 69.1); 64 images 0.8 - 1.0.  Not where columns lie apart in memory (1x1 layers
 //   of planes of one pixel: 0.82).
+// - their backward-weight in fp32 (rows across on both sides, the batch the reduction), whole steps of one layer, us: blocks times
+//   images from 30 000 on 0 to 122 faster (256 images 9216 -> 4096 472 / 410, 4096 -> 4096 255 / 235, 4096 -> 1000 136 / 127), 16 000 to
+//   26 000 -4.5 to 1.8, below or with fewer than 64 blocks -13 to 0.  Error against 64 bits 0.2 to 0.8 of what it was.
 int pieces_mt(const IgemmProblem &p)
 {
     if (p.A.check || p.B.k.r1_lim) return 0;
@@ -99,6 +102,8 @@ int pieces_mt(const IgemmProblem &p)
     const uint64_t rows = (uint64_t)(p.M + 127) / 128 * 128, blocks = rows / 128 * ((p.N + 127) / 128) * p.groups;
     if (p.B.lanes_k || !image) {
         const bool bq = quad_ok(p.B, p.K) && p.K % 4 == 0, rows_in_line = !p.B.lanes_k && p.B.row.d2.d == 1 && p.B.row.s1 == 1;
+        if (fp32 && !aq && rows_in_line && p.B.k.d1.d == 1 && p.B.k.d2.d == 1)
+            return blocks >= 64 && blocks * p.K >= 30000 && p.M * 100ull >= rows * 84 ? 128 : 0;
         return fp32 && aq && (bq || rows_in_line) && p.N >= 1000 && p.K >= 512 && p.M * 100ull >= rows * 84 ? 128 : 0;
     }
     if (p.M <= 16) return (p.K >= 180 && blocks >= 600) || (p.K >= 4096 && p.N >= 16384) ? 16 : 0;
