@@ -402,6 +402,85 @@ template <int ROWS, bool AHEAD, bool SCATTER> __global__ __launch_bounds__(256) 
             if (i0 + el < a.total) finish_kept(i0 + el);
 }
 
+// The same, four consecutive columns a thread (they are four consecutive elements of C): one look at the maps and one 16-byte
+// load a slice for the four.  An element's sums are added in the same order.  Bound by launch and HBM: 384 x 1728 in two groups,
+// 25 slices (66 MB), 21.2 -> 14.3 us alone; the 98 sums of a GoogLeNet-shaped step 8.6 -> 7.6 in the mean beside other streams.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void finish_store4(const FinishArgs &a, uint32_t i, f4 s)
+{
+    const uint32_t g = fdiv(i, a.divMN), rem = i - g * a.divMN.d;
+    const uint32_t m = fdiv(rem, a.divN), n = rem - m * a.divN.d;
+    if (a.bias_mode == 1) s += a.bias[(int64_t)g * a.bias_gstride + m];
+    else if (a.bias_mode == 2) s += *reinterpret_cast<const f4u *>(a.bias + (int64_t)g * a.bias_gstride + n);
+    if (a.relu)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = fmaxf(s[e], 0.f);
+    const int64_t idx = (int64_t)g * a.c_gstride + ((int32_t)m * a.c_row_stride + map_info(a.c_col, n).off);
+    if (a.gate) {
+        const f4u gt = *reinterpret_cast<const f4u *>(a.gate + idx);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = gt[e] > 0.f ? s[e] : 0.f;
+    }
+    f4u *dst = reinterpret_cast<f4u *>(a.c_ptr + idx);
+    if (a.accumulate) s += *dst;
+    *dst = s;
+}
+template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_finish4_kernel(const FinishArgs a)
+{
+    if (a.r_dy && blockIdx.x >= a.finish_blocks) {
+        const int m = (int)(blockIdx.x - a.finish_blocks);
+        __shared__ float red[256];
+        const float s = bias_channel_sum(a.r_dy, a.rM, a.rP, m, 0, a.rN, a.r_divQP, 256u, red);
+        if (threadIdx.x == 0) a.r_db[m] = s;
+        return;
+    }
+    const uint32_t nblk = a.r_dy ? a.finish_blocks : gridDim.x, quads = a.total / 4;
+    const int64_t plane = a.plane / 4;
+    const f4 *part = reinterpret_cast<const f4 *>(a.part);
+    // slices r, r + ROWS, ...
+    auto sum = [&](uint32_t i, int r) {
+        f4 s = {0.f, 0.f, 0.f, 0.f};
+        if (ROWS == 1) { s = part[i]; r = 1; }           // (a chain of one starts with its first slice, of eight with zero)
+        if constexpr (!AHEAD)
+            for (int k = r; k < a.splits; k += ROWS) s += part[(int64_t)k * plane + i];
+        else for (int k0 = r; k0 < a.splits; k0 += 8 * ROWS) {
+            f4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = k0 + ROWS * u < a.splits ? part[(int64_t)(k0 + ROWS * u) * plane + i] : f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (k0 + ROWS * u < a.splits) s += v[u];
+        }
+        return s;
+    };
+    if (ROWS == 1) {
+        for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < quads; i += nblk * 256) finish_store4(a, 4 * i, sum(i, 0));
+        return;
+    }
+    __shared__ f4 rows[8][32];
+    const int el = threadIdx.x & 31, r = threadIdx.x >> 5;
+    for (uint32_t i0 = blockIdx.x * 32; i0 < quads; i0 += nblk * 32) {
+        const uint32_t i = i0 + el;
+        rows[r][el] = i < quads ? sum(i, r) : f4{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+        if (r == 0 && i < quads) {
+            f4 s = rows[0][el];
+#pragma unroll
+            for (int k = 1; k < 8; ++k) s += rows[k][el];
+            finish_store4(a, 4 * i, s);
+        }
+        __syncthreads();
+    }
+}
+
+// Do aligned groups of four columns lie one behind the other in C?
+bool columns_in_quads(const IgemmProblem &p)
+{
+    const IndexMap &c = p.c_col;
+    return !p.c_scatter && p.N % 4 == 0 && c.d2.d == 1 && (c.d1.d == 1 ? c.s1 == 1 : c.d1.d % 4 == 0 && c.s2 == 1);
+}
+
 }  // namespace
 
 // K slices for row tiles of mt rows: as many as make one round of resident blocks, at least 128
@@ -543,7 +622,9 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
         if (rider_taken) *rider_taken = true;
     }
     const bool rows = pl.splits >= 16;
-    const unsigned blocks = rows ? std::min((a.total + 31) / 32, 65536u) : std::min((a.total + 255) / 256, 16384u);
+    const bool quads = columns_in_quads(p0);
+    const uint32_t items = quads ? a.total / 4 : a.total;
+    const unsigned blocks = rows ? std::min((items + 31) / 32, 65536u) : std::min((items + 255) / 256, 16384u);
     a.finish_blocks = blocks;
     auto launch = [&](auto *kernel) { hipLaunchKernelGGL(kernel, dim3(blocks + riders), dim3(256), 0, stream, a); };
     auto pick = [&](auto SC) {
@@ -551,7 +632,10 @@ int igemm_run(const IgemmProblem &p0, void *ws, size_t ws_bytes, hipStream_t str
         if (rows) pl.splits >= 40 ? launch(&splitk_finish_kernel<8, true, scatter>) : launch(&splitk_finish_kernel<8, false, scatter>);
         else pl.splits >= 6 ? launch(&splitk_finish_kernel<1, true, scatter>) : launch(&splitk_finish_kernel<1, false, scatter>);
     };
-    if (p0.c_scatter) pick(std::true_type{});
+    if (quads) {
+        if (rows) pl.splits >= 40 ? launch(&splitk_finish4_kernel<8, true>) : launch(&splitk_finish4_kernel<8, false>);
+        else pl.splits >= 6 ? launch(&splitk_finish4_kernel<1, true>) : launch(&splitk_finish4_kernel<1, false>);
+    } else if (p0.c_scatter) pick(std::true_type{});
     else pick(std::false_type{});
     CG_HIP_TRY(hipGetLastError());
     return CG_OK;
