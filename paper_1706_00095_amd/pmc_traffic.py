@@ -30,7 +30,7 @@ def label(name):
     name = name.replace("(anonymous namespace)::", "").replace("void ", "")
     math = {"0": "", "1": ",bf16", "2": ",bf16x3"}      # last template argument of the gathered kernel: the arithmetic
     pieces = {3: "", 2: ",bf16x3", 1: ",bf16"}          # first template argument of the kernels that cut operands
-    m = re.match(r"cg::split_patch_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), \w+>", name)
+    m = re.match(r"cg::split_patch_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), \w+(?:, \w+)?>", name)
     if m:
         np_, tm, wm, wk, nsl = map(int, m.groups())
         return f"igemm_patch{'16' if wk == 2 else ''}_kernel<{wm * tm * 16}x128,{nsl}{pieces[np_]}>"

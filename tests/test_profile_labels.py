@@ -11,6 +11,7 @@ MATRIX = {
     "void cg::split_patch_kernel<3, 2, 4, 1, 4, false>(cg::IgemmProblem)": "igemm_patch_kernel<128x128,4>",
     "void cg::split_patch_kernel<3, 3, 1, 2, 5, true>(cg::IgemmProblem)": "igemm_patch16_kernel<48x128,5>",
     "void cg::split_patch_kernel<2, 1, 4, 1, 6, false>(cg::IgemmProblem)": "igemm_patch_kernel<64x128,6,bf16x3>",
+    "void cg::split_patch_kernel<3, 3, 4, 1, 4, false, true>(cg::IgemmProblem)": "igemm_patch_kernel<192x128,4>",
     "void cg::stem_fwd_kernel<3, 2>(cg::StemArgs)": "igemm_stem_kernel<96>",
     "void cg::direct_kernel<2, 1>(cg::DirectArgs)": "igemm_direct_kernel<16x32,4c>",
     "void cg::split_wgrad_kernel<3, 2, 8>(cg::IgemmProblem)": "igemm_kernel<128x144,band8>",
