@@ -1293,7 +1293,7 @@ int maxpool_bwd_launch(const float *dy, const int32_t *argmax, float *dx, const 
 // which of a channel's products the compiler contracts with a sum goes with its place in the turn.  32 images, forward and backward, us: 64
 // channels of 56x56 (50 000 threads of 48 channels) 50.8 / 15.7 and 92.5 / 32.6 (6 channels a chunk; 8 the same), 192 channels of 56x56 (100 000)
 // backward 104 / 66; 800 000 threads 16.0, 32.9 and 69.  Where there are more with 48 channels, halving them only adds halos (14 % more bytes): 256 images,
-// backward, 256 channels of 27x27 (281 000) 121 / 139, 96 channels of 55x55 (387 000) 164 / 177.
+// backward, 256 channels of 27x27 (281 000) 134 / 139, 96 channels of 55x55 (387 000) 168 / 177.
 constexpr uint64_t kLrnThreads = 250000;
 static LrnShape lrn_shape(int N, int C, int HW)
 {
