@@ -323,8 +323,10 @@ __global__ __launch_bounds__(TB) void maxpool_bwd_cell_direct_kernel(const float
     const uint32_t i = blockIdx.x * TB + threadIdx.x;
     if (i >= total) return;
     const uint32_t pl = fdiv(i, divCells), cell = i - pl * divCells.d, ca = fdiv(cell, divCW), cb = cell - ca * divCW.d;
-    // the cell's elements are those whose padded coordinates are 2 ca, 2 ca + 1: all of them lie in windows ca - 1 and ca
-    const int ih0 = (int)ca * ST - p, iw0 = (int)cb * ST - p, oh0 = (int)ca - (KT - 1) / ST, ow0 = (int)cb - (KT - 1) / ST;
+    // The first cell is the one that holds element 0 (whatever lies in front of it is padding only): with v = ca + p / 2 a cell's
+    // elements are those whose padded coordinates are 2 v and 2 v + 1, and all of them lie in windows v - 1 and v.
+    const int ih0 = (int)ca * ST - p % ST, iw0 = (int)cb * ST - p % ST;
+    const int oh0 = (int)ca + p / ST - (KT - 1) / ST, ow0 = (int)cb + p / ST - (KT - 1) / ST;
     const int32_t *ap = argmax + (size_t)pl * (uint32_t)(OH * OW);
     const float *gp = dy + (size_t)pl * (uint32_t)(OH * OW);
     int32_t wa[NWC][NWC];
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(TB) void maxpool_bwd_cell_direct_kernel(const float
         }
     const size_t at = (size_t)pl * (uint32_t)(H * W);
     typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
-    const bool c0 = iw0 >= 0, c1 = iw0 + 1 < W, both = c0 && c1;           // (a row's two elements move as one 8-byte access)
+    const bool c0 = iw0 >= 0, c1 = iw0 + 1 < W, both = c0 && c1;           // (-1 <= iw0 < W; a row's two elements move as one 8-byte access)
     f2u gt[ST], old[ST];
 #pragma unroll
     for (int r = 0; r < ST; ++r) {
@@ -1224,7 +1226,7 @@ int maxpool_bwd_launch(const float *dy, const int32_t *argmax, float *dx, const 
     if ((uint64_t)N * C >= (1ull << 31) || (uint64_t)H * W >= (1ull << 24)) return CG_EUNSUPPORTED;
     const uint32_t planes = (uint32_t)N * C;
     auto cells = [&]() -> int {
-        const uint32_t cw = (uint32_t)(W + p + 1) / 2, per = cw * ((uint32_t)(H + p + 1) / 2);
+        const uint32_t cw = (uint32_t)(W + p % 2 + 1) / 2, per = cw * ((uint32_t)(H + p % 2 + 1) / 2);
         if ((uint64_t)planes * per >= (1ull << 31)) return CG_EUNSUPPORTED;
         auto launch = [&](auto *kernel) {
             hipLaunchKernelGGL(kernel, dim3((planes * per + TB - 1) / TB), dim3(TB), 0, st, dy, argmax, dx, gate, planes * per, H, W,

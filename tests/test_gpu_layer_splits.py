@@ -40,17 +40,22 @@ def _check(orc32, layers, in_shape, B, fuse):
 
 # planes of 12 317 (winners and dy in 24 KB, dx not beside them) and 17 685 elements (winners and dy not either), one of odd rows only
 @pytest.mark.parametrize("side", [(113, 109), (131, 135), (120, 111)])
-@pytest.mark.parametrize("pad", [0, 1])
-def test_pooling_of_large_planes(orc32, side, pad):
+@pytest.mark.parametrize("pad", [0, 1, 2])
+# who the pools read: both the rectifier (the second one's gradient is added), one the rectifier (behind its gate), one each the
+# rectifier and the convolution in front of it (behind the gate and added)
+@pytest.mark.parametrize("inputs", [(1, 1), (1,), (1, 0)])
+def test_pooling_of_large_planes(orc32, side, pad, inputs):
+    pools = [dict(kind="maxpool", inputs=[i], k=3, stride=2, pad=pad) for i in inputs]
     layers = [
         dict(kind="conv", inputs=[-1], M=3, k=3, stride=1, pad=1, groups=1),
         dict(kind="relu", inputs=[0]),
-        dict(kind="maxpool", inputs=[1], k=3, stride=2, pad=pad),
-        dict(kind="maxpool", inputs=[1], k=3, stride=2, pad=pad),
-        dict(kind="concat", inputs=[2, 3]),
-        dict(kind="avgpool", inputs=[4]),
-        dict(kind="fc", inputs=[5], out=4),
-        dict(kind="softmax_ce", inputs=[6]),
+        *pools,
+        *([dict(kind="concat", inputs=[2, 3])] if len(pools) == 2 else []),
+    ]
+    layers += [
+        dict(kind="avgpool", inputs=[len(layers) - 1]),
+        dict(kind="fc", inputs=[len(layers)], out=4),
+        dict(kind="softmax_ce", inputs=[len(layers) + 1]),
     ]
     _check(orc32, layers, (2,) + side, 2, 1)
 
