@@ -100,6 +100,7 @@ int pieces_mt(const IgemmProblem &p)
     const bool fp32 = p.math == CG_MATH_FP32, aq = quad_ok(p.A, p.K), image = p.B.row.d1.d > 1;
     if (!aq && p.A.lanes_k) return 0;
     const uint64_t rows = (uint64_t)(p.M + 127) / 128 * 128, blocks = rows / 128 * ((p.N + 127) / 128) * p.groups;
+    if (rows / 128 > 65535) return 0;            // more row tiles than a launch takes along y: the gathered kernel has taller ones
     if (p.B.lanes_k || !image) {
         const bool bq = quad_ok(p.B, p.K) && p.K % 4 == 0, rows_in_line = !p.B.lanes_k && p.B.row.d2.d == 1 && p.B.row.s1 == 1;
         if (fp32 && !aq && rows_in_line && p.B.k.d1.d == 1 && p.B.k.d2.d == 1)

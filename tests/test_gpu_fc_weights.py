@@ -31,3 +31,18 @@ def test_weight_gradient(B, IN, OUT, pieces):
     # B additions in a row, each rounded to nearest, of zero-mean terms: sqrt(B / 6) * 2^-24, and the result's own rounding
     assert np.linalg.norm(err) < ((B / 6) ** 0.5 + 1) * 2.0 ** -24 * np.linalg.norm(ref)
     assert np.abs(err).max() < 2.0 ** -24 * (B + 1) * np.abs(dy).max() * np.abs(t["x"]).max()
+
+
+def test_outputs_beyond_the_row_tiles_of_the_kernel_in_pieces():
+    """65 536 tiles of 128 rows, one more than a launch takes along y: the kernel with taller tiles runs it."""
+    B, IN, OUT = 2, 1, 65535 * 128 + 1
+    layers = [dict(kind="fc", inputs=[-1], out=OUT), dict(kind="softmax_ce", inputs=[0])]
+    t = cg_synth.net_tensors(layers, (IN, 1, 1), B, 1, seed=B, num_classes=OUT)
+    gn = GpuNet(layers, (IN, 1, 1), B, t)
+    gn.step((0.0, 0.0, 0.0, 1.0), cg.CG_STEP_SERIAL)
+    gn.sync()
+    dy = host(gn.act(0, 1)).reshape(B, OUT).astype(np.float64)
+    ref = (dy * t["x"].reshape(B, 1)).sum(0)
+    err = np.abs(host(gn.g[0])[:OUT] - ref)
+    # two products and their sum, each rounded to nearest, and half of the smallest subnormal
+    assert (err <= 3 * 2.0 ** -24 * np.abs(dy * t["x"].reshape(B, 1)).sum(0) + 2.0 ** -149).all()
