@@ -42,6 +42,8 @@ namespace cg {
 
 namespace {
 
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));      // four bf16
+
 template <int NP, int TM, int WK, int NSL, bool CUT> struct PatchLds {
     // In 16-byte units; behind the octets of every piece lies one unit of zeros.  Four octets of channels are a group's; where
     // registers allow no third block and two more octets find room beside another block, the octets of the groups go round: a
@@ -350,19 +352,19 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
                 for (int cb = 0; cb < ncb16; ++cb) {
                     // a unit of 16 channels, four consecutive ones a lane, its loads in flight together
                     float a[4][TM], b[4];
+                    const uint32_t unit = (uint32_t)(t * ncb16 + cb) * unit_bytes;
+                    auto row_of = [&](int i) { return m0 + (uint32_t)((wm * TM + i) * 16 + l16); };
+                    v2u pc[TM][CUT ? NP : 1];
+                    if constexpr (CUT) {
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        const uint32_t row = m0 + (uint32_t)((wm * TM + i) * 16 + l16);
-                        if constexpr (CUT) {            // (the pieces may be infinite where the value is not)
-                            const StridedTaps &f = p.taps;
+                        for (int i = 0; i < TM; ++i)
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                const int c = 16 * cb + 4 * q + v, m = pg.flip ? c : (int)row, ci = pg.flip ? (int)row : c;
-                                a[v][i] = row < p.M && c < (int)pg.Cred ? f.w[(((size_t)g * f.Mg + m) * f.Cg + ci) * KK + t] : 0.f;
-                            }
-                        } else {
-                            const uint32_t unit = (uint32_t)(t * ncb16 + cb) * unit_bytes;
-                            const auto f = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, row < p.M ? row * 64u + unit + 16u * (uint32_t)q : OOB_K, 0, 0);
+                            for (int k = 0; k < NP; ++k)
+                                pc[i][k] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rsrcA, row_of(i) < p.M ? row_of(i) * ROW_BYTES + unit + 8u * (uint32_t)q : OOB_K, k * piece_bytes, 0));
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) {
+                            const auto f = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, row_of(i) < p.M ? row_of(i) * ROW_BYTES + unit + 16u * (uint32_t)q : OOB_K, 0, 0);
 #pragma unroll
                             for (int v = 0; v < 4; ++v) a[v][i] = __uint_as_float((uint32_t)f[v]);
                         }
@@ -372,6 +374,31 @@ __global__ __launch_bounds__(256, 2) void split_patch_kernel(const IgemmProblem 
                         const int c = 16 * cb + 4 * q + v;
                         const uint32_t at = ok && c < (int)pg.Cred ? (uint32_t)(img + c * pg.chan_stride + sy * pg.Ws + sx) * 4u : OOB_K;
                         b[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrcB, at, 0, 0));
+                    }
+                    if constexpr (CUT) {
+                        // the pieces' sum is the value exactly, but for values whose scaled pieces are no finite numbers (from 2^104
+                        // up, infinities, NaN): those come from the filters themselves
+                        float z = 0.f;
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                float s = 0.f;
+#pragma unroll
+                                for (int k = 0; k < NP; ++k) s += __uint_as_float(v % 2 ? pc[i][k][v / 2] & 0xffff0000u : pc[i][k][v / 2] << 16);
+                                z = fmaf(s, 0.f, z);
+                                a[v][i] = s * (1.f / kCutScale);
+                            }
+                        if (!(z == 0.f)) {
+                            const StridedTaps &f = p.taps;
+#pragma unroll
+                            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) {
+                                    const int c = 16 * cb + 4 * q + v, m = pg.flip ? c : (int)row_of(i), ci = pg.flip ? (int)row_of(i) : c;
+                                    if (row_of(i) < p.M && c < (int)pg.Cred) a[v][i] = f.w[(((size_t)g * f.Mg + m) * f.Cg + ci) * KK + t];
+                                }
+                        }
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v) add(a[v], b[v]);

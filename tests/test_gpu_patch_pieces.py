@@ -29,7 +29,7 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("values", ["normal", "range"])
+@pytest.mark.parametrize("values", ["normal", "range", "inputs"])
 @pytest.mark.parametrize("case", SHAPES, ids=lambda c: "-".join(map(str, (c[0],) + c[1])))
 def test_pieces_beforehand_or_in_registers(case, values):
     which, (B, C, H, M, k, stride, pad, G), resident, name = case
@@ -42,6 +42,10 @@ def test_pieces_beforehand_or_in_registers(case, values):
         at = rng.permutation(w.size)
         w[at[:4]] = [3e38, 2.0 ** 104, -1.5e-44, 1e-40]
         w[at[4]], w[at[5]] = np.inf, np.nan
+    if values == "inputs":          # sums done again from filters of the whole range, subnormal ones and 2^104 and more among them
+        t["w"] = (t["w"] * 2.0 ** rng.integers(-140, 106, size=t["w"].shape)).astype(np.float32)
+        src = t["x" if which == "fwd" else "dy"]
+        src[0, 0], src[-1, -1, 0, 0], src[-1, 1, -1, -1] = np.inf, np.nan, -np.inf
     t = {n: torch.from_numpy(v).cuda() for n, v in t.items()}
     p = cg.CG_PASS_FWD if which == "fwd" else cg.CG_PASS_BWD_DATA
     copy = max(M * ((C // G + 15) // 16 * 16), C * stride * stride * ((M // G + 15) // 16 * 16)) * (k + stride) ** 2 * 6
