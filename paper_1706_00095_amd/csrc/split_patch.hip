@@ -558,10 +558,28 @@ int patch_launch(const IgemmProblem &p, hipStream_t stream)
 
 }  // namespace
 
-// 192-row tiles have registers for a second set of pieces only where the patch goes round (PatchLds): 27x27 planes, 96 -> 192
-// channels 5x5, five chunks, 791 / 780 - 818 us (fp32 / pieces); 13x13, two groups, 384 -> 384 3x3, four chunks, 310 / 285.
-// Lower tiles take 6 to 18 % less with pieces.
-bool patch_wants_pieces(const IgemmProblem &p) { return p.M <= 48 || p.patch.nsl == 4 || patch_mt(p.M, p.N, p.groups) != 192; }
+// Filters in pieces instead of fp32 ones: 1140 random passes, times with fp32 filters over those with pieces.
+// - up to 48 rows 1.04 - 1.2 (16-row tiles of four chunks 0.97 - 1.10)
+// - 192-row tiles have registers for a second set of pieces only where the patch goes round (PatchLds): 27x27 planes, 96 -> 192
+//   channels 5x5, five chunks, 791 / 780 - 818 us; 13x13, two groups, 384 -> 384 3x3, four chunks, 310 / 285
+// - 64- and 128-row tiles of five and six chunks 0.99 - 1.12
+// - 128-row tiles of four chunks, whose patch goes round: 0.97 - 1.07 where there is a second group of channels, 0.93 - 0.98 where there
+//   is none (16 -> 293 channels 3x3, 36 images of 17x17, 21 / 22 us); strided backward-data 0.89 - 1.01 (410 -> 114 3x3 stride 2, eight of
+//   34x34, 59 / 64); forward of a round and up to 80 blocks more, which go out as a second launch, 0.92 - 0.99 (128 -> 414 2x2 in two
+//   groups, 45 of 21x21, 54 / 59)
+// - 64-row tiles of four chunks: strided backward-data 1.01 - 1.08.  The others follow the rounds of resident blocks: up to one round
+//   0.93 - 1.0, one to one and a half 0.98 - 1.04, up to two 0.95 - 0.99 (90 -> 300 3x3 in two groups, 150 of 13x13, 57 / 61), beyond
+//   0.98 - 1.04; fewer than 450 indices 0.95 - 1.0 whatever the blocks
+bool patch_wants_pieces(const IgemmProblem &p)
+{
+    if (p.M <= 48) return true;
+    const int mt = patch_mt(p.M, p.N, p.groups);
+    if (p.patch.nsl != 4) return mt != 192;
+    if (mt == 192) return true;
+    const uint64_t blocks = (uint64_t)patch_pixel_tiles(p) * ((p.M + mt - 1) / mt) * p.groups, rb = igemm_resident_blocks();
+    if (mt == 128) return !p.c_scatter && p.patch.Cred > 32 && (p.patch.flip || blocks <= rb || blocks > rb + 80);
+    return p.c_scatter || (p.K >= 450 && (blocks > 2 * rb || (blocks > rb && blocks * 2 <= rb * 3)));
+}
 
 static std::atomic<uint32_t> g_patch_min_tiles{512};
 bool patch_forced() { return g_patch_min_tiles.load(std::memory_order_relaxed) <= 1; }
