@@ -1291,17 +1291,21 @@ int maxpool_bwd_launch(const float *dy, const int32_t *argmax, float *dx, const 
 }
 
 // Channels of a chunk: a thread waits for its loads channel after channel, so small tensors take short chunks, whose windows'
-// halos are read again, until there are this many threads (four waves a SIMD).  Always a multiple of four: the loops are unrolled, and
-// which of a channel's products the compiler contracts with a sum goes with its place in the turn.  32 images, forward and backward, us: 64
-// channels of 56x56 (50 000 threads of 48 channels) 50.8 / 15.7 and 92.5 / 32.6 (6 channels a chunk; 8 the same), 192 channels of 56x56 (100 000)
-// backward 104 / 66; 800 000 threads 16.0, 32.9 and 69.  Where there are more with 48 channels, halving them only adds halos (14 % more bytes): 256 images,
-// backward, 256 channels of 27x27 (281 000) 134 / 139, 96 channels of 55x55 (387 000) 168 / 177.
-constexpr uint64_t kLrnThreads = 250000;
-static LrnShape lrn_shape(int N, int C, int HW)
+// halos are read again.  Always a multiple of four: the loops are unrolled, and which of a channel's products the compiler contracts
+// with a sum goes with its place in the turn.  The lines go with the elements of the tensor and not with its
+// threads (64 and 96 channels are two chunks of 48 both); backward's lie earlier, where three tensors move, not two.  96 channels of
+// 55x55, 256 of 27x27, 192 and 64 of 56x56, 16 to 256 images; us with 48 / 24 / 12 / 8 channels on both sides of each line:
+//   forward   12 M elements 61.0 / 35.7 / 24.5 / 23.3   17 M  65.1 / 39.4 / 32.6 / 38.0   20 M 65.3 / 40.6 / 39.8 / 42.8
+//             21 M 70.9 / 48.3 / 52.4 / 52.4            40 M  78.9 / 73.4 / 75.7 / 77.3   42 M 92.8 / 94.9 / 98.1 / 100
+//   backward  9 M 84.9 / 51.8 / 36.8 / 36.3             13 M  83.0 / 54.4 / 44.1 / 48.9   17 M 95.6 / 62.2 / 58.1 / 68.2
+//             19 M 99.2 / 70.2 / 83.8 / 77.1            33 M  113 / 112 / 121 / 132       38 M 120 / 144 / 139 / 149
+struct LrnLines { uint64_t from48, from24, from12; };
+constexpr LrnLines kLrnFwd{40000000, 20000000, 13000000}, kLrnBwd{34000000, 17000000, 10000000};
+static LrnShape lrn_shape(int N, int C, int HW, const LrnLines &lines)
 {
+    const uint64_t elems = (uint64_t)N * C * HW;
     const uint32_t q = (uint32_t)(HW + LRN_V - 1) / LRN_V;
-    int ch = LRN_CH;
-    while (ch > 8 && (uint64_t)N * q * (uint32_t)((C + ch - 1) / ch) < kLrnThreads) ch = ch > 12 ? ch / 2 : 8;
+    const int ch = elems >= lines.from48 ? LRN_CH : elems >= lines.from24 ? 24 : elems >= lines.from12 ? 12 : 8;
     const uint32_t chunks = (uint32_t)((C + ch - 1) / ch);
     return LrnShape{C, HW, ch, (uint32_t)N * chunks * q, make_fastdiv(q), make_fastdiv(chunks)};
 }
@@ -1312,7 +1316,7 @@ int lrn_fwd_launch(const float *x, float *y, int N, int C, int HW, int size, flo
     if (size <= 0 || N <= 0 || C <= 0 || HW <= 0) return CG_EINVAL;
     const float aos = alpha / (float)size;
     if ((uint64_t)N * ((C + LRN_CH - 1) / LRN_CH) > 65535u && (size == 3 || size == 5 || size == 7)) return CG_EUNSUPPORTED;
-    const LrnShape sh = lrn_shape(N, C, HW);
+    const LrnShape sh = lrn_shape(N, C, HW, kLrnFwd);
     const dim3 grid((sh.total + TB - 1) / TB);
     switch (size) {
     case 3: hipLaunchKernelGGL(lrn_fwd_stream_kernel<3>, grid, dim3(TB), 0, st, x, y, sh, aos, beta, kappa); break;
@@ -1333,7 +1337,7 @@ int lrn_bwd_launch(const float *x, const float *dy, float *dx, int N, int C, int
     if (size <= 0 || N <= 0 || C <= 0 || HW <= 0) return CG_EINVAL;
     const float aos = alpha / (float)size, coef = 2.f * alpha * beta / (float)size;
     if ((uint64_t)N * ((C + LRN_CH - 1) / LRN_CH) > 65535u && (size == 3 || size == 5 || size == 7)) return CG_EUNSUPPORTED;
-    const LrnShape sh = lrn_shape(N, C, HW);
+    const LrnShape sh = lrn_shape(N, C, HW, kLrnBwd);
     const dim3 grid((sh.total + TB - 1) / TB);
 #define CG_LRN_BWD(SZ)                                                                                                \
     do {                                                                                                              \
@@ -1389,7 +1393,8 @@ int lrn_pool_fwd_launch(const float *x, float *y, int32_t *argmax, int N, int C,
     const int nbands = (OH + prb - 1) / prb;
     prb = (OH + nbands - 1) / nbands;
     if ((uint64_t)N * ((C + LP_CH - 1) / LP_CH) * nbands >= (1ull << 31)) return CG_EUNSUPPORTED;
-    // As above, by blocks: 32 images of 192 channels of 56x56 (768 blocks of 32 channels) 85.6 / 52.4 us (8 channels; 19 of that from
+    // As above, by blocks (8 to 256 images of the four layers above: the length that this takes is within 9 % of the best, within 4 % mostly,
+    // and at most 3 % behind 32 channels): 32 images of 192 channels of 56x56 (768 blocks of 32 channels) 85.6 / 52.4 us (8 channels; 19 of that from
     // the window's size at compile time, 2048 blocks 55.5), 256 of 96 channels of 55x55 and of 256 of 27x27 121 / 115 in the mean.
     int ch = LP_CH;
     while (ch > 4 && (uint64_t)N * ((C + ch - 1) / ch) * nbands < 4096) ch /= 2;

@@ -60,9 +60,10 @@ def test_pooling_of_large_planes(orc32, side, pad, inputs):
     _check(orc32, layers, (2,) + side, 2, 1)
 
 
-# channels behind the last whole chunk of 8, 12 (70 images), 24 (115) and 48 (170); planes of whole groups of four pixels and not; both window sizes
+# channels behind the last whole chunk: of 8, then (50 channels) forward / backward of 8 / 12, 12 / 24, 24 / 24, 24 / 48 and 48 / 48; planes of whole
+# groups of four pixels and not; all window sizes
 @pytest.mark.parametrize("size,M,side,B", [(5, 77, (12, 11), 2), (3, 13, (9, 9), 1), (5, 6, (8, 8), 3), (7, 50, (10, 7), 2), (5, 50, (56, 54), 70),
-                                           (5, 50, (56, 54), 115), (5, 50, (56, 54), 170)])
+                                           (5, 50, (56, 54), 115), (5, 50, (56, 54), 170), (5, 50, (56, 54), 240), (5, 50, (56, 54), 270)])
 @pytest.mark.parametrize("fuse", [0, 1])
 def test_lrn_chunks(orc32, size, M, side, B, fuse):
     layers = [
