@@ -475,11 +475,15 @@ template <int ROWS, bool AHEAD> __global__ __launch_bounds__(256) void splitk_fi
     }
 }
 
-// Do aligned groups of four columns lie one behind the other in C?
+// Are the sums of K slices added four columns a thread?  Where aligned groups of four columns lie one behind the other in C, from
+// 32 768 elements on.  Fewer leave a quarter of the blocks for as long a chain of loads a thread: 2 to 512 slices, us, one column /
+// four: 512 to 12 288 elements 3.4 / 3.5 up to 48 slices, 4.2 / 4.7 with 200, 5.5 / 6.4 with 512; 32 768 and 36 864 within 0.3 of each other,
+// 8.2 / 8.0 with 256; 147 456 4.6 / 3.2 with 16 and 53 / 46 with 512; 331 776 14.8 / 10.2 with 39.  (Both add an element's
+// sums in the same order.)
 bool columns_in_quads(const IgemmProblem &p)
 {
     const IndexMap &c = p.c_col;
-    return !p.c_scatter && p.N % 4 == 0 && c.d2.d == 1 && (c.d1.d == 1 ? c.s1 == 1 : c.d1.d % 4 == 0 && c.s2 == 1);
+    return (uint64_t)p.groups * p.M * p.N >= 32768 && !p.c_scatter && p.N % 4 == 0 && c.d2.d == 1 && (c.d1.d == 1 ? c.s1 == 1 : c.d1.d % 4 == 0 && c.s2 == 1);
 }
 
 }  // namespace
@@ -648,7 +652,7 @@ namespace {
 
 // block (m, s) sums the samples of slice s; the slices are added afterwards in slice order.
 // The (image, group of four pixels) pairs of the slice are spread over the threads, each moving
-// 16 bytes (4-byte aligned: planes of an odd pixel count start anywhere) with four loads in flight.
+// 16 bytes (4-byte aligned: planes of an odd pixel count start anywhere).
 __global__ __launch_bounds__(256) void bias_grad_partial_kernel(const float *__restrict__ dy, int N, int M, int P,
                                                                 int n_per, FastDiv divQP, float *__restrict__ part)
 {

@@ -32,8 +32,10 @@ def test_sliced_1x1_layers(B, C, H, M):
     assert torch.equal(dw.double().cpu().view(M, C), ref) and torch.equal(db.double().cpu(), yd.sum((0, 2, 3)))
 
 
-# windows: columns of dw in whole groups of four (8 * 9) and not (7 * 9), few pixels and many
-@pytest.mark.parametrize("B,C,H,M", [(2, 8, 30, 24), (2, 7, 30, 24), (40, 8, 56, 40), (40, 7, 56, 40)])
+# windows: columns of dw in whole groups of four (8 * 9, 64 * 9, 512 * 9) and not (7 * 9, 63 * 9), few slices and many; 32 768 elements of dw is
+# where four columns a thread begin (57 and 56 rows of 576 columns)
+@pytest.mark.parametrize("B,C,H,M", [(2, 8, 30, 24), (2, 7, 30, 24), (40, 8, 56, 40), (40, 7, 56, 40), (2, 64, 30, 57), (2, 64, 30, 56), (40, 64, 30, 57),
+                                     (40, 63, 30, 60), (4, 512, 12, 40), (60, 512, 12, 40)])
 def test_sliced_weight_gradients(B, C, H, M):
     rng = np.random.default_rng(C + H)
     d = cg.conv_desc(B, C, H, H, M, 3, pad=1)
