@@ -107,3 +107,19 @@ def test_pieces_beforehand_or_in_registers(case, values):
         size = _reference(which, *(v.abs().nan_to_num(0, 0, 0) for v in (x, w, dy)), H, OH, k, stride, pad, G)
         # a rounding or a dropped product per term, at most half of the smallest subnormal each at the lower end
         assert ok.any() and bool(((got - ref).abs()[ok] <= (terms + 2) * (2.0 ** -24 * size[ok] + 2.0 ** -149)).all())
+
+
+# pass, (B, C, H, M, k, stride, pad, groups): a grouped 5x5 layer, ragged channels, a strided one
+@pytest.mark.parametrize("which,shape", [("bd", (32, 96, 27, 256, 5, 1, 2, 2)), ("fwd", (44, 70, 27, 48, 5, 1, 2, 1)), ("bd", (64, 12, 55, 48, 5, 2, 2, 1))])
+def test_half_as_much_again_as_reported_holds_pieces(which, shape):
+    B, C, H, M, k, stride, pad, G = shape
+    d = cg.conv_desc(B, C, H, H, M, k, stride=stride, pad=pad, groups=G)
+    OH, OW = cg.cg_conv_out_shape(d)
+    x, w, y = (torch.ones(s, device="cuda") for s in ((B, C, H, H), (M, C // G, k, k), (B, M, OH, OW)))
+    need = cg.cg_conv_workspace_bytes(d, cg.CG_PASS_FWD if which == "fwd" else cg.CG_PASS_BWD_DATA)
+    rows, red = (M, C // G) if which == "fwd" else (C * stride * stride, M // G)
+    fp32 = rows * ((red + 15) // 16 * 16) * ((k + stride - 1) // stride) ** 2 * 4
+    ws = torch.full((need // 2 * 3,), 255, dtype=torch.uint8, device="cuda")
+    _, names = _logged(lambda: cg.cg_conv_fwd(d, x, w, None, y, ws) if which == "fwd" else cg.cg_conv_bwd_data(d, y, w, x, ws))
+    assert all("igemm_patch" in n for n in names), names
+    assert bool((ws[fp32:fp32 // 2 * 3] != 255).any())
