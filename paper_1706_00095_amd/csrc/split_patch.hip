@@ -459,8 +459,16 @@ template <int NP, int NSL> int launch_tiles(const IgemmProblem &p, int mt, hipSt
         if (mt == 32) return launch_cfg<NP, 2, 1, 2, NSL>(p, stream);
         if (mt == 16) return launch_cfg<NP, 1, 1, 2, NSL>(p, stream);
     }
-    if (mt == 192) return launch_cfg<NP, 3, 4, 1, NSL>(p, stream);
-    if (mt == 128) return launch_cfg<NP, 2, 4, 1, NSL>(p, stream);
+    // (what patch_wants_pieces leaves to fp32 filters whatever the size has no instance with three pieces)
+    constexpr bool CUT3 = NP == 3 && CG_CUT;
+    if (mt == 192) {
+        if constexpr (CUT3 && NSL != 4) return CG_EUNSUPPORTED;
+        else return launch_cfg<NP, 3, 4, 1, NSL>(p, stream);
+    }
+    if (mt == 128) {
+        if constexpr (CUT3 && NSL == 4 && CG_SCATTER) return CG_EUNSUPPORTED;
+        else return launch_cfg<NP, 2, 4, 1, NSL>(p, stream);
+    }
     return launch_cfg<NP, 1, 4, 1, NSL>(p, stream);
 }
 
