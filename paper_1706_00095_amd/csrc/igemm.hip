@@ -405,7 +405,7 @@ template <int ROWS, bool AHEAD, bool SCATTER> __global__ __launch_bounds__(256) 
 
 // The same, four consecutive columns a thread (they are four consecutive elements of C): one look at the maps and one 16-byte
 // load a slice for the four.  An element's sums are added in the same order.  Bound by launch and HBM: 384 x 1728 in two groups,
-// 25 slices (66 MB), 21.2 -> 14.3 us alone; the 98 sums of a GoogLeNet-shaped step 8.6 -> 7.6 in the mean beside other streams.
+// 25 slices (66 MB), 21.2 -> 14.3 us alone.
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void finish_store4(const FinishArgs &a, uint32_t i, f4 s)

@@ -7,24 +7,25 @@
 //                            small ones first; what is dropped (m*l, l*m, l*l) is 2^-29 of a product at the median, at
 //                            most 2^-24.  A step's products are added up from zero and then to the accumulator
 //                            (MmaStep, OWN): the error against 64 bits is 4.2e-8 where the fp32 instruction has
-//                            1.7e-7 (256 images, 256 channels of 13x13, 384 rows, 3x3), in 373 us instead of 591.
-//                            Sums that end as an infinity or a NaN are computed anew in fp32 (sums_in_fp32):
-//                            1.8 ms for the same pass where every sum is one.
+//                            1.7e-7 (256 images, 256 channels of 13x13, 384 rows, 3x3), in 355 us instead of 591.
+//                            Sums that end as an infinity or a NaN are computed anew in fp32 (sums_in_fp32): 523 us for
+//                            the same pass with one infinity in its input, 1.8 ms where every sum is one.
 //   NP = 2 (CG_MATH_BF16X3): x = h + l, three products.
 //   NP = 1 (CG_MATH_BF16):   x = h.
 //
 // What bounds it: the matrix pipe.  v_mfma_f32_16x16x32_bf16 rather than 32x32x16: on random operands
 // the former holds 1970 TFLOP/s, the latter 1700 (power; both 2450 on zeros), with the same LDS traffic
 // for the same wave tile.  Power bounds the rest too: the clock stands at 2.0 GHz of 2.4 with the pipe 53 % busy, and what a
-// variant leaves out comes off the time whether or not it overlapped (256 images of 13x13, 256 -> 384 channels 3x3, 375 us: cutting
-// filters 55, bringing and cutting the patch 26, reading fragments 35, own sums 20).  So the filters come cut.
+// variant leaves out comes off the time whether or not it overlapped (256 images of 13x13, 256 -> 384 channels 3x3, fp32 filters, 375 us: cutting
+// them 55, bringing and cutting the patch 26, reading fragments 35, own sums 20).  So the filters come cut.
 //
 // Split of the work.  A block is four waves and 128 pixels; wave w owns 16*TM rows of its own and
 // ALL 128 pixels.  So the filters are shared by nobody and need no LDS: a lane fetches its eight
 // consecutive reduction indices of a row straight from L2 (the filter copy is laid out so that a wave's load is
 // contiguous), a 16-byte load per piece, cut once by the kernel that makes the copy: every pixel tile cut the same values
 // again before (375 -> 346 us there; 5x5 of 48 rows 670 -> 568).  Where a workspace has no room for three pieces
-// (half as much again as the values) the copy is fp32, two loads, and a lane cuts its values in registers.  The
+// (half as much again as the values), or fp32 is the faster form (patch_wants_pieces), the copy is fp32, two loads, and a lane
+// cuts its values in registers.  The
 // image patch is cut once per block, on its way into LDS, 32 channels at a time, as
 // [piece][octet of channels][slot][8 channels]: a lane's operand is then one 16-byte read per piece
 // whose address runs over consecutive slots, and one patch serves every tap.  There is no barrier
