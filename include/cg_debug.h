@@ -23,7 +23,8 @@ int cg_debug_patch_min_tiles(int tiles);
 
 /* Test hook: the number of blocks the GPU keeps resident at once (512 = 256
  * compute units x 2), which decides where a patch-kernel launch is cut into a
- * launch of whole rounds and a launch of smaller tiles for the rest.  Tests
+ * launch of whole rounds and a launch of smaller tiles for the rest, the height of
+ * its tiles and, with it, the form of its filter copy.  Tests
  * lower it so that small shapes take the two-launch path.  Process-wide. */
 int cg_debug_resident_blocks(int blocks);
 
